@@ -376,15 +376,148 @@ __global__ __launch_bounds__(256) void gemm_generic_k(GemmArgs a)
     }
 }
 
+// The same products without LDS, for every K whose rows are whole 16-byte groups (the tile kernel above keeps the others).
+// Sixteen lanes share an output column: each walks k in steps of 16 VE elements, and the sixteen partial sums are added by a
+// fixed tree, so an output's sum does not depend on RT, CN or the other rows of the launch.  A few rows leave the 64x64
+// tiles a handful of workgroups with a serial k loop and a barrier pair per 16 k (K = 688, N = 256: 4 workgroups, 68 us; here
+// 16 workgroups whose loads are all requested at once, 5 us, which is the launch itself).  RT x CN outputs per lane group
+// balance the loads per FMA: 8 x 1 spreads a small product over as many wavefronts as possible, 32 x CN re-uses each loaded
+// vector 32 / CN times.
+template <typename T> struct Vec16;   // 16 bytes of T as floats
+template <> struct Vec16<float> {
+    static constexpr int N = 4;
+    float4 r;
+    __device__ inline void load(const float *p) { r = *(const float4 *)p; }
+    __device__ inline void zero() { r = make_float4(0.f, 0.f, 0.f, 0.f); }
+    __device__ inline float at(int e) const { return e == 0 ? r.x : e == 1 ? r.y : e == 2 ? r.z : r.w; }
+};
+template <> struct Vec16<bf16_t> {
+    static constexpr int N = 8;
+    uint4 r;
+    __device__ inline void load(const bf16_t *p) { r = *(const uint4 *)p; }
+    __device__ inline void zero() { r = make_uint4(0, 0, 0, 0); }
+    __device__ inline float at(int e) const
+    {
+        const uint32_t w = e < 2 ? r.x : e < 4 ? r.y : e < 6 ? r.z : r.w;
+        return bf16_to_f((bf16_t)((e & 1) ? w >> 16 : w & 0xffffu));
+    }
+};
+
+template <typename T, int EPI, int RT, int CN>
+__global__ __launch_bounds__(256) void gemm_rows_k(GemmArgs a)
+{
+    const int R = min(*a.pR, a.max_rows);
+    const int r0 = blockIdx.y * RT;
+    if (r0 >= R) return;
+    constexpr bool DUAL = EPI == EPI_SWIGLU;
+    constexpr int VE = Vec16<T>::N, U = RT == 8 ? 4 : 1;   // vectors requested per round and operand row
+    const T *X = (const T *)a.X, *W = (const T *)a.W, *W2 = (const T *)a.W2;
+    const int lane = threadIdx.x & 63, l16 = lane & 15, K = a.K, N = a.N;
+    const int n0 = (blockIdx.x * 16 + (threadIdx.x >> 6) * 4 + (lane >> 4)) * CN;
+    const T *xp[RT], *wp[CN], *up[DUAL ? CN : 1];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) xp[i] = X + (size_t)min(r0 + i, R - 1) * K;
+#pragma unroll
+    for (int c = 0; c < CN; ++c) {
+        wp[c] = W + (size_t)min(n0 + c, N - 1) * K;
+        if constexpr (DUAL) up[c] = W2 + (size_t)min(n0 + c, N - 1) * K;
+    }
+    float acc[CN][RT], acc2[DUAL ? CN : 1][RT];
+#pragma unroll
+    for (int c = 0; c < CN; ++c)
+#pragma unroll
+        for (int i = 0; i < RT; ++i) { acc[c][i] = 0.f; if constexpr (DUAL) acc2[c][i] = 0.f; }
+    for (int k0 = l16 * VE; k0 < K; k0 += 16 * VE * U) {
+        Vec16<T> w[U][CN], u2[U][DUAL ? CN : 1];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + u * 16 * VE;
+#pragma unroll
+            for (int c = 0; c < CN; ++c) {
+                w[u][c].zero();
+                if (k < K) w[u][c].load(wp[c] + k);
+                if constexpr (DUAL) { u2[u][c].zero(); if (k < K) u2[u][c].load(up[c] + k); }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + u * 16 * VE;
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                Vec16<T> x;
+                x.zero();
+                if (k < K) x.load(xp[i] + k);
+#pragma unroll
+                for (int c = 0; c < CN; ++c)
+#pragma unroll
+                    for (int e = 0; e < VE; ++e) {
+                        acc[c][i] = fmaf(x.at(e), w[u][c].at(e), acc[c][i]);
+                        if constexpr (DUAL) acc2[c][i] = fmaf(x.at(e), u2[u][c].at(e), acc2[c][i]);
+                    }
+            }
+        }
+    }
+    // sum over the sixteen lanes, halving the rows a lane carries with the distance (8, 4, 2), then the last pair
+    auto reduce8 = [&](float (&v)[8]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float keep = (l16 & 8) ? v[i + 4] : v[i], send = (l16 & 8) ? v[i] : v[i + 4];
+            v[i] = keep + __shfl_xor(send, 8);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const float keep = (l16 & 4) ? v[i + 2] : v[i], send = (l16 & 4) ? v[i] : v[i + 2];
+            v[i] = keep + __shfl_xor(send, 4);
+        }
+        const float keep = (l16 & 2) ? v[1] : v[0], send = (l16 & 2) ? v[0] : v[1];
+        v[0] = keep + __shfl_xor(send, 2);
+        v[0] += __shfl_xor(v[0], 1);
+        return v[0];
+    };
+    const int rsub = ((l16 >> 3) & 1) * 4 + ((l16 >> 2) & 1) * 2 + ((l16 >> 1) & 1);
+#pragma unroll
+    for (int c = 0; c < CN; ++c)
+#pragma unroll
+        for (int b = 0; b < RT; b += 8) {
+            float v[8], v2[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) { v[i] = acc[c][b + i]; v2[i] = DUAL ? acc2[DUAL ? c : 0][b + i] : 0.f; }
+            const float s = reduce8(v);
+            float s2 = 0.f;
+            if constexpr (DUAL) s2 = reduce8(v2);
+            const int r = r0 + b + rsub, n = n0 + c;
+            if ((l16 & 1) || r >= R || n >= N) continue;
+            const size_t o = (size_t)r * N + n;
+            if (EPI == EPI_STORE_F32) a.Yf[o] = s + (a.bias ? to_f<T>(((const T *)a.bias)[n]) : 0.f);
+            else if (EPI == EPI_RESID) a.Yf[o] += s;
+            else if (EPI == EPI_SWIGLU) ((T *)a.Yt)[o] = from_f<T>(silu_f(s) * s2);
+            else a.Yf[o] = s * a.scale;
+        }
+}
+
+template <typename T, int EPI>
+static void gemm_generic_go(hipStream_t s, const GemmArgs &a)
+{
+    if (a.K % Vec16<T>::N != 0) {
+        hipLaunchKernelGGL((gemm_generic_k<T, EPI>), dim3((a.N + 63) / 64, (a.max_rows + 63) / 64), dim3(256), 0, s, a);
+        return;
+    }
+    constexpr int CN = EPI == EPI_SWIGLU ? 2 : 4;
+    const long wide = (long)((a.N + 16 * CN - 1) / (16 * CN)) * ((a.max_rows + 31) / 32);
+    if (wide >= 512)   // two workgroups per compute unit without the finer split
+        hipLaunchKernelGGL((gemm_rows_k<T, EPI, 32, CN>), dim3((a.N + 16 * CN - 1) / (16 * CN), (a.max_rows + 31) / 32), dim3(256), 0, s, a);
+    else
+        hipLaunchKernelGGL((gemm_rows_k<T, EPI, 8, 1>), dim3((a.N + 15) / 16, (a.max_rows + 7) / 8), dim3(256), 0, s, a);
+}
+
 template <typename T>
 static void gemm_generic_t(hipStream_t s, int epi, const GemmArgs &a)
 {
-    dim3 grid((a.N + 63) / 64, (a.max_rows + 63) / 64), block(256);
     switch (epi) {
-    case EPI_STORE_F32: hipLaunchKernelGGL((gemm_generic_k<T, EPI_STORE_F32>), grid, block, 0, s, a); break;
-    case EPI_RESID: hipLaunchKernelGGL((gemm_generic_k<T, EPI_RESID>), grid, block, 0, s, a); break;
-    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_generic_k<T, EPI_SWIGLU>), grid, block, 0, s, a); break;
-    default: hipLaunchKernelGGL((gemm_generic_k<T, EPI_LOGITS>), grid, block, 0, s, a); break;
+    case EPI_STORE_F32: gemm_generic_go<T, EPI_STORE_F32>(s, a); break;
+    case EPI_RESID: gemm_generic_go<T, EPI_RESID>(s, a); break;
+    case EPI_SWIGLU: gemm_generic_go<T, EPI_SWIGLU>(s, a); break;
+    default: gemm_generic_go<T, EPI_LOGITS>(s, a); break;
     }
 }
 
@@ -456,57 +589,104 @@ void launch_rope_scatter(hipStream_t s, int dtype, const float *qkv, int n_slabs
 }
 
 // ------------------------------------------------------------------------------------------------ attention
-// One wavefront per (row, query head).  Keys: the cache positions [0, lim) of the row's sequence and the slots of
+// One workgroup per (row, query head).  Keys: the cache positions [0, lim) of the row's sequence and the slots of
 // the row's staging tiles named by its slot masks; for a block row these are the D keys of its block (mask equation, Sec. 3.3:
-// causal below the block start, full mutual attention inside the block).  Each lane walks a strided subset of the keys with a running
-// (max, sum, output); the 64 partial results are merged at the end.
+// causal below the block start, full mutual attention inside the block).  They form a list of 16-key tiles (the cache's, then
+// the staging tiles); the four wavefronts take four tiles at a time with a running (max, sum, output) each, merged at the end.
+// Scores: one lane per key, the key's features as 16-byte loads.  Output: one lane per feature, four slots per load (the
+// tile's own order), the weights handed over through LDS: one lane per key would read every value alone (20.7 us at 64 to 128
+// keys and head_dim 64; this 5 us, the launch and three dependent memory round trips).
 template <typename T, int HD>
-__global__ __launch_bounds__(64) void attn_generic_k(const T *q, T *out, const T *pool, KvGeom kg, RowMeta rm, SeqState st,
-                                                     int Hq)
+__global__ __launch_bounds__(256) void attn_generic_k(const T *q, T *out, const T *pool, KvGeom kg, RowMeta rm, SeqState st,
+                                                      int Hq)
 {
     const int r = blockIdx.y;
     if (r >= rm.counts[0]) return;
-    const int hq = blockIdx.x, G = Hq / kg.n_kv_heads, hk = hq / G, lane = threadIdx.x;
+    constexpr int FD = (HD + 63) / 64;   // features per lane
+    const int hq = blockIdx.x, G = Hq / kg.n_kv_heads, hk = hq / G, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int b = rm.seq[r], lim = rm.lim[r], stg = rm.stg[r], stg2 = rm.stg2[r];
     const uint32_t sm_all = (uint32_t)rm.smask[r];
     const uint32_t smask = stg >= 0 ? sm_all & 0xffffu : 0u, smask2 = stg2 >= 0 ? sm_all >> 16 : 0u;
-    // key index lim + i stands for slot i of the second staging tile (i < 16), lim + 16 + i for slot i of the row's own tile
-    const int total = lim + (smask ? 16 + 32 - __clz(smask) : (smask2 ? 32 - __clz(smask2) : 0));
+    const int n_cache = (lim + PAGE - 1) / PAGE, at2 = smask2 ? n_cache : -1, at1 = smask ? n_cache + (smask2 ? 1 : 0) : -1;
+    const int n_tiles = n_cache + (smask ? 1 : 0) + (smask2 ? 1 : 0);
     __shared__ float qs[HD];
-    __shared__ float part[64][HD + 1];
+    __shared__ __attribute__((aligned(16))) float ps[4][64];
+    __shared__ float wm[4], wl[4], wo[4][HD];
     const float scale = 1.0f / sqrtf((float)HD);
-    for (int i = lane; i < HD; i += 64) qs[i] = to_f<T>(q[((size_t)r * Hq + hq) * HD + i]);
+    for (int i = threadIdx.x; i < HD; i += 256) qs[i] = to_f<T>(q[((size_t)r * Hq + hq) * HD + i]);
     __syncthreads();
-    float m = -INFINITY, l = 0.f, o[HD];
+    float m = -INFINITY, l = 0.f, o[FD];
 #pragma unroll
-    for (int i = 0; i < HD; ++i) o[i] = 0.f;
-    for (int j = lane; j < total; j += 64) {
-        int page, slot;
-        if (j < lim) { page = st.page_table[(size_t)b * kg.pages_per_seq + j / PAGE]; slot = j % PAGE; }
-        else if (j < lim + 16) { page = stg2; slot = j - lim; if (!((smask2 >> slot) & 1u)) continue; }
-        else { page = stg; slot = j - lim - 16; if (!((smask >> slot) & 1u)) continue; }
-        const T *Kb = pool + kg.tile(page, hk), *Vb = Kb + PAGE * HD;
-        float sdot = 0.f;
+    for (int f = 0; f < FD; ++f) o[f] = 0.f;
+    for (int t0 = wave * 4; t0 < n_tiles; t0 += 16) {
+        const int t = t0 + (lane >> 4), slot = lane & 15;
+        int page = 0;
+        bool vis = false;
+        if (t == at1) { page = stg; vis = (smask >> slot) & 1u; }
+        else if (t == at2) { page = stg2; vis = (smask2 >> slot) & 1u; }
+        else if (t < n_cache) { page = max(st.page_table[(size_t)b * kg.pages_per_seq + t], 0); vis = t * PAGE + slot < lim; }
+        float s = -INFINITY;
+        if (vis) {
+            const T *Kb = pool + kg.tile(page, hk) + slot * 8;
+            float dot = 0.f;
+            Vec16<T> kv[HD / Vec16<T>::N];
 #pragma unroll
-        for (int i = 0; i < HD; ++i) sdot += qs[i] * to_f<T>(Kb[k_off(slot, i)]);
-        sdot *= scale;
-        float mn = fmaxf(m, sdot), corr = __expf(m - mn), p = __expf(sdot - mn);
+            for (int i = 0; i < HD / Vec16<T>::N; ++i) kv[i].load(Kb + k_off(0, i * Vec16<T>::N));
+#pragma unroll
+            for (int i = 0; i < HD / Vec16<T>::N; ++i)
+#pragma unroll
+                for (int e = 0; e < Vec16<T>::N; ++e) dot += qs[i * Vec16<T>::N + e] * kv[i].at(e);
+            s = dot * scale;
+        }
+        float mx = s;
+        for (int d = 32; d > 0; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
+        const float mn = fmaxf(m, mx);
+        const float corr = m == -INFINITY ? 0.f : __expf(m - mn), p = vis && mn > -INFINITY ? __expf(s - mn) : 0.f;
+        m = mn;
         l = l * corr + p;
 #pragma unroll
-        for (int i = 0; i < HD; ++i) o[i] = o[i] * corr + p * to_f<T>(Vb[v_off(slot, i)]);
-        m = mn;
-    }
-    float M = m;
-    for (int s = 32; s > 0; s >>= 1) M = fmaxf(M, __shfl_xor(M, s));
-    float f = (m == -INFINITY) ? 0.f : __expf(m - M);
-    float L = l * f;
-    for (int s = 32; s > 0; s >>= 1) L += __shfl_xor(L, s);
+        for (int f = 0; f < FD; ++f) o[f] *= corr;
+        ps[wave][lane] = p;   // read back by the same wavefront only
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int i = 0; i < HD; ++i) part[lane][i] = o[i] * f;
+        for (int tt = 0; tt < 4; ++tt) {
+            if (t0 + tt >= n_tiles) break;
+            const T *Vb = pool + kg.tile(__shfl(page, tt * 16), hk) + PAGE * HD;
+#pragma unroll
+            for (int f = 0; f < FD; ++f) {
+                const int i = lane + f * 64;
+                if (i >= HD) continue;
+#pragma unroll
+                for (int sg = 0; sg < 4; ++sg) {
+                    const float4 p4 = *(const float4 *)&ps[wave][tt * 16 + sg * 4];
+                    float v[4];
+                    if constexpr (sizeof(T) == 4) {
+                        const float4 x = *(const float4 *)(Vb + v_off(sg * 4, i));
+                        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+                    } else {
+                        const uint2 x = *(const uint2 *)(Vb + v_off(sg * 4, i));
+                        v[0] = bf16_to_f((bf16_t)(x.x & 0xffffu)); v[1] = bf16_to_f((bf16_t)(x.x >> 16));
+                        v[2] = bf16_to_f((bf16_t)(x.y & 0xffffu)); v[3] = bf16_to_f((bf16_t)(x.y >> 16));
+                    }
+                    o[f] += p4.x * v[0] + p4.y * v[1] + p4.z * v[2] + p4.w * v[3];
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    for (int d = 32; d > 0; d >>= 1) l += __shfl_xor(l, d);
+    if (lane == 0) { wm[wave] = m; wl[wave] = l; }
+#pragma unroll
+    for (int f = 0; f < FD; ++f)
+        if (lane + f * 64 < HD) wo[wave][lane + f * 64] = o[f];
     __syncthreads();
-    for (int i = lane; i < HD; i += 64) {
+    float M = -INFINITY;
+    for (int w = 0; w < 4; ++w) M = fmaxf(M, wm[w]);
+    float L = 0.f, f4[4];
+    for (int w = 0; w < 4; ++w) { f4[w] = wm[w] == -INFINITY ? 0.f : __expf(wm[w] - M); L += wl[w] * f4[w]; }
+    for (int i = threadIdx.x; i < HD; i += 256) {
         float acc = 0.f;
-        for (int w = 0; w < 64; ++w) acc += part[w][i];
+        for (int w = 0; w < 4; ++w) acc += wo[w][i] * f4[w];
         out[((size_t)r * Hq + hq) * HD + i] = from_f<T>(acc / L);
     }
 }
@@ -515,7 +695,7 @@ template <typename T>
 static void attn_generic_t(hipStream_t s, const void *q, void *out, const void *pool_layer, const KvGeom &kg,
                            const RowMeta &rm, const SeqState &st, int Hq, int max_rows)
 {
-    dim3 grid(Hq, max_rows), block(64);
+    dim3 grid(Hq, max_rows), block(256);
     switch (kg.head_dim) {
     case 32: hipLaunchKernelGGL((attn_generic_k<T, 32>), grid, block, 0, s, (const T *)q, (T *)out, (const T *)pool_layer, kg, rm, st, Hq); break;
     case 64: hipLaunchKernelGGL((attn_generic_k<T, 64>), grid, block, 0, s, (const T *)q, (T *)out, (const T *)pool_layer, kg, rm, st, Hq); break;

@@ -667,6 +667,23 @@ def test_fp32_wide_hidden_rows(hidden):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype,hidden,ffn,vocab,B,D,d", [("fp32", 36, 42, 33003, 1, 5, 32), ("fp32", 68, 260, 97, 3, 3, 96), ("fp32", 260, 64, 33001, 9, 4, 128),
+                                                          ("bf16", 72, 136, 33003, 3, 4, 64), ("bf16", 36, 44, 101, 2, 9, 32)])
+def test_generic_row_gemm_edges(dtype, hidden, ffn, vocab, B, D, d):
+    """The generic products on both sides of their dispatch: rows of whole 16-byte groups (k extents shorter than one round of
+    sixteen lanes, and not a multiple of it) or not; row counts around multiples of 8 and 32; vocabularies on both sides of the
+    32-row variant, ragged against its column blocks; attention lists of 1 to 6 tiles with one or two staging tiles."""
+    m = gpu_cfg(hidden=hidden, ffn=ffn, vocab=vocab, n_layers=2, head_dim=d, dtype=dtype, has_qkv_bias=True)
+    om, g_dev, layers_dev = both_models(m, seed=61 + B, std=0.3 if dtype == "fp32" else 0.05)
+    prompts = [syn.uniform_int(6, f"rg{i}", 1 + 11 * i, 0, m.vocab - 1).numpy() for i in range(B)]
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=B, max_seq_len=160, D=D, tau=0.5, prefill_rows=33)
+    bf = dtype == "bf16"
+    assert ctx.kernel_info.startswith("generic")
+    st, _ = lockstep(ctx, om, prompts, D, 0.5, 3, logit_tol=2e-2 if bf else 1e-4, conf_tol=1e-3 if bf else 1e-5, bf16=bf, max_len=160, verify_rule=0)
+    print("generic edges", (dtype, hidden, ffn, vocab, B, D, d), st)
+    ctx.close()
+
+
 # ------------------------------------------------------------------ seeded random shapes
 def _random_case(seed):
     rng = np.random.RandomState(seed)
