@@ -24,6 +24,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 constexpr int XS_STRIDE = 72;   // bf16 elements per LDS row of the activation slice (64 + 8 padding)
+constexpr int ZT_STRIDE = 68;   // floats per LDS row of a wavefront's 32 x 64 logits (64 + 4 padding)
 
 bool mfma_supported(const sdlm_model_cfg *m)
 {
@@ -86,7 +87,10 @@ template <int MT, int NT, int EPI, int WV = 4>
 __global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void gemm_mfma_k(MfmaArgs a)
 {
     static_assert(WV == 4 || (WV == 8 && MT % 2 == 0), "eight wavefronts stage two 32-row sub-tiles per load round");
-    __shared__ __attribute__((aligned(16))) bf16_t Xs[2][MT * 32][XS_STRIDE];
+    // the activation slices; the LM head's epilogue afterwards turns its logits around in the same memory
+    constexpr size_t XS_BYTES = sizeof(bf16_t) * 2 * MT * 32 * XS_STRIDE, ZT_BYTES = EPI == EPI_LMHEAD ? sizeof(float) * WV * 32 * ZT_STRIDE : 0;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[XS_BYTES > ZT_BYTES ? XS_BYTES : ZT_BYTES];
+    auto Xs = reinterpret_cast<bf16_t (*)[MT * 32][XS_STRIDE]>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keeps the weight stream's base in SGPRs
     // workgroup id -> tile.  The grid has two parts: the row blocks that certainly hold rows (mblk < m_sure), then the
@@ -353,13 +357,16 @@ __global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void ge
             }
         }
     } else {
-        // LM head: logits of this workgroup's 128*NT vocabulary entries -> per-row (max, argmax, sum exp, entropy sum)
+        // LM head: logits of this workgroup's 128*NT vocabulary entries -> per-row (max, argmax, sum exp, entropy sum).
+        // Logits the caller asked for go through LDS, 32 rows x 64 entries per wavefront at a time, so that a store is 256
+        // contiguous bytes of one row: from the accumulators it would be 64 single values 4 V bytes apart, and the address
+        // unit takes one cache line at a time.  V = 151936, with logits: h = 2048, 128 rows 200 -> 156 us; h = 3584, 256 rows
+        // (V = 152064) 384 -> 314 us; few rows gain nothing (4 rows, h = 1536: 92 -> 91 us).
         __shared__ float sm_m[WV][MT * 32];
         __shared__ int sm_a[WV][MT * 32];
         __shared__ float sm_s[WV][MT * 32], sm_e[WV][MT * 32];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            const int r = m0 + mt * 32 + brow;
             float m = -INFINITY;
             int arg = 0;   // stays a valid id even if every logit is NaN
 #pragma unroll
@@ -370,7 +377,6 @@ __global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void ge
                     float z = acc[nt][mt][v] * a.scale;
                     acc[nt][mt][v] = z;
                     if (n < a.N) {
-                        if (a.logits && r < R) a.logits[(size_t)r * a.N + n] = z;
                         if (z > m || (z == m && n < arg)) { m = z; arg = n; }
                     }
                 }
@@ -379,7 +385,25 @@ __global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void ge
             if (om > m || (om == m && oa < arg)) { m = om; arg = oa; }
             if (lane < 32) { sm_m[wave][mt * 32 + lane] = m; sm_a[wave][mt * 32 + lane] = arg; }
         }
-        __syncthreads();
+        __syncthreads();   // also: nobody reads the activation slices any more
+        if (a.logits) {
+            static_assert(EPI != EPI_LMHEAD || NT == 2, "a row of a wavefront's logits is one store of 64 lanes");
+            float *zt = reinterpret_cast<float *>(smem) + wave * 32 * ZT_STRIDE;   // this wavefront's own part: no barrier
+            const int n = ntile[0] * 32 + lane;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *(float4 *)&zt[brow * ZT_STRIDE + nt * 32 + q * 8 + fbase] =
+                            make_float4(acc[nt][mt][q * 4], acc[nt][mt][q * 4 + 1], acc[nt][mt][q * 4 + 2], acc[nt][mt][q * 4 + 3]);
+                const int r0 = m0 + mt * 32, live = min(32, R - r0);
+                float *dst = a.logits + (size_t)r0 * a.N + n;
+                if (n < a.N)
+                    for (int j = 0; j < live; ++j) dst[(size_t)j * a.N] = zt[j * ZT_STRIDE + lane];
+            }
+        }
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             float m = sm_m[0][mt * 32 + brow];
