@@ -231,12 +231,16 @@ __device__ inline float block_sum(float v, float *red)
 // out[j,:] = x[row,:] * g / sqrt(mean(x[row,:]^2) + eps), row = row_index ? row_index[j] : j.  When the projection
 // that produced the residual update was split along k, its partial sums (n_slabs slabs of [rows, h]) are first added
 // to x[row,:] in slab order and written back, so the residual stream is complete after this kernel.
-// A row lives in registers between the two passes (NV float4 per thread, h <= 1024 NV).
-template <typename T, int NV>
-__global__ __launch_bounds__(256) void rmsnorm_k(T *out, float *x, const T *g, int h, float eps, const int32_t *row_index,
-                                                 const int32_t *p_count, int sure, const float *slabs, int n_slabs, size_t slab_stride)
+// A row lives in registers between the two passes (TH threads, NV float4 each, h <= 4 TH NV).
+// Bound, with few rows: the memory round trips, one for the row and one per SU slabs; a row therefore gets the threads that let
+// its slabs be requested together.  256 threads -> now: h = 5120, 8 rows 11.0 -> 6.5 us; h = 3584, 70 rows 7.8 -> 5.7 us, 512 rows
+// 9.8 -> 8.6 us; h = 2048, 256 rows 6.5 -> 5.8 us.  With many rows: bandwidth, and small workgroups hide one row's reduction
+// behind another's loads (h = 3584, 4096 rows without slabs: 256 threads 18.6 us = 4.7 TB/s, 1024 threads 21.9 us).
+template <typename T, int TH, int NV>
+__global__ __launch_bounds__(TH) void rmsnorm_k(T *out, float *x, const T *g, int h, float eps, const int32_t *row_index,
+                                                const int32_t *p_count, int sure, const float *slabs, int n_slabs, size_t slab_stride)
 {
-    __shared__ float red[4];
+    __shared__ float red[TH / 64];
     const int j = blockIdx.x;
     if (j >= sure && j >= *p_count) return;   // the first `sure` rows exist for certain: no wait for the device count
     const int row = row_index ? row_index[j] : j;
@@ -244,7 +248,7 @@ __global__ __launch_bounds__(256) void rmsnorm_k(T *out, float *x, const T *g, i
     float4 v[NV], gv[NV];   // the gains are requested together with the row, not after the reduction
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int k = (i * 256 + threadIdx.x) * 4;
+        const int k = (i * TH + threadIdx.x) * 4;
         v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         gv[i] = v[i];
         if (k < h) {
@@ -259,17 +263,18 @@ __global__ __launch_bounds__(256) void rmsnorm_k(T *out, float *x, const T *g, i
         }
     }
     // The slabs are added in slab order, but requested SU at a time (as many as the registers of the row width allow): one
-    // memory round trip per SU slabs instead of one per slab.  A slab index past the end is clamped for the load (a valid address, a cache hit) and its add skipped.
+    // memory round trip per SU slabs instead of one per slab.  Slabs past the end are neither requested nor added.
     constexpr int SU = NV <= 2 ? 8 : (NV <= 4 ? 4 : (NV == 8 ? 2 : 1));
     for (int s0 = 0; s0 < n_slabs; s0 += SU) {
         float4 p[SU][NV];
 #pragma unroll
         for (int u = 0; u < SU; ++u) {
-            const int sl = min(s0 + u, n_slabs - 1);
+            if (s0 + u < n_slabs) {
 #pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                const int k = (i * 256 + threadIdx.x) * 4;
-                p[u][i] = k < h ? *(const float4 *)(slabs + sl * slab_stride + (size_t)row * h + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+                for (int i = 0; i < NV; ++i) {
+                    const int k = (i * TH + threadIdx.x) * 4;
+                    p[u][i] = k < h ? *(const float4 *)(slabs + (s0 + u) * slab_stride + (size_t)row * h + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+                }
             }
         }
 #pragma unroll
@@ -283,7 +288,7 @@ __global__ __launch_bounds__(256) void rmsnorm_k(T *out, float *x, const T *g, i
     float ss = 0.f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int k = (i * 256 + threadIdx.x) * 4;
+        const int k = (i * TH + threadIdx.x) * 4;
         if (k < h && n_slabs > 0) *(float4 *)(xr + k) = v[i];
         ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
     }
@@ -291,7 +296,7 @@ __global__ __launch_bounds__(256) void rmsnorm_k(T *out, float *x, const T *g, i
     const float inv = 1.0f / sqrtf(ss / (float)h + eps);
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int k = (i * 256 + threadIdx.x) * 4;
+        const int k = (i * TH + threadIdx.x) * 4;
         if (k >= h) continue;
         const float o0 = v[i].x * inv * gv[i].x, o1 = v[i].y * inv * gv[i].y;
         const float o2 = v[i].z * inv * gv[i].z, o3 = v[i].w * inv * gv[i].w;
@@ -309,8 +314,12 @@ template <typename T>
 static void rmsnorm_t(hipStream_t s, void *out, float *x, const void *g, int h, float eps, const int32_t *row_index,
                       const int32_t *p_count, int max_rows, int min_rows, const float *slabs, int n_slabs, size_t slab_stride)
 {
-#define SDLM_RMS(NV) hipLaunchKernelGGL((rmsnorm_k<T, NV>), dim3(max_rows), dim3(256), 0, s, (T *)out, x, (const T *)g, h, eps, row_index, p_count, min_rows, slabs, n_slabs, slab_stride)
-    if (h <= 2048) SDLM_RMS(2); else if (h <= 4096) SDLM_RMS(4); else if (h <= 8192) SDLM_RMS(8); else SDLM_RMS(16);
+#define SDLM_RMS(TH, NV) hipLaunchKernelGGL((rmsnorm_k<T, TH, NV>), dim3(max_rows), dim3(TH), 0, s, (T *)out, x, (const T *)g, h, eps, row_index, p_count, min_rows, slabs, n_slabs, slab_stride)
+    if (max_rows > 1024) {   // between the measured 992 rows (with slabs) and 2205 (without: 12.6 us with 256 threads, 13.4 us with 1024)
+        if (h <= 2048) SDLM_RMS(256, 2); else if (h <= 4096) SDLM_RMS(256, 4); else if (h <= 8192) SDLM_RMS(256, 8); else SDLM_RMS(256, 16);
+        return;
+    }
+    if (h <= 1024) SDLM_RMS(256, 1); else if (h <= 2048) SDLM_RMS(512, 1); else if (h <= 4096) SDLM_RMS(1024, 1); else if (h <= 8192) SDLM_RMS(1024, 2); else SDLM_RMS(1024, 4);
 #undef SDLM_RMS
 }
 
