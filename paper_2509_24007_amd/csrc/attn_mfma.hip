@@ -250,28 +250,36 @@ __global__ __launch_bounds__(256, 4) void attn_mfma_k(AttnArgs a)
 // exactly those partial results and running maxima are requested one round trip in.  The hint only steers these early
 // requests: the chunk count that decides the result is derived from the rows' limits as in the attention kernel, and
 // what a hint misses is fetched afterwards.
-__global__ __launch_bounds__(256) void attn_combine_k(AttnArgs a)
+//
+// A workgroup has CG groups of 256 threads; thread group cg merges chunks CU cg .. CU cg + CU - 1 of every CG CU chunks, and
+// the groups' sums are added in group order.  The launch takes the variant by the chunks that the grid may have: up to 4 are
+// one round trip with CU = 4 (registers for more in flight only cost occupancy: prefill of 4096 rows 26.2 us, 29.2 us with CU = 8);
+// up to 16 take CU = 8 (7B shape, 7 sequences, 11 chunks: 7.7 -> 7.2 us); beyond, four thread groups make 32 chunks one round trip
+// (32B shape, one sequence, 60 chunks: 24.1 -> 10.7 us, 6 sequences of the 7B shape with 31 chunks 9.4 -> 6.9 us).
+template <int CG, int CU>
+__global__ __launch_bounds__(256 * CG) void attn_combine_k(AttnArgs a)
 {
-    constexpr int CU = 4, V4 = HD / 4, EPT = 16 * V4 / 256;   // chunks requested together; float4 per query; elements per thread
-    const int g = blockIdx.x, hk = blockIdx.y, nq = blockIdx.z, tid = threadIdx.x, lane = tid & 63;
+    constexpr int V4 = HD / 4, EPT = 16 * V4 / 256;   // CU: chunks a thread requests together; V4: float4 per query; EPT: elements per thread
+    const int g = blockIdx.x, hk = blockIdx.y, nq = blockIdx.z, lane = threadIdx.x & 63;
+    const int cg = threadIdx.x >> 8, tid = threadIdx.x & 255;
     const size_t item0 = ((size_t)g * a.kg.n_kv_heads + hk) * a.max_chunks;
     const int hint = a.rm.grp_hint[g];   // in bounds for every group of the grid
     const int n_groups = a.rm.counts[1];
     const int cp = max(a.rm.counts[3], a.chunk_pages);
     const int row0 = a.rm.grp_row0[g], nrows = a.rm.grp_n[g];
     const int hc = min(hint & 0xff, a.max_chunks), hq = ((hint >> 8) & 0xff) * a.G;   // chunks and queries to expect
-    const int mq = tid & 15, mc = tid >> 4;
+    const int mq = tid >> 4, mc = tid & 15;   // the first thread group's part in the running maxima: query, chunk (mod 16)
     float2 ml0 = make_float2(0.f, 0.f);
     f32x4 po[EPT][CU];
     const bool ml_early = hc > 1 && mc < hc;
-    if (ml_early) ml0 = a.part_ml[(item0 + mc) * QMAX + nq * 16 + mq];
+    if (cg == 0 && ml_early) ml0 = a.part_ml[(item0 + mc) * QMAX + nq * 16 + mq];
 #pragma unroll
     for (int j = 0; j < EPT; ++j) {
         const int e = tid + j * 256, qi = nq * 16 + e / V4, d4 = (e % V4) * 4;
 #pragma unroll
         for (int u = 0; u < CU; ++u) {
             po[j][u] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (hc > 1 && u < hc && qi < hq) po[j][u] = *(const f32x4 *)(a.part_o + ((item0 + u) * QMAX + qi) * HD + d4);
+            if (hc > 1 && cg * CU + u < hc && qi < hq) po[j][u] = *(const f32x4 *)(a.part_o + ((item0 + cg * CU + u) * QMAX + qi) * HD + d4);
         }
     }
     if (g >= n_groups) return;
@@ -282,45 +290,73 @@ __global__ __launch_bounds__(256) void attn_combine_k(AttnArgs a)
     const int n_pages = (lim + PAGE - 1) / PAGE;
     const int n_chunks = max(1, (n_pages + cp - 1) / cp);
     if (n_chunks == 1) return;   // the attention kernel wrote the final result itself
-    __shared__ float sf[16][65], sl[16][65];   // [query][chunk]: running maximum, then 2^{c(m_c - M)} / L; row sum
-    for (int c = mc; c < n_chunks; c += 16) {
-        const float2 ml = (c < 16 && ml_early) ? ml0 : a.part_ml[(item0 + c) * QMAX + nq * 16 + mq];
-        sf[mq][c] = ml.x;
-        sl[mq][c] = ml.y;
-    }
-    __syncthreads();
-    if (tid < 16 && nq * 16 + tid < QR) {
-        float M = -INFINITY;
-        for (int c = 0; c < n_chunks; ++c) M = fmaxf(M, sf[tid][c]);
-        float L = 0.f;
-        for (int c = 0; c < n_chunks; ++c) {
-            const float m = sf[tid][c];
-            const float f = m == -INFINITY ? 0.f : exp2f((m - M) * a.c);
-            sf[tid][c] = f;
-            L += sl[tid][c] * f;
+    __shared__ float sf[16][65];   // [query][chunk]: 2^{c(m_c - M)} / L
+    __shared__ f32x4 sum[CG > 1 ? CG - 1 : 1][EPT][256];
+    if (cg == 0) {
+        // sixteen lanes a query: chunks mc, mc + 16, mc + 32, mc + 48 (at most 64 chunks, 16 with one thread group)
+        constexpr int NI = CG == 1 ? 1 : 4;
+        float m[NI], l[NI], M = -INFINITY, L = 0.f;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int c = mc + i * 16;
+            m[i] = -INFINITY; l[i] = 0.f;
+            if (c < n_chunks) {
+                const float2 ml = (i == 0 && ml_early) ? ml0 : a.part_ml[(item0 + c) * QMAX + nq * 16 + mq];
+                m[i] = ml.x; l[i] = ml.y;
+            }
+            M = fmaxf(M, m[i]);
         }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            m[i] = m[i] == -INFINITY ? 0.f : exp2f((m[i] - M) * a.c);
+            L += l[i] * m[i];
+        }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) L += __shfl_xor(L, o);
         const float inv = 1.0f / L;
-        for (int c = 0; c < n_chunks; ++c) sf[tid][c] *= inv;
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+            if (mc + i * 16 < n_chunks) sf[mq][mc + i * 16] = m[i] * inv;
     }
     __syncthreads();
+    f32x4 o[EPT];
 #pragma unroll
     for (int j = 0; j < EPT; ++j) {
         const int e = tid + j * 256, ql = e / V4, d4 = (e % V4) * 4, qi = nq * 16 + ql;
+        o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (qi >= QR) continue;
-        f32x4 o = {0.f, 0.f, 0.f, 0.f};
-        for (int c0 = 0; c0 < n_chunks; c0 += CU) {
+        for (int c0 = cg * CU; c0 < n_chunks; c0 += CG * CU) {
 #pragma unroll
             for (int u = 0; u < CU; ++u) {
-                const bool have = c0 == 0 && hc > 1 && u < hc && qi < hq;   // requested at the top
+                const bool have = c0 == cg * CU && hc > 1 && c0 + u < hc && qi < hq;   // requested at the top
                 if (!have && c0 + u < n_chunks) po[j][u] = *(const f32x4 *)(a.part_o + ((item0 + c0 + u) * QMAX + qi) * HD + d4);
             }
 #pragma unroll
             for (int u = 0; u < CU; ++u)
-                if (c0 + u < n_chunks) o += po[j][u] * sf[ql][c0 + u];
+                if (c0 + u < n_chunks) o[j] += po[j][u] * sf[ql][c0 + u];
         }
+    }
+    if constexpr (CG > 1) {
+        if (cg > 0) {
+#pragma unroll
+            for (int j = 0; j < EPT; ++j) sum[cg - 1][j][tid] = o[j];
+        }
+        __syncthreads();
+        if (cg > 0) return;
+#pragma unroll
+        for (int j = 0; j < EPT; ++j)
+#pragma unroll
+            for (int k = 0; k < CG - 1; ++k) o[j] += sum[k][j][tid];
+    }
+#pragma unroll
+    for (int j = 0; j < EPT; ++j) {
+        const int e = tid + j * 256, ql = e / V4, d4 = (e % V4) * 4, qi = nq * 16 + ql;
+        if (qi >= QR) continue;
         const int rl = qi / a.G, hg = qi % a.G;
         bf16_t *op = a.out + ((size_t)(row0 + rl) * a.Hq + hk * a.G + hg) * HD + d4;
-        *(uint2 *)op = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
+        *(uint2 *)op = make_uint2(pack_bf16(o[j][0], o[j][1]), pack_bf16(o[j][2], o[j][3]));
     }
 }
 
@@ -400,7 +436,9 @@ bool launch_attn_mfma(hipStream_t s, const sdlm_model_cfg *m, int max_seq_len, c
         if (two_staging) hipLaunchKernelGGL(attn_mfma_k<true>, dim3(max_groups, kg.n_kv_heads, a.max_chunks), dim3(256), 0, s, a);
         else hipLaunchKernelGGL(attn_mfma_k<false>, dim3(max_groups, kg.n_kv_heads, a.max_chunks), dim3(256), 0, s, a);
     }
-    else if (a.max_chunks > 1) hipLaunchKernelGGL(attn_combine_k, dim3(max_groups, kg.n_kv_heads, NQ), dim3(256), 0, s, a);
+    else if (a.max_chunks > 16) hipLaunchKernelGGL((attn_combine_k<4, 8>), dim3(max_groups, kg.n_kv_heads, NQ), dim3(1024), 0, s, a);
+    else if (a.max_chunks > 4) hipLaunchKernelGGL((attn_combine_k<1, 8>), dim3(max_groups, kg.n_kv_heads, NQ), dim3(256), 0, s, a);
+    else if (a.max_chunks > 1) hipLaunchKernelGGL((attn_combine_k<1, 4>), dim3(max_groups, kg.n_kv_heads, NQ), dim3(256), 0, s, a);
     return a.max_chunks > 1;
 }
 
