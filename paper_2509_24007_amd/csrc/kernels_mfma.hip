@@ -83,14 +83,16 @@ template <int MT, int NT> constexpr int w_sets() { return (MT >= 4) ? 2 : 3; }
 
 // WV wavefronts per workgroup: 4, or 8 (a 128-row x 512-column tile whose activation slice is staged once for eight
 // wavefronts instead of once for four: fewer bytes through the compute unit's load path per MFMA).
-template <int MT, int NT, int EPI, int WV = 4>
-__global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void gemm_mfma_k(MfmaArgs a)
+// KH = 2: the wavefronts form two halves that take a half of k each (gate/up with few column blocks, see choose); the halves'
+// sums meet in LDS before the epilogue.  The columns of a workgroup are then those of WV / 2 wavefronts.
+template <int MT, int NT, int EPI, int WV = 4, int KH = 1>
+__global__ __launch_bounds__(WV * 64, (WV == 8 || KH == 2 ? 1 : (MT == 4 ? 2 : 1))) void gemm_mfma_k(MfmaArgs a)
 {
     static_assert(WV == 4 || (WV == 8 && MT % 2 == 0), "eight wavefronts stage two 32-row sub-tiles per load round");
     // the activation slices; the LM head's epilogue afterwards turns its logits around in the same memory
-    constexpr size_t XS_BYTES = sizeof(bf16_t) * 2 * MT * 32 * XS_STRIDE, ZT_BYTES = EPI == EPI_LMHEAD ? sizeof(float) * WV * 32 * ZT_STRIDE : 0;
+    constexpr size_t XS_BYTES = sizeof(bf16_t) * 2 * KH * MT * 32 * XS_STRIDE, ZT_BYTES = EPI == EPI_LMHEAD ? sizeof(float) * WV * 32 * ZT_STRIDE : 0;
     __shared__ __attribute__((aligned(16))) unsigned char smem[XS_BYTES > ZT_BYTES ? XS_BYTES : ZT_BYTES];
-    auto Xs = reinterpret_cast<bf16_t (*)[MT * 32][XS_STRIDE]>(smem);
+    auto Xs = reinterpret_cast<bf16_t (*)[KH * MT * 32][XS_STRIDE]>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keeps the weight stream's base in SGPRs
     // workgroup id -> tile.  The grid has two parts: the row blocks that certainly hold rows (mblk < m_sure), then the
@@ -115,7 +117,10 @@ __global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void ge
     const int R = m0 + MT * 32 <= a.rows_sure ? a.rows_sure : min(*a.pR, a.max_rows);
     if (m0 >= R) return;
     const int KS = a.K >> 4, S = a.K >> 6;
-    const int s_begin = split * a.stages_per_split, s_end = min(S, s_begin + a.stages_per_split);
+    constexpr int CW = WV / KH;                                    // wavefronts side by side
+    const int cwave = wave % CW, half = KH == 1 ? 0 : wave / CW;   // column and k half of this wavefront
+    const int s_first = split * a.stages_per_split, s_count = min(S - s_first, a.stages_per_split);   // this split's slices; KH = 2: an even number
+    const int s_begin = s_first + half * (s_count / KH), s_end = s_begin + s_count / KH;
     if (s_begin >= s_end) return;
 
     // Addresses are (wave-uniform base) + (32-bit per-lane offset): the loads then take their base from SGPRs and
@@ -124,17 +129,19 @@ __global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void ge
     int ntile[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-        ntile[nt] = (nblk * WV + wave) * NT + nt;
+        ntile[nt] = (nblk * CW + cwave) * NT + nt;
         int tl = min(ntile[nt], a.n_tiles - 1);
         wp[nt] = a.Wp + ((size_t)tl * KS) * 512;
     }
     const uint32_t wlane = lane * 8;
-    // activation slice: MT*32 rows x 64 k = MT*256 16-byte chunks, XC per thread (a round of loads covers XR rows)
-    constexpr int XR = WV * 8, XC = MT * 32 / XR;
+    // activation slice: MT*32 rows x 64 k = MT*256 16-byte chunks, XC per thread (a round of loads covers XR rows); with two k
+    // halves a slice of each, rounds alternating between them
+    constexpr int XR = WV * 8, XC = KH * MT * 32 / XR;
     const int xrow = tid >> 3, xchunk = tid & 7;
     uint32_t xoff[XC];
 #pragma unroll
-    for (int i = 0; i < XC; ++i) xoff[i] = (uint32_t)min(m0 + i * XR + xrow, R - 1) * (uint32_t)a.K + xchunk * 8;
+    for (int i = 0; i < XC; ++i) xoff[i] = (uint32_t)min(m0 + i / KH * XR + xrow, R - 1) * (uint32_t)a.K + xchunk * 8 + (i % KH) * (s_count / KH) * 64;
+    constexpr auto xs_row = [](int i) { return i % KH * (MT * 32) + i / KH * XR; };   // LDS row where load round i begins
 
     f32x16 acc[NT][MT];
 #pragma unroll
@@ -163,18 +170,18 @@ __global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void ge
     }
 #define SDLM_LOAD_X(stage)                                                                                        \
     {                                                                                                             \
-        const size_t xo_ = (size_t)min((stage), s_last) * 64;                                                     \
+        const size_t xo_ = (size_t)(min((stage), s_last) - half * (s_count / KH)) * 64;                                                     \
         _Pragma("unroll") for (int i = 0; i < XCA_; ++i) xr[i] = *(const u32x4 *)(a.X + xo_ + xoff[i]);          \
     }
     constexpr int WSETS = w_sets<MT, NT>();
-    const int brow = lane & 31, bk = (lane >> 5) * 8;
+    const int brow = lane & 31, bk = (lane >> 5) * 8, lrow = half * (MT * 32) + brow;   // lrow: LDS row of the lane's operand
 /* ---- three weight sets (small tiles): one k-step = request the LDS operands of the next k-step, run this k-step's
    MFMAs, and pin that order; the slice's global loads are issued at its top */
 #define SDLM_KSTEP(WC, ks, has_next)                                                                              \
     {                                                                                                             \
         if (has_next) {                                                                                           \
             _Pragma("unroll") for (int mt = 0; mt < MTA_; ++mt)                                                  \
-                bn_[mt] = *(const bf16x8 *)&Xs[buf][mt * 32 + brow][((ks) + 1) * 16 + bk];                        \
+                bn_[mt] = *(const bf16x8 *)&Xs[buf][mt * 32 + lrow][((ks) + 1) * 16 + bk];                        \
         }                                                                                                         \
         _Pragma("unroll") for (int mt = 0; mt < MTA_; ++mt)                                                      \
             _Pragma("unroll") for (int nt = 0; nt < NT; ++nt)                                                    \
@@ -189,11 +196,11 @@ __global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void ge
         SDLM_LOAD_W(WN, (stage) + 2);                                                                             \
         __builtin_amdgcn_sched_barrier(0);                                                                        \
         bf16x8 bc_[MT], bn_[MT];                                                                                  \
-        _Pragma("unroll") for (int mt = 0; mt < MTA_; ++mt) bc_[mt] = *(const bf16x8 *)&Xs[buf][mt * 32 + brow][bk]; \
+        _Pragma("unroll") for (int mt = 0; mt < MTA_; ++mt) bc_[mt] = *(const bf16x8 *)&Xs[buf][mt * 32 + lrow][bk]; \
         __builtin_amdgcn_sched_group_barrier(0x100, MTA_, 0);                                                     \
         SDLM_KSTEP(WC, 0, 1) SDLM_KSTEP(WC, 1, 1) SDLM_KSTEP(WC, 2, 1) SDLM_KSTEP(WC, 3, 0)                       \
         __builtin_amdgcn_sched_barrier(0);                                                                        \
-        _Pragma("unroll") for (int i = 0; i < XCA_; ++i) *(u32x4 *)&Xs[buf ^ 1][i * XR + xrow][xchunk * 8] = xr[i]; \
+        _Pragma("unroll") for (int i = 0; i < XCA_; ++i) *(u32x4 *)&Xs[buf ^ 1][xs_row(i) + xrow][xchunk * 8] = xr[i]; \
         buf ^= 1;                                                                                                 \
         __syncthreads();                                                                                          \
     }
@@ -212,7 +219,7 @@ __global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void ge
     if constexpr ((mt) < MTA_) {                                                                                  \
         _Pragma("unroll") for (int nt = 0; nt < NT; ++nt)                                                        \
             acc[nt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(WC[nt][ks], bq_[mt], acc[nt][mt], 0, 0, 0);     \
-        bq_[mt] = *(const bf16x8 *)&Xs[SRC][(mt) * 32 + brow][(koff) + bk];                                       \
+        bq_[mt] = *(const bf16x8 *)&Xs[SRC][(mt) * 32 + lrow][(koff) + bk];                                       \
         __builtin_amdgcn_sched_group_barrier(0x020, (vm), 0);                                                     \
         __builtin_amdgcn_sched_group_barrier(0x008, NT, 0);                                                       \
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                                        \
@@ -221,17 +228,18 @@ __global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void ge
 #define SDLM_WVM(i) (((i) + 1) * 4 * NT / (2 * MTA_) - (i) * 4 * NT / (2 * MTA_))
 #define SDLM_KSTEP2(WC, ks, SRC, koff, VM)                                                                        \
     SDLM_SLOT(WC, ks, 0, SRC, koff, VM(0)) SDLM_SLOT(WC, ks, 1, SRC, koff, VM(1)) SDLM_SLOT(WC, ks, 2, SRC, koff, VM(2)) \
-    SDLM_SLOT(WC, ks, 3, SRC, koff, VM(3)) SDLM_SLOT(WC, ks, 4, SRC, koff, VM(4)) SDLM_SLOT(WC, ks, 5, SRC, koff, VM(5))
+    SDLM_SLOT(WC, ks, 3, SRC, koff, VM(3)) SDLM_SLOT(WC, ks, 4, SRC, koff, VM(4)) SDLM_SLOT(WC, ks, 5, SRC, koff, VM(5)) \
+    SDLM_SLOT(WC, ks, 6, SRC, koff, VM(6)) SDLM_SLOT(WC, ks, 7, SRC, koff, VM(7))
 #define SDLM_VM_W0(mt) SDLM_WVM(mt)
 #define SDLM_VM_W1(mt) SDLM_WVM(MTA_ + (mt))
-#define SDLM_VM_ONE(mt) ((mt) < XCA_ ? 1 : 0)
+#define SDLM_VM_ONE(mt) ((mt) < XCA_ / KH ? KH : 0)
 #define SDLM_VM_NONE(mt) 0
 #define SDLM_STAGE2(WC, WN, stage)                                                                                \
     {                                                                                                             \
         SDLM_LOAD_W(WN, (stage) + 1);                                                                             \
         SDLM_KSTEP2(WC, 0, buf, 16, SDLM_VM_W0) SDLM_KSTEP2(WC, 1, buf, 32, SDLM_VM_W1)                           \
         __builtin_amdgcn_sched_barrier(0);                                                                        \
-        _Pragma("unroll") for (int i = 0; i < XCA_; ++i) *(u32x4 *)&Xs[buf ^ 1][i * XR + xrow][xchunk * 8] = xr[i]; \
+        _Pragma("unroll") for (int i = 0; i < XCA_; ++i) *(u32x4 *)&Xs[buf ^ 1][xs_row(i) + xrow][xchunk * 8] = xr[i]; \
         __builtin_amdgcn_sched_barrier(0);                                                                        \
         SDLM_LOAD_X((stage) + 2);                                                                                 \
         SDLM_KSTEP2(WC, 2, buf, 48, SDLM_VM_ONE)                                                                  \
@@ -247,17 +255,17 @@ __global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void ge
    drain all outstanding loads at the loop head); the remaining slices are peeled. */
 #define SDLM_MAIN(MTA_VALUE)                                                                                      \
     {                                                                                                             \
-        constexpr int MTA_ = MTA_VALUE, XCA_ = (MTA_VALUE * 32 + XR - 1) / XR;   /* live sub-tiles; load rounds that cover them */ \
+        constexpr int MTA_ = MTA_VALUE, XCA_ = KH * ((MTA_VALUE * 32 + XR - 1) / XR);   /* live sub-tiles; load rounds that cover them */ \
         int buf = 0;                                                                                              \
         SDLM_LOAD_X(s_begin);                                                                                     \
         SDLM_LOAD_W(w0, s_begin);                                                                                 \
         if (WSETS == 3) SDLM_LOAD_W(w1, s_begin + 1);                                                             \
-        _Pragma("unroll") for (int i = 0; i < XCA_; ++i) *(u32x4 *)&Xs[0][i * XR + xrow][xchunk * 8] = xr[i];    \
+        _Pragma("unroll") for (int i = 0; i < XCA_; ++i) *(u32x4 *)&Xs[0][xs_row(i) + xrow][xchunk * 8] = xr[i];    \
         __syncthreads();                                                                                          \
         bf16x8 bq_[MT];                                                                                           \
         if constexpr (WSETS == 2) {   /* the pipelined slice expects its first fragments and the next activations */ \
             SDLM_LOAD_X(s_begin + 1);                                                                             \
-            _Pragma("unroll") for (int mt = 0; mt < MTA_; ++mt) bq_[mt] = *(const bf16x8 *)&Xs[0][mt * 32 + brow][bk]; \
+            _Pragma("unroll") for (int mt = 0; mt < MTA_; ++mt) bq_[mt] = *(const bf16x8 *)&Xs[0][mt * 32 + lrow][bk]; \
         }                                                                                                         \
         int s = s_begin;                                                                                          \
         if constexpr (WSETS == 3) {                                                                               \
@@ -275,11 +283,16 @@ __global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void ge
                 SDLM_STAGE2(w0, w1, s)                                                                            \
                 SDLM_STAGE2(w1, w0, s + 1)                                                                        \
             }                                                                                                     \
-            if (s < s_end) SDLM_STAGE2(w0, w1, s)                                                                 \
+            if constexpr (MT < 8) {   /* 256-row tiles: an even number of slices */                                \
+                if (s < s_end) SDLM_STAGE2(w0, w1, s)                                                             \
+            }                                                                                                     \
         }                                                                                                         \
     }
     const int mt_act = min(MT, (R - m0 + 31) >> 5);   // >= 1: m0 < R
-    if constexpr (MT == 6) {
+    if constexpr (MT == 8) {
+        if (mt_act == 8) SDLM_MAIN(8) else if (mt_act == 7) SDLM_MAIN(7) else if (mt_act == 6) SDLM_MAIN(6) else if (mt_act == 5) SDLM_MAIN(5)
+        else if (mt_act == 4) SDLM_MAIN(4) else if (mt_act == 3) SDLM_MAIN(3) else if (mt_act == 2) SDLM_MAIN(2) else SDLM_MAIN(1)
+    } else if constexpr (MT == 6) {
         if (mt_act == 6) SDLM_MAIN(6) else if (mt_act == 5) SDLM_MAIN(5) else if (mt_act == 4) SDLM_MAIN(4) else if (mt_act == 3) SDLM_MAIN(3)
         else if (mt_act == 2) SDLM_MAIN(2) else SDLM_MAIN(1)
     } else if constexpr (MT == 4) {
@@ -303,6 +316,32 @@ __global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void ge
 #undef SDLM_LOAD_W
 #undef SDLM_LOAD_X
 
+    if constexpr (KH == 2) {
+        // each half finishes every other 32-row sub-tile: it hands the other ones over and adds what it is handed
+        static_assert(KH == 1 || (MT + 1) / 2 * NT * 4096 * WV <= (int)XS_BYTES, "the halves' exchange reuses the activation slices' memory");
+        float *px = reinterpret_cast<float *>(smem);
+        __syncthreads();
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+            if ((mt & 1) != half && mt < mt_act)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *(float4 *)&px[((((wave * ((MT + 1) / 2) + mt / 2) * NT + nt) * 4 + q) * 64 + lane) * 4] =
+                            make_float4(acc[nt][mt][q * 4], acc[nt][mt][q * 4 + 1], acc[nt][mt][q * 4 + 2], acc[nt][mt][q * 4 + 3]);
+        __syncthreads();
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+            if ((mt & 1) == half && mt < mt_act)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float4 o = *(const float4 *)&px[(((((wave ^ CW) * ((MT + 1) / 2) + mt / 2) * NT + nt) * 4 + q) * 64 + lane) * 4];
+                        acc[nt][mt][q * 4] += o.x; acc[nt][mt][q * 4 + 1] += o.y; acc[nt][mt][q * 4 + 2] += o.z; acc[nt][mt][q * 4 + 3] += o.w;
+                    }
+    }
     // accumulator element v of lane l: output feature 8*(v/4) + 4*(l/32) + v%4 of the tile, activation row l%32
     const int fbase = (lane >> 5) * 4;
     if (EPI == EPI_STORE_F32 || EPI == EPI_RESID) {
@@ -344,7 +383,7 @@ __global__ __launch_bounds__(WV * 64, (WV == 8 ? 1 : (MT == 4 ? 2 : 1))) void ge
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
                 int r = m0 + mt * 32 + brow;
-                if (r >= R) continue;
+                if (r >= R || (KH == 2 && (mt & 1) != half)) continue;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     int n = j * 32 + q * 8 + fbase;
@@ -708,7 +747,7 @@ void launch_qkv_rope_skinny(hipStream_t s, const sdlm_model_cfg *m, const void *
 }
 
 // ------------------------------------------------------------------------------------------------ launch policy
-struct TileChoice { int MT, NT, splits, WV; };
+struct TileChoice { int MT, NT, splits, WV, KH; };
 
 static int sure_blocks(int rows, int min_rows, int MT)
 {
@@ -725,6 +764,7 @@ static TileChoice choose(int epi, int rows, int min_rows, int N, int K, size_t s
     c.MT = rows <= 32 ? 1 : rows <= 64 ? 2 : 4;
     c.NT = 2;
     c.WV = 4;
+    c.KH = 1;
     // Gate/up with 129..192 certain rows and enough column blocks for one workgroup on (nearly) every compute unit: one
     // 192-row block per column block, so that no weight band is streamed by two workgroups.  (For the split-k
     // projections the same tile was measured: it wants more splits, and the slab traffic costs more than it saves.)
@@ -770,10 +810,29 @@ static TileChoice choose(int epi, int rows, int min_rows, int N, int K, size_t s
     return c;
 }
 
+// Gate/up launches of 33 .. 256 rows whose shape `choose` does not serve well (K a multiple of 128):
+//   * Up to 128 rows and at most 256 column blocks of 64 features: workgroups of 128 x 64 features whose wavefronts take half of k
+//     each.  Bound by the weights in flight: F / 128 workgroups of the plain tile leave most compute units without any (h = 2048,
+//     F = 11008: 86 workgroups); half the columns double the workgroups, and k in halves keeps four wavefronts in each.
+//     h = 2048, F = 11008: 66 rows 32.9 -> 24.4 us, 48 rows 35.6 -> 24.8; h = 1536, F = 8960: 96 rows 24.5 -> 19.7, 48 rows 27.4 ->
+//     18.9.  Beyond 128 rows (192- and 256-row tiles in halves: 160 rows 31.8 -> 32.5) and for the split-k projections (160 rows,
+//     QKV 11.8 -> 19.4, O 8.8 -> 14.0, down 20.8 -> 23.4) the activations' share of the load path takes it back; with more
+//     than 256 column blocks the plain tile already occupies the chip.
+//   * Where `choose` takes the 192-row tile and the step may have more rows: a 256-row tile, so that the rows beyond 192 are not a second
+//     row block that streams every weight again.  h = 5120, F = 27648, 193..224 rows: 205.6 -> 131.8 us.  (Its 256 accumulator
+//     registers leave room for the operands only with an even number of slices, without a peeled last one.)
+static void refine_gateup(int rows, int N, int K, TileChoice *c)
+{
+    if (K % 128) return;
+    if (rows > 32 && rows <= 128 && (N + 63) / 64 <= 256) { c->KH = 2; c->MT = rows <= 64 ? 2 : 4; c->NT = 2; c->WV = 4; }
+    else if (c->MT == 6 && rows > 192) c->MT = 8;
+}
+
 template <int EPI>
 static void launch_cfg(hipStream_t s, const TileChoice &c, MfmaArgs &a, int min_rows)
 {
-    a.n_blocks = (a.n_tiles + c.WV * c.NT - 1) / (c.WV * c.NT);
+    const int per_wg = c.WV / c.KH * c.NT;
+    a.n_blocks = (a.n_tiles + per_wg - 1) / per_wg;
     a.m_blocks = (a.max_rows + c.MT * 32 - 1) / (c.MT * 32);
     a.splits = c.splits;
     int S = a.K / 64;
@@ -782,6 +841,14 @@ static void launch_cfg(hipStream_t s, const TileChoice &c, MfmaArgs &a, int min_
     a.rows_sure = min_rows < 0 ? 0 : (min_rows > a.max_rows ? a.max_rows : min_rows);
     const int first = a.n_blocks * a.splits * a.m_sure, rest = a.n_blocks * a.splits * (a.m_blocks - a.m_sure);
     dim3 grid((first + 7) / 8 * 8 + (rest + 7) / 8 * 8), block(c.WV * 64);
+    if constexpr (EPI == EPI_SWIGLU) {
+        if (c.KH == 2) {
+            if (c.MT == 2) hipLaunchKernelGGL((gemm_mfma_k<2, 2, EPI, 4, 2>), grid, block, 0, s, a);
+            else hipLaunchKernelGGL((gemm_mfma_k<4, 2, EPI, 4, 2>), grid, block, 0, s, a);
+            return;
+        }
+        if (c.MT == 8) { hipLaunchKernelGGL((gemm_mfma_k<8, 2, EPI>), grid, block, 0, s, a); return; }
+    }
 #define SDLM_GO(MT_, NT_) hipLaunchKernelGGL((gemm_mfma_k<MT_, NT_, EPI>), grid, block, 0, s, a)
     if (EPI == EPI_SWIGLU || EPI == EPI_LMHEAD || c.NT == 2) {
         if (c.MT == 1) SDLM_GO(1, 2); else if (c.MT == 2) SDLM_GO(2, 2); else if (c.MT == 6 && EPI == EPI_SWIGLU) hipLaunchKernelGGL((gemm_mfma_k<(EPI == EPI_SWIGLU ? 6 : 4), 2, EPI>), grid, block, 0, s, a);
@@ -815,6 +882,7 @@ int launch_gemm_mfma(hipStream_t s, int epi, const GemmArgs &g, float *slabs, si
         return 1;
     }
     TileChoice c = choose(epi, g.max_rows, g.min_rows, g.N, g.K, slab_room_floats);
+    if (epi == EPI_SWIGLU) refine_gateup(g.max_rows, g.N, g.K, &c);
     a.slab = (size_t)g.max_rows * g.N;
     if (c.splits > 1) a.Yf = slabs;
     switch (epi) {

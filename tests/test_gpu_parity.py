@@ -654,6 +654,58 @@ def test_bf16_gate_up_of_at_most_32_rows(B, D, hidden, ffn):
     ctx.close()
 
 
+@pytest.mark.parametrize("B,D,hidden,ffn", [(5, 4, 128, 2112), (8, 4, 1408, 1088), (13, 4, 384, 2112), (16, 4, 1024, 192), (26, 4, 256, 24640), (32, 4, 128, 24576)])
+def test_bf16_gate_up_of_33_to_256_rows(B, D, hidden, ffn):
+    """The gate/up shapes between the small-step kernel and the 128-row tiles: k in two halves inside a workgroup (one slice,
+    an odd number and many slices per half; up to 64 and up to 128 rows, a ragged last column block), and the 256-row tile (more
+    than 128 certain rows, wide matrix; the step after a full commit has B * 2D rows, the one after single tokens B * (D + 1))."""
+    m = mfma_cfg(n_layers=1, n_q_heads=4, n_kv_heads=2, hidden=hidden, ffn=ffn, vocab=1000, has_qkv_bias=True)
+    om, g_dev, layers_dev = both_models(m, seed=80 + B, std=0.03)
+    lens = [3 + 5 * (i % 6) for i in range(B)]
+    prompts = [syn.uniform_int(6, f"gu{i}", n, 0, m.vocab - 1).numpy() for i, n in enumerate(lens)]
+    steps = 4
+    ids, cnt = syn.make_overrides(22, steps, B, D, m.vocab)
+    cnt = cnt.clone()
+    cnt[0] = D
+    cnt[1] = 1
+    max_len = max(lens) + steps * D + D
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=B, max_seq_len=max_len, D=D, tau=0.5)
+    st, _ = lockstep(ctx, om, prompts, D, 0.5, steps, logit_tol=2e-2, conf_tol=1e-3, overrides=(ids, cnt), bf16=True, max_len=max_len)
+    print("gate/up 33..256 rows", (B, D, hidden, ffn), st)
+    ctx.close()
+
+
+@pytest.mark.parametrize("B,D,vocab", [(1, 1, 33), (1, 4, 1001), (3, 5, 257), (9, 7, 999), (11, 16, 2050)])
+def test_bf16_requested_logits_rows_and_ragged_vocabulary(B, D, vocab):
+    """Requested logits leave the LM head as whole rows: every row-tile height, row counts beside a multiple of 32, vocabularies
+    that end inside a wavefront's 64 entries, and nothing written outside the caller's [B * D, V]."""
+    m = mfma_cfg(n_layers=1, hidden=128, ffn=192, vocab=vocab)
+    om, g_dev, layers_dev = both_models(m, seed=90 + B, std=0.05)
+    prompts = [syn.uniform_int(7, f"lg{i}", 2 + i, 0, vocab - 1).numpy() for i in range(B)]
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=B, max_seq_len=64, D=D, tau=0.5)
+    lockstep(ctx, om, prompts, D, 0.5, 1, logit_tol=2e-2, conf_tol=1e-3, bf16=True, max_len=64)
+    guard = torch.full((B * D + 2, vocab), -7.0, device="cuda")
+    ids = torch.empty(B, D, dtype=torch.int32, device="cuda")
+    cnt = torch.empty(B, dtype=torch.int32, device="cuda")
+    ctx.decode_step(ids, cnt, None, guard[1:-1])
+    torch.cuda.synchronize()
+    assert (guard[0] == -7.0).all() and (guard[-1] == -7.0).all() and (guard[1:-1] != -7.0).all()
+    ctx.close()
+
+
+@pytest.mark.parametrize("prompt", [100, 500, 640, 1500, 2100])
+def test_bf16_split_kv_merge_by_number_of_chunks(prompt):
+    """The split-KV merge of one sequence with 1 .. 17 chunks of 128 keys (variants for up to 4, 16 and 64): logits against the oracle."""
+    m = mfma_cfg(n_layers=1, n_q_heads=4, n_kv_heads=2, hidden=128, ffn=192, vocab=1000)
+    om, g_dev, layers_dev = both_models(m, seed=95, std=0.08)
+    p = syn.uniform_int(8, f"mg{prompt}", prompt, 0, m.vocab - 1).numpy()
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=1, max_seq_len=prompt + 32, D=4, tau=0.5)
+    # flips: each one is bounded by its row's own measured logit error inside lockstep; a share of 8 rows has no meaning (random
+    # logits: the top-2 gap is below twice a 6e-3 error in one row out of ten, so 2 of 8 occurs in one prompt out of five)
+    lockstep(ctx, om, [p], 4, 0.5, 2, logit_tol=2e-2, conf_tol=1e-3, bf16=True, max_len=prompt + 32, flip_ceiling=1.0)
+    ctx.close()
+
+
 @pytest.mark.parametrize("hidden", [4100, 8200, 16384])
 def test_fp32_wide_hidden_rows(hidden):
     """Rows wider than 4096 elements: the RMSNorm variants that hold 8 and 16 vectors of a row per thread (and the
