@@ -21,6 +21,7 @@ namespace sdlm {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 constexpr int XS_STRIDE = 72;   // bf16 elements per LDS row of the activation slice (64 + 8 padding)
@@ -544,18 +545,17 @@ __global__ __launch_bounds__(256) void lm_combine_k(const float4 *part, int n_bl
     }
 }
 
-// ------------------------------------------------------------------------------------------------ gate/up for <= 32 rows
-// The step of a single sequence has at most 2D <= 32 rows, and the gate/up projection cannot be split along k between
-// workgroups (SiLU(gate) * up needs complete sums): the tiled kernel above would run it as N/128 workgroups, far too
-// few to keep the weight stream busy.  Here a workgroup owns one 32-feature block (its gate tile and its up tile),
-// its four wavefronts each take a quarter of k, and the quarters are added in wavefront order through LDS.  Both
-// operands come straight from global memory in the MFMA operand order: the weights as a contiguous run, the rows
-// (at most 32 x K, shared by every workgroup, so served by L2) 16 bytes per lane and k step; rows beyond the live
-// ones repeat the last row and their results are dropped.  Loads are issued eight k steps at a time into two register
+// ------------------------------------------------------------------------------------------------ gate/up for 17 .. 32 rows
+// A step of at most 32 rows cannot split the gate/up projection along k between workgroups (SiLU(gate) * up needs complete
+// sums): the tiled kernel above would run it as N/128 workgroups, far too few to keep the weight stream busy.  Here a workgroup
+// owns one 32-feature block (its gate tile and its up tile), its four wavefronts each take a quarter of k, and the quarters are
+// added in wavefront order through LDS.  Both operands come straight from global memory in the MFMA operand order: the weights as a
+// contiguous run, the rows (at most 32 x K, shared by every workgroup, so served by L2) 16 bytes per lane and k step; rows beyond
+// the live ones repeat the last row and their results are dropped.  Loads are issued eight k steps at a time into two register
 // sets: sixteen k steps (48 KB per wavefront) are in flight before the first MFMA.
 constexpr int SK_U = 8, SK_W = 4;   // k steps per register set; wavefronts (measured: eight wavefronts are slower)
 
-__global__ __launch_bounds__(SK_W * 64) void swiglu_skinny_k(MfmaArgs a)
+__global__ __launch_bounds__(SK_W * 64) void swiglu_skinny32_k(MfmaArgs a)
 {
     __shared__ float part[SK_W][2][16][64];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -616,14 +616,143 @@ __global__ __launch_bounds__(SK_W * 64) void swiglu_skinny_k(MfmaArgs a)
     else *(uint32_t *)dst = pack_bf16(o[0], o[EL - 1]);
 }
 
-// ------------------------------------------------------------------------------------------------ QKV + RoPE + K/V placement for <= 32 rows
-// For steps of at most 32 rows (a single sequence, or a few with small blocks) the QKV projection, the rotation and the
-// K/V placement are one kernel: such steps are bound by their kernel boundaries, and here the projection needs no split
-// along k between workgroups, so its epilogue sees complete sums.  Same scheme as the gate/up kernel above: a workgroup
-// owns two 32-feature tiles, here features [32 t, 32 t + 32) and the same range 64 further on of one head, i.e. both
-// members of every rotate-half pair (i, i + d/2); its four wavefronts each take a quarter of k and the quarters are added
-// in wavefront order through LDS.  The epilogue is the RoPE + K/V placement kernel's: queries and keys rotated at the
-// row's position, a pending row's K/V to the cache slot of its position, any other row's to slot `kind` of its staging tile.
+// ------------------------------------------------------------------------------------------------ steps of few rows
+// The step of a single sequence, or of a few with small blocks, has at most 16 or 32 rows.  Its products are weight streams and
+// nothing else, bound by how evenly the stream is dealt out to the compute units and by how much of it is requested at
+// once.  They share one inner loop: a workgroup owns two 16-feature tiles, its four wavefronts each take a quarter of its k range,
+// and the quarters are added in wavefront order through LDS.  Both operands come straight from global memory in the order of
+// v_mfma_f32_16x16x32_bf16: a 16-feature half of a packed 32 x 16 tile pair is four runs of 256 bytes per load, the rows (shared by
+// every workgroup, so served by L2) are 64-byte pieces; rows beyond the live ones repeat the last row and their results are
+// dropped.  NB = 1 serves at most 16 rows, NB = 2 at most 32.  Against workgroups of 32-feature tiles (the tiled kernel for O and
+// down, which also stages the rows in LDS slice by slice), before -> after, up to 8 live rows:
+//   h = 1536, F = 8960    QKV 9.7 -> 6.6 us, O 5.4 -> 4.4, down 9.4 -> 7.2, gate/up 16.2 -> 14.7
+//   h = 3584, F = 18944   QKV 17.8 -> 12.0,  O 8.0 -> 7.2, down 26.7 -> 28.5 (the one that loses, with a quarter of the slabs), gate/up 53.4 -> 51.5
+//   h = 5120, F = 27648   QKV 24 -> 17.0 us, O and down 66.4 -> 62.3 (5.1 TB/s), gate/up 102.5 -> 99.9 (5.7 TB/s)
+// With 17 to 32 rows the rows' requests double: QKV, whose 2 x 32-feature workgroups were fewest, still gains (h = 2048 12.9 -> 10.7 us,
+// h = 5120 28.4 -> 22.4); gate/up (h = 5120 115 -> 130) and down (h = 3584 27.6 -> 38) lose and keep their kernels.
+constexpr int sk_u(int NB) { return NB == 1 ? 8 : 6; }   // k steps (of 32) per register set: two wavefronts per SIMD
+
+// Products of the features whose first elements `wa` and `wb` point to (each the start of a 16-feature half of a packed tile)
+// with the rows of X, over k steps [k_begin, k_end); steps beyond k_end repeat the last one.  `with_rows` runs after
+// the row count is known and the first operands are requested: the caller's own requests go there.  Returns the row count.
+// Result: element v of lane l is feature 4 * (l / 16) + v of the tile, row 16 * nb + l % 16.
+template <int NB, class F>
+__device__ inline int skinny_dot(const bf16_t *wa, const bf16_t *wb, const bf16_t *X, const int32_t *pR, int max_rows, int K, int k_begin, int k_end,
+                                 int lane, f32x4 (&aa)[NB], f32x4 (&ab)[NB], F with_rows)
+{
+    constexpr int U = sk_u(NB);
+    const int k_last = max(k_end, 1) - 1;   // a wavefront without any k step still requests within the matrix
+    // lane -> k half of the step's 32 (lane / 32), 8 of 16 (lane / 16 % 2), feature (lane % 16)
+    const uint32_t wl = (lane >> 5) * 512 + ((lane & 15) + ((lane >> 4) & 1) * 32) * 8;
+    bf16x8 a0[U], b0[U], x0[NB][U], a1[U], b1[U], x1[NB][U];
+    const bf16_t *xp[NB];
+    auto load_w = [&](bf16x8 (&A)[U], bf16x8 (&B)[U], int k) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const size_t o = (size_t)min(k + u, k_last) * 1024;
+            A[u] = *(const bf16x8 *)(wa + o + wl);
+            B[u] = *(const bf16x8 *)(wb + o + wl);
+        }
+    };
+    auto load_x = [&](bf16x8 (&Xr)[NB][U], int k) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) Xr[nb][u] = *(const bf16x8 *)(xp[nb] + min(k + u, k_last) * 32);
+    };
+    auto mma = [&](const bf16x8 (&A)[U], const bf16x8 (&B)[U], const bf16x8 (&Xr)[NB][U], int k) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (k + u < k_end) {
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    aa[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[u], Xr[nb][u], aa[nb], 0, 0, 0);
+                    ab[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[u], Xr[nb][u], ab[nb], 0, 0, 0);
+                }
+            }
+    };
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) { aa[nb] = f32x4{0.f, 0.f, 0.f, 0.f}; ab[nb] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+    load_w(a0, b0, k_begin);   // the weights do not wait for the row count
+    if (k_begin + U < k_end) load_w(a1, b1, k_begin + U);
+    const int R = min(*pR, max_rows);
+    if (R <= 0) return 0;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) xp[nb] = X + (size_t)min(nb * 16 + (lane & 15), R - 1) * K + (lane >> 4) * 8;
+    load_x(x0, k_begin);
+    if (k_begin + U < k_end) load_x(x1, k_begin + U);
+    with_rows(R);
+    for (int k = k_begin; k < k_end; k += 2 * U) {
+        mma(a0, b0, x0, k);
+        if (k + 2 * U < k_end) { load_w(a0, b0, k + 2 * U); load_x(x0, k + 2 * U); }
+        mma(a1, b1, x1, k + U);
+        if (k + 3 * U < k_end) { load_w(a1, b1, k + 3 * U); load_x(x1, k + 3 * U); }
+    }
+    return R;
+}
+
+// The four quarters of k, added in wavefront order.  Wavefront nb < NB finishes rows 16 nb .. 16 nb + 15; the others return false.
+template <int NB>
+__device__ inline bool skinny_sum(f32x4 (&part)[SK_W][2][NB][64], const f32x4 (&aa)[NB], const f32x4 (&ab)[NB], int wave, int lane, f32x4 &sa, f32x4 &sb)
+{
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) { part[wave][0][nb][lane] = aa[nb]; part[wave][1][nb][lane] = ab[nb]; }
+    __syncthreads();
+    if (wave >= NB) return false;
+    sa = part[0][0][wave][lane]; sb = part[0][1][wave][lane];
+#pragma unroll
+    for (int w = 1; w < SK_W; ++w) { sa += part[w][0][wave][lane]; sb += part[w][1][wave][lane]; }
+    return true;
+}
+
+// Gate/up: SiLU(gate) * up needs complete sums, so k cannot be split between workgroups; a workgroup owns 16 features.
+__global__ __launch_bounds__(SK_W * 64) void swiglu_skinny16_k(MfmaArgs a)
+{
+    constexpr int NB = 1;
+    __shared__ f32x4 part[SK_W][2][NB][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j = blockIdx.x >> 1, h = blockIdx.x & 1;   // features 32 j + 16 h ..: halves of tiles 2j (gate) and 2j + 1 (up) of the fused matrix
+    const int KS = a.K >> 4, K32 = a.K >> 5, per = (K32 + SK_W - 1) / SK_W;
+    const bf16_t *wg = a.Wp + ((size_t)(2 * j) * KS) * 512 + h * 128;
+    f32x4 ag[NB], au[NB], gs, us;
+    const int R = skinny_dot<NB>(wg, wg + (size_t)KS * 512, a.X, a.pR, a.max_rows, a.K, wave * per, min(K32, wave * per + per), lane, ag, au, [](int) {});
+    if (R <= 0 || !skinny_sum<NB>(part, ag, au, wave, lane, gs, us)) return;
+    const int row = wave * 16 + (lane & 15), n = j * 32 + h * 16 + (lane >> 4) * 4;
+    if (row >= R || n >= a.N) return;
+    float o[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = silu_f(gs[e]) * us[e];
+    *(uint2 *)(a.Yt + (size_t)row * a.n_out + n) = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
+}
+
+// O and down projection: a workgroup owns a packed tile's 32 features and one of `splits` ranges of k; slabs as in the tiled kernel.
+__global__ __launch_bounds__(SK_W * 64) void resid_skinny_k(MfmaArgs a)
+{
+    constexpr int NB = 1;
+    __shared__ f32x4 part[SK_W][2][NB][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tile = blockIdx.x / a.splits, split = blockIdx.x % a.splits;
+    const int K32 = a.K >> 5, k0 = (int)((long)K32 * split / a.splits), k1 = (int)((long)K32 * (split + 1) / a.splits), per = (k1 - k0 + SK_W - 1) / SK_W;
+    const int kb = min(k1, k0 + wave * per);
+    const bf16_t *w = a.Wp + (size_t)tile * (a.K >> 4) * 512;
+    f32x4 aa[NB], ab[NB], s[2];
+    const int R = skinny_dot<NB>(w, w + 128, a.X, a.pR, a.max_rows, a.K, kb, min(k1, kb + per), lane, aa, ab, [](int) {});
+    if (R <= 0 || !skinny_sum<NB>(part, aa, ab, wave, lane, s[0], s[1])) return;
+    const int row = wave * 16 + (lane & 15);
+    if (row >= R) return;
+    float *dst = a.Yf + (a.splits > 1 ? (size_t)split * a.slab : 0) + (size_t)row * a.n_out + tile * 32 + (lane >> 4) * 4;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        f32x4 *p = (f32x4 *)(dst + t * 16);
+        if (a.splits > 1) *p = s[t]; else *p += s[t];
+    }
+}
+
+// QKV projection, rotation and K/V placement in one kernel: such steps are bound by their kernel boundaries, and here the
+// projection needs no split along k between workgroups, so its epilogue sees complete sums.  A workgroup owns features
+// [16 t, 16 t + 16) and the same range 64 further on of one head, i.e. both members of every rotate-half pair (i, i + d/2).  The
+// epilogue is the RoPE + K/V placement kernel's: queries and keys rotated at the row's position, a pending row's K/V to the cache
+// slot of its position, any other row's to slot `kind` of its staging tile.
 struct QkvSkinnyArgs {
     const bf16_t *X, *Wp, *bias;
     const int32_t *pR;
@@ -635,78 +764,41 @@ struct QkvSkinnyArgs {
     const float2 *rope;
 };
 
-constexpr int QK_U = 12;   // k steps per register set: two sets cover a quarter of k = 1536 at once (one memory round trip)
-
+template <int NB>
 __global__ __launch_bounds__(SK_W * 64) void qkv_rope_skinny_k(QkvSkinnyArgs a)
 {
-    __shared__ float part[SK_W][2][16][64];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int head = blockIdx.x >> 1, hh = blockIdx.x & 1;   // heads: Hq of q, then Hkv of k, then Hkv of v; hh: which 32 of the first 64 features
-    const int KS = a.K >> 4, per = (KS + SK_W - 1) / SK_W;
-    const int k_begin = wave * per, k_end = min(KS, k_begin + per);
-    const bf16_t *wa = a.Wp + ((size_t)(head * 4 + hh) * KS) * 512 + lane * 8, *wb = wa + (size_t)2 * KS * 512;
-    bf16x8 g0[QK_U], u0[QK_U], x0[QK_U], g1[QK_U], u1[QK_U], x1[QK_U];
-#define SDLM_SK_LOAD_W(G, U, kb) \
-    _Pragma("unroll") for (int u = 0; u < QK_U; ++u) { \
-        const size_t o = (size_t)min((kb) + u, KS - 1) * 512; \
-        G[u] = *(const bf16x8 *)(wa + o); U[u] = *(const bf16x8 *)(wb + o); }
-#define SDLM_SK_LOAD_X(X, kb) \
-    _Pragma("unroll") for (int u = 0; u < QK_U; ++u) X[u] = *(const bf16x8 *)(xp + min((kb) + u, KS - 1) * 16);
-#define SDLM_SK_MMA(G, U, X, kb) \
-    _Pragma("unroll") for (int u = 0; u < QK_U; ++u) if ((kb) + u < k_end) { \
-        aa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(G[u], X[u], aa, 0, 0, 0); \
-        ab = __builtin_amdgcn_mfma_f32_32x32x16_bf16(U[u], X[u], ab, 0, 0, 0); }
-    SDLM_SK_LOAD_W(g0, u0, k_begin)   // the weights do not wait for the row count
-    if (k_begin + QK_U < k_end) { SDLM_SK_LOAD_W(g1, u1, k_begin + QK_U) }
-    const int R = min(*a.pR, a.max_rows);
-    if (R <= 0) return;
-    const int row = lane & 31, rr = min(row, R - 1);
-    const int pos = a.rm.pos[rr], kind = a.rm.kind[rr], b = a.rm.seq[rr], stg = a.rm.stg[rr];   // requested with the operands
-    const bf16_t *xp = a.X + (size_t)rr * a.K + (lane >> 5) * 8;
-    SDLM_SK_LOAD_X(x0, k_begin)
-    if (k_begin + QK_U < k_end) { SDLM_SK_LOAD_X(x1, k_begin + QK_U) }
-    // what the epilogue needs beside the sums is requested now as well: rotation factors, bias, the page of a cached position
+    __shared__ f32x4 part[SK_W][2][NB][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int head = blockIdx.x >> 2, t16 = blockIdx.x & 3;   // heads: Hq of q, then Hkv of k, then Hkv of v; t16: which 16 of the first 64 features
+    const int KS = a.K >> 4, K32 = a.K >> 5, per = (K32 + SK_W - 1) / SK_W;
+    const bf16_t *wa = a.Wp + ((size_t)(head * 4 + (t16 >> 1)) * KS) * 512 + (t16 & 1) * 128;
     const int d = a.kg.head_dim, half = d >> 1, Hk = a.kg.n_kv_heads;
-    const int i0 = hh * 32 + wave * 8 + (lane >> 5) * 4;   // this lane's four features: index within the first half of the head
+    const int i0 = t16 * 16 + (lane >> 4) * 4;   // this lane's four features: index within the first half of the head
     const bool is_q = head < a.Hq, is_v = head >= a.Hq + Hk;
+    const int row = wave * 16 + (lane & 15);
     float2 t[4];
     float blo[4] = {0.f, 0.f, 0.f, 0.f}, bhi[4] = {0.f, 0.f, 0.f, 0.f};
+    int page = -1, slot = 0;
+    f32x4 aa[NB], ab[NB], sa, sb;
+    // what the epilogue needs beside the sums is requested with the operands: rotation factors, bias, the page of a cached position
+    const int R = skinny_dot<NB>(wa, wa + (size_t)2 * KS * 512, a.X, a.pR, a.max_rows, a.K, wave * per, min(K32, wave * per + per), lane, aa, ab, [&](int rows) {
+        if (wave >= NB) return;
+        const int rr = min(row, rows - 1), pos = a.rm.pos[rr], kind = a.rm.kind[rr], b = a.rm.seq[rr], stg = a.rm.stg[rr];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        t[e] = is_v ? make_float2(1.f, 0.f) : a.rope[(size_t)pos * half + i0 + e];
-        if (a.bias) { blo[e] = bf16_to_f(a.bias[head * d + i0 + e]); bhi[e] = bf16_to_f(a.bias[head * d + half + i0 + e]); }
-    }
-    int page = stg, slot = kind;
-    if (!is_q && kind < 0) { page = a.st.page_table[(size_t)b * a.kg.pages_per_seq + pos / PAGE]; slot = pos % PAGE; }
-    f32x16 aa, ab;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) { aa[v] = 0.f; ab[v] = 0.f; }
-    for (int k0 = k_begin; k0 < k_end; k0 += 2 * QK_U) {
-        SDLM_SK_MMA(g0, u0, x0, k0)
-        if (k0 + 2 * QK_U < k_end) { SDLM_SK_LOAD_W(g0, u0, k0 + 2 * QK_U) SDLM_SK_LOAD_X(x0, k0 + 2 * QK_U) }
-        SDLM_SK_MMA(g1, u1, x1, k0 + QK_U)
-        if (k0 + 3 * QK_U < k_end) { SDLM_SK_LOAD_W(g1, u1, k0 + 3 * QK_U) SDLM_SK_LOAD_X(x1, k0 + 3 * QK_U) }
-    }
-#undef SDLM_SK_LOAD_W
-#undef SDLM_SK_LOAD_X
-#undef SDLM_SK_MMA
-#pragma unroll
-    for (int v = 0; v < 16; ++v) { part[wave][0][v][lane] = aa[v]; part[wave][1][v][lane] = ab[v]; }
-    __syncthreads();
-    // accumulator element v of lane l: feature 8*(v/4) + 4*(l/32) + v%4 of the tile, activation row l%32; wavefront w
-    // finishes elements 4w .. 4w+3 of every lane: four consecutive features of one row, and their partners 64 further on
-    static_assert(SK_W == 4, "one wavefront finishes four consecutive features");
-    if (row >= R) return;
+        for (int e = 0; e < 4; ++e) {
+            t[e] = is_v ? make_float2(1.f, 0.f) : a.rope[(size_t)pos * half + i0 + e];
+            if (a.bias) { blo[e] = bf16_to_f(a.bias[head * d + i0 + e]); bhi[e] = bf16_to_f(a.bias[head * d + half + i0 + e]); }
+        }
+        page = stg; slot = kind;
+        if (!is_q && kind < 0) { page = a.st.page_table[(size_t)b * a.kg.pages_per_seq + pos / PAGE]; slot = pos % PAGE; }
+    });
+    if (R <= 0 || !skinny_sum<NB>(part, aa, ab, wave, lane, sa, sb) || row >= R) return;
     float lo[4], hi[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        float sa = part[0][0][wave * 4 + e][lane], sb = part[0][1][wave * 4 + e][lane];
-#pragma unroll
-        for (int w = 1; w < SK_W; ++w) { sa += part[w][0][wave * 4 + e][lane]; sb += part[w][1][wave * 4 + e][lane]; }
-        sa += blo[e]; sb += bhi[e];
-        lo[e] = is_v ? sa : sa * t[e].x - sb * t[e].y;
-        hi[e] = is_v ? sb : sb * t[e].x + sa * t[e].y;
+        const float va = sa[e] + blo[e], vb = sb[e] + bhi[e];
+        lo[e] = is_v ? va : va * t[e].x - vb * t[e].y;
+        hi[e] = is_v ? vb : vb * t[e].x + va * t[e].y;
     }
     if (is_q) {
         bf16_t *q = a.q_out + ((size_t)row * a.Hq + head) * d + i0;
@@ -743,10 +835,25 @@ void launch_qkv_rope_skinny(hipStream_t s, const sdlm_model_cfg *m, const void *
     a.X = (const bf16_t *)X; a.Wp = (const bf16_t *)w_packed; a.bias = (const bf16_t *)bias; a.pR = p_rows;
     a.max_rows = max_rows; a.K = m->hidden; a.Hq = m->n_q_heads;
     a.q_out = (bf16_t *)q_out; a.pool = (bf16_t *)pool_layer; a.kg = kg; a.rm = rm; a.st = st; a.rope = rope;
-    hipLaunchKernelGGL(qkv_rope_skinny_k, dim3(2 * (m->n_q_heads + 2 * m->n_kv_heads)), dim3(SK_W * 64), 0, s, a);
+    const dim3 grid(4 * (m->n_q_heads + 2 * m->n_kv_heads));
+    if (max_rows <= 16) hipLaunchKernelGGL(qkv_rope_skinny_k<1>, grid, dim3(SK_W * 64), 0, s, a);
+    else hipLaunchKernelGGL(qkv_rope_skinny_k<2>, grid, dim3(SK_W * 64), 0, s, a);
 }
 
 // ------------------------------------------------------------------------------------------------ launch policy
+// k splits of an O or down projection of at most 16 rows: at most two workgroups per compute unit, so that all run at once (h = 1536,
+// F = 8960: 11 splits, 528 workgroups 8.9 us, 10 splits 7.2 us; h = 3584, F = 18944: 560 workgroups 31 us, 448 workgroups 28.5 us, and no
+// better in 1008 workgroups, which leave no unit idle at the end), and at least 512 of k each.
+static int skinny_splits(int rows, int N, int K, size_t slab_room_floats)
+{
+    long sp = 512 / (N / 32);
+    const long cap_k = K / 512, cap_m = (long)(slab_room_floats / ((size_t)rows * N));
+    sp = sp > cap_k ? cap_k : sp;
+    sp = sp > cap_m ? cap_m : sp;
+    sp = sp > 16 ? 16 : sp;
+    return (int)(sp < 1 ? 1 : sp);
+}
+
 struct TileChoice { int MT, NT, splits, WV, KH; };
 
 static int sure_blocks(int rows, int min_rows, int MT)
@@ -878,8 +985,20 @@ int launch_gemm_mfma(hipStream_t s, int epi, const GemmArgs &g, float *slabs, si
     a.n_out = g.N;
     a.n_tiles = epi == EPI_SWIGLU ? 2 * (int)(mfma_pad_n(g.N) / 32) : (int)(mfma_pad_n(g.N) / 32);
     if (epi == EPI_SWIGLU && g.max_rows <= 32) {
-        hipLaunchKernelGGL(swiglu_skinny_k, dim3(a.n_tiles / 2), dim3(SK_W * 64), 0, s, a);
+        if (g.max_rows <= 16) hipLaunchKernelGGL(swiglu_skinny16_k, dim3(a.n_tiles), dim3(SK_W * 64), 0, s, a);
+        else hipLaunchKernelGGL(swiglu_skinny32_k, dim3(a.n_tiles / 2), dim3(SK_W * 64), 0, s, a);
         return 1;
+    }
+    if (epi == EPI_RESID && g.max_rows <= 16) {
+        const int splits = skinny_splits(g.max_rows, g.N, g.K, slab_room_floats);
+        a.slab = (size_t)g.max_rows * g.N;
+        a.splits = splits;
+        if (splits > 1) a.Yf = slabs;
+        const dim3 grid(a.n_tiles * splits);
+        hipLaunchKernelGGL(resid_skinny_k, grid, dim3(SK_W * 64), 0, s, a);
+        if (splits > 1 && !defer_reduce)
+            hipLaunchKernelGGL(reduce_slabs_k, dim3(g.max_rows), dim3(256), 0, s, g.Yf, slabs, splits, a.slab, g.N, g.pR, g.max_rows);
+        return splits;
     }
     TileChoice c = choose(epi, g.max_rows, g.min_rows, g.N, g.K, slab_room_floats);
     if (epi == EPI_SWIGLU) refine_gateup(g.max_rows, g.N, g.K, &c);

@@ -654,6 +654,25 @@ def test_bf16_gate_up_of_at_most_32_rows(B, D, hidden, ffn):
     ctx.close()
 
 
+@pytest.mark.parametrize("B,D,hidden,ffn,heads", [(1, 1, 64, 64, 1), (1, 8, 192, 1024, 4), (2, 4, 576, 4160, 6), (1, 9, 1088, 8256, 10), (4, 2, 128, 9216, 8)])
+def test_bf16_products_of_few_rows(B, D, hidden, ffn, heads):
+    """The weight streams of steps of at most 16 rows (and QKV up to 32): k extents that leave wavefronts without a k step, that end
+    inside a register set and that take several; one k range and up to sixteen split ones; row counts on both sides of 16."""
+    m = mfma_cfg(n_layers=2, n_q_heads=heads, n_kv_heads=1 if heads == 1 else 2, hidden=hidden, ffn=ffn, vocab=1000, has_qkv_bias=True)
+    om, g_dev, layers_dev = both_models(m, seed=100 + B + D, std=0.03)
+    prompts = [syn.uniform_int(5, f"fr{i}", 3 + 14 * i, 0, m.vocab - 1).numpy() for i in range(B)]
+    steps = 4
+    ids, cnt = syn.make_overrides(23, steps, B, D, m.vocab)
+    cnt = cnt.clone()
+    cnt[1] = D                                       # the step after a full commit has B * 2D rows
+    max_len = max(len(p) for p in prompts) + steps * D + D
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=B, max_seq_len=max_len, D=D, tau=0.5)
+    assert ctx.kernel_info == "mfma-bf16"
+    st, _ = lockstep(ctx, om, prompts, D, 0.5, steps, logit_tol=2e-2, conf_tol=1e-3, overrides=(ids, cnt), bf16=True, max_len=max_len)
+    print("few rows", (B, D, hidden, ffn), st)
+    ctx.close()
+
+
 @pytest.mark.parametrize("B,D,hidden,ffn", [(5, 4, 128, 2112), (8, 4, 1408, 1088), (13, 4, 384, 2112), (16, 4, 1024, 192), (26, 4, 256, 24640), (32, 4, 128, 24576)])
 def test_bf16_gate_up_of_33_to_256_rows(B, D, hidden, ffn):
     """The gate/up shapes between the small-step kernel and the 128-row tiles: k in two halves inside a workgroup (one slice,
