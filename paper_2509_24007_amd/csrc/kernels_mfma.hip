@@ -623,21 +623,21 @@ __global__ __launch_bounds__(SK_W * 64) void swiglu_skinny32_k(MfmaArgs a)
 // and the quarters are added in wavefront order through LDS.  Both operands come straight from global memory in the order of
 // v_mfma_f32_16x16x32_bf16: a 16-feature half of a packed 32 x 16 tile pair is four runs of 256 bytes per load, the rows (shared by
 // every workgroup, so served by L2) are 64-byte pieces; rows beyond the live ones repeat the last row and their results are
-// dropped.  NB = 1 serves at most 16 rows, NB = 2 at most 32.  Against workgroups of 32-feature tiles (the tiled kernel for O and
+// dropped.  NB = 1 serves at most 16 rows, NB = 2 at most 32 (QKV also takes more rows, in blocks: see qkv_skinny_units).  Against workgroups of 32-feature tiles (the tiled kernel for O and
 // down, which also stages the rows in LDS slice by slice), before -> after, up to 8 live rows:
 //   h = 1536, F = 8960    QKV 9.7 -> 6.6 us, O 5.4 -> 4.4, down 9.4 -> 7.2, gate/up 16.2 -> 14.7
 //   h = 3584, F = 18944   QKV 17.8 -> 12.0,  O 8.0 -> 7.2, down 26.7 -> 28.5 (the one that loses, with a quarter of the slabs), gate/up 53.4 -> 51.5
 //   h = 5120, F = 27648   QKV 24 -> 17.0 us, O and down 66.4 -> 62.3 (5.1 TB/s), gate/up 102.5 -> 99.9 (5.7 TB/s)
 // With 17 to 32 rows the rows' requests double: QKV, whose 2 x 32-feature workgroups were fewest, still gains (h = 2048 12.9 -> 10.7 us,
 // h = 5120 28.4 -> 22.4); gate/up (h = 5120 115 -> 130) and down (h = 3584 27.6 -> 38) lose and keep their kernels.
-constexpr int sk_u(int NB) { return NB == 1 ? 8 : 6; }   // k steps (of 32) per register set: two wavefronts per SIMD
+constexpr int sk_u(int NB) { return NB == 1 ? 8 : NB == 2 ? 6 : 3; }   // k steps (of 32) per register set: two wavefronts per SIMD
 
 // Products of the features whose first elements `wa` and `wb` point to (each the start of a 16-feature half of a packed tile)
-// with the rows of X, over k steps [k_begin, k_end); steps beyond k_end repeat the last one.  `with_rows` runs after
+// with the 16 NB rows of X from m0 on, over k steps [k_begin, k_end); steps beyond k_end repeat the last one.  `with_rows` runs after
 // the row count is known and the first operands are requested: the caller's own requests go there.  Returns the row count.
-// Result: element v of lane l is feature 4 * (l / 16) + v of the tile, row 16 * nb + l % 16.
+// Result: element v of lane l is feature 4 * (l / 16) + v of the tile, row m0 + 16 * nb + l % 16.
 template <int NB, class F>
-__device__ inline int skinny_dot(const bf16_t *wa, const bf16_t *wb, const bf16_t *X, const int32_t *pR, int max_rows, int K, int k_begin, int k_end,
+__device__ inline int skinny_dot(const bf16_t *wa, const bf16_t *wb, const bf16_t *X, const int32_t *pR, int max_rows, int m0, int K, int k_begin, int k_end,
                                  int lane, f32x4 (&aa)[NB], f32x4 (&ab)[NB], F with_rows)
 {
     constexpr int U = sk_u(NB);
@@ -676,9 +676,9 @@ __device__ inline int skinny_dot(const bf16_t *wa, const bf16_t *wb, const bf16_
     load_w(a0, b0, k_begin);   // the weights do not wait for the row count
     if (k_begin + U < k_end) load_w(a1, b1, k_begin + U);
     const int R = min(*pR, max_rows);
-    if (R <= 0) return 0;
+    if (R <= m0) return 0;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) xp[nb] = X + (size_t)min(nb * 16 + (lane & 15), R - 1) * K + (lane >> 4) * 8;
+    for (int nb = 0; nb < NB; ++nb) xp[nb] = X + (size_t)min(m0 + nb * 16 + (lane & 15), R - 1) * K + (lane >> 4) * 8;
     load_x(x0, k_begin);
     if (k_begin + U < k_end) load_x(x1, k_begin + U);
     with_rows(R);
@@ -715,7 +715,7 @@ __global__ __launch_bounds__(SK_W * 64) void swiglu_skinny16_k(MfmaArgs a)
     const int KS = a.K >> 4, K32 = a.K >> 5, per = (K32 + SK_W - 1) / SK_W;
     const bf16_t *wg = a.Wp + ((size_t)(2 * j) * KS) * 512 + h * 128;
     f32x4 ag[NB], au[NB], gs, us;
-    const int R = skinny_dot<NB>(wg, wg + (size_t)KS * 512, a.X, a.pR, a.max_rows, a.K, wave * per, min(K32, wave * per + per), lane, ag, au, [](int) {});
+    const int R = skinny_dot<NB>(wg, wg + (size_t)KS * 512, a.X, a.pR, a.max_rows, 0, a.K, wave * per, min(K32, wave * per + per), lane, ag, au, [](int) {});
     if (R <= 0 || !skinny_sum<NB>(part, ag, au, wave, lane, gs, us)) return;
     const int row = wave * 16 + (lane & 15), n = j * 32 + h * 16 + (lane >> 4) * 4;
     if (row >= R || n >= a.N) return;
@@ -736,7 +736,7 @@ __global__ __launch_bounds__(SK_W * 64) void resid_skinny_k(MfmaArgs a)
     const int kb = min(k1, k0 + wave * per);
     const bf16_t *w = a.Wp + (size_t)tile * (a.K >> 4) * 512;
     f32x4 aa[NB], ab[NB], s[2];
-    const int R = skinny_dot<NB>(w, w + 128, a.X, a.pR, a.max_rows, a.K, kb, min(k1, kb + per), lane, aa, ab, [](int) {});
+    const int R = skinny_dot<NB>(w, w + 128, a.X, a.pR, a.max_rows, 0, a.K, kb, min(k1, kb + per), lane, aa, ab, [](int) {});
     if (R <= 0 || !skinny_sum<NB>(part, aa, ab, wave, lane, s[0], s[1])) return;
     const int row = wave * 16 + (lane & 15);
     if (row >= R) return;
@@ -757,6 +757,7 @@ struct QkvSkinnyArgs {
     const bf16_t *X, *Wp, *bias;
     const int32_t *pR;
     int max_rows, K, Hq;
+    int m_blocks, m_sure;   // row blocks; row blocks below m_sure certainly hold rows
     bf16_t *q_out, *pool;
     KvGeom kg;
     RowMeta rm;
@@ -765,23 +766,32 @@ struct QkvSkinnyArgs {
 };
 
 template <int NB>
-__global__ __launch_bounds__(SK_W * 64) void qkv_rope_skinny_k(QkvSkinnyArgs a)
+__global__ __launch_bounds__(SK_W * 64, 2) void qkv_rope_skinny_k(QkvSkinnyArgs a)
 {
     __shared__ f32x4 part[SK_W][2][NB][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int head = blockIdx.x >> 2, t16 = blockIdx.x & 3;   // heads: Hq of q, then Hkv of k, then Hkv of v; t16: which 16 of the first 64 features
+    // workgroup id -> (row block, column block), as in the tiled kernel: certain row blocks first, the row blocks of one
+    // column block on one XCD, so that its weights leave memory once
+    const int n_cols = 4 * (a.Hq + 2 * a.kg.n_kv_heads), n_first = n_cols * a.m_sure, first8 = (n_first + 7) & ~7;
+    const bool sure = (int)blockIdx.x < first8;
+    const int bid = sure ? blockIdx.x : blockIdx.x - first8, mb = sure ? a.m_sure : a.m_blocks - a.m_sure;
+    const int per8 = (n_cols * mb + 7) >> 3, wg = (bid & 7) * per8 + (bid >> 3);
+    if (wg >= n_cols * mb) return;
+    const int m0 = ((sure ? 0 : a.m_sure) + wg % mb) * NB * 16, col = wg / mb;
+    if (!sure && m0 >= *a.pR) return;
+    const int head = col >> 2, t16 = col & 3;   // heads: Hq of q, then Hkv of k, then Hkv of v; t16: which 16 of the first 64 features
     const int KS = a.K >> 4, K32 = a.K >> 5, per = (K32 + SK_W - 1) / SK_W;
     const bf16_t *wa = a.Wp + ((size_t)(head * 4 + (t16 >> 1)) * KS) * 512 + (t16 & 1) * 128;
     const int d = a.kg.head_dim, half = d >> 1, Hk = a.kg.n_kv_heads;
     const int i0 = t16 * 16 + (lane >> 4) * 4;   // this lane's four features: index within the first half of the head
     const bool is_q = head < a.Hq, is_v = head >= a.Hq + Hk;
-    const int row = wave * 16 + (lane & 15);
+    const int row = m0 + wave * 16 + (lane & 15);
     float2 t[4];
     float blo[4] = {0.f, 0.f, 0.f, 0.f}, bhi[4] = {0.f, 0.f, 0.f, 0.f};
     int page = -1, slot = 0;
     f32x4 aa[NB], ab[NB], sa, sb;
     // what the epilogue needs beside the sums is requested with the operands: rotation factors, bias, the page of a cached position
-    const int R = skinny_dot<NB>(wa, wa + (size_t)2 * KS * 512, a.X, a.pR, a.max_rows, a.K, wave * per, min(K32, wave * per + per), lane, aa, ab, [&](int rows) {
+    const int R = skinny_dot<NB>(wa, wa + (size_t)2 * KS * 512, a.X, a.pR, a.max_rows, m0, a.K, wave * per, min(K32, wave * per + per), lane, aa, ab, [&](int rows) {
         if (wave >= NB) return;
         const int rr = min(row, rows - 1), pos = a.rm.pos[rr], kind = a.rm.kind[rr], b = a.rm.seq[rr], stg = a.rm.stg[rr];
 #pragma unroll
@@ -823,21 +833,48 @@ __global__ __launch_bounds__(SK_W * 64) void qkv_rope_skinny_k(QkvSkinnyArgs a)
     }
 }
 
-bool qkv_rope_skinny_applies(const sdlm_model_cfg *m, int max_rows)
+static int sure_blocks(int rows, int min_rows, int MT)
 {
-    return mfma_supported(m) && max_rows <= 32 && m->head_dim == 128;
+    const int mb = (rows + MT * 32 - 1) / (MT * 32);
+    if (min_rows <= 0) return mb;
+    const int ms = (min_rows + MT * 32 - 1) / (MT * 32);
+    return ms < 1 ? 1 : (ms > mb ? mb : ms);
 }
 
-void launch_qkv_rope_skinny(hipStream_t s, const sdlm_model_cfg *m, const void *X, const void *w_packed, const void *bias, const int32_t *p_rows,
-                            int max_rows, void *q_out, void *pool_layer, const KvGeom &kg, const RowMeta &rm, const SeqState &st, const float2 *rope)
+// 16-row units per workgroup of the fused launch; 0: the tiled projection and the RoPE + K/V placement kernel serve this step better.
+// Row blocks repeat the weight stream (from L2) and a workgroup's time grows with k times its rows, where the tiled kernel splits
+// k between workgroups: row blocks pay while all workgroups fit the chip at once (about one per compute unit).
+//   32-row blocks, counted for the mean of certain and possible rows: h = 2048, 66 rows, 240 workgroups 15.1 -> 10.5 us (both kernels
+//   before -> fused); h = 1536, 60 rows 13.6 -> 8.9; but h = 2048, 400 workgroups 17.1 -> 16.2, h = 3584, 432 workgroups 17.1 -> 22.5.
+//   64-row blocks, k of at most 2048: h = 2048, 160 rows, 240 workgroups 17.1 -> 15.2 us; h = 5120, 48 rows, 224 workgroups 28.2 -> 30.6.
+static int qkv_skinny_units(const sdlm_model_cfg *m, int max_rows, int min_rows)
 {
+    if (!mfma_supported(m)) return 0;
+    if (max_rows <= 16) return 1;
+    if (max_rows <= 32) return 2;
+    const long cols = 4 * (m->n_q_heads + 2 * m->n_kv_heads), units = 256;
+    if (cols * (sure_blocks(max_rows, min_rows, 1) + (max_rows + 31) / 32) <= 2 * units) return 2;
+    if (m->hidden <= 2048 && cols * sure_blocks(max_rows, min_rows, 2) <= units) return 4;
+    return 0;
+}
+
+bool qkv_rope_skinny_applies(const sdlm_model_cfg *m, int max_rows, int min_rows) { return qkv_skinny_units(m, max_rows, min_rows) > 0; }
+
+void launch_qkv_rope_skinny(hipStream_t s, const sdlm_model_cfg *m, const void *X, const void *w_packed, const void *bias, const int32_t *p_rows,
+                            int max_rows, int min_rows, void *q_out, void *pool_layer, const KvGeom &kg, const RowMeta &rm, const SeqState &st, const float2 *rope)
+{
+    const int NB = qkv_skinny_units(m, max_rows, min_rows), rows = NB * 16;
     QkvSkinnyArgs a;
     a.X = (const bf16_t *)X; a.Wp = (const bf16_t *)w_packed; a.bias = (const bf16_t *)bias; a.pR = p_rows;
     a.max_rows = max_rows; a.K = m->hidden; a.Hq = m->n_q_heads;
+    a.m_blocks = (max_rows + rows - 1) / rows;
+    a.m_sure = min(max((min_rows + rows - 1) / rows, 1), a.m_blocks);
     a.q_out = (bf16_t *)q_out; a.pool = (bf16_t *)pool_layer; a.kg = kg; a.rm = rm; a.st = st; a.rope = rope;
-    const dim3 grid(4 * (m->n_q_heads + 2 * m->n_kv_heads));
-    if (max_rows <= 16) hipLaunchKernelGGL(qkv_rope_skinny_k<1>, grid, dim3(SK_W * 64), 0, s, a);
-    else hipLaunchKernelGGL(qkv_rope_skinny_k<2>, grid, dim3(SK_W * 64), 0, s, a);
+    const int n_cols = 4 * (m->n_q_heads + 2 * m->n_kv_heads);
+    const dim3 grid((n_cols * a.m_sure + 7) / 8 * 8 + (n_cols * (a.m_blocks - a.m_sure) + 7) / 8 * 8), block(SK_W * 64);
+    if (NB == 1) hipLaunchKernelGGL(qkv_rope_skinny_k<1>, grid, block, 0, s, a);
+    else if (NB == 2) hipLaunchKernelGGL(qkv_rope_skinny_k<2>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(qkv_rope_skinny_k<4>, grid, block, 0, s, a);
 }
 
 // ------------------------------------------------------------------------------------------------ launch policy
@@ -855,14 +892,6 @@ static int skinny_splits(int rows, int N, int K, size_t slab_room_floats)
 }
 
 struct TileChoice { int MT, NT, splits, WV, KH; };
-
-static int sure_blocks(int rows, int min_rows, int MT)
-{
-    const int mb = (rows + MT * 32 - 1) / (MT * 32);
-    if (min_rows <= 0) return mb;
-    const int ms = (min_rows + MT * 32 - 1) / (MT * 32);
-    return ms < 1 ? 1 : (ms > mb ? mb : ms);
-}
 
 // rows: bound of the launch (grid); min_rows: rows that are certainly there.
 static TileChoice choose(int epi, int rows, int min_rows, int N, int K, size_t slab_room_floats)

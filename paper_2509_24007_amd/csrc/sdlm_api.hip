@@ -276,9 +276,9 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
         char *pool_l = c->pool + (size_t)l * c->kg.layer_stride * e;
         run_taps(c, l, 0, c->x, (size_t)rows * h * 4);
         { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xn, c->x, w.attn_norm, h, m.rms_eps, nullptr, c->rm.counts, rows, rows_sure, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
-        if (c->L.mfma && qkv_rope_skinny_applies(&m, rows)) {
+        if (c->L.mfma && qkv_rope_skinny_applies(&m, rows, rows_sure)) {
             Phase p(c, SDLM_PH_QKV);   // projection, rotation and K/V placement in one launch
-            launch_qkv_rope_skinny(s, &m, c->xn, w.wqkv, m.has_qkv_bias ? w.bqkv : nullptr, c->rm.counts, rows, c->q, pool_l, c->kg, c->rm, c->st, c->rope);
+            launch_qkv_rope_skinny(s, &m, c->xn, w.wqkv, m.has_qkv_bias ? w.bqkv : nullptr, c->rm.counts, rows, rows_sure, c->q, pool_l, c->kg, c->rm, c->st, c->rope);
         } else {
             int qkv_slabs = 1;
             {

@@ -673,6 +673,26 @@ def test_bf16_products_of_few_rows(B, D, hidden, ffn, heads):
     ctx.close()
 
 
+@pytest.mark.parametrize("B,D,hidden,heads,kv", [(9, 3, 192, 4, 2), (33, 1, 128, 6, 2), (11, 6, 1088, 4, 1), (17, 6, 448, 14, 2), (25, 4, 2048, 12, 2), (25, 4, 2112, 12, 2), (9, 4, 64, 28, 4)])
+def test_bf16_qkv_row_blocks(B, D, hidden, heads, kv):
+    """The fused QKV launch by row blocks of 32 and of 64 and the separate kernels on the other side of its rule: ragged last
+    blocks, blocks that only exist after a full commit (B * 2D rows) and are empty after single tokens."""
+    m = mfma_cfg(n_layers=2, n_q_heads=heads, n_kv_heads=kv, hidden=hidden, ffn=192, vocab=1000, has_qkv_bias=True)
+    om, g_dev, layers_dev = both_models(m, seed=110 + B + heads, std=0.03)
+    prompts = [syn.uniform_int(5, f"rb{i}", 3 + 5 * (i % 7), 0, m.vocab - 1).numpy() for i in range(B)]
+    steps = 4
+    ids, cnt = syn.make_overrides(24, steps, B, D, m.vocab)
+    cnt = cnt.clone()
+    cnt[0] = D
+    cnt[1] = 1
+    max_len = max(len(p) for p in prompts) + steps * D + D
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=B, max_seq_len=max_len, D=D, tau=0.5)
+    assert ctx.kernel_info == "mfma-bf16"
+    st, _ = lockstep(ctx, om, prompts, D, 0.5, steps, logit_tol=2e-2, conf_tol=1e-3, overrides=(ids, cnt), bf16=True, max_len=max_len)
+    print("qkv row blocks", (B, D, hidden, heads, kv), st)
+    ctx.close()
+
+
 @pytest.mark.parametrize("B,D,hidden,ffn", [(5, 4, 128, 2112), (8, 4, 1408, 1088), (13, 4, 384, 2112), (16, 4, 1024, 192), (26, 4, 256, 24640), (32, 4, 128, 24576)])
 def test_bf16_gate_up_of_33_to_256_rows(B, D, hidden, ffn):
     """The gate/up shapes between the small-step kernel and the 128-row tiles: k in two halves inside a workgroup (one slice,
