@@ -254,7 +254,8 @@ __global__ __launch_bounds__(256, 4) void attn_mfma_k(AttnArgs a)
 // A workgroup has CG groups of 256 threads; thread group cg merges chunks CU cg .. CU cg + CU - 1 of every CG CU chunks, and
 // the groups' sums are added in group order.  The launch takes the variant by the chunks that the grid may have: up to 4 are
 // one round trip with CU = 4 (registers for more in flight only cost occupancy: prefill of 4096 rows 26.2 us, 29.2 us with CU = 8);
-// up to 16 take CU = 8 (7B shape, 7 sequences, 11 chunks: 7.7 -> 7.2 us); beyond, four thread groups make 32 chunks one round trip
+// up to 8 take CU = 8, up to 16 two thread groups of them (7B shape, 7 sequences, 11 chunks: 7.7 -> 7.2 us with one group, 6.9 with
+// two; 1.5B shape, one sequence, 9 chunks: 6.6 us with one, 5.8 with two); beyond, four thread groups make 32 chunks one round trip
 // (32B shape, one sequence, 60 chunks: 24.1 -> 10.7 us, 6 sequences of the 7B shape with 31 chunks 9.4 -> 6.9 us).
 template <int CG, int CU>
 __global__ __launch_bounds__(256 * CG) void attn_combine_k(AttnArgs a)
@@ -374,6 +375,11 @@ static void chunking(const sdlm_model_cfg *m, int max_seq_len, int groups, int *
     long items = (long)groups * m->n_kv_heads;
     int cp = 64;                                     // 1024 keys
     while (cp > 8 && items * ((pages + cp - 1) / cp) < 512) cp >>= 1;
+    // Down to 64 keys where even 128 leave units without a work item: one then makes two trips through its loop instead of four, which
+    // is all that the launch waits for (1.5B shape, one sequence of 512 keys: attention 9.2 -> 7.3 us, the merge of nine chunks
+    // instead of five 4.9 -> 5.8; 3B shape, four sequences of 300 to 700 keys: 10.2 -> 7.9 and 5.0 -> 6.1).  With every unit busy
+    // the partial results cost what the shorter loop gains (3B shape, 33 sequences: step 3209 -> 3222 us).
+    if (cp == 8 && items * ((pages + cp - 1) / cp) < 256) cp = 4;
     while ((pages + cp - 1) / cp > 64) cp <<= 1;     // the merge kernel keeps at most 64 scale factors per query
     *chunk_pages = cp;
     *max_chunks = (pages + cp - 1) / cp;
@@ -437,6 +443,7 @@ bool launch_attn_mfma(hipStream_t s, const sdlm_model_cfg *m, int max_seq_len, c
         else hipLaunchKernelGGL(attn_mfma_k<false>, dim3(max_groups, kg.n_kv_heads, a.max_chunks), dim3(256), 0, s, a);
     }
     else if (a.max_chunks > 16) hipLaunchKernelGGL((attn_combine_k<4, 8>), dim3(max_groups, kg.n_kv_heads, NQ), dim3(1024), 0, s, a);
+    else if (a.max_chunks > 8) hipLaunchKernelGGL((attn_combine_k<2, 8>), dim3(max_groups, kg.n_kv_heads, NQ), dim3(512), 0, s, a);
     else if (a.max_chunks > 4) hipLaunchKernelGGL((attn_combine_k<1, 8>), dim3(max_groups, kg.n_kv_heads, NQ), dim3(256), 0, s, a);
     else if (a.max_chunks > 1) hipLaunchKernelGGL((attn_combine_k<1, 4>), dim3(max_groups, kg.n_kv_heads, NQ), dim3(256), 0, s, a);
     return a.max_chunks > 1;

@@ -62,11 +62,11 @@ __host__ __device__ inline int v_off(int slot, int i) { return (((i >> 4) << 2) 
 // large enough that the launch has about 2.25 work items per compute unit (measured by whole-step time on the 7B and 32B
 // shapes, batch 64 and 32: all work items resident at once, two to three per unit, is the fastest split; finer chunks
 // add partial results to merge, coarser ones leave the units unevenly loaded),
-// a multiple of 8, and never below `floor_pages` (the host's bound: partial-result scratch, 64 chunks per item).
+// a multiple of 8 (or 4, for launches that leave units idle: see chunking), and never below `floor_pages` (the host's bound: partial-result scratch, 64 chunks per item).
 __host__ __device__ inline int attn_chunk_pages(long item_pages, int floor_pages)
 {
     long cp = (item_pages + 575) / 576;
-    cp = (cp + 7) / 8 * 8;
+    cp = cp <= 4 ? 4 : (cp + 7) / 8 * 8;
     return cp > floor_pages ? (int)cp : floor_pages;
 }
 

@@ -732,9 +732,9 @@ def test_bf16_requested_logits_rows_and_ragged_vocabulary(B, D, vocab):
     ctx.close()
 
 
-@pytest.mark.parametrize("prompt", [100, 500, 640, 1500, 2100])
+@pytest.mark.parametrize("prompt", [100, 300, 500, 640, 980, 1500, 2100])
 def test_bf16_split_kv_merge_by_number_of_chunks(prompt):
-    """The split-KV merge of one sequence with 1 .. 17 chunks of 128 keys (variants for up to 4, 16 and 64): logits against the oracle."""
+    """The split-KV merge of one sequence with 2 .. 34 chunks of 64 keys (variants for up to 4, 8, 16 and 64): logits against the oracle."""
     m = mfma_cfg(n_layers=1, n_q_heads=4, n_kv_heads=2, hidden=128, ffn=192, vocab=1000)
     om, g_dev, layers_dev = both_models(m, seed=95, std=0.08)
     p = syn.uniform_int(8, f"mg{prompt}", prompt, 0, m.vocab - 1).numpy()
