@@ -657,9 +657,11 @@ __global__ __launch_bounds__(256) void attn_generic_k(const T *q, T *out, const 
         for (int f = 0; f < FD; ++f) o[f] *= corr;
         ps[wave][lane] = p;   // read back by the same wavefront only
         __builtin_amdgcn_wave_barrier();
+        const uint64_t seen = __ballot(vis);   // bit 16 tt + slot: the row sees that slot of tile t0 + tt
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
             if (t0 + tt >= n_tiles) break;
+            const uint32_t seen_t = (uint32_t)(seen >> (tt * 16)) & 0xffffu;
             const T *Vb = pool + kg.tile(__shfl(page, tt * 16), hk) + PAGE * HD;
 #pragma unroll
             for (int f = 0; f < FD; ++f) {
@@ -676,6 +678,10 @@ __global__ __launch_bounds__(256) void attn_generic_k(const T *q, T *out, const 
                         const uint2 x = *(const uint2 *)(Vb + v_off(sg * 4, i));
                         v[0] = bf16_to_f((bf16_t)(x.x & 0xffffu)); v[1] = bf16_to_f((bf16_t)(x.x >> 16));
                         v[2] = bf16_to_f((bf16_t)(x.y & 0xffffu)); v[3] = bf16_to_f((bf16_t)(x.y >> 16));
+                    }
+                    if (seen_t != 0xffffu) {   // an unseen slot may hold anything, and 0 times a non-finite value is not 0
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] = (seen_t >> (sg * 4 + e)) & 1u ? v[e] : 0.f;
                     }
                     o[f] += p4.x * v[0] + p4.y * v[1] + p4.z * v[2] + p4.w * v[3];
                 }

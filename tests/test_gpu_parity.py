@@ -775,6 +775,33 @@ def test_generic_row_gemm_edges(dtype, hidden, ffn, vocab, B, D, d):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype,d,D,paged", [("fp32", 32, 4, True), ("fp32", 96, 5, False), ("bf16", 64, 4, False), ("bf16", 32, 5, True)])
+def test_generic_attention_ignores_unseen_slots(dtype, d, D, paged):
+    """Cache and staging slots that a row does not see have no part in its result, whatever an earlier prompt left there: prompts of a
+    token whose embedding is not a number fill pages and staging tiles (a step and its verification pass), then clean prompts use them."""
+    m = gpu_cfg(head_dim=d, dtype=dtype)
+    om, g_dev, layers_dev = both_models(m, seed=71, std=0.3 if dtype == "fp32" else 0.05)
+    bad = m.vocab - 2
+    g_dev = dict(g_dev, embed=g_dev["embed"].clone())
+    g_dev["embed"][bad] = float("nan")
+    lens = [1, 17, 33]
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=3, max_seq_len=96, D=D, tau=0.5, paged=paged, n_pages=18 if paged else 0)
+    assert ctx.kernel_info.startswith("generic")
+    ids = torch.empty(3, D, dtype=torch.int32, device="cuda")
+    cnt = torch.empty(3, dtype=torch.int32, device="cuda")
+    logits = torch.empty(3, D, m.vocab, device="cuda")
+    ctx.prefill([[bad] * 64] * 3)
+    ctx.decode_step(ids, cnt, None, logits)
+    ctx.verify_step(0)
+    torch.cuda.synchronize()
+    assert logits.isnan().all()
+    prompts = [syn.uniform_int(31, f"un{i}", n, 0, m.vocab - 3).numpy() for i, n in enumerate(lens)]
+    bf = dtype == "bf16"
+    _, seqs = lockstep(ctx, om, prompts, D, 0.5, 3, logit_tol=2e-2 if bf else 1e-4, conf_tol=1e-3 if bf else 1e-5, bf16=bf, max_len=96, verify_rule=0)
+    assert all(bad not in [int(t) for t in s.tokens] for s in seqs)   # else the step above was not clean
+    ctx.close()
+
+
 # ------------------------------------------------------------------ seeded random shapes
 def _random_case(seed):
     rng = np.random.RandomState(seed)
