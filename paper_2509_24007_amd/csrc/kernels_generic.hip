@@ -650,7 +650,7 @@ __global__ __launch_bounds__(256) void attn_generic_k(const T *q, T *out, const 
         float mx = s;
         for (int d = 32; d > 0; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
         const float mn = fmaxf(m, mx);
-        const float corr = m == -INFINITY ? 0.f : __expf(m - mn), p = vis && mn > -INFINITY ? __expf(s - mn) : 0.f;
+        const float corr = m == -INFINITY ? 0.f : __expf(m - mn), p = s == -INFINITY ? 0.f : __expf(s - mn);   // a NaN score stays one, whatever mn is
         m = mn;
         l = l * corr + p;
 #pragma unroll

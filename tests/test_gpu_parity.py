@@ -802,6 +802,35 @@ def test_generic_attention_ignores_unseen_slots(dtype, d, D, paged):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype,d,lead,tail", [("fp32", 32, 64, 70), ("fp32", 128, 256, 20), ("bf16", 64, 192, 3), ("bf16", 96, 320, 1)])
+def test_generic_attention_keeps_non_finite_scores(dtype, d, lead, tail):
+    """A score that is not a number makes the result of its row not a number, also where a wavefront has no other key in its tiles
+    (runs of whole 64-key groups, of one wavefront and of all four, before the finite keys) and the values are finite.  The keys of
+    one token overflow: only its embedding has feature 0, which every key weight multiplies by 3e38 or -3e38."""
+    m = gpu_cfg(head_dim=d, dtype=dtype, n_layers=1, has_qkv_bias=False)
+    _, g_dev, layers_dev = both_models(m, seed=72, std=0.3 if dtype == "fp32" else 0.05)
+    bad = m.vocab - 2
+    embed, L = g_dev["embed"].clone(), {k: v if v is None else v.clone() for k, v in layers_dev[0].items()}
+    embed[:, 0] = 0
+    embed[bad] = 0
+    embed[bad, 0] = 1
+    L["wq"][:, 0] = 0
+    L["wk"][:, 0] = torch.where(torch.arange(L["wk"].shape[0], device="cuda") % 3 == 0, 3e38, -3e38).to(L["wk"].dtype)
+    clean = [int(t) for t in syn.uniform_int(32, "nf", tail, 0, m.vocab - 3)]
+    ctx = gpu_context(m, dict(g_dev, embed=embed), [L], max_batch=2, max_seq_len=lead + tail + 8, D=4, tau=0.5)
+    assert ctx.kernel_info.startswith("generic")
+    ids = torch.empty(2, 4, dtype=torch.int32, device="cuda")
+    cnt = torch.empty(2, dtype=torch.int32, device="cuda")
+    logits = torch.empty(2, 4, m.vocab, device="cuda")
+    ctx.prefill([[bad] * lead + clean, clean])
+    ctx.decode_step(ids, cnt, None, logits)
+    torch.cuda.synchronize()
+    k, v = ctx.read_kv(0, 0, 0, 0, lead)
+    assert not k.isfinite().any() and v.isfinite().all()
+    assert logits[0].isnan().all() and logits[1].isfinite().all()
+    ctx.close()
+
+
 # ------------------------------------------------------------------ seeded random shapes
 def _random_case(seed):
     rng = np.random.RandomState(seed)
