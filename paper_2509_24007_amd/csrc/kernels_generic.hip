@@ -2,6 +2,8 @@
 // fused epilogues, RoPE + K/V placement, block-masked attention, the vocabulary reduction, prefix acceptance
 // and commit.  Storage is fp32 or bf16; all arithmetic is fp32.  They serve the fp32 debug mode and every small
 // integer/elementwise step of the bf16 mode; the bf16 mode's contractions run on the matrix-core kernels.
+#include <type_traits>
+
 #include "internal.hpp"
 
 namespace sdlm {
@@ -657,11 +659,8 @@ __global__ __launch_bounds__(256) void attn_generic_k(const T *q, T *out, const 
         for (int f = 0; f < FD; ++f) o[f] *= corr;
         ps[wave][lane] = p;   // read back by the same wavefront only
         __builtin_amdgcn_wave_barrier();
-        const uint64_t seen = __ballot(vis);   // bit 16 tt + slot: the row sees that slot of tile t0 + tt
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
-            if (t0 + tt >= n_tiles) break;
-            const uint32_t seen_t = (uint32_t)(seen >> (tt * 16)) & 0xffffu;
+        // An unseen slot may hold anything, and 0 times a non-finite value is not 0: such values are cleared.
+        auto add_values = [&](int tt, uint32_t seen_t, auto whole) {   // seen_t: the tile's slots that the row sees; whole: all of them
             const T *Vb = pool + kg.tile(__shfl(page, tt * 16), hk) + PAGE * HD;
 #pragma unroll
             for (int f = 0; f < FD; ++f) {
@@ -670,21 +669,31 @@ __global__ __launch_bounds__(256) void attn_generic_k(const T *q, T *out, const 
 #pragma unroll
                 for (int sg = 0; sg < 4; ++sg) {
                     const float4 p4 = *(const float4 *)&ps[wave][tt * 16 + sg * 4];
-                    float v[4];
+                    uint32_t v[4];
                     if constexpr (sizeof(T) == 4) {
-                        const float4 x = *(const float4 *)(Vb + v_off(sg * 4, i));
+                        const uint4 x = *(const uint4 *)(Vb + v_off(sg * 4, i));
                         v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
                     } else {
                         const uint2 x = *(const uint2 *)(Vb + v_off(sg * 4, i));
-                        v[0] = bf16_to_f((bf16_t)(x.x & 0xffffu)); v[1] = bf16_to_f((bf16_t)(x.x >> 16));
-                        v[2] = bf16_to_f((bf16_t)(x.y & 0xffffu)); v[3] = bf16_to_f((bf16_t)(x.y >> 16));
+                        v[0] = x.x << 16; v[1] = x.x & 0xffff0000u; v[2] = x.y << 16; v[3] = x.y & 0xffff0000u;
                     }
-                    if (seen_t != 0xffffu) {   // an unseen slot may hold anything, and 0 times a non-finite value is not 0
+                    if constexpr (!whole) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] = (seen_t >> (sg * 4 + e)) & 1u ? v[e] : 0.f;
+                        for (int e = 0; e < 4; ++e) v[e] &= 0u - ((seen_t >> (sg * 4 + e)) & 1u);
                     }
-                    o[f] += p4.x * v[0] + p4.y * v[1] + p4.z * v[2] + p4.w * v[3];
+                    o[f] += p4.x * __uint_as_float(v[0]) + p4.y * __uint_as_float(v[1]) + p4.z * __uint_as_float(v[2]) + p4.w * __uint_as_float(v[3]);
                 }
+            }
+        };
+        const uint64_t seen = __ballot(vis);   // bit 16 tt + slot: the row sees that slot of tile t0 + tt
+        if (seen == ~0ull) {   // unrolled, the loads of four tiles of more than 64 features crowd the registers (d = 128, fp32, 4000 keys: a layer 208 -> 302 us)
+#pragma unroll (HD <= 64 ? 4 : 1)
+            for (int tt = 0; tt < 4; ++tt) add_values(tt, 0xffffu, std::true_type{});
+        } else {
+#pragma unroll
+            for (int tt = 0; tt < 4; ++tt) {
+                if (t0 + tt >= n_tiles) break;
+                add_values(tt, (uint32_t)(seen >> (tt * 16)) & 0xffffu, std::false_type{});
             }
         }
         __builtin_amdgcn_wave_barrier();
