@@ -387,13 +387,13 @@ __global__ __launch_bounds__(256) void gemm_generic_k(GemmArgs a)
     }
 }
 
-// The same products without LDS, for every K whose rows are whole 16-byte groups (the tile kernel above keeps the others).
+// The same products without LDS, for few rows and for K whose rows are whole 16-byte groups (see gemm_generic_go).
 // Sixteen lanes share an output column: each walks k in steps of 16 VE elements, and the sixteen partial sums are added by a
 // fixed tree, so an output's sum does not depend on RT, CN or the other rows of the launch.  A few rows leave the 64x64
 // tiles a handful of workgroups with a serial k loop and a barrier pair per 16 k (K = 688, N = 256: 4 workgroups, 68 us; here
 // 16 workgroups whose loads are all requested at once, 5 us, which is the launch itself).  RT x CN outputs per lane group
-// balance the loads per FMA: 8 x 1 spreads a small product over as many wavefronts as possible, 32 x CN re-uses each loaded
-// vector 32 / CN times.
+// balance the loads per FMA: 8 x 1 spreads a small product over as many wavefronts as possible, 32 x 4 re-uses each loaded
+// vector 8 times more often.
 template <typename T> struct Vec16;   // 16 bytes of T as floats
 template <> struct Vec16<float> {
     static constexpr int N = 4;
@@ -506,19 +506,35 @@ __global__ __launch_bounds__(256) void gemm_rows_k(GemmArgs a)
         }
 }
 
+// Which kernel: rows without LDS spend their time per output, tiles per 64 x 64 tile and k slice with little more until every
+// compute unit has one or two.  `tiles` (N * rows / 4096) is where the lines lie, measured for both types, K from 128 to 8960 and N from 256
+// to 151936 (us, rows without LDS -> tiles):
+//   bf16  N = 896, K = 896: 1024 rows 86 -> 128, 2048 rows 172 -> 164, 4096 rows 331 -> 195;  K = 4864: 1024 rows 340 -> 774, 4096 1324 -> 1000
+//   gate/up, N = 4864, K = 896: bf16 256 rows 139 -> 179, 384 rows 208 -> 190, 4096 rows 2138 -> 1233;  fp32 256 rows 191 -> 222, 384 rows 282 -> 233
+//   short K (the lanes' final sum weighs more): gate/up, N = 3072, K = 128: bf16 96 rows 18.6 -> 24.5, 256 rows 41.7 -> 24.5
+//   V = 151936, K = 896: fp32 16 rows 352 -> 437, 24 rows 523 -> 453; bf16 24 rows 350 -> 425, 32 rows 465 -> 430 (a tile's 64 rows are then
+//   mostly padding, so the line is one of rows)
+// 32-row groups of four columns serve the fp32 products of one matrix between one and one and a half tiles per unit, three of their
+// workgroups a unit (N = 4096, K = 896: 384 rows 78 us, tiles 135, eight-row groups 172; 448 rows 181, tiles 137).  They lose
+// with bf16 (384 rows 102, and 245 for gate/up, N = 4864, against 208) and with two matrices.
 template <typename T, int EPI>
 static void gemm_generic_go(hipStream_t s, const GemmArgs &a)
 {
-    if (a.K % Vec16<T>::N != 0) {
+    constexpr bool FP32 = sizeof(T) == 4, ONE32 = FP32 && EPI != EPI_SWIGLU;
+    const long outputs = (long)a.N * a.max_rows;
+    const bool many = a.max_rows > (FP32 ? 16 : 24) && outputs * 512 > (ONE32 ? 384L : 352L) * 4096 * min(a.K, 512);
+    if (a.K % Vec16<T>::N != 0 || many) {
         hipLaunchKernelGGL((gemm_generic_k<T, EPI>), dim3((a.N + 63) / 64, (a.max_rows + 63) / 64), dim3(256), 0, s, a);
         return;
     }
-    constexpr int CN = EPI == EPI_SWIGLU ? 2 : 4;
-    const long wide = (long)((a.N + 16 * CN - 1) / (16 * CN)) * ((a.max_rows + 31) / 32);
-    if (wide >= 512)   // two workgroups per compute unit without the finer split
-        hipLaunchKernelGGL((gemm_rows_k<T, EPI, 32, CN>), dim3((a.N + 16 * CN - 1) / (16 * CN), (a.max_rows + 31) / 32), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL((gemm_rows_k<T, EPI, 8, 1>), dim3((a.N + 15) / 16, (a.max_rows + 7) / 8), dim3(256), 0, s, a);
+    if constexpr (ONE32) {
+        const dim3 wide((a.N + 63) / 64, (a.max_rows + 31) / 32);
+        if (a.max_rows > 8 && (long)wide.x * wide.y >= 512) {
+            hipLaunchKernelGGL((gemm_rows_k<T, EPI, 32, 4>), wide, dim3(256), 0, s, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((gemm_rows_k<T, EPI, 8, 1>), dim3((a.N + 15) / 16, (a.max_rows + 7) / 8), dim3(256), 0, s, a);
 }
 
 template <typename T>

@@ -831,6 +831,26 @@ def test_generic_attention_keeps_non_finite_scores(dtype, d, lead, tail):
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype,hidden,heads,kv,d,ffn,vocab,lens,D", [
+    ("fp32", 264, 12, 2, 64, 1096, 97, [800], 2), ("bf16", 264, 12, 2, 64, 1096, 97, [501, 300], 2),          # QKV and gate/up by tiles, O and down by rows
+    ("fp32", 260, 2, 1, 32, 72, 97, [901], 3), ("bf16", 264, 2, 1, 32, 72, 97, [450, 453], 3),                # O and down by tiles, QKV and gate/up by rows
+    ("fp32", 512, 12, 2, 64, 40, 97, [1100], 1), ("fp32", 1032, 8, 2, 64, 40, 97, [1087], 1),                 # QKV, O by 32-row groups of four columns
+    ("fp32", 264, 2, 1, 32, 72, 33003, [3] * 8, 4), ("bf16", 264, 2, 1, 32, 72, 33003, [3] * 9, 5),           # LM head by tiles
+    ("fp32", 264, 2, 1, 32, 72, 33003, [3] * 4, 4), ("bf16", 264, 2, 1, 32, 72, 33003, [3] * 6, 4)])          # ... and just not
+def test_generic_products_of_many_rows(dtype, hidden, heads, kv, d, ffn, vocab, lens, D):
+    """The generic products on both sides of the line between rows without LDS and tiles, every epilogue, with ragged last rows and
+    columns: prefill passes of 800 to 1100 rows (one step's logits depend on all of their keys and values) and LM heads of 16 to 45 rows."""
+    m = gpu_cfg(hidden=hidden, n_q_heads=heads, n_kv_heads=kv, head_dim=d, ffn=ffn, vocab=vocab, n_layers=2 if sum(lens) < 1000 else 1, dtype=dtype)
+    om, g_dev, layers_dev = both_models(m, seed=73, std=0.05)
+    prompts = [syn.uniform_int(33, f"mr{i}", n, 0, m.vocab - 1).numpy() for i, n in enumerate(lens)]
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=len(lens), max_seq_len=max(lens) + 2 * D, D=D, tau=0.5)
+    bf = dtype == "bf16"
+    assert ctx.kernel_info.startswith("generic")
+    st, _ = lockstep(ctx, om, prompts, D, 0.5, 1, logit_tol=2e-2 if bf else 1e-4, conf_tol=1e-3 if bf else 1e-5, bf16=bf, max_len=max(lens) + 2 * D)
+    print("many rows", (dtype, hidden, heads, ffn, vocab, len(lens), D), st)
+    ctx.close()
+
+
 # ------------------------------------------------------------------ seeded random shapes
 def _random_case(seed):
     rng = np.random.RandomState(seed)
