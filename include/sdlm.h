@@ -234,8 +234,12 @@ int sdlm_debug_read_kv(sdlm_ctx *ctx, int32_t layer, int32_t seq, int32_t kv_hea
 /*
  * Host logic only (no GPU work): the launch shape the bf16 matrix-core GEMM takes for `rows` launch rows of which
  * `min_rows` certainly exist (0: unknown), an [n, k] weight matrix (k a multiple of 64) and an epilogue (0: plain fp32
- * store, 1: residual add, 2: SiLU(gate)*up, 3: LM head).  Outputs: rows and columns of a workgroup's tile (512 columns:
- * a workgroup of eight wavefronts, else four) and the number of splits along k.  For tests of the tile policy.  Errors: SDLM_EINVAL.
+ * store, 1: residual add, 2: SiLU(gate)*up, 3: LM head).  Outputs: rows and columns of a workgroup's tile and the number
+ * of splits along k between workgroups.  Columns count rows of the weight matrix, for epilogue 2 those of gate and up
+ * together (n of each).  A tile of 16 rows, or for epilogue 2 of 32 x 64, is a kernel without LDS tiles; for epilogue 2, 64 or
+ * 128 rows x 128 columns is a workgroup whose wavefronts take half of k each; 512 columns are eight wavefronts.  Not covered:
+ * QKV projections of few rows, which run together with RoPE and the K/V placement in a launch of their own.  For tests of the
+ * tile policy.  Errors: SDLM_EINVAL.
  */
 int sdlm_debug_gemm_plan(int32_t epilogue, int32_t rows, int32_t min_rows, int32_t n, int32_t k, int32_t *tile_rows, int32_t *tile_cols,
                          int32_t *splits);

@@ -84,7 +84,7 @@ template <int MT, int NT> constexpr int w_sets() { return (MT >= 4) ? 2 : 3; }
 
 // WV wavefronts per workgroup: 4, or 8 (a 128-row x 512-column tile whose activation slice is staged once for eight
 // wavefronts instead of once for four: fewer bytes through the compute unit's load path per MFMA).
-// KH = 2: the wavefronts form two halves that take a half of k each (gate/up with few column blocks, see choose); the halves'
+// KH = 2: the wavefronts form two halves that take a half of k each (gate/up with few column blocks, see refine_gateup); the halves'
 // sums meet in LDS before the epilogue.  The columns of a workgroup are then those of WV / 2 wavefronts.
 template <int MT, int NT, int EPI, int WV = 4, int KH = 1>
 __global__ __launch_bounds__(WV * 64, (WV == 8 || KH == 2 ? 1 : (MT == 4 ? 2 : 1))) void gemm_mfma_k(MfmaArgs a)
@@ -883,7 +883,7 @@ void launch_qkv_rope_skinny(hipStream_t s, const sdlm_model_cfg *m, const void *
 // better in 1008 workgroups, which leave no unit idle at the end), and at least 512 of k each.
 static int skinny_splits(int rows, int N, int K, size_t slab_room_floats)
 {
-    long sp = 512 / (N / 32);
+    long sp = 512 / (long)(mfma_pad_n(N) / 32);
     const long cap_k = K / 512, cap_m = (long)(slab_room_floats / ((size_t)rows * N));
     sp = sp > cap_k ? cap_k : sp;
     sp = sp > cap_m ? cap_m : sp;
@@ -891,16 +891,35 @@ static int skinny_splits(int rows, int N, int K, size_t slab_room_floats)
     return (int)(sp < 1 ? 1 : sp);
 }
 
-struct TileChoice { int MT, NT, splits, WV, KH; };
+// What a product runs as: FEW16 / FEW32 are the kernels without LDS tiles for steps of few rows (16 rows x two 16-feature tiles, 32 rows x two
+// 32-feature tiles a workgroup), TILED the tiled kernel.
+enum { TILED = 0, FEW16, FEW32 };
+struct TileChoice { int kind, MT, NT, splits, WV, KH; };
 
-// rows: bound of the launch (grid); min_rows: rows that are certainly there.
+// Gate/up launches of 33 .. 256 rows whose shape the plain tiles do not serve well (K a multiple of 128):
+//   * Up to 128 rows and at most 256 column blocks of 64 features: workgroups of 128 x 64 features whose wavefronts take half of k
+//     each.  Bound by the weights in flight: F / 128 workgroups of the plain tile leave most compute units without any (h = 2048,
+//     F = 11008: 86 workgroups); half the columns double the workgroups, and k in halves keeps four wavefronts in each.
+//     h = 2048, F = 11008: 66 rows 32.9 -> 24.4 us, 48 rows 35.6 -> 24.8; h = 1536, F = 8960: 96 rows 24.5 -> 19.7, 48 rows 27.4 ->
+//     18.9.  Beyond 128 rows (192- and 256-row tiles in halves: 160 rows 31.8 -> 32.5) and for the split-k projections (160 rows,
+//     QKV 11.8 -> 19.4, O 8.8 -> 14.0, down 20.8 -> 23.4) the activations' share of the load path takes it back; with more
+//     than 256 column blocks the plain tile already occupies the chip.
+//   * Where the 192-row tile would be taken and the step may have more rows: a 256-row tile, so that the rows beyond 192 are not a second
+//     row block that streams every weight again.  h = 5120, F = 27648, 193..224 rows: 205.6 -> 131.8 us.  (Its 256 accumulator
+//     registers leave room for the operands only with an even number of slices, without a peeled last one.)
+static void refine_gateup(int rows, int N, int K, TileChoice *c)
+{
+    if (K % 128) return;
+    if (rows > 32 && rows <= 128 && (N + 63) / 64 <= 256) { c->KH = 2; c->MT = rows <= 64 ? 2 : 4; c->NT = 2; c->WV = 4; }
+    else if (c->MT == 6 && rows > 192) c->MT = 8;
+}
+
+// rows: bound of the launch (grid); min_rows: rows that are certainly there.  The one place where a launch shape is decided.
 static TileChoice choose(int epi, int rows, int min_rows, int N, int K, size_t slab_room_floats)
 {
-    TileChoice c;
-    c.MT = rows <= 32 ? 1 : rows <= 64 ? 2 : 4;
-    c.NT = 2;
-    c.WV = 4;
-    c.KH = 1;
+    if (epi == EPI_SWIGLU && rows <= 32) return {rows <= 16 ? FEW16 : FEW32, 1, 2, 1, SK_W, SK_W};
+    if (epi == EPI_RESID && rows <= 16) return {FEW16, 1, 1, skinny_splits(rows, N, K, slab_room_floats), SK_W, SK_W};
+    TileChoice c{TILED, rows <= 32 ? 1 : rows <= 64 ? 2 : 4, 2, 1, 4, 1};
     // Gate/up with 129..192 certain rows and enough column blocks for one workgroup on (nearly) every compute unit: one
     // 192-row block per column block, so that no weight band is streamed by two workgroups.  (For the split-k
     // projections the same tile was measured: it wants more splits, and the slab traffic costs more than it saves.)
@@ -909,7 +928,6 @@ static TileChoice choose(int epi, int rows, int min_rows, int N, int K, size_t s
         int mb = (rows + c.MT * 32 - 1) / (c.MT * 32);
         if ((long)((N + 255) / 256) * mb < 256) c.NT = 1;
     }
-    c.splits = 1;
     if (epi == EPI_STORE_F32 || epi == EPI_RESID) {
         const int S = K / 64;
         const int cap_k = S / 4 > 0 ? S / 4 : 1;                             // at least 4 stages (256 deep) per split
@@ -937,31 +955,14 @@ static TileChoice choose(int epi, int rows, int min_rows, int N, int K, size_t s
         const int S = K / 64, per = (S + c.splits - 1) / c.splits;
         c.splits = (S + per - 1) / per;
     }
-    // A launch that would put two 128 x 256 workgroups on every compute unit runs as 128 x 512 workgroups of eight wavefronts
+    // A launch of more 128 x 256 workgroups than compute units runs as 128 x 512 workgroups of eight wavefronts
     // (measured on the 7B gate/up shape: 2.5 % faster; with fewer workgroups than units the wider tile only idles units)
     if ((epi == EPI_SWIGLU || epi == EPI_RESID) && c.MT == 4 && c.NT == 2 && c.splits == 1) {   // (measured and not faster: the LM head, the prefill QKV projection)
         const long blocks4 = epi == EPI_SWIGLU ? (N + 127) / 128 : (N + 255) / 256;
         if (blocks4 * sure_blocks(rows, min_rows, c.MT) > 256) c.WV = 8;
     }
+    if (epi == EPI_SWIGLU) refine_gateup(rows, N, K, &c);
     return c;
-}
-
-// Gate/up launches of 33 .. 256 rows whose shape `choose` does not serve well (K a multiple of 128):
-//   * Up to 128 rows and at most 256 column blocks of 64 features: workgroups of 128 x 64 features whose wavefronts take half of k
-//     each.  Bound by the weights in flight: F / 128 workgroups of the plain tile leave most compute units without any (h = 2048,
-//     F = 11008: 86 workgroups); half the columns double the workgroups, and k in halves keeps four wavefronts in each.
-//     h = 2048, F = 11008: 66 rows 32.9 -> 24.4 us, 48 rows 35.6 -> 24.8; h = 1536, F = 8960: 96 rows 24.5 -> 19.7, 48 rows 27.4 ->
-//     18.9.  Beyond 128 rows (192- and 256-row tiles in halves: 160 rows 31.8 -> 32.5) and for the split-k projections (160 rows,
-//     QKV 11.8 -> 19.4, O 8.8 -> 14.0, down 20.8 -> 23.4) the activations' share of the load path takes it back; with more
-//     than 256 column blocks the plain tile already occupies the chip.
-//   * Where `choose` takes the 192-row tile and the step may have more rows: a 256-row tile, so that the rows beyond 192 are not a second
-//     row block that streams every weight again.  h = 5120, F = 27648, 193..224 rows: 205.6 -> 131.8 us.  (Its 256 accumulator
-//     registers leave room for the operands only with an even number of slices, without a peeled last one.)
-static void refine_gateup(int rows, int N, int K, TileChoice *c)
-{
-    if (K % 128) return;
-    if (rows > 32 && rows <= 128 && (N + 63) / 64 <= 256) { c->KH = 2; c->MT = rows <= 64 ? 2 : 4; c->NT = 2; c->WV = 4; }
-    else if (c->MT == 6 && rows > 192) c->MT = 8;
 }
 
 template <int EPI>
@@ -1000,10 +1001,12 @@ static void launch_cfg(hipStream_t s, const TileChoice &c, MfmaArgs &a, int min_
 #undef SDLM_GO
 }
 
-void mfma_gemm_plan(int epi, int rows, int min_rows, int N, int K, size_t slab_room_floats, int *MT, int *NT, int *splits, int *wavefronts)
+void mfma_gemm_plan(int epi, int rows, int min_rows, int N, int K, size_t slab_room_floats, int *tile_rows, int *tile_cols, int *splits)
 {
-    TileChoice c = choose(epi, rows, min_rows, N, K, slab_room_floats);
-    *MT = c.MT; *NT = c.NT; *splits = c.splits; *wavefronts = c.WV;
+    const TileChoice c = choose(epi, rows, min_rows, N, K, slab_room_floats);
+    *tile_rows = c.kind == FEW16 ? 16 : 32 * c.MT;
+    *tile_cols = c.kind == FEW16 ? 32 : 32 * c.NT * (c.WV / c.KH);
+    *splits = c.splits;
 }
 
 int launch_gemm_mfma(hipStream_t s, int epi, const GemmArgs &g, float *slabs, size_t slab_room_floats, bool defer_reduce)
@@ -1013,30 +1016,22 @@ int launch_gemm_mfma(hipStream_t s, int epi, const GemmArgs &g, float *slabs, si
     a.Yf = g.Yf; a.Yt = (bf16_t *)g.Yt; a.pR = g.pR; a.max_rows = g.max_rows; a.N = g.N; a.K = g.K; a.scale = g.scale;
     a.n_out = g.N;
     a.n_tiles = epi == EPI_SWIGLU ? 2 * (int)(mfma_pad_n(g.N) / 32) : (int)(mfma_pad_n(g.N) / 32);
-    if (epi == EPI_SWIGLU && g.max_rows <= 32) {
-        if (g.max_rows <= 16) hipLaunchKernelGGL(swiglu_skinny16_k, dim3(a.n_tiles), dim3(SK_W * 64), 0, s, a);
-        else hipLaunchKernelGGL(swiglu_skinny32_k, dim3(a.n_tiles / 2), dim3(SK_W * 64), 0, s, a);
-        return 1;
-    }
-    if (epi == EPI_RESID && g.max_rows <= 16) {
-        const int splits = skinny_splits(g.max_rows, g.N, g.K, slab_room_floats);
-        a.slab = (size_t)g.max_rows * g.N;
-        a.splits = splits;
-        if (splits > 1) a.Yf = slabs;
-        const dim3 grid(a.n_tiles * splits);
-        hipLaunchKernelGGL(resid_skinny_k, grid, dim3(SK_W * 64), 0, s, a);
-        if (splits > 1 && !defer_reduce)
-            hipLaunchKernelGGL(reduce_slabs_k, dim3(g.max_rows), dim3(256), 0, s, g.Yf, slabs, splits, a.slab, g.N, g.pR, g.max_rows);
-        return splits;
-    }
-    TileChoice c = choose(epi, g.max_rows, g.min_rows, g.N, g.K, slab_room_floats);
-    if (epi == EPI_SWIGLU) refine_gateup(g.max_rows, g.N, g.K, &c);
+    const TileChoice c = choose(epi, g.max_rows, g.min_rows, g.N, g.K, slab_room_floats);
     a.slab = (size_t)g.max_rows * g.N;
+    a.splits = c.splits;
     if (c.splits > 1) a.Yf = slabs;
-    switch (epi) {
-    case EPI_STORE_F32: launch_cfg<EPI_STORE_F32>(s, c, a, g.min_rows); break;
-    case EPI_RESID: launch_cfg<EPI_RESID>(s, c, a, g.min_rows); break;
-    default: launch_cfg<EPI_SWIGLU>(s, c, a, g.min_rows); break;
+    if (c.kind == TILED) {
+        switch (epi) {
+        case EPI_STORE_F32: launch_cfg<EPI_STORE_F32>(s, c, a, g.min_rows); break;
+        case EPI_RESID: launch_cfg<EPI_RESID>(s, c, a, g.min_rows); break;
+        default: launch_cfg<EPI_SWIGLU>(s, c, a, g.min_rows); break;
+        }
+    } else if (epi == EPI_RESID) {
+        hipLaunchKernelGGL(resid_skinny_k, dim3(a.n_tiles * c.splits), dim3(SK_W * 64), 0, s, a);
+    } else if (c.kind == FEW16) {
+        hipLaunchKernelGGL(swiglu_skinny16_k, dim3(a.n_tiles), dim3(SK_W * 64), 0, s, a);
+    } else {
+        hipLaunchKernelGGL(swiglu_skinny32_k, dim3(a.n_tiles / 2), dim3(SK_W * 64), 0, s, a);
     }
     if (c.splits > 1 && epi == EPI_RESID && !defer_reduce)
         hipLaunchKernelGGL(reduce_slabs_k, dim3(g.max_rows), dim3(256), 0, s, g.Yf, slabs, c.splits, a.slab, g.N, g.pR, g.max_rows);
