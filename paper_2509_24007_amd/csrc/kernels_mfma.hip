@@ -624,10 +624,14 @@ __global__ __launch_bounds__(SK_W * 64) void swiglu_skinny32_k(MfmaArgs a)
 // v_mfma_f32_16x16x32_bf16: a 16-feature half of a packed 32 x 16 tile pair is four runs of 256 bytes per load, the rows (shared by
 // every workgroup, so served by L2) are 64-byte pieces; rows beyond the live ones repeat the last row and their results are
 // dropped.  NB = 1 serves at most 16 rows, NB = 2 at most 32 (QKV also takes more rows, in blocks: see qkv_skinny_units).  Against workgroups of 32-feature tiles (the tiled kernel for O and
-// down, which also stages the rows in LDS slice by slice), before -> after, up to 8 live rows:
-//   h = 1536, F = 8960    QKV 9.7 -> 6.6 us, O 5.4 -> 4.4, down 9.4 -> 7.2, gate/up 16.2 -> 14.7
-//   h = 3584, F = 18944   QKV 17.8 -> 12.0,  O 8.0 -> 7.2, down 26.7 -> 28.5 (the one that loses, with a quarter of the slabs), gate/up 53.4 -> 51.5
-//   h = 5120, F = 27648   QKV 24 -> 17.0 us, O and down 66.4 -> 62.3 (5.1 TB/s), gate/up 102.5 -> 99.9 (5.7 TB/s)
+// down, which also stages the rows in LDS slice by slice), before -> after in a step of 5 / 16 rows (us; what
+// is launched where is decided by few16_resid and few16_gateup):
+//   h = 1536, F = 8960    QKV 9.4 -> 6.8 / 10.0 -> 7.9,  O 5.5 -> 4.6 / 5.5 -> 5.0, down 9.3 -> 6.9 / 9.6 -> 7.9, gate/up 15.9 -> 14.7 / 17.2 -> 17.3
+//   h = 2048, F = 11008   QKV 10.9 -> 7.2 / 12.5 -> 8.0, O 5.6 -> 5.0 / 5.9 -> 5.2, down 12.3 -> 11.3 / 11.9 -> 13.0 (with half the slabs),
+//                         gate/up 22.0 -> 19.2 / 23.2 -> 21.7
+//   h = 3584, F = 18944   QKV 17.6 -> 12.0 / 18.6 -> 13.3, O 7.9 -> 7.5 / 8.2 -> 8.2 (4 slabs instead of 14), gate/up 53.3 -> 50.9 / 54.6 -> 55.9
+//   h = 5120, F = 27648   QKV 25.1 -> 17.1 / 26.9 -> 19.3, O and down 68.1 -> 63.5 / 70.6 -> 70.7 (3 slabs instead of 12 and 13),
+//                         gate/up 104.4 -> 101.5 / 108.5 -> 111.4
 // With 17 to 32 rows the rows' requests double: QKV, whose 2 x 32-feature workgroups were fewest, still gains (h = 2048 12.9 -> 10.7 us,
 // h = 5120 28.4 -> 22.4); gate/up (h = 5120 115 -> 130) and down (h = 3584 27.6 -> 38) lose and keep their kernels.
 constexpr int sk_u(int NB) { return NB == 1 ? 8 : NB == 2 ? 6 : 3; }   // k steps (of 32) per register set: two wavefronts per SIMD
@@ -878,9 +882,8 @@ void launch_qkv_rope_skinny(hipStream_t s, const sdlm_model_cfg *m, const void *
 }
 
 // ------------------------------------------------------------------------------------------------ launch policy
-// k splits of an O or down projection of at most 16 rows: at most two workgroups per compute unit, so that all run at once (h = 1536,
-// F = 8960: 11 splits, 528 workgroups 8.9 us, 10 splits 7.2 us; h = 3584, F = 18944: 560 workgroups 31 us, 448 workgroups 28.5 us, and no
-// better in 1008 workgroups, which leave no unit idle at the end), and at least 512 of k each.
+// k splits of an O or down projection in the stream for at most 16 rows: at most two workgroups per compute unit, so that all run at
+// once (h = 1536, F = 8960: 11 splits, 528 workgroups 8.9 us, 10 splits 7.2 us), and at least 512 of k each.
 static int skinny_splits(int rows, int N, int K, size_t slab_room_floats)
 {
     long sp = 512 / (long)(mfma_pad_n(N) / 32);
@@ -889,6 +892,33 @@ static int skinny_splits(int rows, int N, int K, size_t slab_room_floats)
     sp = sp > cap_m ? cap_m : sp;
     sp = sp > 16 ? 16 : sp;
     return (int)(sp < 1 ? 1 : sp);
+}
+
+// Whether an O or down projection of at most 16 rows runs as that stream, or as the tiled kernel.  Up to k = 6144 the stream has the shorter
+// launch by 5 to 35 %, whatever the rows (us with the RMSNorm that adds the slabs, tiled -> stream: N = K = 1536 7.9 -> 7.5, 3584 14.2 -> 12.2,
+// 5120 18.6 -> 18.5, all at 16 rows, and more at fewer).  With longer k the rows' requests, which the stream repeats in every workgroup,
+// begin to weigh, and two things turn it:
+//   * workgroups that are neither one round of the units nor (nearly) two: N = 3584, K = 18944, 448 workgroups: 5 rows 30.8 -> 30.6, 8 rows 31.1 -> 31.9,
+//     16 rows 31.9 -> 35.5; N = 6144, K = 16384, 384: 5 rows 46.6 -> 47.5, 16 rows 48.5 -> 52.7;
+//   * more than 12 rows, where the tiled kernel's own workgroups are one to two rounds: N = 4096, K = 14336: 8 rows 28.4 -> 28.2, 16 rows 29.2 -> 30.4;
+//     N = 2048, K = 11008: 10 rows 16.7 -> 16.0, 16 rows 16.9 -> 17.1.  Elsewhere the stream keeps its lead: N = 1536, K = 8960 (192 tiled
+//     workgroups) 16 rows 14.5 -> 12.5, N = 5120, K = 27648 (520) 62.1 -> 58.8.
+static bool few16_resid(int min_rows, int N, int K, int splits)
+{
+    if (K <= 6144) return true;
+    const long wgs = (long)(N / 32) * splits, blocks = (N + 127) / 128, tiled = blocks * min(16L, (512 + blocks - 1) / blocks);
+    return !(wgs > 256 && wgs < 480) && !(min_rows > 12 && tiled >= 256 && tiled <= 512);
+}
+
+// Whether gate/up of at most 16 rows runs in 16-feature blocks, or in the 32-feature blocks that serve up to 32 rows.  The finer blocks spread
+// the stream better over the units (us, 32 -> 16 features, at 5 / 16 rows: N = 8960, K = 1536 15.5 -> 14.2 / 16.8 -> 16.7; N = 11008, K = 2048 21.7 -> 17.8 /
+// 22.7 -> 20.5; N = 18944, K = 3584 52.0 -> 49.6 / 54.9 -> 56.3; N = 27648, K = 5120 99.9 -> 97.6 / 104.7 -> 106.7), but repeat the rows' requests
+// twice as often.  The coarser ones win where they are one round of the units themselves (N = 6912, K = 2560, 216 blocks: 15.3 -> 16.0 / 15.8 -> 18.6;
+// N = 8192, K = 3072, 256: 19.9 -> 19.2 / 20.4 -> 21.7), and with more than 12 rows where they are more than two.
+static bool few16_gateup(int min_rows, int N)
+{
+    const int blocks32 = (N + 31) / 32;
+    return !(blocks32 >= 144 && blocks32 <= 256 && min_rows > 4) && !(blocks32 > 512 && min_rows > 12);
 }
 
 // What a product runs as: FEW16 / FEW32 are the kernels without LDS tiles for steps of few rows (16 rows x two 16-feature tiles, 32 rows x two
@@ -917,8 +947,11 @@ static void refine_gateup(int rows, int N, int K, TileChoice *c)
 // rows: bound of the launch (grid); min_rows: rows that are certainly there.  The one place where a launch shape is decided.
 static TileChoice choose(int epi, int rows, int min_rows, int N, int K, size_t slab_room_floats)
 {
-    if (epi == EPI_SWIGLU && rows <= 32) return {rows <= 16 ? FEW16 : FEW32, 1, 2, 1, SK_W, SK_W};
-    if (epi == EPI_RESID && rows <= 16) return {FEW16, 1, 1, skinny_splits(rows, N, K, slab_room_floats), SK_W, SK_W};
+    if (epi == EPI_SWIGLU && rows <= 32) return {rows <= 16 && few16_gateup(min_rows, N) ? FEW16 : FEW32, 1, 2, 1, SK_W, SK_W};
+    if (epi == EPI_RESID && rows <= 16) {
+        const int sp = skinny_splits(rows, N, K, slab_room_floats);
+        if (few16_resid(min_rows, N, K, sp)) return {FEW16, 1, 1, sp, SK_W, SK_W};
+    }
     TileChoice c{TILED, rows <= 32 ? 1 : rows <= 64 ? 2 : 4, 2, 1, 4, 1};
     // Gate/up with 129..192 certain rows and enough column blocks for one workgroup on (nearly) every compute unit: one
     // 192-row block per column block, so that no weight band is streamed by two workgroups.  (For the split-k

@@ -89,6 +89,12 @@ def test_policy_on_the_benchmark_shapes():
     # steps of few rows: streams without LDS tiles, at most 16 k splits
     assert sdlm.gemm_plan(SWIGLU, 8, 5, 8960, 1536) == (16, 32, 1) and sdlm.gemm_plan(SWIGLU, 32, 20, 8960, 1536) == (32, 64, 1)
     assert sdlm.gemm_plan(RESID, 8, 5, 1536, 8960) == (16, 32, 10) and sdlm.gemm_plan(RESID, 8, 5, 1536, 1536) == (16, 32, 3)
+    # ... and where they lose, the kernels for more rows: long k with workgroups between one and two rounds of the units, 13 to 16 rows
+    assert sdlm.gemm_plan(RESID, 8, 5, 3584, 18944) == (32, 128, 16) and sdlm.gemm_plan(RESID, 16, 16, 3584, 3584) == (16, 32, 4)
+    assert sdlm.gemm_plan(RESID, 16, 16, 2048, 11008) == (32, 128, 16) and sdlm.gemm_plan(RESID, 16, 10, 2048, 11008) == (16, 32, 8)
+    assert sdlm.gemm_plan(RESID, 16, 16, 5120, 27648) == (16, 32, 3) and sdlm.gemm_plan(RESID, 16, 16, 1536, 8960) == (16, 32, 10)
+    assert sdlm.gemm_plan(SWIGLU, 16, 16, 18944, 3584) == (32, 64, 1) and sdlm.gemm_plan(SWIGLU, 16, 10, 18944, 3584) == (16, 32, 1)
+    assert sdlm.gemm_plan(SWIGLU, 16, 5, 6912, 2560) == (32, 64, 1) and sdlm.gemm_plan(SWIGLU, 16, 16, 11008, 2048) == (16, 32, 1)
     # gate/up of 33 to 128 rows: k in halves where the 64-feature blocks are one round of the compute units
     assert sdlm.gemm_plan(SWIGLU, 66, 66, 11008, 2048) == (128, 128, 1) and sdlm.gemm_plan(SWIGLU, 64, 40, 8960, 1536) == (64, 128, 1)
     assert sdlm.gemm_plan(SWIGLU, 70, 42, 18944, 3584) == (128, 256, 1)

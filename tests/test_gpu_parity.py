@@ -673,6 +673,25 @@ def test_bf16_products_of_few_rows(B, D, hidden, ffn, heads):
     ctx.close()
 
 
+@pytest.mark.parametrize("B,D,hidden,ffn,heads", [(3, 2, 3584, 6208, 2), (8, 1, 2048, 6208, 2), (7, 1, 128, 16448, 2), (5, 1, 64, 4608, 2)])
+def test_bf16_few_rows_on_the_kernels_for_more(B, D, hidden, ffn, heads):
+    """Steps of at most 16 rows whose down projection (long k) or gate/up keeps the kernel for more rows: uneven rounds of the units, more
+    than 12 certain rows, 32-feature blocks of one round and of more than two."""
+    m = mfma_cfg(n_layers=1, n_q_heads=heads, n_kv_heads=1, hidden=hidden, ffn=ffn, vocab=300, has_qkv_bias=True)
+    om, g_dev, layers_dev = both_models(m, seed=120 + B, std=0.03)
+    prompts = [syn.uniform_int(5, f"fm{i}", 3 + 4 * i, 0, m.vocab - 1).numpy() for i in range(B)]
+    steps = 3
+    ids, cnt = syn.make_overrides(25, steps, B, D, m.vocab)
+    cnt = cnt.clone()
+    cnt[1] = D
+    max_len = max(len(p) for p in prompts) + steps * D + D
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=B, max_seq_len=max_len, D=D, tau=0.5)
+    assert ctx.kernel_info == "mfma-bf16"
+    st, _ = lockstep(ctx, om, prompts, D, 0.5, steps, logit_tol=2e-2, conf_tol=1e-3, overrides=(ids, cnt), bf16=True, max_len=max_len)
+    print("few rows, kernels for more", (B, D, hidden, ffn, heads), st)
+    ctx.close()
+
+
 @pytest.mark.parametrize("B,D,hidden,heads,kv", [(9, 3, 192, 4, 2), (33, 1, 128, 6, 2), (11, 6, 1088, 4, 1), (17, 6, 448, 14, 2), (25, 4, 2048, 12, 2), (25, 4, 2112, 12, 2), (9, 4, 64, 28, 4)])
 def test_bf16_qkv_row_blocks(B, D, hidden, heads, kv):
     """The fused QKV launch by row blocks of 32 and of 64 and the separate kernels on the other side of its rule: ragged last
