@@ -252,12 +252,14 @@ __global__ __launch_bounds__(256, 4) void attn_mfma_k(AttnArgs a)
 // what a hint misses is fetched afterwards.
 //
 // A workgroup has CG groups of 256 threads; thread group cg merges chunks CU cg .. CU cg + CU - 1 of every CG CU chunks, and
-// the groups' sums are added in group order.  The launch takes the variant by the chunks that the grid may have: up to 4 are
-// one round trip with CU = 4 (registers for more in flight only cost occupancy: prefill of 4096 rows 26.2 us, 29.2 us with CU = 8);
-// up to 8 take CU = 8, up to 16 two thread groups of them (7B shape, 7 sequences, 11 chunks: 7.7 -> 7.2 us with one group, 6.9 with
-// two; 1.5B shape, one sequence, 9 chunks: 6.6 us with one, 5.8 with two); beyond, four thread groups make 32 chunks one round trip
-// (32B shape, one sequence, 60 chunks: 24.1 -> 10.7 us, 6 sequences of the 7B shape with 31 chunks 9.4 -> 6.9 us).
-template <int CG, int CU>
+// the groups' sums are added in group order; 16 NI is the most chunks it can merge.  One group that requests four chunks at a time is the fastest
+// wherever the launch fills the chip, and for few chunks anyway: registers and threads for more in flight cost occupancy and
+// launch time.  Four groups of eight make 32 chunks one round trip where a launch of many chunks is nothing but its round trips.  us, <1,4,4> / <4,8,4>:
+//   4 kv heads x 1 group, 5 chunks 4.8 / 5.5, 12 chunks 5.9 / 5.8, 24 chunks 8.2 / 6.5, 60 chunks 15.1 / 8.6;  x 16 groups, 24 chunks 14.3 / 12.7, 60 30.6 / 23.5
+//   x 32 groups, 5 chunks 5.4 / 9.8, 24 chunks 16.4 / 19.7, 60 chunks 35.0 / 34.2;  x 512 groups, 2 chunks 27.3 / 120, 16 chunks 176 / 220
+// (In a step the early requests of four groups also pay for 9 to 12 chunks of few groups: 1.5B shape, one sequence of 670 keys, 0.6 us a layer.)
+// NI = 1 where the launch cannot have more than 16 chunks: 4.6 us for 4 x 1 groups of 5 chunks, 25.6 for 4 x 512 of 2.
+template <int CG, int CU, int NI>
 __global__ __launch_bounds__(256 * CG) void attn_combine_k(AttnArgs a)
 {
     constexpr int V4 = HD / 4, EPT = 16 * V4 / 256;   // CU: chunks a thread requests together; V4: float4 per query; EPT: elements per thread
@@ -294,8 +296,7 @@ __global__ __launch_bounds__(256 * CG) void attn_combine_k(AttnArgs a)
     __shared__ float sf[16][65];   // [query][chunk]: 2^{c(m_c - M)} / L
     __shared__ f32x4 sum[CG > 1 ? CG - 1 : 1][EPT][256];
     if (cg == 0) {
-        // sixteen lanes a query: chunks mc, mc + 16, mc + 32, mc + 48 (at most 64 chunks, 16 with one thread group)
-        constexpr int NI = CG == 1 ? 1 : 4;
+        // sixteen lanes a query: chunks mc, mc + 16, ... (at most 16 NI chunks)
         float m[NI], l[NI], M = -INFINITY, L = 0.f;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
@@ -426,7 +427,7 @@ size_t mfma_attn_scratch_bytes(const sdlm_model_cfg *m, const sdlm_run_cfg *r, i
     return worst * ((size_t)QMAX * HD * 4 + QMAX * 8) + 256;
 }
 
-bool launch_attn_mfma(hipStream_t s, const sdlm_model_cfg *m, int max_seq_len, const void *q, void *out, const void *pool_layer,
+bool launch_attn_mfma(hipStream_t s, const sdlm_model_cfg *m, int max_seq_len, int max_len, const void *q, void *out, const void *pool_layer,
                       const KvGeom &kg, const RowMeta &rm, const SeqState &st, int D, int max_groups, void *scratch, size_t scratch_bytes,
                       int part, bool two_staging)
 {
@@ -442,10 +443,14 @@ bool launch_attn_mfma(hipStream_t s, const sdlm_model_cfg *m, int max_seq_len, c
         if (two_staging) hipLaunchKernelGGL(attn_mfma_k<true>, dim3(max_groups, kg.n_kv_heads, a.max_chunks), dim3(256), 0, s, a);
         else hipLaunchKernelGGL(attn_mfma_k<false>, dim3(max_groups, kg.n_kv_heads, a.max_chunks), dim3(256), 0, s, a);
     }
-    else if (a.max_chunks > 16) hipLaunchKernelGGL((attn_combine_k<4, 8>), dim3(max_groups, kg.n_kv_heads, NQ), dim3(1024), 0, s, a);
-    else if (a.max_chunks > 8) hipLaunchKernelGGL((attn_combine_k<2, 8>), dim3(max_groups, kg.n_kv_heads, NQ), dim3(512), 0, s, a);
-    else if (a.max_chunks > 4) hipLaunchKernelGGL((attn_combine_k<1, 8>), dim3(max_groups, kg.n_kv_heads, NQ), dim3(256), 0, s, a);
-    else if (a.max_chunks > 1) hipLaunchKernelGGL((attn_combine_k<1, 4>), dim3(max_groups, kg.n_kv_heads, NQ), dim3(256), 0, s, a);
+    else if (a.max_chunks > 1) {
+        // Which merge: by the chunks that the longest sequence may have now, not by those that the capacity admits.
+        const int chunks = (min(max_len, max_seq_len) + PAGE * a.chunk_pages - 1) / (PAGE * a.chunk_pages);
+        const dim3 grid(max_groups, kg.n_kv_heads, NQ);
+        if (chunks > 8 && max_groups * kg.n_kv_heads <= 64) hipLaunchKernelGGL((attn_combine_k<4, 8, 4>), grid, dim3(1024), 0, s, a);
+        else if (a.max_chunks > 16) hipLaunchKernelGGL((attn_combine_k<1, 4, 4>), grid, dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((attn_combine_k<1, 4, 1>), grid, dim3(256), 0, s, a);
+    }
     return a.max_chunks > 1;
 }
 

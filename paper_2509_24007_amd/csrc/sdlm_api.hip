@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -192,6 +193,7 @@ struct sdlm_ctx {
     std::vector<int32_t> n_host;         // landing buffer of refresh_lengths (sized once, so that a step allocates nothing)
     char *static_scratch = nullptr;      // this GPU's copy of the library-owned scratch array (sdlm_decode_step_static)
     std::string static_err;              // why static_scratch is missing
+    bool capturing = false;              // the launches of a step are being recorded into its graph
     bool no_events = false;              // a call that must not create HIP events is running
     std::vector<Tap> taps;
     // graph replay of the decode step (opt-in): the launch sequence of a step is fixed once the batch is, all sizes
@@ -270,6 +272,8 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
     const size_t e = c->L.esz;
     hipStream_t s = c->stream;
     c->pend_slabs = 0;   // a fresh residual stream: nothing pending from an earlier pass
+    int max_len = c->r.max_seq_len;   // captured launches are replayed while the sequences grow
+    if (!c->capturing) max_len = *std::max_element(c->n_ub.begin(), c->n_ub.begin() + c->batch);
     { Phase p(c, SDLM_PH_ROWS); launch_embed(s, dt, c->x, c->embed, c->rm, rows, h, m.vocab); }
     for (int l = 0; l < m.n_layers; ++l) {
         const LayerW &w = c->lw[l];
@@ -296,12 +300,12 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
         bool merge = false;
         {
             Phase p(c, SDLM_PH_ATTN);
-            if (c->L.mfma) merge = launch_attn_mfma(s, &c->m, c->r.max_seq_len, c->q, c->att, pool_l, c->kg, c->rm, c->st, c->r.block_D, groups, c->attn_part, c->L.attn_bytes, 0, two_staging);
+            if (c->L.mfma) merge = launch_attn_mfma(s, &c->m, c->r.max_seq_len, max_len, c->q, c->att, pool_l, c->kg, c->rm, c->st, c->r.block_D, groups, c->attn_part, c->L.attn_bytes, 0, two_staging);
             else launch_attn_generic(s, dt, c->q, c->att, pool_l, c->kg, c->rm, c->st, m.n_q_heads, rows);
         }
         if (merge) {
             Phase p(c, SDLM_PH_ATTN_MERGE);
-            launch_attn_mfma(s, &c->m, c->r.max_seq_len, c->q, c->att, pool_l, c->kg, c->rm, c->st, c->r.block_D, groups, c->attn_part, c->L.attn_bytes, 1, two_staging);
+            launch_attn_mfma(s, &c->m, c->r.max_seq_len, max_len, c->q, c->att, pool_l, c->kg, c->rm, c->st, c->r.block_D, groups, c->attn_part, c->L.attn_bytes, 1, two_staging);
         }
         run_taps(c, l, 1, c->att, (size_t)rows * nq * e);
         {
@@ -652,7 +656,9 @@ static int decode_step_impl(sdlm_ctx *c, int32_t *ids, int32_t *count, float *co
             drop_graph(c);
             hipGraph_t g = nullptr;
             HIPCHK(c, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
+            c->capturing = true;
             launch_all();
+            c->capturing = false;
             hipError_t e1 = hipStreamEndCapture(s, &g);
             if (e1 != hipSuccess || !g) return fail(c, SDLM_EHIP, "graph capture of the decode step failed: %s", hipGetErrorString(e1));
             hipError_t e2 = hipGraphInstantiate(&c->graph_exec, g, nullptr, nullptr, 0);

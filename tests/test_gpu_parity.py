@@ -751,17 +751,44 @@ def test_bf16_requested_logits_rows_and_ragged_vocabulary(B, D, vocab):
     ctx.close()
 
 
+@pytest.mark.parametrize("capacity", [32, 18000])
 @pytest.mark.parametrize("prompt", [100, 300, 500, 640, 980, 1500, 2100])
-def test_bf16_split_kv_merge_by_number_of_chunks(prompt):
-    """The split-KV merge of one sequence with 2 .. 34 chunks of 64 keys (variants for up to 4, 8, 16 and 64): logits against the oracle."""
+def test_bf16_split_kv_merge_by_number_of_chunks(prompt, capacity):
+    """The split-KV merge of one sequence with 2 .. 34 chunks of 64 keys, where the context holds little more (variants by the chunks it has and may
+    have), and of 1 .. 8 chunks of 512 keys where it holds far more: logits against the oracle."""
     m = mfma_cfg(n_layers=1, n_q_heads=4, n_kv_heads=2, hidden=128, ffn=192, vocab=1000)
     om, g_dev, layers_dev = both_models(m, seed=95, std=0.08)
     p = syn.uniform_int(8, f"mg{prompt}", prompt, 0, m.vocab - 1).numpy()
-    ctx = gpu_context(m, g_dev, layers_dev, max_batch=1, max_seq_len=prompt + 32, D=4, tau=0.5)
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=1, max_seq_len=prompt + capacity, D=4, tau=0.5)
     # flips: each one is bounded by its row's own measured logit error inside lockstep; a share of 8 rows has no meaning (random
     # logits: the top-2 gap is below twice a 6e-3 error in one row out of ten, so 2 of 8 occurs in one prompt out of five)
     lockstep(ctx, om, [p], 4, 0.5, 2, logit_tol=2e-2, conf_tol=1e-3, bf16=True, max_len=prompt + 32, flip_ceiling=1.0)
     ctx.close()
+
+
+def test_bf16_split_kv_merge_of_many_groups_and_chunks():
+    """Seventeen chunks of a sequence in a batch whose merge is the one for many row groups, against the same sequence alone (33 chunks, the
+    merge for few groups): one step each, eager and replayed from a graph (whose launches must serve every length)."""
+    m = mfma_cfg(n_layers=1, n_q_heads=8, n_kv_heads=4, hidden=128, ffn=192, vocab=1000)
+    _, g_dev, layers_dev = both_models(m, seed=96, std=0.08)
+    prompts = [syn.uniform_int(8, f"mm{i}", 4200 if i == 11 else 3 + i, 0, m.vocab - 1).numpy() for i in range(17)]
+    out = []
+    for ps, at in ((prompts, 11), ([prompts[11]], 0)):
+        ctx = gpu_context(m, g_dev, layers_dev, max_batch=len(ps), max_seq_len=4300, D=4, tau=0.5, paged=True, n_pages=320, stream=torch.cuda.Stream())
+        ids = torch.empty(len(ps), 4, dtype=torch.int32, device="cuda")
+        cnt = torch.empty(len(ps), dtype=torch.int32, device="cuda")
+        logits = torch.empty(len(ps), 4, m.vocab, device="cuda")
+        for graph in (False, True):
+            ctx.prefill(ps)
+            ctx.graph(graph)
+            ctx.decode_step(ids, cnt, None, logits)
+            torch.cuda.synchronize()
+            out.append(logits[at].clone())
+        ctx.close()
+    # two correct bf16 paths of one layer: 4 * 2^-9 of the largest logit covers the rounding of the attention output (2^-9) on its way through
+    # the O projection, the MLP and the head
+    for z in out[1:]:
+        assert (z - out[0]).abs().max() <= 4 * 2.0 ** -9 * out[0].abs().max()
 
 
 @pytest.mark.parametrize("hidden", [4100, 8200, 16384])
