@@ -236,8 +236,8 @@ __device__ inline float block_sum(float v, float *red)
 // A row lives in registers between the two passes (TH threads, NV float4 each, h <= 4 TH NV).
 // Bound, with few rows: the memory round trips, one for the row and one per SU slabs; a row therefore gets the threads that let
 // its slabs be requested together.  256 threads -> now: h = 5120, 8 rows 11.0 -> 6.5 us; h = 3584, 70 rows 7.8 -> 5.7 us, 512 rows
-// 9.8 -> 8.6 us; h = 2048, 256 rows 6.5 -> 5.8 us.  With many rows: bandwidth, and small workgroups hide one row's reduction
-// behind another's loads (h = 3584, 4096 rows without slabs: 256 threads 18.6 us = 4.7 TB/s, 1024 threads 21.9 us).
+// 9.8 -> 8.6 us; h = 2048, 256 rows 6.5 -> 5.8 us.  With more rows than workgroups fit the chip at once: bandwidth, and small workgroups hide
+// one row's reduction behind another's loads (see rmsnorm_t).
 template <typename T, int TH, int NV>
 __global__ __launch_bounds__(TH) void rmsnorm_k(T *out, float *x, const T *g, int h, float eps, const int32_t *row_index,
                                                 const int32_t *p_count, int sure, const float *slabs, int n_slabs, size_t slab_stride)
@@ -317,11 +317,17 @@ static void rmsnorm_t(hipStream_t s, void *out, float *x, const void *g, int h, 
                       const int32_t *p_count, int max_rows, int min_rows, const float *slabs, int n_slabs, size_t slab_stride)
 {
 #define SDLM_RMS(TH, NV) hipLaunchKernelGGL((rmsnorm_k<T, TH, NV>), dim3(max_rows), dim3(TH), 0, s, (T *)out, x, (const T *)g, h, eps, row_index, p_count, min_rows, slabs, n_slabs, slab_stride)
-    if (max_rows > 1024) {   // between the measured 992 rows (with slabs) and 2205 (without: 12.6 us with 256 threads, 13.4 us with 1024)
-        if (h <= 2048) SDLM_RMS(256, 2); else if (h <= 4096) SDLM_RMS(256, 4); else if (h <= 8192) SDLM_RMS(256, 8); else SDLM_RMS(256, 16);
-        return;
-    }
-    if (h <= 1024) SDLM_RMS(256, 1); else if (h <= 2048) SDLM_RMS(512, 1); else if (h <= 4096) SDLM_RMS(1024, 1); else if (h <= 8192) SDLM_RMS(1024, 2); else SDLM_RMS(1024, 4);
+    // Wide workgroups while those of all rows are on the chip at once (four a compute unit of 512 threads, two of 1024, one of 1024 with more
+    // than 4096 values a row, for their registers), counted halfway between the certain and the possible rows.  us, 256 threads / wide:
+    //   h = 2048   1024 rows without slabs 4.4 / 4.4, 2048 rows 6.6 / 6.7
+    //   h = 3584   512 rows, 4 slabs 9.3 / 8.4, without 4.5 / 4.4;  640 rows, 4 slabs 11.6 / 11.8, without 4.9 / 5.7;  4096 rows 18.2 / 20.8
+    //   h = 5120   256 rows, 4 slabs 8.1 / 5.9, without 4.8 / 4.0;  384 rows, 4 slabs 11.1 / 11.1, without 5.0 / 5.9;  640 rows 15.4 / 18.1, 5.8 / 8.0
+    const int rows = (max_rows + min(max(min_rows, 0), max_rows) + 1) / 2;
+    if (h <= 1024) SDLM_RMS(256, 1);
+    else if (h <= 2048) { if (rows <= 1024) SDLM_RMS(512, 1); else SDLM_RMS(256, 2); }
+    else if (h <= 4096) { if (rows <= 512) SDLM_RMS(1024, 1); else SDLM_RMS(256, 4); }
+    else if (h <= 8192) { if (rows <= 256) SDLM_RMS(1024, 2); else SDLM_RMS(256, 8); }
+    else { if (rows <= 256) SDLM_RMS(1024, 4); else SDLM_RMS(256, 16); }
 #undef SDLM_RMS
 }
 

@@ -793,14 +793,48 @@ def test_bf16_split_kv_merge_of_many_groups_and_chunks():
 
 @pytest.mark.parametrize("hidden", [4100, 8200, 16384])
 def test_fp32_wide_hidden_rows(hidden):
-    """Rows wider than 4096 elements: the RMSNorm variants that hold 8 and 16 vectors of a row per thread (and the
-    widest row the library accepts)."""
+    """Rows wider than 4096 elements: the RMSNorm variants of few rows that hold two and four vectors of a row per thread (and
+    the widest row the library accepts)."""
     m = gpu_cfg(hidden=hidden, n_layers=1, ffn=48, vocab=97)
     om, g_dev, layers_dev = both_models(m, seed=33, std=0.02)
     prompts = [np.array([3, 1, 4, 1, 5], dtype=np.int32), np.array([9, 2], dtype=np.int32)]
     ctx = gpu_context(m, g_dev, layers_dev, max_batch=2, max_seq_len=32, D=3, tau=0.5)
     st, _ = lockstep(ctx, om, prompts, 3, 0.5, 3, logit_tol=1e-4, conf_tol=1e-5)
     print("wide rows", hidden, st)
+    ctx.close()
+
+
+@pytest.mark.parametrize("hidden,rows", [(1028, 1024), (1028, 1025), (2052, 512), (2052, 513), (4100, 256), (4100, 257), (8200, 257), (16384, 300)])
+def test_fp32_rmsnorm_of_many_rows(hidden, rows):
+    """Prefill passes on both sides of the rows up to which RMSNorm takes wide workgroups, and the variants of 256 threads that hold 2, 4, 8 and 16
+    vectors of a row per thread: one step's logits depend on every key and value of the pass."""
+    m = gpu_cfg(hidden=hidden, n_q_heads=1, n_kv_heads=1, n_layers=1, ffn=8, vocab=97)
+    om, g_dev, layers_dev = both_models(m, seed=34, std=0.02)
+    prompts = [syn.uniform_int(34, "rn", rows, 0, m.vocab - 1).numpy()]
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=1, max_seq_len=rows + 8, D=2, tau=0.5)
+    st, _ = lockstep(ctx, om, prompts, 2, 0.5, 1, logit_tol=1e-4, conf_tol=1e-5, max_len=rows + 8)
+    print("rmsnorm of many rows", hidden, rows, st)
+    ctx.close()
+
+
+@pytest.mark.parametrize("B,D,hidden", [(40, 4, 4160), (43, 6, 2112), (64, 7, 2112)])
+def test_bf16_rmsnorm_of_many_rows_with_slabs(B, D, hidden):
+    """Steps of more rows than RMSNorm takes wide workgroups for, after split-k projections (their slabs are added in the same kernel), and a step
+    (43 x 6) whose certain rows are below that line and whose possible ones are above it."""
+    m = mfma_cfg(n_layers=2, n_q_heads=2, n_kv_heads=1, hidden=hidden, ffn=1024, vocab=300, has_qkv_bias=True)
+    # std = 1 / sqrt(h): a projection keeps the size of its input, scores have a standard deviation of sqrt(128) = 11, and the roundings of q
+    # and k to bf16 (2^-9 of the value each) move them by 0.03.  At std = 0.03 (scores of 42, moved by 0.12) single attention weights are off by
+    # a tenth and a logit by 3e-2, with any order of the sums.
+    om, g_dev, layers_dev = both_models(m, seed=130 + B, std=hidden ** -0.5)
+    prompts = [syn.uniform_int(5, f"rs{i}", 2 + i % 5, 0, m.vocab - 1).numpy() for i in range(B)]
+    ids, cnt = syn.make_overrides(26, 3, B, D, m.vocab)
+    cnt = cnt.clone()
+    cnt[1] = D
+    max_len = 8 + 4 * D
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=B, max_seq_len=max_len, D=D, tau=0.5)
+    assert ctx.kernel_info == "mfma-bf16"
+    st, _ = lockstep(ctx, om, prompts, D, 0.5, 3, logit_tol=2e-2, conf_tol=1e-3, overrides=(ids, cnt), bf16=True, max_len=max_len, oracle_seqs=[0, 1, B // 2, B - 1])
+    print("rmsnorm with slabs", (B, D, hidden), st)
     ctx.close()
 
 
