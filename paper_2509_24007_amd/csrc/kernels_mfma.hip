@@ -623,7 +623,7 @@ __global__ __launch_bounds__(SK_W * 64) void swiglu_skinny32_k(MfmaArgs a)
 // and the quarters are added in wavefront order through LDS.  Both operands come straight from global memory in the order of
 // v_mfma_f32_16x16x32_bf16: a 16-feature half of a packed 32 x 16 tile pair is four runs of 256 bytes per load, the rows (shared by
 // every workgroup, so served by L2) are 64-byte pieces; rows beyond the live ones repeat the last row and their results are
-// dropped.  NB = 1 serves at most 16 rows, NB = 2 at most 32 (QKV also takes more rows, in blocks: see qkv_skinny_units).  Against workgroups of 32-feature tiles (the tiled kernel for O and
+// dropped.  NB = 1 serves at most 16 rows, NB = 2 at most 32 (QKV also takes more rows, in blocks: see qkv_rows).  Against workgroups of 32-feature tiles (the tiled kernel for O and
 // down, which also stages the rows in LDS slice by slice), before -> after in a step of 5 / 16 rows (us; what
 // is launched where is decided by few16_resid and few16_gateup):
 //   h = 1536, F = 8960    QKV 9.4 -> 6.8 / 10.0 -> 7.9,  O 5.5 -> 4.6 / 5.5 -> 5.0, down 9.3 -> 6.9 / 9.6 -> 7.9, gate/up 15.9 -> 14.7 / 17.2 -> 17.3
@@ -761,7 +761,7 @@ struct QkvSkinnyArgs {
     const bf16_t *X, *Wp, *bias;
     const int32_t *pR;
     int max_rows, K, Hq;
-    int m_blocks, m_sure;   // row blocks; row blocks below m_sure certainly hold rows
+    int m_sure, m_rest;     // row blocks that certainly hold rows, and that may
     bf16_t *q_out, *pool;
     KvGeom kg;
     RowMeta rm;
@@ -769,20 +769,11 @@ struct QkvSkinnyArgs {
     const float2 *rope;
 };
 
+// The 16 NB rows from m0 on, columns `col`.
 template <int NB>
-__global__ __launch_bounds__(SK_W * 64, 2) void qkv_rope_skinny_k(QkvSkinnyArgs a)
+__device__ inline void qkv_rope_rows(const QkvSkinnyArgs &a, f32x4 (&part)[SK_W][2][NB][64], int m0, int col)
 {
-    __shared__ f32x4 part[SK_W][2][NB][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // workgroup id -> (row block, column block), as in the tiled kernel: certain row blocks first, the row blocks of one
-    // column block on one XCD, so that its weights leave memory once
-    const int n_cols = 4 * (a.Hq + 2 * a.kg.n_kv_heads), n_first = n_cols * a.m_sure, first8 = (n_first + 7) & ~7;
-    const bool sure = (int)blockIdx.x < first8;
-    const int bid = sure ? blockIdx.x : blockIdx.x - first8, mb = sure ? a.m_sure : a.m_blocks - a.m_sure;
-    const int per8 = (n_cols * mb + 7) >> 3, wg = (bid & 7) * per8 + (bid >> 3);
-    if (wg >= n_cols * mb) return;
-    const int m0 = ((sure ? 0 : a.m_sure) + wg % mb) * NB * 16, col = wg / mb;
-    if (!sure && m0 >= *a.pR) return;
     const int head = col >> 2, t16 = col & 3;   // heads: Hq of q, then Hkv of k, then Hkv of v; t16: which 16 of the first 64 features
     const int KS = a.K >> 4, K32 = a.K >> 5, per = (K32 + SK_W - 1) / SK_W;
     const bf16_t *wa = a.Wp + ((size_t)(head * 4 + (t16 >> 1)) * KS) * 512 + (t16 & 1) * 128;
@@ -837,6 +828,26 @@ __global__ __launch_bounds__(SK_W * 64, 2) void qkv_rope_skinny_k(QkvSkinnyArgs 
     }
 }
 
+// Row blocks of 16 NB rows; those that may be empty are of 16 NR rows.
+template <int NB, int NR>
+__global__ __launch_bounds__(SK_W * 64, 2) void qkv_rope_skinny_k(QkvSkinnyArgs a)
+{
+    __shared__ f32x4 part[SK_W * 2 * NB * 64];
+    // workgroup id -> (row block, column block), as in the tiled kernel: certain row blocks first, the row blocks of one
+    // column block on one XCD, so that its weights leave memory once
+    const int n_cols = 4 * (a.Hq + 2 * a.kg.n_kv_heads), n_first = n_cols * a.m_sure, first8 = (n_first + 7) & ~7;
+    const bool sure = (int)blockIdx.x < first8;
+    const int bid = sure ? blockIdx.x : blockIdx.x - first8, mb = sure ? a.m_sure : a.m_rest;
+    const int per8 = (n_cols * mb + 7) >> 3, wg = (bid & 7) * per8 + (bid >> 3);
+    if (wg >= n_cols * mb) return;
+    if (sure) {
+        qkv_rope_rows<NB>(a, *reinterpret_cast<f32x4 (*)[SK_W][2][NB][64]>(part), wg % mb * NB * 16, wg / mb);
+    } else {
+        const int m0 = a.m_sure * NB * 16 + wg % mb * NR * 16;
+        if (m0 < *a.pR) qkv_rope_rows<NR>(a, *reinterpret_cast<f32x4 (*)[SK_W][2][NR][64]>(part), m0, wg / mb);
+    }
+}
+
 static int sure_blocks(int rows, int min_rows, int MT)
 {
     const int mb = (rows + MT * 32 - 1) / (MT * 32);
@@ -845,40 +856,54 @@ static int sure_blocks(int rows, int min_rows, int MT)
     return ms < 1 ? 1 : (ms > mb ? mb : ms);
 }
 
-// 16-row units per workgroup of the fused launch; 0: the tiled projection and the RoPE + K/V placement kernel serve this step better.
+// How the fused launch deals out its rows; units = 0: the tiled projection and the RoPE + K/V placement kernel serve this step better.
 // Row blocks repeat the weight stream (from L2) and a workgroup's time grows with k times its rows, where the tiled kernel splits
 // k between workgroups: row blocks pay while all workgroups fit the chip at once (about one per compute unit).
 //   32-row blocks, counted for the mean of certain and possible rows: h = 2048, 66 rows, 240 workgroups 15.1 -> 10.5 us (both kernels
 //   before -> fused); h = 1536, 60 rows 13.6 -> 8.9; but h = 2048, 400 workgroups 17.1 -> 16.2, h = 3584, 432 workgroups 17.1 -> 22.5.
 //   64-row blocks, k of at most 2048: h = 2048, 160 rows, 240 workgroups 17.1 -> 15.2 us; h = 5120, 48 rows, 224 workgroups 28.2 -> 30.6.
-static int qkv_skinny_units(const sdlm_model_cfg *m, int max_rows, int min_rows)
+// Where the blocks that may be empty would put a second 64-row workgroup on some units, they are of 32 rows (a layer of h = 2048, 16 sequences, D = 8:
+// all 256 rows 129.5 us with 64 rows, 126.2 with 32, 127.9 with the separate kernels; 128 us at 160 rows were 111 either way).  With
+// 32 rows where they do fit, a layer takes 3 % longer (24 sequences, D = 4, 192 rows: 114.2 -> 118.2 us).  With k above 1536 the separate kernels take over
+// where even so the possible rows are more than 640 32-row workgroups (20 sequences, D = 8, all 320 rows: 147.4 -> 145.8 us a layer); k = 1536 gains there
+// still (48 sequences, D = 4, 384 rows: 122.9 -> 120.6).
+struct QkvRows { int units, rest_units, m_sure, m_rest; };   // 16-row units of a certain row block and of one that may be empty; how many of each
+
+static QkvRows qkv_rows(const sdlm_model_cfg *m, int max_rows, int min_rows)
 {
-    if (!mfma_supported(m)) return 0;
-    if (max_rows <= 16) return 1;
-    if (max_rows <= 32) return 2;
-    const long cols = 4 * (m->n_q_heads + 2 * m->n_kv_heads), units = 256;
-    if (cols * (sure_blocks(max_rows, min_rows, 1) + (max_rows + 31) / 32) <= 2 * units) return 2;
-    if (m->hidden <= 2048 && cols * sure_blocks(max_rows, min_rows, 2) <= units) return 4;
-    return 0;
+    if (!mfma_supported(m)) return {};
+    const int cols = 4 * (m->n_q_heads + 2 * m->n_kv_heads), chip = 256;
+    auto with = [&](int units, int rest_units) {
+        const int rows = 16 * units, rest = 16 * rest_units, all = (max_rows + rows - 1) / rows;
+        const int m_sure = min(max((min_rows + rows - 1) / rows, 1), all);
+        return QkvRows{units, rest_units, m_sure, max(0, (max_rows - m_sure * rows + rest - 1) / rest)};
+    };
+    if (max_rows <= 16) return with(1, 1);
+    if (max_rows <= 32) return with(2, 2);
+    if (cols * (sure_blocks(max_rows, min_rows, 1) + (max_rows + 31) / 32) <= 2 * chip) return with(2, 2);
+    if (m->hidden > 2048 || cols * sure_blocks(max_rows, min_rows, 2) > chip) return {};
+    if (cols * ((max_rows + 63) / 64) <= chip || m->hidden <= 1536) return with(4, 4);
+    const QkvRows q = with(4, 2);
+    return cols * (2 * q.m_sure + q.m_rest) <= 640 ? q : QkvRows{};
 }
 
-bool qkv_rope_skinny_applies(const sdlm_model_cfg *m, int max_rows, int min_rows) { return qkv_skinny_units(m, max_rows, min_rows) > 0; }
+bool qkv_rope_skinny_applies(const sdlm_model_cfg *m, int max_rows, int min_rows) { return qkv_rows(m, max_rows, min_rows).units > 0; }
 
 void launch_qkv_rope_skinny(hipStream_t s, const sdlm_model_cfg *m, const void *X, const void *w_packed, const void *bias, const int32_t *p_rows,
                             int max_rows, int min_rows, void *q_out, void *pool_layer, const KvGeom &kg, const RowMeta &rm, const SeqState &st, const float2 *rope)
 {
-    const int NB = qkv_skinny_units(m, max_rows, min_rows), rows = NB * 16;
+    const QkvRows q = qkv_rows(m, max_rows, min_rows);
     QkvSkinnyArgs a;
     a.X = (const bf16_t *)X; a.Wp = (const bf16_t *)w_packed; a.bias = (const bf16_t *)bias; a.pR = p_rows;
     a.max_rows = max_rows; a.K = m->hidden; a.Hq = m->n_q_heads;
-    a.m_blocks = (max_rows + rows - 1) / rows;
-    a.m_sure = min(max((min_rows + rows - 1) / rows, 1), a.m_blocks);
+    a.m_sure = q.m_sure; a.m_rest = q.m_rest;
     a.q_out = (bf16_t *)q_out; a.pool = (bf16_t *)pool_layer; a.kg = kg; a.rm = rm; a.st = st; a.rope = rope;
     const int n_cols = 4 * (m->n_q_heads + 2 * m->n_kv_heads);
-    const dim3 grid((n_cols * a.m_sure + 7) / 8 * 8 + (n_cols * (a.m_blocks - a.m_sure) + 7) / 8 * 8), block(SK_W * 64);
-    if (NB == 1) hipLaunchKernelGGL(qkv_rope_skinny_k<1>, grid, block, 0, s, a);
-    else if (NB == 2) hipLaunchKernelGGL(qkv_rope_skinny_k<2>, grid, block, 0, s, a);
-    else hipLaunchKernelGGL(qkv_rope_skinny_k<4>, grid, block, 0, s, a);
+    const dim3 grid((n_cols * a.m_sure + 7) / 8 * 8 + (n_cols * a.m_rest + 7) / 8 * 8), block(SK_W * 64);
+    if (q.units == 1) hipLaunchKernelGGL((qkv_rope_skinny_k<1, 1>), grid, block, 0, s, a);
+    else if (q.units == 2) hipLaunchKernelGGL((qkv_rope_skinny_k<2, 2>), grid, block, 0, s, a);
+    else if (q.rest_units == 4) hipLaunchKernelGGL((qkv_rope_skinny_k<4, 4>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((qkv_rope_skinny_k<4, 2>), grid, block, 0, s, a);
 }
 
 // ------------------------------------------------------------------------------------------------ launch policy

@@ -692,10 +692,12 @@ def test_bf16_few_rows_on_the_kernels_for_more(B, D, hidden, ffn, heads):
     ctx.close()
 
 
-@pytest.mark.parametrize("B,D,hidden,heads,kv", [(9, 3, 192, 4, 2), (33, 1, 128, 6, 2), (11, 6, 1088, 4, 1), (17, 6, 448, 14, 2), (25, 4, 2048, 12, 2), (25, 4, 2112, 12, 2), (9, 4, 64, 28, 4)])
+@pytest.mark.parametrize("B,D,hidden,heads,kv", [(9, 3, 192, 4, 2), (33, 1, 128, 6, 2), (11, 6, 1088, 4, 1), (17, 6, 448, 14, 2), (25, 4, 2048, 12, 2), (25, 4, 2112, 12, 2), (9, 4, 64, 28, 4),
+                                                  (15, 8, 1600, 16, 2), (13, 9, 1600, 16, 2), (20, 8, 1600, 16, 2)])
 def test_bf16_qkv_row_blocks(B, D, hidden, heads, kv):
-    """The fused QKV launch by row blocks of 32 and of 64 and the separate kernels on the other side of its rule: ragged last
-    blocks, blocks that only exist after a full commit (B * 2D rows) and are empty after single tokens."""
+    """The fused QKV launch by row blocks of 32 and of 64 and the separate kernels on the other side of its rules: ragged last
+    blocks, blocks that only exist after a full commit (B * 2D rows) and are empty after single tokens, such blocks of 64 rows and of 32
+    (h = 1600: 240 and 234 possible rows beside 135 and 130 certain ones; 320 beside 180 take the separate kernels)."""
     m = mfma_cfg(n_layers=2, n_q_heads=heads, n_kv_heads=kv, hidden=hidden, ffn=192, vocab=1000, has_qkv_bias=True)
     om, g_dev, layers_dev = both_models(m, seed=110 + B + heads, std=0.03)
     prompts = [syn.uniform_int(5, f"rb{i}", 3 + 5 * (i % 7), 0, m.vocab - 1).numpy() for i in range(B)]
