@@ -318,11 +318,11 @@ static void rmsnorm_t(hipStream_t s, void *out, float *x, const void *g, int h, 
 {
 #define SDLM_RMS(TH, NV) hipLaunchKernelGGL((rmsnorm_k<T, TH, NV>), dim3(max_rows), dim3(TH), 0, s, (T *)out, x, (const T *)g, h, eps, row_index, p_count, min_rows, slabs, n_slabs, slab_stride)
     // Wide workgroups while those of all rows are on the chip at once (four a compute unit of 512 threads, two of 1024, one of 1024 with more
-    // than 4096 values a row, for their registers), counted halfway between the certain and the possible rows.  us, 256 threads / wide:
+    // than 4096 values a row, for their registers), counted in certain rows: a step has few more, as a rule.  us, 256 threads / wide:
     //   h = 2048   1024 rows without slabs 4.4 / 4.4, 2048 rows 6.6 / 6.7
     //   h = 3584   512 rows, 4 slabs 9.3 / 8.4, without 4.5 / 4.4;  640 rows, 4 slabs 11.6 / 11.8, without 4.9 / 5.7;  4096 rows 18.2 / 20.8
     //   h = 5120   256 rows, 4 slabs 8.1 / 5.9, without 4.8 / 4.0;  384 rows, 4 slabs 11.1 / 11.1, without 5.0 / 5.9;  640 rows 15.4 / 18.1, 5.8 / 8.0
-    const int rows = (max_rows + min(max(min_rows, 0), max_rows) + 1) / 2;
+    const int rows = min_rows > 0 ? min(min_rows, max_rows) : max_rows;
     if (h <= 1024) SDLM_RMS(256, 1);
     else if (h <= 2048) { if (rows <= 1024) SDLM_RMS(512, 1); else SDLM_RMS(256, 2); }
     else if (h <= 4096) { if (rows <= 512) SDLM_RMS(1024, 1); else SDLM_RMS(256, 4); }
