@@ -951,17 +951,19 @@ static bool few16_gateup(int min_rows, int N)
 enum { TILED = 0, FEW16, FEW32 };
 struct TileChoice { int kind, MT, NT, splits, WV, KH; };
 
-// Gate/up launches of 33 .. 256 rows whose shape the plain tiles do not serve well (K a multiple of 128):
-//   * Up to 128 rows and at most 256 column blocks of 64 features: workgroups of 128 x 64 features whose wavefronts take half of k
-//     each.  Bound by the weights in flight: F / 128 workgroups of the plain tile leave most compute units without any (h = 2048,
+// Gate/up launches of more than 32 rows whose shape the plain tiles do not serve well (K a multiple of 128):
+//   * Up to 128 possible rows and at most 256 column blocks of 64 features: workgroups of 64 or 128 rows x 64 features whose wavefronts
+//     take half of k each.  Bound by the weights in flight: F / 128 workgroups of the plain tile leave most compute units without any (h = 2048,
 //     F = 11008: 86 workgroups); half the columns double the workgroups, and k in halves keeps four wavefronts in each.
 //     h = 2048, F = 11008: 66 rows 32.9 -> 24.4 us, 48 rows 35.6 -> 24.8; h = 1536, F = 8960: 96 rows 24.5 -> 19.7, 48 rows 27.4 ->
-//     18.9.  Beyond 128 rows (192- and 256-row tiles in halves: 160 rows 31.8 -> 32.5) and for the split-k projections (160 rows,
-//     QKV 11.8 -> 19.4, O 8.8 -> 14.0, down 20.8 -> 23.4) the activations' share of the load path takes it back; with more
-//     than 256 column blocks the plain tile already occupies the chip.
-//   * Where the 192-row tile would be taken and the step may have more rows: a 256-row tile, so that the rows beyond 192 are not a second
-//     row block that streams every weight again.  h = 5120, F = 27648, 193..224 rows: 205.6 -> 131.8 us.  (Its 256 accumulator
-//     registers leave room for the operands only with an even number of slices, without a peeled last one.)
+//     18.9; h = 4096, F = 16384 (256 blocks): 48 rows 70.9 -> 52.4, 128 rows 66.9 -> 56.7.  One such workgroup fills a unit (its registers), so beyond
+//     256 blocks there is a second round: h = 3584, F = 18944 (296): 48 rows 64.2 -> 65.2, 70 rows 55.6 -> 70.5; h = 5120, F = 27648 (432): 48 rows
+//     111.5 -> 104.0, 96 rows 99.4 -> 112.7.  Beyond 128 rows (192- and 256-row tiles in halves: 160 rows 31.8 -> 32.5) and for the split-k
+//     projections (160 rows, QKV 11.8 -> 19.4, O 8.8 -> 14.0, down 20.8 -> 23.4) the activations' share of the load path takes it back.
+//   * Where the 192-row tile would be taken (129 to 192 certain rows) and more than 192 are possible: a 256-row tile, so that the rows from 193 to 256
+//     are not a second row block that streams every weight again.  A layer of h = 5120, F = 27648: 208 rows 406 -> 337 us, 256 rows 431 -> 361; up to
+//     192 rows it costs 0.8 (315.8 -> 316.6 at 156), and beyond 256, where both need a second block, 6 (20 sequences, D = 8, 320 rows: 423 -> 429).  (Its
+//     256 accumulator registers leave room for the operands only with an even number of slices, without a peeled last one.)
 static void refine_gateup(int rows, int N, int K, TileChoice *c)
 {
     if (K % 128) return;

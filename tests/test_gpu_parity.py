@@ -289,7 +289,7 @@ def mfma_cfg(**kw):
     ("g6-D4-batch1-long", dict(n_q_heads=12, n_kv_heads=2, hidden=384, ffn=1024), [700], 4, 0.6, False),
     ("g4-batch20-128-row-tiles", dict(n_q_heads=8, n_kv_heads=2, vocab=4096 + 160), [3 + 7 * i for i in range(20)], 4, 0.6, True),
     ("g5-D16", dict(n_q_heads=10, n_kv_heads=2, hidden=320, ffn=640, has_qkv_bias=False), [2, 50], 16, 0.3, True),
-    ("g4-batch36-192-row-gate-up-tile", dict(n_q_heads=8, n_kv_heads=2, hidden=256, ffn=24576), [3 + 2 * i for i in range(36)], 4, 0.6, True),
+    ("g4-batch36-256-row-gate-up-tile", dict(n_q_heads=8, n_kv_heads=2, hidden=256, ffn=24576), [3 + 2 * i for i in range(36)], 4, 0.6, True),
 ])
 def test_bf16_mfma_path(name, kw, lens, D, tau, paged):
     """The bf16 product path: MFMA GEMMs, MFMA block-masked attention (split KV), fused LM-head reduction."""
@@ -714,11 +714,13 @@ def test_bf16_qkv_row_blocks(B, D, hidden, heads, kv):
     ctx.close()
 
 
-@pytest.mark.parametrize("B,D,hidden,ffn", [(5, 4, 128, 2112), (8, 4, 1408, 1088), (13, 4, 384, 2112), (16, 4, 1024, 192), (26, 4, 256, 24640), (32, 4, 128, 24576)])
+@pytest.mark.parametrize("B,D,hidden,ffn", [(5, 4, 128, 2112), (8, 4, 1408, 1088), (13, 4, 384, 2112), (16, 4, 1024, 192), (26, 4, 256, 24640), (32, 4, 128, 24576),
+                                             (48, 2, 256, 24576), (48, 2, 192, 24640), (26, 4, 320, 24576)])
 def test_bf16_gate_up_of_33_to_256_rows(B, D, hidden, ffn):
     """The gate/up shapes between the small-step kernel and the 128-row tiles: k in two halves inside a workgroup (one slice,
-    an odd number and many slices per half; up to 64 and up to 128 rows, a ragged last column block), and the 256-row tile (more
-    than 128 certain rows, wide matrix; the step after a full commit has B * 2D rows, the one after single tokens B * (D + 1))."""
+    an odd number and many slices per half; up to 64 and up to 128 rows, a ragged last column block), the 256-row tile (more
+    than 128 certain rows, wide matrix; the step after a full commit has B * 2D rows, the one after single tokens B * (D + 1)) and the 192-row
+    one (at most 192 possible rows, or an odd number of slices; even and odd slices, a second row block after the full commit)."""
     m = mfma_cfg(n_layers=1, n_q_heads=4, n_kv_heads=2, hidden=hidden, ffn=ffn, vocab=1000, has_qkv_bias=True)
     om, g_dev, layers_dev = both_models(m, seed=80 + B, std=0.03)
     lens = [3 + 5 * (i % 6) for i in range(B)]
