@@ -956,9 +956,9 @@ struct TileChoice { int kind, MT, NT, splits, WV, KH; };
 //     take half of k each.  Bound by the weights in flight: F / 128 workgroups of the plain tile leave most compute units without any (h = 2048,
 //     F = 11008: 86 workgroups); half the columns double the workgroups, and k in halves keeps four wavefronts in each.
 //     h = 2048, F = 11008: 66 rows 32.9 -> 24.4 us, 48 rows 35.6 -> 24.8; h = 1536, F = 8960: 96 rows 24.5 -> 19.7, 48 rows 27.4 ->
-//     18.9; h = 4096, F = 16384 (256 blocks): 48 rows 70.9 -> 52.4, 128 rows 66.9 -> 56.7.  One such workgroup fills a unit (its registers), so beyond
-//     256 blocks there is a second round: h = 3584, F = 18944 (296): 48 rows 64.2 -> 65.2, 70 rows 55.6 -> 70.5; h = 5120, F = 27648 (432): 48 rows
-//     111.5 -> 104.0, 96 rows 99.4 -> 112.7.  Beyond 128 rows (192- and 256-row tiles in halves: 160 rows 31.8 -> 32.5) and for the split-k
+//     18.9; h = 4096, F = 16384 (256 blocks): 48 rows 70.9 -> 52.4, 128 rows 66.9 -> 56.7.  A workgroup of 128 rows fills a unit (360 registers), so
+//     beyond 256 blocks there is a second round: h = 3584, F = 18944 (296): 70 rows 55.6 -> 70.5; h = 5120, F = 27648 (432): 96 rows 99.4 -> 112.7; those of
+//     64 rows are two a unit and about even there (48 rows 64.2 -> 65.2 and 111.5 -> 104.0).  Beyond 128 rows (192- and 256-row tiles in halves: 160 rows 31.8 -> 32.5) and for the split-k
 //     projections (160 rows, QKV 11.8 -> 19.4, O 8.8 -> 14.0, down 20.8 -> 23.4) the activations' share of the load path takes it back.
 //   * Where the 192-row tile would be taken (129 to 192 certain rows) and more than 192 are possible: a 256-row tile, so that the rows from 193 to 256
 //     are not a second row block that streams every weight again.  A layer of h = 5120, F = 27648: 208 rows 406 -> 337 us, 256 rows 431 -> 361; up to

@@ -5,12 +5,16 @@
 
 Reads *_kernel_trace.csv (per-dispatch start/end timestamps) and/or *_counter_collection.csv (per-dispatch counter
 values) below the directory and groups dispatches by (kernel name, grid size, workgroup size): launches of one
-kernel from the decode loop share a grid and so form one group, apart from the prefill launches of the same kernel.
+kernel from the decode loop share a grid and so form one group, apart from the prefill launches of the same kernel.  Only this
+library's kernels are listed (namespace sdlm); torch's and the runtime's copies and fills are not, and have no part in the percentages.
 """
 import collections
 import csv
 import glob
 import sys
+
+
+OURS = "sdlm::"
 
 
 def short(name):
@@ -25,6 +29,8 @@ def main():
     dur = collections.defaultdict(list)
     for f in glob.glob(d + "/**/*kernel_trace.csv", recursive=True):
         for r in csv.DictReader(open(f)):
+            if OURS not in r["Kernel_Name"]:
+                continue
             key = (short(r["Kernel_Name"]), r.get("Grid_Size", r.get("Grid_Size_X", "?")), r.get("Workgroup_Size", r.get("Workgroup_Size_X", "?")))
             dur[key].append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
     if dur:
@@ -37,6 +43,8 @@ def main():
     cnt = collections.defaultdict(lambda: collections.defaultdict(list))
     for f in glob.glob(d + "/**/*counter_collection.csv", recursive=True):
         for r in csv.DictReader(open(f)):
+            if OURS not in r["Kernel_Name"]:
+                continue
             key = (short(r["Kernel_Name"]), r["Grid_Size"], r["Workgroup_Size"])
             cnt[key][r["Counter_Name"]].append(float(r["Counter_Value"]))
     if cnt:
