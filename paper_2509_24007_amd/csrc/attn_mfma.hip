@@ -257,7 +257,8 @@ __global__ __launch_bounds__(256, 4) void attn_mfma_k(AttnArgs a)
 // launch time.  Four groups of eight make 32 chunks one round trip where a launch of many chunks is nothing but its round trips.  us, <1,4,4> / <4,8,4>:
 //   4 kv heads x 1 group, 5 chunks 4.8 / 5.5, 12 chunks 5.9 / 5.8, 24 chunks 8.2 / 6.5, 60 chunks 15.1 / 8.6;  x 16 groups, 24 chunks 14.3 / 12.7, 60 30.6 / 23.5
 //   x 32 groups, 5 chunks 5.4 / 9.8, 24 chunks 16.4 / 19.7, 60 chunks 35.0 / 34.2;  x 512 groups, 2 chunks 27.3 / 120, 16 chunks 176 / 220
-// (In a step the early requests of four groups also pay for 9 to 12 chunks of few groups: 1.5B shape, one sequence of 670 keys, 0.6 us a layer.)
+// Two groups serve 9 to 16 chunks of few row groups, where a step gains more than the merge alone shows (1.5B shape, one sequence: of 670 keys 0.6 us a
+// layer against <1,4,4>, of 512 keys 0.2 us against <4,8,4>).
 // NI = 1 where the launch cannot have more than 16 chunks: 4.6 us for 4 x 1 groups of 5 chunks, 25.6 for 4 x 512 of 2.
 template <int CG, int CU, int NI>
 __global__ __launch_bounds__(256 * CG) void attn_combine_k(AttnArgs a)
@@ -447,7 +448,9 @@ bool launch_attn_mfma(hipStream_t s, const sdlm_model_cfg *m, int max_seq_len, i
         // Which merge: by the chunks that the longest sequence may have now, not by those that the capacity admits.
         const int chunks = (min(max_len, max_seq_len) + PAGE * a.chunk_pages - 1) / (PAGE * a.chunk_pages);
         const dim3 grid(max_groups, kg.n_kv_heads, NQ);
-        if (chunks > 8 && max_groups * kg.n_kv_heads <= 64) hipLaunchKernelGGL((attn_combine_k<4, 8, 4>), grid, dim3(1024), 0, s, a);
+        const bool few = max_groups * kg.n_kv_heads <= 64;
+        if (few && chunks > 16) hipLaunchKernelGGL((attn_combine_k<4, 8, 4>), grid, dim3(1024), 0, s, a);
+        else if (few && chunks > 8) hipLaunchKernelGGL((attn_combine_k<2, 8, 4>), grid, dim3(512), 0, s, a);
         else if (a.max_chunks > 16) hipLaunchKernelGGL((attn_combine_k<1, 4, 4>), grid, dim3(256), 0, s, a);
         else hipLaunchKernelGGL((attn_combine_k<1, 4, 1>), grid, dim3(256), 0, s, a);
     }
