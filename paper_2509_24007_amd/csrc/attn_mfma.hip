@@ -379,7 +379,8 @@ static void chunking(const sdlm_model_cfg *m, int max_seq_len, int groups, int *
     while (cp > 8 && items * ((pages + cp - 1) / cp) < 512) cp >>= 1;
     // Down to 64 keys where even 128 leave units without a work item: one then makes two trips through its loop instead of four, which
     // is all that the launch waits for (1.5B shape, one sequence of 512 keys: attention 9.2 -> 7.3 us, the merge of nine chunks
-    // instead of five 4.9 -> 5.8; 3B shape, four sequences of 300 to 700 keys: 10.2 -> 7.9 and 5.0 -> 6.1).  With every unit busy
+    // instead of five 4.9 -> 5.6; 3B shape, four sequences of 300 to 700 keys: 10.2 -> 7.9 and 5.0 -> 6.1).  Only with a capacity of up to 4096
+    // tokens: the launch is sized for it, and a merge takes at most 64 chunks.  With every unit busy
     // the partial results cost what the shorter loop gains (3B shape, 33 sequences: step 3209 -> 3222 us).
     if (cp == 8 && items * ((pages + cp - 1) / cp) < 256) cp = 4;
     while ((pages + cp - 1) / cp > 64) cp <<= 1;     // the merge kernel keeps at most 64 scale factors per query
