@@ -7,17 +7,17 @@ from that stage's input as the library produced it (read through the debug taps)
 at that stage; the chain starts at the embedding of seeded tokens and ends at ids, confidences and gamma.
 (2) Whole-path parity, logits after all layers against the oracle: the full models (depth, width, vocabulary,
 batch, cache layout and therefore the launch shapes of the benchmark) on short prompts, which the oracle finishes
-in seconds per sequence, in lockstep for a few steps; and configs[1] whole, at its own prompt length.  Measured (library against exact oracle | the oracle's
+in seconds per sequence, in lockstep for a few steps; and the 1.5B workload whole, at its own prompt length.  Measured (library against exact oracle | the oracle's
 rounding-point model against exact oracle, same rows; maximum / median of the row-normalised logit error):
-  configs[1] 1.5B, 28 layers   2.3e-2 / 2.0e-2 | 2.3e-2 / 1.9e-2
-  configs[2] 3B,   36 layers   3.3e-2 / 2.2e-2 | 3.2e-2 / 2.2e-2
-  configs[3] 7B,   28 layers   4.5e-2 / 3.3e-2 | 4.5e-2 / 3.3e-2
-  configs[4] 32B,  64 layers   8.3e-2 / 6.8e-2 | 9.3e-2 / 6.8e-2
+  1.5B, batch 1,  28 layers   2.3e-2 / 2.0e-2 | 2.3e-2 / 1.9e-2
+  3B,   batch 16, 36 layers   3.3e-2 / 2.2e-2 | 3.2e-2 / 2.2e-2
+  7B,   batch 64, 28 layers   4.5e-2 / 3.3e-2 | 4.5e-2 / 3.3e-2
+  32B,  batch 32, 64 layers   8.3e-2 / 6.8e-2 | 9.3e-2 / 6.8e-2
 
 The stated bf16 bar is a row-normalised logit error of 2e-2.  On these random-weight models the rounding a bf16
 pipeline cannot avoid (bf16 inputs of every contraction, bf16 K/V) is amplified from layer to layer, and the CPU
 oracle's own model of those rounding points lands at the bar at 28 layers (rounding-model oracle against exact
-oracle, configs[1], the same 40 rows as below, measured on the CPU alone: median 1.8e-2, p90 2.0e-2, max 2.3e-2).
+oracle, the 1.5B workload, the same 40 rows as below, measured on the CPU alone: median 1.8e-2, p90 2.0e-2, max 2.3e-2).
 The tests therefore run that rounding-model oracle next to the exact one on the same rows and assert that the
 library is no further from the exact oracle than 1.5 x what this ideal bf16 pipeline loses (maximum against
 maximum, median against median; a tolerance derived from the arithmetic and measured in the same run), and then
@@ -240,7 +240,7 @@ def test_fullsize_stagewise(name):
 
 @pytest.mark.timeout(600)
 def test_c2_bf16_whole_path():
-    """configs[1] (1.5B-shaped, batch 1, prompt 512, D=4, tau=0.9): the first steps in lockstep with the oracle,
+    """The 1.5B-shaped workload (batch 1, prompt 512, D=4, tau=0.9): the first steps in lockstep with the oracle,
     then the remaining steps free-running with the invariants that hold at any size."""
     wl = syn.workloads()["C2"]
     m, r = wl.model, wl.run

@@ -22,7 +22,7 @@ def gpu_cfg(**kw):
 
 
 def test_c1_tiny_fp32_free_running():
-    """configs[0]: 32 free-running steps, ids and gamma bit-exact against the stored oracle trajectory."""
+    """The tiny fp32 workload: 32 free-running steps, ids and gamma bit-exact against the stored oracle trajectory."""
     wl = syn.workloads()["C1"]
     m, r = wl.model, wl.run
     om, g_dev, layers_dev = both_models(m, wl.seed, 0.02)

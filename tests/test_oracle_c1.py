@@ -1,4 +1,4 @@
-"""The tiny fp32 workload (configs[0]) through the oracle: stored trajectory and full-recompute agreement."""
+"""The tiny fp32 workload through the oracle: stored trajectory and full-recompute agreement."""
 import json
 import os
 
