@@ -126,7 +126,8 @@ struct GemmArgs {
 };
 
 void launch_assemble_decode(hipStream_t s, const SeqState &st, const RowMeta &rm, int B, int D, int mask_id, int group_rows,
-                            int staging_base, int causal, int n_kv_heads, int chunk_floor);
+                            int staging_base, int causal, int n_kv_heads, int chunk_floor, int dtype, float *x, const void *E, int h, int V);   // E: also gather the embeddings into x, or null
+bool assemble_embeds(int B, int D, int h);   // whether the row assembly gathers the embeddings of such a step as well
 // Rows one sequence contributes to a verification pass, (D-2) causal rows + (D-1) D block rows, and whether they share
 // one staging tile (they fit its 16 slots: D <= 4) or take one tile per input plus one for the causal rows.
 int verify_rows_per_seq(int D, bool *shared_tile);
@@ -147,6 +148,12 @@ void launch_embed(hipStream_t s, int dtype, float *x, const void *E, const RowMe
 void launch_rmsnorm(hipStream_t s, int dtype, void *out, float *x, const void *g, int h, float eps, const int32_t *row_index,
                     const int32_t *p_count, int max_rows, int min_rows, const float *slabs, int n_slabs, size_t slab_stride);   // min_rows: rows that certainly exist
 void launch_gemm_generic(hipStream_t s, int dtype, int epi, const GemmArgs &a);
+// Products of few rows with the RMSNorm in front of them (gate/up, logits: X is the fp32 residual stream) or without (residual), and the QKV
+// projection with norm, rotation and K/V placement.  row_index: rows of X, null: as they are.
+bool generic_few_applies(int dtype, int rows, int K);
+void launch_gemm_few(hipStream_t s, int dtype, int epi, const GemmArgs &a, const void *gain, float eps, const int32_t *row_index);
+void launch_qkv_few(hipStream_t s, int dtype, const GemmArgs &a, const void *gain, float eps, void *q_out, void *pool_layer, const KvGeom &kg, const RowMeta &rm,
+                    const SeqState &st, const float2 *rope, int n_q_heads);
 void launch_rope_scatter(hipStream_t s, int dtype, const float *qkv, int n_slabs, size_t slab_stride, void *q_out, void *pool_layer,
                          const KvGeom &kg, const RowMeta &rm, const SeqState &st, const float2 *rope, int n_q_heads, int max_rows, int min_rows);
 void launch_attn_generic(hipStream_t s, int dtype, const void *q, void *out, const void *pool_layer, const KvGeom &kg,
@@ -155,6 +162,10 @@ void launch_lm_reduce(hipStream_t s, const float *logits, int V, int32_t *ids, f
                       const int32_t *p_rows, int max_rows);
 void launch_accept(hipStream_t s, const SeqState &st, const int32_t *ids_rows, const float *conf_rows, int B, int D,
                    float tau, int rule, int32_t *ids_out, int32_t *count_out, float *conf_out);
+// Reduction and acceptance in one launch, for small vocabularies.
+bool lm_accept_applies(int V);
+void launch_lm_accept(hipStream_t s, const float *logits, int V, int conf_fn, const SeqState &st, int B, int D, float tau, int rule, int32_t *ids_out,
+                      int32_t *count_out, float *conf_out);
 void launch_commit(hipStream_t s, const SeqState &st, int B, int D, const int32_t *ids_ovr, const int32_t *cnt_ovr,
                    int paged, int n_pages, int pages_per_seq, int V);
 void launch_read_kv(hipStream_t s, int dtype, const void *pool_layer, const KvGeom &kg, const SeqState &st, int seq,

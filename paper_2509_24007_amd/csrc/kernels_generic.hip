@@ -8,11 +8,26 @@
 
 namespace sdlm {
 
+// Embeddings of R rows by one workgroup, four features a thread and eight requests under way.  One workgroup is enough while the gather is a few round trips; it
+// saves a launch of 2.4 us (h = 256, 8 rows: assembly and gather 5.2 -> 3.4 us; the rule of assemble_embeds).
+template <typename T>
+__device__ inline void embed_rows(float *x, const T *E, const int32_t *tok, int R, int h, int V)
+{
+    const int per = h / 4, n = R * per;   // h is a multiple of 4
+    for (int e = threadIdx.x; e < n; e += blockDim.x) {
+        const int r = e / per, k = e % per * 4;
+        const T *src = E + (size_t)min(max(tok[r], 0), V - 1) * h + k;
+        *(float4 *)(x + (size_t)r * h + k) = make_float4(to_f<T>(src[0]), to_f<T>(src[1]), to_f<T>(src[2]), to_f<T>(src[3]));
+    }
+}
+
 // ------------------------------------------------------------------------------------------------ row assembly
 // Rows of a decode step, per sequence: the pending tokens (positions c..n-1, causal), then the block
 // [x_last, [m] x (D-1)] at positions n-1 .. n+D-2 (block definition, Sec. 3.2).  A block row may see the cache
 // below position s = n-1 only; the causal copy of x_last at s is for later steps.
-__global__ void assemble_decode_k(SeqState st, RowMeta rm, int B, int D, int mask_id, int gr, int stg0, int causal, int Hkv, int cp_floor)
+// E: embedding table (storage type T), gathered here into x for few rows (see launch_assemble_decode), else null.
+template <typename T>
+__global__ void assemble_decode_k(SeqState st, RowMeta rm, int B, int D, int mask_id, int gr, int stg0, int causal, int Hkv, int cp_floor, float *x, const T *E, int h, int V)
 {
     __shared__ int row0[1025], grp0[1025], cp_s;
     if (threadIdx.x == 0) {
@@ -57,12 +72,19 @@ __global__ void assemble_decode_k(SeqState st, RowMeta rm, int B, int D, int mas
             rm.grp_hint[g] = attn_group_hint(lim_max, gn, cp_s);
         }
     }
+    if (!E) return;
+    __syncthreads();   // the rows' tokens are written by this workgroup
+    embed_rows(x, E, rm.tok, row0[B], h, V);
 }
 
+// Up to 8192 values (h = 1536, 8 rows, 12288: no difference to the launch of its own).
+bool assemble_embeds(int B, int D, int h) { return B <= 4 && (long)B * 2 * D * h <= 8192; }
+
 void launch_assemble_decode(hipStream_t s, const SeqState &st, const RowMeta &rm, int B, int D, int mask_id, int group_rows, int staging_base,
-                            int causal, int n_kv_heads, int chunk_floor)
+                            int causal, int n_kv_heads, int chunk_floor, int dtype, float *x, const void *E, int h, int V)
 {
-    hipLaunchKernelGGL(assemble_decode_k, dim3(1), dim3(256), 0, s, st, rm, B, D, mask_id, group_rows, staging_base, causal, n_kv_heads, chunk_floor);
+    if (dtype == 0) hipLaunchKernelGGL(assemble_decode_k<float>, dim3(1), dim3(256), 0, s, st, rm, B, D, mask_id, group_rows, staging_base, causal, n_kv_heads, chunk_floor, x, (const float *)E, h, V);
+    else hipLaunchKernelGGL(assemble_decode_k<bf16_t>, dim3(1), dim3(256), 0, s, st, rm, B, D, mask_id, group_rows, staging_base, causal, n_kv_heads, chunk_floor, x, (const bf16_t *)E, h, V);
 }
 
 // Rows of the verification pass of a self-speculative step (Sec. 3.4, "Self-Speculative Decoding").  With yhat^1..yhat^D
@@ -512,6 +534,198 @@ __global__ __launch_bounds__(256) void gemm_rows_k(GemmArgs a)
         }
 }
 
+// ------------------------------------------------------------------------------------------------ steps of few rows
+// A step of a small model on this path is a chain of launches with next to nothing in them (2.4 us each at the least), so the norms,
+// the rotation and the K/V placement join the products they feed.  A product of at most FEW_ROWS rows reads the residual stream itself: the
+// lanes that walk a column's k also sum the squares of the rows, and the row's factor 1 / rms is applied to the finished sum.
+// A wavefront owns a column and walks k with all of its lanes, eight rows at a time; four columns a workgroup, and workgroups of neighbouring columns on one
+// XCD, so that a cache line of results has one owner (N = 256, K = 256, eight XCDs in every line of the residual stream: 6.9 us, so 2.9).  Sixteen lanes
+// a column request the rows four times over and walk k in turns (K = 688: 7.3 us, so 5.3); four columns a wavefront take longer with their arithmetic (8.0).
+// us a step, norms and products apart -> now: h = 256, F = 688, 2 layers, 8 rows 84.7 -> 60.1; h = 896, F = 4864, 4 layers fp32 8 / 16 / 32 rows 417 -> 258 / 438 -> 308 / 470 -> 370,
+// bf16 307 -> 219 / 330 -> 272 / 352 -> 340; h = 2048, F = 11008, 2 layers fp32 477 -> 350 / 551 -> 482 / 738 -> 674.  Beyond 32 rows the norms, repeated
+// for every column, outweigh their launches.
+constexpr int FEW_ROWS = 32;
+
+struct FewArgs {
+    const void *X;                  // [R, K]: fp32 residual stream (NORM) or activations of the storage type
+    const void *gain;               // [K], NORM
+    const int32_t *row_index;       // NORM: row of X behind each row of the product, null: the same
+    const void *W, *W2, *bias;
+    float *Yf;
+    void *Yt;
+    const int32_t *pR;
+    int max_rows, N, K;
+    float scale, eps;
+};
+
+// Vec16<T>::N consecutive elements of a row of X as floats.
+template <typename T, bool NORM> struct FewX {
+    Vec16<T> v;
+    __device__ inline void load(const void *p, size_t o) { v.load((const T *)p + o); }
+    __device__ inline float at(int e) const { return v.at(e); }
+};
+template <> struct FewX<bf16_t, true> {
+    Vec16<float> a, b;
+    __device__ inline void load(const void *p, size_t o) { a.load((const float *)p + o); b.load((const float *)p + o + 4); }
+    __device__ inline float at(int e) const { return e < 4 ? a.at(e) : b.at(e - 4); }
+};
+
+// Sums of eight values over the wavefront, by a fixed tree: the values a lane carries halve while there are several, so that lane l ends with
+// the sum of value l / 8.
+__device__ inline float few_sum(float (&v)[8], int lane)
+{
+#pragma unroll
+    for (int h = 4, d = 32; h > 0; h >>= 1, d >>= 1)
+#pragma unroll
+        for (int i = 0; i < h; ++i) {
+            const float keep = (lane & d) ? v[i + h] : v[i], send = (lane & d) ? v[i] : v[i + h];
+            v[i] = keep + __shfl_xor(send, d);
+        }
+#pragma unroll
+    for (int d = 4; d > 0; d >>= 1) v[0] += __shfl_xor(v[0], d);
+    return v[0];
+}
+
+// Products of NW weight rows with eight rows from r0 on; s[j] in lane l is the sum of w[j] and row r0 + l / 8.
+template <typename T, bool NORM, int NW>
+__device__ inline void few_dot(const FewArgs &a, const T *const (&w)[NW], int r0, int R, int lane, float (&s)[NW])
+{
+    constexpr int VE = Vec16<T>::N, U = NORM ? 2 : 3;   // k steps requested together, weights and rows
+    const int K = a.K;
+    size_t xo[8];
+    float acc[NW][8], ss[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int r = min(r0 + i, R - 1);
+        xo[i] = (size_t)(NORM && a.row_index ? a.row_index[r] : r) * K;
+        ss[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < NW; ++j) acc[j][i] = 0.f;
+    }
+    for (int k0 = lane * VE; k0 < K; k0 += 64 * VE * U) {
+        Vec16<T> wv[U][NW], gv[U];
+        FewX<T, NORM> x[U][8];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u > 0 && k0 - lane * VE + u * 64 * VE >= K) break;   // no lane has such a step
+            const int k = min(k0 + u * 64 * VE, K - VE);             // a lane beyond the end requests but does not use
+#pragma unroll
+            for (int j = 0; j < NW; ++j) wv[u][j].load(w[j] + k);
+            if constexpr (NORM) gv[u].load((const T *)a.gain + k);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[u][i].load(a.X, xo[i] + k);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (k0 + u * 64 * VE >= K) continue;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int e = 0; e < VE; ++e) {
+                    const float xe = x[u][i].at(e);
+                    float xg = xe;
+                    if constexpr (NORM) { ss[i] = fmaf(xe, xe, ss[i]); xg = xe * gv[u].at(e); }
+#pragma unroll
+                    for (int j = 0; j < NW; ++j) acc[j][i] = fmaf(xg, wv[u][j].at(e), acc[j][i]);
+                }
+        }
+    }
+    float inv = 1.f;
+    if constexpr (NORM) inv = 1.0f / sqrtf(few_sum(ss, lane) / (float)K + a.eps);
+#pragma unroll
+    for (int j = 0; j < NW; ++j) s[j] = few_sum(acc[j], lane) * inv;
+}
+
+// Column of this wavefront: the workgroups of one XCD (blockIdx.x % 8) own neighbouring columns.
+__device__ inline int few_column() { return ((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) * 4 + (threadIdx.x >> 6); }
+
+template <typename T, int EPI>
+__global__ __launch_bounds__(256) void gemm_few_k(FewArgs a)
+{
+    const int R = min(*a.pR, a.max_rows), r0 = blockIdx.y * 8, n = few_column();
+    if (r0 >= R || n >= a.N) return;
+    constexpr int NW = EPI == EPI_SWIGLU ? 2 : 1;
+    const int lane = threadIdx.x & 63, r = r0 + (lane >> 3);
+    const size_t o = (size_t)r * a.N + n;
+    const bool mine = !(lane & 7) && r < R;
+    float s[NW], old = 0.f;
+    if (EPI == EPI_RESID && mine) old = a.Yf[o];   // requested with the operands
+    const T *w[NW];
+    w[0] = (const T *)a.W + (size_t)n * a.K;
+    if constexpr (NW == 2) w[1] = (const T *)a.W2 + (size_t)n * a.K;
+    few_dot<T, EPI != EPI_RESID, NW>(a, w, r0, R, lane, s);
+    if (!mine) return;
+    if (EPI == EPI_RESID) a.Yf[o] = old + s[0];
+    else if (EPI == EPI_SWIGLU) ((T *)a.Yt)[o] = from_f<T>(silu_f(s[0]) * s[NW - 1]);
+    else a.Yf[o] = s[0] * a.scale;
+}
+
+// QKV projection with the norm in front and rotation and K/V placement behind it (rope_scatter_k's): a wavefront owns a rotate-half pair.
+template <typename T>
+__global__ __launch_bounds__(256) void qkv_few_k(FewArgs a, T *q_out, T *pool, KvGeom kg, RowMeta rm, SeqState st, const float2 *rope, int Hq)
+{
+    const int R = min(*a.pR, a.max_rows), r0 = blockIdx.y * 8;
+    const int d = kg.head_dim, half = d >> 1, Hk = kg.n_kv_heads, lane = threadIdx.x & 63, p = few_column(), head = p / half, i = p % half;
+    if (r0 >= R || head >= Hq + 2 * Hk) return;
+    const int r = r0 + (lane >> 3), rc = min(r, R - 1);
+    const int pos = rm.pos[rc], kind = rm.kind[rc], b = rm.seq[rc], stg = rm.stg[rc];   // requested before the product
+    const T *w[2] = {(const T *)a.W + (size_t)(head * d + i) * a.K, (const T *)a.W + (size_t)(head * d + i + half) * a.K};
+    float x[2];
+    few_dot<T, true, 2>(a, w, r0, R, lane, x);
+    if ((lane & 7) || r >= R) return;
+    if (a.bias) { x[0] += to_f<T>(((const T *)a.bias)[head * d + i]); x[1] += to_f<T>(((const T *)a.bias)[head * d + i + half]); }
+    const bool is_v = head >= Hq + Hk;
+    const float2 t = is_v ? make_float2(1.f, 0.f) : rope[(size_t)pos * half + i];
+    const T lo = from_f<T>(is_v ? x[0] : x[0] * t.x - x[1] * t.y), hi = from_f<T>(is_v ? x[1] : x[1] * t.x + x[0] * t.y);
+    if (head < Hq) {
+        T *q = q_out + ((size_t)r * Hq + head) * d + i;
+        q[0] = lo; q[half] = hi;
+        return;
+    }
+    int page = stg, slot = kind;
+    if (kind < 0) { page = st.page_table[(size_t)b * kg.pages_per_seq + pos / PAGE]; slot = pos % PAGE; }
+    if (page < 0) return;   // unbacked position: only reachable after a reported pool exhaustion
+    T *tile = pool + kg.tile(page, is_v ? head - Hq - Hk : head - Hq);
+    if (!is_v) { tile[k_off(slot, i)] = lo; tile[k_off(slot, i + half)] = hi; }
+    else { tile[PAGE * d + v_off(slot, i)] = lo; tile[PAGE * d + v_off(slot, i + half)] = hi; }
+}
+
+bool generic_few_applies(int dtype, int rows, int K) { return rows <= FEW_ROWS && K % (dtype == 0 ? 4 : 8) == 0; }
+
+static dim3 few_grid(int cols, int rows) { return dim3((cols + 31) / 32 * 8, (rows + 7) / 8); }   // four columns a workgroup, a multiple of eight workgroups
+
+template <typename T>
+static void gemm_few_t(hipStream_t s, int epi, const FewArgs &a)
+{
+    const dim3 grid = few_grid(a.N, a.max_rows), block(256);
+    if (epi == EPI_RESID) hipLaunchKernelGGL((gemm_few_k<T, EPI_RESID>), grid, block, 0, s, a);
+    else if (epi == EPI_SWIGLU) hipLaunchKernelGGL((gemm_few_k<T, EPI_SWIGLU>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((gemm_few_k<T, EPI_LOGITS>), grid, block, 0, s, a);
+}
+
+// Residual: X is the input of the projection.  Gate/up and logits: X is the residual stream, normalised here.
+void launch_gemm_few(hipStream_t s, int dtype, int epi, const GemmArgs &g, const void *gain, float eps, const int32_t *row_index)
+{
+    const FewArgs a{g.X, gain, row_index, g.W, g.W2, nullptr, g.Yf, g.Yt, g.pR, g.max_rows, g.N, g.K, g.scale, eps};
+    if (dtype == 0) gemm_few_t<float>(s, epi, a);
+    else gemm_few_t<bf16_t>(s, epi, a);
+}
+
+template <typename T>
+static void qkv_few_t(hipStream_t s, const FewArgs &a, void *q_out, void *pool_layer, const KvGeom &kg, const RowMeta &rm, const SeqState &st, const float2 *rope, int Hq)
+{
+    const int pairs = (Hq + 2 * kg.n_kv_heads) * kg.head_dim / 2;
+    hipLaunchKernelGGL((qkv_few_k<T>), few_grid(pairs, a.max_rows), dim3(256), 0, s, a, (T *)q_out, (T *)pool_layer, kg, rm, st, rope, Hq);
+}
+
+void launch_qkv_few(hipStream_t s, int dtype, const GemmArgs &g, const void *gain, float eps, void *q_out, void *pool_layer, const KvGeom &kg, const RowMeta &rm,
+                    const SeqState &st, const float2 *rope, int n_q_heads)
+{
+    const FewArgs a{g.X, gain, nullptr, g.W, nullptr, g.bias, nullptr, nullptr, g.pR, g.max_rows, g.N, g.K, 1.f, eps};
+    if (dtype == 0) qkv_few_t<float>(s, a, q_out, pool_layer, kg, rm, st, rope, n_q_heads);
+    else qkv_few_t<bf16_t>(s, a, q_out, pool_layer, kg, rm, st, rope, n_q_heads);
+}
+
 // Which kernel: rows without LDS spend their time per output, tiles per 64 x 64 tile and k slice with little more until every
 // compute unit has one or two.  `tiles` (N * rows / 4096) is where the lines lie, measured for both types, K from 128 to 8960 and N from 256
 // to 151936 (us, rows without LDS -> tiles):
@@ -808,37 +1022,107 @@ void launch_lm_reduce(hipStream_t s, const float *logits, int V, int32_t *ids, f
 // ------------------------------------------------------------------------------------------------ acceptance
 // gamma_tau (Sec. 3.4): the largest j in 1..D whose cumulative product of confidences is >= tau, at least 1.
 // The product is a float product taken left to right.  rule 1: leading positions whose own confidence is >= tau.
-__global__ void accept_k(SeqState st, const int32_t *ids_rows, const float *conf_rows, int B, int D, float tau, int rule,
-                         int32_t *ids_out, int32_t *count_out, float *conf_out)
+// Position j of sequence b: the count is the same in every position's thread, and stored by the first.
+__device__ inline void accept_row(const SeqState &st, const int32_t *ids, const float *conf, int b, int D, int j, float tau, int rule, int32_t *ids_out, int32_t *count_out,
+                                  float *conf_out)
 {
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
     int best = 1;
     if (rule == 0) {
         float prod = 1.0f;
-        for (int j = 1; j <= D; ++j) {
-            prod = prod * conf_rows[b * D + j - 1];
-            if (prod >= tau && j > best) best = j;
+        for (int i = 1; i <= D; ++i) {
+            prod = prod * conf[i - 1];
+            if (prod >= tau && i > best) best = i;
         }
     } else {
-        int j = 0;
-        while (j < D && conf_rows[b * D + j] >= tau) ++j;
-        if (j > best) best = j;
+        int i = 0;
+        while (i < D && conf[i] >= tau) ++i;
+        if (i > best) best = i;
     }
-    st.last_count[b] = best;
-    count_out[b] = best;
-    for (int j = 0; j < D; ++j) {
-        int id = ids_rows[b * D + j];
-        st.last_ids[b * D + j] = id;
-        ids_out[b * D + j] = id;
-        if (conf_out) conf_out[b * D + j] = conf_rows[b * D + j];
+    if (j == 0) { st.last_count[b] = best; count_out[b] = best; }
+    st.last_ids[b * D + j] = ids[j];
+    ids_out[b * D + j] = ids[j];
+    if (conf_out) conf_out[b * D + j] = conf[j];
+}
+
+__global__ void accept_k(SeqState st, const int32_t *ids_rows, const float *conf_rows, int B, int D, float tau, int rule,
+                         int32_t *ids_out, int32_t *count_out, float *conf_out)
+{
+    const int e = blockIdx.x * blockDim.x + threadIdx.x, b = e / D;
+    if (b < B) accept_row(st, ids_rows + b * D, conf_rows + b * D, b, D, e % D, tau, rule, ids_out, count_out, conf_out);
+}
+
+// Vocabulary reduction and acceptance of one sequence's D rows in one launch, for small vocabularies: 1024 threads in equal parts of the rows (a
+// wavefront at least), each part as lm_reduce_k.  V = 4096, D = 4: 8.7 + 3.1 us as two launches, 5.8 here.  Beyond 16384 a row is
+// worth a workgroup of its own.
+__global__ __launch_bounds__(1024) void lm_accept_k(const float *logits, int V, int conf_fn, SeqState st, int D, int parts, float tau, int rule, int32_t *ids_out,
+                                                    int32_t *count_out, float *conf_out)
+{
+    __shared__ float sm[16], ss[16], se[16], conf[MAX_D];
+    __shared__ int sa[16], ids[MAX_D];
+    const int tpr = 1024 / parts, row = threadIdx.x / tpr, t = threadIdx.x % tpr, wave = threadIdx.x >> 6, wpr = tpr >> 6, w0 = row * wpr, b = blockIdx.x;
+    const bool live = row < D;
+    const float *z = logits + (size_t)(b * D + (live ? row : 0)) * V;
+    constexpr int U = 16;
+    float m = -INFINITY, x[U];
+    int arg = 0;   // stays a valid id even if every logit is NaN
+    for (int v0 = t; v0 < V; v0 += U * tpr) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = v0 + u * tpr < V ? z[v0 + u * tpr] : -INFINITY;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (x[u] > m) { m = x[u]; arg = v0 + u * tpr; }
     }
+    for (int o = 32; o > 0; o >>= 1) {
+        float om = __shfl_xor(m, o);
+        int oa = __shfl_xor(arg, o);
+        if (om > m || (om == m && oa < arg)) { m = om; arg = oa; }
+    }
+    if ((threadIdx.x & 63) == 0) { sm[wave] = m; sa[wave] = arg; }
+    __syncthreads();
+    m = sm[w0]; arg = sa[w0];
+    for (int w = 1; w < wpr; ++w)
+        if (sm[w0 + w] > m || (sm[w0 + w] == m && sa[w0 + w] < arg)) { m = sm[w0 + w]; arg = sa[w0 + w]; }
+    float S = 0.f, E = 0.f;
+    for (int v0 = t; v0 < V; v0 += U * tpr) {
+        if (V > U * tpr) {   // else the values are still there
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] = v0 + u * tpr < V ? z[v0 + u * tpr] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (v0 + u * tpr < V) {
+                float dlt = x[u] - m, e = __expf(dlt);
+                S += e;
+                E += e * dlt;
+            }
+    }
+    for (int o = 32; o > 0; o >>= 1) { S += __shfl_xor(S, o); E += __shfl_xor(E, o); }
+    if ((threadIdx.x & 63) == 0) { ss[wave] = S; se[wave] = E; }
+    __syncthreads();
+    if (live && t == 0) {
+        S = 0.f; E = 0.f;
+        for (int w = 0; w < wpr; ++w) { S += ss[w0 + w]; E += se[w0 + w]; }
+        ids[row] = arg;
+        conf[row] = conf_fn == 0 ? 1.0f / S : 1.0f - (logf(S) - E / S) / logf((float)V);
+    }
+    __syncthreads();
+    if (threadIdx.x < D) accept_row(st, ids, conf, b, D, threadIdx.x, tau, rule, ids_out, count_out, conf_out);
+}
+
+bool lm_accept_applies(int V) { return V <= 16384; }
+
+void launch_lm_accept(hipStream_t s, const float *logits, int V, int conf_fn, const SeqState &st, int B, int D, float tau, int rule, int32_t *ids_out,
+                      int32_t *count_out, float *conf_out)
+{
+    int parts = 1;
+    while (parts < D) parts *= 2;
+    hipLaunchKernelGGL(lm_accept_k, dim3(B), dim3(1024), 0, s, logits, V, conf_fn, st, D, parts, tau, rule, ids_out, count_out, conf_out);
 }
 
 void launch_accept(hipStream_t s, const SeqState &st, const int32_t *ids_rows, const float *conf_rows, int B, int D,
                    float tau, int rule, int32_t *ids_out, int32_t *count_out, float *conf_out)
 {
-    hipLaunchKernelGGL(accept_k, dim3((B + 63) / 64), dim3(64), 0, s, st, ids_rows, conf_rows, B, D, tau, rule, ids_out, count_out, conf_out);
+    hipLaunchKernelGGL(accept_k, dim3((B * D + 63) / 64), dim3(64), 0, s, st, ids_rows, conf_rows, B, D, tau, rule, ids_out, count_out, conf_out);
 }
 
 // ------------------------------------------------------------------------------------------------ commit

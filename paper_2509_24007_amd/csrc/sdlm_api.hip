@@ -261,10 +261,17 @@ void run_taps(sdlm_ctx *c, int layer, int which, const void *src, size_t bytes)
             (void)hipMemcpyAsync(t.dst, src, bytes, hipMemcpyDeviceToDevice, c->stream);
 }
 
+// Whether a pass of at most `rows` rows takes the generic path's kernels for few rows.  (Taps also read what these keep in registers.)
+bool few_rows(const sdlm_ctx *c, int rows)
+{
+    return !c->L.mfma && c->taps.empty() && generic_few_applies(c->m.dtype, rows, c->m.hidden) && generic_few_applies(c->m.dtype, rows, c->m.ffn) &&
+           generic_few_applies(c->m.dtype, rows, c->m.n_q_heads * c->m.head_dim);
+}
+
 // The decoder layers over the rows described by c->rm.  `rows` bounds the launch grids (the device-side row
 // count decides what is computed); `rows_sure` is a host-known lower bound of that count (it only steers launch shapes).
-// `cache_only`: the pass only has to leave its rows' K/V in the cache (prefill): the last layer then ends after the K/V placement.
-void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_only, bool two_staging = false)
+// `cache_only`: the pass only has to leave its rows' K/V in the cache (prefill): the last layer then ends after the K/V placement.  `embedded`: x holds the rows' embeddings.
+void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_only, bool embedded = false, bool two_staging = false)
 {
     const sdlm_model_cfg &m = c->m;
     const int dt = m.dtype, h = m.hidden, F = m.ffn, d = m.head_dim;
@@ -274,13 +281,19 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
     c->pend_slabs = 0;   // a fresh residual stream: nothing pending from an earlier pass
     int max_len = c->r.max_seq_len;   // captured launches are replayed while the sequences grow
     if (!c->capturing) max_len = *std::max_element(c->n_ub.begin(), c->n_ub.begin() + c->batch);
-    { Phase p(c, SDLM_PH_ROWS); launch_embed(s, dt, c->x, c->embed, c->rm, rows, h, m.vocab); }
+    if (!embedded) { Phase p(c, SDLM_PH_ROWS); launch_embed(s, dt, c->x, c->embed, c->rm, rows, h, m.vocab); }
+    // generic path: norms, rotation and K/V placement inside the products (not in a prefill, whose cache contents do not depend on the other prompts)
+    const bool few = !cache_only && few_rows(c, rows);
     for (int l = 0; l < m.n_layers; ++l) {
         const LayerW &w = c->lw[l];
         char *pool_l = c->pool + (size_t)l * c->kg.layer_stride * e;
         run_taps(c, l, 0, c->x, (size_t)rows * h * 4);
-        { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xn, c->x, w.attn_norm, h, m.rms_eps, nullptr, c->rm.counts, rows, rows_sure, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
-        if (c->L.mfma && qkv_rope_skinny_applies(&m, rows, rows_sure)) {
+        if (!few) { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xn, c->x, w.attn_norm, h, m.rms_eps, nullptr, c->rm.counts, rows, rows_sure, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
+        if (few) {
+            Phase p(c, SDLM_PH_QKV);
+            GemmArgs a{c->x, w.wqkv, nullptr, m.has_qkv_bias ? w.bqkv : nullptr, nullptr, nullptr, c->rm.counts, rows, nqkv, h, 1.f, rows_sure};
+            launch_qkv_few(s, dt, a, w.attn_norm, m.rms_eps, c->q, pool_l, c->kg, c->rm, c->st, c->rope, m.n_q_heads);
+        } else if (c->L.mfma && qkv_rope_skinny_applies(&m, rows, rows_sure)) {
             Phase p(c, SDLM_PH_QKV);   // projection, rotation and K/V placement in one launch
             launch_qkv_rope_skinny(s, &m, c->xn, w.wqkv, m.has_qkv_bias ? w.bqkv : nullptr, c->rm.counts, rows, rows_sure, c->q, pool_l, c->kg, c->rm, c->st, c->rope);
         } else {
@@ -315,14 +328,16 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
                 // the split-k partial sums of a residual projection are added by the next RMSNorm (unless a tap wants x now)
                 int sp = launch_gemm_mfma(s, EPI_RESID, a, c->slabs, c->L.slab_floats, c->taps.empty());
                 if (sp > 1 && c->taps.empty()) { c->pend_slabs = sp; c->pend_stride = (size_t)rows * h; }
-            } else launch_gemm_generic(s, dt, EPI_RESID, a);
+            } else if (few) launch_gemm_few(s, dt, EPI_RESID, a, nullptr, 0.f, nullptr);
+            else launch_gemm_generic(s, dt, EPI_RESID, a);
         }
         run_taps(c, l, 6, c->x, (size_t)rows * h * 4);
-        { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xn, c->x, w.ffn_norm, h, m.rms_eps, nullptr, c->rm.counts, rows, rows_sure, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
+        if (!few) { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xn, c->x, w.ffn_norm, h, m.rms_eps, nullptr, c->rm.counts, rows, rows_sure, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
         {
             Phase p(c, SDLM_PH_GATEUP);
-            GemmArgs a{c->xn, w.w_gate, w.w_up, nullptr, nullptr, c->act, c->rm.counts, rows, F, h, 1.f, rows_sure};
-            if (c->L.mfma) launch_gemm_mfma(s, EPI_SWIGLU, a, c->slabs, c->L.slab_floats, false); else launch_gemm_generic(s, dt, EPI_SWIGLU, a);
+            GemmArgs a{few ? (const void *)c->x : c->xn, w.w_gate, w.w_up, nullptr, nullptr, c->act, c->rm.counts, rows, F, h, 1.f, rows_sure};
+            if (few) launch_gemm_few(s, dt, EPI_SWIGLU, a, w.ffn_norm, m.rms_eps, nullptr);
+            else if (c->L.mfma) launch_gemm_mfma(s, EPI_SWIGLU, a, c->slabs, c->L.slab_floats, false); else launch_gemm_generic(s, dt, EPI_SWIGLU, a);
         }
         run_taps(c, l, 2, c->act, (size_t)rows * F * e);
         {
@@ -332,18 +347,21 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
                 // the split-k partial sums of a residual projection are added by the next RMSNorm (unless a tap wants x now)
                 int sp = launch_gemm_mfma(s, EPI_RESID, a, c->slabs, c->L.slab_floats, c->taps.empty());
                 if (sp > 1 && c->taps.empty()) { c->pend_slabs = sp; c->pend_stride = (size_t)rows * h; }
-            } else launch_gemm_generic(s, dt, EPI_RESID, a);
+            } else if (few) launch_gemm_few(s, dt, EPI_RESID, a, nullptr, 0.f, nullptr);
+            else launch_gemm_generic(s, dt, EPI_RESID, a);
         }
         run_taps(c, l, 3, c->x, (size_t)rows * h * 4);
     }
 }
 
-// Final RMSNorm of the rows listed in rm.blk_row, LM head, per-row arg-max and confidence (-> ids_rows, conf_rows).
-void run_lm_head(sdlm_ctx *c, int lm_rows, float *logits)
+// Final RMSNorm of the rows listed in rm.blk_row, LM head, per-row arg-max and confidence (-> ids_rows, conf_rows; generic path: only if `reduce`).
+void run_lm_head(sdlm_ctx *c, int lm_rows, float *logits, bool reduce = true)
 {
     hipStream_t s = c->stream;
     const int dt = c->m.dtype, h = c->m.hidden, V = c->m.vocab;
-    { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xhat, c->x, c->final_norm, h, c->m.rms_eps, c->rm.blk_row, c->rm.counts + 2, lm_rows, lm_rows, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
+    // 8192: V = 20000, h = 896, 12 rows 10 us (fp32) and 36 us (bf16) slower with the norm inside, V = 4096, h = 256 0.6 faster
+    const bool few = few_rows(c, lm_rows) && V <= 8192;
+    if (!few) { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xhat, c->x, c->final_norm, h, c->m.rms_eps, c->rm.blk_row, c->rm.counts + 2, lm_rows, lm_rows, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
     run_taps(c, 0, 4, c->xhat, (size_t)lm_rows * h * c->L.esz);
     {
         Phase p(c, SDLM_PH_LMHEAD);
@@ -352,9 +370,10 @@ void run_lm_head(sdlm_ctx *c, int lm_rows, float *logits)
                                c->ids_rows, c->conf_rows);
         } else {
             float *z = logits ? logits : c->logits;
-            GemmArgs a{c->xhat, c->lm_head, nullptr, nullptr, z, nullptr, c->rm.counts + 2, lm_rows, V, h, c->m.logit_scale};
-            launch_gemm_generic(s, dt, EPI_LOGITS, a);
-            launch_lm_reduce(s, z, V, c->ids_rows, c->conf_rows, c->r.conf_fn, c->rm.counts + 2, lm_rows);
+            GemmArgs a{few ? (const void *)c->x : c->xhat, c->lm_head, nullptr, nullptr, z, nullptr, c->rm.counts + 2, lm_rows, V, h, c->m.logit_scale};
+            if (few) launch_gemm_few(s, dt, EPI_LOGITS, a, c->final_norm, c->m.rms_eps, c->rm.blk_row);
+            else launch_gemm_generic(s, dt, EPI_LOGITS, a);
+            if (reduce) launch_lm_reduce(s, z, V, c->ids_rows, c->conf_rows, c->r.conf_fn, c->rm.counts + 2, lm_rows);
         }
     }
 }
@@ -645,10 +664,15 @@ static int decode_step_impl(sdlm_ctx *c, int32_t *ids, int32_t *count, float *co
     auto launch_all = [&]() {
         const int rows = B * 2 * D, groups = B * ((2 * D + c->L.group_rows - 1) / c->L.group_rows);
         const int cp_floor = c->L.mfma ? mfma_attn_chunk_floor(&c->m, c->r.max_seq_len, groups, c->L.attn_bytes) : 0;
-        { Phase p(c, SDLM_PH_ROWS); launch_assemble_decode(s, c->st, c->rm, B, D, c->m.mask_token_id, c->L.group_rows, c->kg.staging_base, c->m.block_causal, c->m.n_kv_heads, cp_floor); }
-        run_layers(c, rows, groups, B * (D + (c->committed ? 1 : 0)), false);   // after a commit every sequence has >= 1 pending row
-        run_lm_head(c, B * D, logits);
-        { Phase p(c, SDLM_PH_ACCEPT); launch_accept(s, c->st, c->ids_rows, c->conf_rows, B, D, c->r.tau, c->r.accept_rule, ids, count, conf); }
+        const bool embeds = assemble_embeds(B, D, c->m.hidden);
+        { Phase p(c, SDLM_PH_ROWS); launch_assemble_decode(s, c->st, c->rm, B, D, c->m.mask_token_id, c->L.group_rows, c->kg.staging_base, c->m.block_causal, c->m.n_kv_heads, cp_floor,
+                                                          c->m.dtype, c->x, embeds ? c->embed : nullptr, c->m.hidden, c->m.vocab); }
+        run_layers(c, rows, groups, B * (D + (c->committed ? 1 : 0)), false, embeds);   // after a commit every sequence has >= 1 pending row
+        const bool reduce = c->L.mfma || !lm_accept_applies(c->m.vocab);
+        run_lm_head(c, B * D, logits, reduce);
+        Phase p(c, SDLM_PH_ACCEPT);
+        if (reduce) launch_accept(s, c->st, c->ids_rows, c->conf_rows, B, D, c->r.tau, c->r.accept_rule, ids, count, conf);
+        else launch_lm_accept(s, logits ? logits : c->logits, c->m.vocab, c->r.conf_fn, c->st, B, D, c->r.tau, c->r.accept_rule, ids, count, conf);
     };
     if (c->graph_on && c->prof == 0 && c->taps.empty() && !eager_only) {
         void *key[4] = {ids, count, conf, logits};
@@ -736,7 +760,7 @@ int sdlm_verify_step(sdlm_ctx *c, int32_t rule, int32_t *ids_tilde, int32_t *cou
         groups = verify_groups_per_seq(D, gr);
         const int cp_floor = c->L.mfma ? mfma_attn_chunk_floor(&c->m, c->r.max_seq_len, B * groups, c->L.attn_bytes) : 0;
         { Phase p(c, SDLM_PH_ROWS); launch_assemble_verify(s, c->st, c->rm, B, D, c->m.mask_token_id, gr, c->kg.staging_base, c->m.block_causal, c->m.n_kv_heads, cp_floor); }
-        run_layers(c, rows, B * groups, rows, false, !shared);
+        run_layers(c, rows, B * groups, rows, false, false, !shared);
         run_lm_head(c, B * (D - 1), logits);
     }
     { Phase p(c, SDLM_PH_ACCEPT); launch_verify_accept(s, c->st, c->ids_rows, B, D, rule, ids_tilde, count); }
