@@ -957,17 +957,45 @@ struct TileChoice { int kind, MT, NT, splits, WV, KH; };
 //     h = 2048, F = 11008: 66 rows 32.9 -> 24.4 us, 48 rows 35.6 -> 24.8; h = 1536, F = 8960: 96 rows 24.5 -> 19.7, 48 rows 27.4 ->
 //     18.9; h = 4096, F = 16384 (256 blocks): 48 rows 70.9 -> 52.4, 128 rows 66.9 -> 56.7.  A workgroup of 128 rows fills a unit (360 registers), so
 //     beyond 256 blocks there is a second round: h = 3584, F = 18944 (296): 70 rows 55.6 -> 70.5; h = 5120, F = 27648 (432): 96 rows 99.4 -> 112.7; those of
-//     64 rows are two a unit and about even there (48 rows 64.2 -> 65.2 and 111.5 -> 104.0).  Beyond 128 rows (192- and 256-row tiles in halves: 160 rows 31.8 -> 32.5) and for the split-k
+//     64 rows are two a unit (48 rows 65.2 and 104.0, the plain 128-row tile 53.0 and 95.1).  With up to 64 possible rows the 128-row workgroup takes over
+//     above 40 certain ones (64 rows, h = 2048 24.7 -> 22.4, h = 1536 18.0 -> 16.5; both are equal up to 32 live rows).  Beyond 128 rows (192- and 256-row tiles in halves: 160 rows 31.8 -> 32.5) and for the split-k
 //     projections (160 rows, QKV 11.8 -> 19.4, O 8.8 -> 14.0, down 20.8 -> 23.4) the activations' share of the load path takes it back.
 //   * Where the 192-row tile would be taken (129 to 192 certain rows) and more than 192 are possible: a 256-row tile, so that the rows from 193 to 256
 //     are not a second row block that streams every weight again.  A layer of h = 5120, F = 27648: 208 rows 406 -> 337 us, 256 rows 431 -> 361; up to
 //     192 rows it costs 0.8 (315.8 -> 316.6 at 156), and beyond 256, where both need a second block, 6 (20 sequences, D = 8, 320 rows: 423 -> 429).  (Its
 //     256 accumulator registers leave room for the operands only with an even number of slices, without a peeled last one.)
-static void refine_gateup(int rows, int N, int K, TileChoice *c)
+static void refine_gateup(int rows, int min_rows, int N, int K, TileChoice *c)
 {
     if (K % 128) return;
-    if (rows > 32 && rows <= 128 && (N + 63) / 64 <= 256) { c->KH = 2; c->MT = rows <= 64 ? 2 : 4; c->NT = 2; c->WV = 4; }
+    if (rows > 32 && rows <= 128 && (N + 63) / 64 <= 256) { c->KH = 2; c->MT = rows <= 64 && min_rows <= 40 ? 2 : 4; c->NT = 2; c->WV = 4; }
     else if (c->MT == 6 && rows > 192) c->MT = 8;
+}
+
+// Estimate, in us, of a plain-store or residual product in 128-row tiles of 128 NT columns with `sp` k splits, and of the consumer's reading of the splits'
+// slabs.  Fitted to 2000 launches (12 matrices of h = 1536 to 5120, 34 to 4096 rows, every split count): a 64-deep slice takes 0.52 us with 128
+// columns and 0.82 with 256, whatever rows of the tile are live, and with more than 400 rows, where the weights are shared, the matrix pipes set 0.70 and 0.97;
+// workgroups of one compute unit share its load path, so their slices add up; weights come at 6.4 TB/s where nothing else bounds; slabs are written at 3.4 TB/s
+// and read by the RMSNorm at 9 and by the rotation at 20 (measured in whole steps).  Its choice is within 0.7 % of the best of the sweep in the geometric mean;
+// as many workgroups of the wide tile as units wherever that fits is 6 % (up to 400 rows) and 4 % slower.  us, (columns, splits):
+// N = 2048, K = 11008, 160 rows (256, 16) 20.0 -> (128, 8) 18.0;  N = 3584, K = 18944, 49 rows (256, 16) 28.7 -> (128, 9) 27.1;  N = 5120 square,
+// 160 rows (256, 6) 20.3 -> (128, 3) 19.7, the norm behind each 0.6 to 2 us shorter;  N = 5120, K = 27648, 992 rows (128, 1) 386 -> (256, 3) 261.
+static float tiled_us(int epi, int NT, int sp, int rows, int N, int K)
+{
+    const int S = K / 64, per = (S + sp - 1) / sp;
+    const long wgs = (long)((N + 128 * NT - 1) / (128 * NT)) * ((rows + 127) / 128) * sp;
+    const float slice = rows <= 400 ? (NT == 1 ? 0.517f : 0.821f) : (NT == 1 ? 0.70f : 0.97f);
+    const float loop = (float)((wgs + 255) / 256 * per) * slice, weights = (float)N * K * 2 / 6.45e6f;
+    const float l2 = loop * loop, w2 = weights * weights;
+    const float slabs = sp > 1 ? (float)sp * rows * N * 4 * (epi == EPI_RESID ? 1 / 3.44e6f + 1 / 9e6f : 1 / 3.44e6f + 1 / 20e6f) : 0.f;
+    return 2.9f + sqrtf(sqrtf(l2 * l2 + w2 * w2)) + slabs;
+}
+
+// Rows to reckon with between the certain ones and the bound.  A step's bound is 2 B D rows and its certain ones B (D + 1), so that the difference of
+// min_rows to half the bound is B: as many pending rows again, two a sequence, are what a trained model leaves.
+static int likely_rows(int rows, int min_rows)
+{
+    if (min_rows <= 0) return rows;
+    return min(rows, max(min_rows, 2 * min_rows - rows / 2));
 }
 
 // rows: bound of the launch (grid); min_rows: rows that are certainly there.  The one place where a launch shape is decided.
@@ -979,48 +1007,57 @@ static TileChoice choose(int epi, int rows, int min_rows, int N, int K, size_t s
         if (few16_resid(min_rows, N, K, sp)) return {FEW16, 1, 1, sp, SK_W, SK_W};
     }
     TileChoice c{TILED, rows <= 32 ? 1 : rows <= 64 ? 2 : 4, 2, 1, 4, 1};
+    // Gate/up of 33 to 64 rows and more column blocks of 64 features than units: 128-row tiles, whose weight stream runs deeper (two sets pipelined across the slice's
+    // end instead of three): h = 3584, F = 18944, 48 rows 64.2 -> 53.0 us; h = 5120, F = 27648 110 -> 95.
+    if (epi == EPI_SWIGLU && rows > 32 && rows <= 64 && (N + 63) / 64 > 256) c.MT = 4;
     // Gate/up with 129..192 certain rows and enough column blocks for one workgroup on (nearly) every compute unit: one
     // 192-row block per column block, so that no weight band is streamed by two workgroups.  (For the split-k
     // projections the same tile was measured: it wants more splits, and the slab traffic costs more than it saves.)
     if (epi == EPI_SWIGLU && min_rows > 128 && min_rows <= 192 && rows <= 384 && (N + 127) / 128 >= 192) c.MT = 6;
-    if (epi != EPI_SWIGLU && epi != EPI_LMHEAD && c.MT < 4) {
-        int mb = (rows + c.MT * 32 - 1) / (c.MT * 32);
-        if ((long)((N + 255) / 256) * mb < 256) c.NT = 1;
-    }
     if (epi == EPI_STORE_F32 || epi == EPI_RESID) {
         const int S = K / 64;
-        const int cap_k = S / 4 > 0 ? S / 4 : 1;                             // at least 4 stages (256 deep) per split
         const long cap_m = (long)(slab_room_floats / ((size_t)rows * N));    // slabs must fit the scratch area
-        auto clamp = [&](long sp) { sp = sp > cap_k ? cap_k : sp; sp = sp > cap_m ? cap_m : sp; sp = sp > 16 ? 16 : sp; return (int)(sp < 1 ? 1 : sp); };
-        if (c.MT == 4) {
-            // Workgroups are dealt out to the compute units round robin and two heavy ones on one unit take twice as
-            // long as one: the fastest shape is one workgroup on as many units as possible, i.e. the largest split
-            // count that keeps (column blocks x occupied row blocks x splits) within the 256 units.  The 256-wide
-            // tile is the more efficient one; the 128-wide tile takes over when the wide one would leave more
-            // than a quarter of the units without work.
-            const long ms = sure_blocks(rows, min_rows, c.MT), nb2 = (N + 255) / 256, nb1 = (N + 127) / 128;
-            int sp2 = clamp(256 / (nb2 * ms));
-            if (K <= 4096 && sp2 > 3) sp2 = 3;   // short k loops: beyond three splits the slabs' write + read-back costs more than the idle units
-            if (nb2 * ms * sp2 >= 192) { c.NT = 2; c.splits = sp2; }
-            else { c.NT = 1; c.splits = clamp(256 / (nb1 * ms)); }
+        // every split owns at least three 64-deep slices and no split is empty: with ceil(S / splits) slices per split the last
+        // ones of an uneven division would be, and their slabs never written
+        auto clamp = [&](long sp) {
+            sp = min(min(sp, cap_m), min(16L, (long)(S / 3)));
+            if (sp <= 1) return 1;
+            const int per = (S + (int)sp - 1) / (int)sp;
+            return (S + per - 1) / per;
+        };
+        if (c.MT == 1) {
+            // Up to 32 rows: workgroups of 128 columns, k split until they are about one round of the units, or with long k (many slices, small slabs) nearly two; a
+            // third workgroup on some units costs a third: 24 rows, N = 5120, K = 27648 13 splits (520 workgroups) 57.8 -> 11 splits 50.6 us;
+            // N = 4608, K = 3584 14 -> 7 splits, half the slabs, 10.6 -> 9.4.
+            c.NT = 1;
+            c.splits = clamp((K > 4096 ? 448 : 256) / ((N + 127) / 128));
         } else {
-            const long wgs = (long)((N + 128 * c.NT - 1) / (128 * c.NT)) * ((rows + c.MT * 32 - 1) / (c.MT * 32));
-            c.splits = clamp((512 + wgs - 1) / wgs);
+            // 128-row tiles from 33 rows on (64-row tiles: N = 4608, K = 3584, 48 rows 13.1 us, so 9.8; N = 5120, K = 27648 61.7 and 50.2)
+            c.MT = 4;
+            const int at = min_rows > 0 ? (min_rows + likely_rows(rows, min_rows)) / 2 : rows;
+            float best = 0.f;
+            for (int NT = 1; NT <= 2; ++NT)
+                for (int want = 1, last = 0; want <= 16; ++want) {
+                    const int sp = clamp(want);
+                    if (sp == last) continue;
+                    last = sp;
+                    const float t = tiled_us(epi, NT, sp, at, N, K);
+                    if (best == 0.f || t < best) { best = t; c.NT = NT; c.splits = sp; }
+                }
         }
     }
-    // every split must own at least one 64-deep slice: with ceil(S / splits) slices per split the last splits of an
-    // uneven division would be empty and their slabs never written
-    if (c.splits > 1) {
-        const int S = K / 64, per = (S + c.splits - 1) / c.splits;
-        c.splits = (S + per - 1) / per;
+    // A launch of more 128 x 256 workgroups than compute units runs as 128 x 512 workgroups of eight wavefronts, whose activation slice is staged once for twice
+    // the columns (7B gate/up 2.5 to 7 % faster), unless the rounds are dealt out worse: a round of 256 of them takes 0.955 of one of 512 small ones, of which
+    // 264 or fewer, about one a unit, take 0.58.  us, eight / four: h = 2048, F = 11008 300 rows 49 / 40, 640 58 / 60, 992 103 / 88, 1280 110 / 113;
+    // h = 3584, F = 18944 400 rows 160 / 133, 700 177 / 190, 992 260 / 243; h = 1536, F = 8960 509 rows 41 / 43, 992 76 / 63.
+    // Beyond four rounds the difference is within 2 % or the wide ones'.  (Measured and not faster: the LM head, the prefill QKV projection.)
+    if ((epi == EPI_SWIGLU || epi == EPI_RESID) && c.MT == 4 && c.NT == 2 && c.splits == 1) {
+        const int cols4 = epi == EPI_SWIGLU ? (N + 127) / 128 : (N + 255) / 256, mb = sure_blocks(rows, min_rows, c.MT);
+        const int b4 = cols4 * mb, rounds8 = ((cols4 + 1) / 2 * mb + 255) / 256, rest4 = b4 % 512;
+        const int t4 = 1000 * (b4 / 512) + (rest4 == 0 ? 0 : rest4 <= 264 ? 580 : 1000);
+        if (b4 > 256 && (rounds8 > 4 || 955 * rounds8 < t4)) c.WV = 8;
     }
-    // A launch of more 128 x 256 workgroups than compute units runs as 128 x 512 workgroups of eight wavefronts
-    // (measured on the 7B gate/up shape: 2.5 % faster; with fewer workgroups than units the wider tile only idles units)
-    if ((epi == EPI_SWIGLU || epi == EPI_RESID) && c.MT == 4 && c.NT == 2 && c.splits == 1) {   // (measured and not faster: the LM head, the prefill QKV projection)
-        const long blocks4 = epi == EPI_SWIGLU ? (N + 127) / 128 : (N + 255) / 256;
-        if (blocks4 * sure_blocks(rows, min_rows, c.MT) > 256) c.WV = 8;
-    }
-    if (epi == EPI_SWIGLU) refine_gateup(rows, N, K, &c);
+    if (epi == EPI_SWIGLU) refine_gateup(rows, min_rows, N, K, &c);
     return c;
 }
 
@@ -1045,17 +1082,16 @@ static void launch_cfg(hipStream_t s, const TileChoice &c, MfmaArgs &a, int min_
         }
         if (c.MT == 8) { hipLaunchKernelGGL((gemm_mfma_k<8, 2, EPI>), grid, block, 0, s, a); return; }
     }
-#define SDLM_GO(MT_, NT_) hipLaunchKernelGGL((gemm_mfma_k<MT_, NT_, EPI>), grid, block, 0, s, a)
-    if (EPI == EPI_SWIGLU || EPI == EPI_LMHEAD || c.NT == 2) {
-        if (c.MT == 1) SDLM_GO(1, 2); else if (c.MT == 2) SDLM_GO(2, 2); else if (c.MT == 6 && EPI == EPI_SWIGLU) hipLaunchKernelGGL((gemm_mfma_k<(EPI == EPI_SWIGLU ? 6 : 4), 2, EPI>), grid, block, 0, s, a);
-        else if (c.WV == 8) hipLaunchKernelGGL((gemm_mfma_k<4, 2, EPI, 8>), grid, block, 0, s, a);
-        else SDLM_GO(4, 2);
+#define SDLM_GO(...) hipLaunchKernelGGL((gemm_mfma_k<__VA_ARGS__>), grid, block, 0, s, a)
+    if constexpr (EPI == EPI_LMHEAD) {
+        if (c.MT == 1) SDLM_GO(1, 2, EPI); else if (c.MT == 2) SDLM_GO(2, 2, EPI); else SDLM_GO(4, 2, EPI);
+    } else if constexpr (EPI == EPI_SWIGLU) {   // up to 32 rows: the kernels without LDS tiles
+        if (c.MT == 2) SDLM_GO(2, 2, EPI); else if (c.MT == 6) SDLM_GO(6, 2, EPI); else if (c.WV == 8) SDLM_GO(4, 2, EPI, 8); else SDLM_GO(4, 2, EPI);
     } else {
-        if (EPI == EPI_STORE_F32 || EPI == EPI_RESID) {
-            if (c.MT == 1) hipLaunchKernelGGL((gemm_mfma_k<1, 1, (EPI == EPI_STORE_F32 || EPI == EPI_RESID) ? EPI : EPI_RESID>), grid, block, 0, s, a);
-            else if (c.MT == 2) hipLaunchKernelGGL((gemm_mfma_k<2, 1, (EPI == EPI_STORE_F32 || EPI == EPI_RESID) ? EPI : EPI_RESID>), grid, block, 0, s, a);
-            else hipLaunchKernelGGL((gemm_mfma_k<4, 1, (EPI == EPI_STORE_F32 || EPI == EPI_RESID) ? EPI : EPI_RESID>), grid, block, 0, s, a);
-        }
+        if (c.MT == 1) SDLM_GO(1, 1, EPI);
+        else if (c.NT == 1) SDLM_GO(4, 1, EPI);
+        else if (EPI == EPI_RESID && c.WV == 8) SDLM_GO(4, 2, EPI_RESID, 8);
+        else SDLM_GO(4, 2, EPI);
     }
 #undef SDLM_GO
 }

@@ -714,6 +714,27 @@ def test_bf16_qkv_row_blocks(B, D, hidden, heads, kv):
     ctx.close()
 
 
+@pytest.mark.parametrize("B,D,hidden,ffn,heads", [(17, 1, 64, 64, 2), (32, 1, 192, 16448, 6), (4, 8, 320, 448, 28), (30, 2, 2112, 192, 3), (50, 4, 128, 8256, 2),
+                                                   (9, 4, 128, 640, 2), (4, 3, 2112, 8256, 2)])
+def test_bf16_projections_on_the_128_row_tiles(B, D, hidden, ffn, heads):
+    """Steps of 33 and more rows: projections on 128-row tiles of 128 and 256 columns, from one slice of k (no split) over divisions that leave the last
+    split short to sixteen splits; gate/up of 33 to 64 rows on the 128-row tile (a matrix of more than 16384 features) and in halves with more than
+    40 certain rows; 24 rows with few slices a split."""
+    m = mfma_cfg(n_layers=1, n_q_heads=heads, n_kv_heads=1, hidden=hidden, ffn=ffn, vocab=300, has_qkv_bias=True)
+    om, g_dev, layers_dev = both_models(m, seed=140 + B, std=0.03)
+    prompts = [syn.uniform_int(5, f"pt{i}", 3 + 4 * (i % 5), 0, m.vocab - 1).numpy() for i in range(B)]
+    steps = 3
+    ids, cnt = syn.make_overrides(26, steps, B, D, m.vocab)
+    cnt = cnt.clone()
+    cnt[0] = D                                       # then a step of B * 2D rows
+    max_len = max(len(p) for p in prompts) + steps * D + D
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=B, max_seq_len=max_len, D=D, tau=0.5)
+    assert ctx.kernel_info == "mfma-bf16"
+    st, _ = lockstep(ctx, om, prompts, D, 0.5, steps, logit_tol=2e-2, conf_tol=1e-3, overrides=(ids, cnt), bf16=True, max_len=max_len)
+    print("128-row tiles", (B, D, hidden, ffn, heads), st)
+    ctx.close()
+
+
 @pytest.mark.parametrize("B,D,hidden,ffn", [(5, 4, 128, 2112), (8, 4, 1408, 1088), (13, 4, 384, 2112), (16, 4, 1024, 192), (26, 4, 256, 24640), (32, 4, 128, 24576),
                                              (48, 2, 256, 24576), (48, 2, 192, 24640), (26, 4, 320, 24576)])
 def test_bf16_gate_up_of_33_to_256_rows(B, D, hidden, ffn):
