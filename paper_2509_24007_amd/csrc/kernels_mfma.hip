@@ -71,7 +71,10 @@ struct MfmaArgs {
     int m_sure;         // row blocks below this index certainly hold rows; they come first in the grid
     int rows_sure;      // rows below this index certainly exist (host-known lower bound of the device row count)
     size_t slab;        // elements between split-k slabs
-    float scale;
+    float scale, eps;
+    const bf16_t *gain; // steps of at most 16 rows: see "norms inside the products"
+    bf16_t *xg;
+    float *ssq;
 };
 
 enum { EPI_LMHEAD = 4 };
@@ -640,11 +643,11 @@ constexpr int sk_u(int NB) { return NB == 1 ? 8 : NB == 2 ? 6 : 3; }   // k step
 // with the 16 NB rows of X from m0 on, over k steps [k_begin, k_end); steps beyond k_end repeat the last one.  `with_rows` runs after
 // the row count is known and the first operands are requested: the caller's own requests go there.  Returns the row count.
 // Result: element v of lane l is feature 4 * (l / 16) + v of the tile, row m0 + 16 * nb + l % 16.
-template <int NB, class F>
+template <int NB, int NT, bool XP, int U, class F>
 __device__ inline int skinny_dot(const bf16_t *wa, const bf16_t *wb, const bf16_t *X, const int32_t *pR, int max_rows, int m0, int K, int k_begin, int k_end,
                                  int lane, f32x4 (&aa)[NB], f32x4 (&ab)[NB], F with_rows)
 {
-    constexpr int U = sk_u(NB);
+    static_assert(!XP || NB == 1, "the ordered rows are one block of 16");
     const int k_last = max(k_end, 1) - 1;   // a wavefront without any k step still requests within the matrix
     // lane -> k half of the step's 32 (lane / 32), 8 of 16 (lane / 16 % 2), feature (lane % 16)
     const uint32_t wl = (lane >> 5) * 512 + ((lane & 15) + ((lane >> 4) & 1) * 32) * 8;
@@ -655,14 +658,14 @@ __device__ inline int skinny_dot(const bf16_t *wa, const bf16_t *wb, const bf16_
         for (int u = 0; u < U; ++u) {
             const size_t o = (size_t)min(k + u, k_last) * 1024;
             A[u] = *(const bf16x8 *)(wa + o + wl);
-            B[u] = *(const bf16x8 *)(wb + o + wl);
+            if constexpr (NT == 2) B[u] = *(const bf16x8 *)(wb + o + wl);
         }
     };
     auto load_x = [&](bf16x8 (&Xr)[NB][U], int k) {
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) Xr[nb][u] = *(const bf16x8 *)(xp[nb] + min(k + u, k_last) * 32);
+            for (int nb = 0; nb < NB; ++nb) Xr[nb][u] = *(const bf16x8 *)(xp[nb] + min(k + u, k_last) * (XP ? 512 : 32));
     };
     auto mma = [&](const bf16x8 (&A)[U], const bf16x8 (&B)[U], const bf16x8 (&Xr)[NB][U], int k) {
 #pragma unroll
@@ -671,7 +674,7 @@ __device__ inline int skinny_dot(const bf16_t *wa, const bf16_t *wb, const bf16_
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
                     aa[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[u], Xr[nb][u], aa[nb], 0, 0, 0);
-                    ab[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[u], Xr[nb][u], ab[nb], 0, 0, 0);
+                    if constexpr (NT == 2) ab[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[u], Xr[nb][u], ab[nb], 0, 0, 0);
                 }
             }
     };
@@ -682,7 +685,10 @@ __device__ inline int skinny_dot(const bf16_t *wa, const bf16_t *wb, const bf16_
     const int R = min(*pR, max_rows);
     if (R <= m0) return 0;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) xp[nb] = X + (size_t)min(m0 + nb * 16 + (lane & 15), R - 1) * K + (lane >> 4) * 8;
+    for (int nb = 0; nb < NB; ++nb) {
+        const int r = min(m0 + nb * 16 + (lane & 15), R - 1);
+        xp[nb] = XP ? X + ((lane >> 4) * 16 + r) * 8 : X + (size_t)r * K + (lane >> 4) * 8;
+    }
     load_x(x0, k_begin);
     if (k_begin + U < k_end) load_x(x1, k_begin + U);
     with_rows(R);
@@ -709,27 +715,137 @@ __device__ inline bool skinny_sum(f32x4 (&part)[SK_W][2][NB][64], const f32x4 (&
     return true;
 }
 
+// ---- norms inside the products: the chain of a step of at most 16 rows (launch_*_few below)
+// Such a step is a chain of launches, and the two RMSNorms of a layer, with the split-k slabs that they add, were two of eight.  Here O and down sum all of k
+// inside a workgroup of 16 features, so that its epilogue has the finished residual stream: it stores x, x times the gains of the norm that follows (bf16, the operand
+// of the next product), and the sum of squares of its 16 features per row.  The next product multiplies its sums by 1 / rms, from those h / 16 sums of squares, which
+// it requests first and adds while its weights are under way.  x g is rounded to bf16 before the factor 1 / rms instead of behind it: the same relative rounding.
+// The operands are kept in the order of the matrix instruction, [k / 32][k / 8 % 4][row][8], so that a load is one run of up to 1 KB and not 64 pieces
+// of 16 bytes; gate/up leaves its result in that order too.  Whole steps of one sequence of 512 tokens, D = 4, us: h = 1536, F = 8960, 28 layers 1613 -> 1513, h = 2048, F = 11008, 18 layers
+// 1279 -> 1215, h = 3584, F = 18944, 8 layers 1209 -> 1138 (16 rows 1259 -> 1186), h = 5120, F = 27648, 8 layers 1976 -> 1965.
+__device__ inline size_t few_off(int row, int k) { return (size_t)(k >> 5) * 512 + (((k >> 3) & 3) * 16 + row) * 8 + (k & 7); }
+
+constexpr int FEW_SSQ = 8;   // requests of 16 bytes a lane: h up to 8192
+
+struct FewRms {
+    float4 v[FEW_SSQ];
+    // wavefront w of SK_W takes every SK_W-th run of 16 sums of its rows; row = lane % 16
+    __device__ void request(const float *ssq, int n, int wave, int lane)
+    {
+#pragma unroll
+        for (int t = 0; t < FEW_SSQ; ++t) {
+            const int i = ((t * SK_W + wave) * 4 + (lane >> 4)) * 4;
+            v[t] = i < n ? *(const float4 *)(ssq + (size_t)(lane & 15) * n + i) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    }
+    __device__ void add(float (&rs)[SK_W][16], int wave, int lane) const
+    {
+        float s = 0.f;
+#pragma unroll
+        for (int t = 0; t < FEW_SSQ; ++t) s += (v[t].x + v[t].y) + (v[t].z + v[t].w);
+        s += __shfl_xor(s, 16);
+        s += __shfl_xor(s, 32);
+        if (lane < 16) rs[wave][lane] = s;
+    }
+    // behind a barrier
+    static __device__ float factor(const float (&rs)[SK_W][16], int row, int h, float eps)
+    {
+        float s = rs[0][row];
+#pragma unroll
+        for (int w = 1; w < SK_W; ++w) s += rs[w][row];
+        return 1.0f / sqrtf(s / (float)h + eps);
+    }
+};
+
 // Gate/up: SiLU(gate) * up needs complete sums, so k cannot be split between workgroups; a workgroup owns 16 features.
+// NORM: rows and result in operand order, the norm's factor here.
+template <bool NORM>
 __global__ __launch_bounds__(SK_W * 64) void swiglu_skinny16_k(MfmaArgs a)
 {
     constexpr int NB = 1;
     __shared__ f32x4 part[SK_W][2][NB][64];
+    __shared__ float rs[SK_W][16];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j = blockIdx.x >> 1, h = blockIdx.x & 1;   // features 32 j + 16 h ..: halves of tiles 2j (gate) and 2j + 1 (up) of the fused matrix
     const int KS = a.K >> 4, K32 = a.K >> 5, per = (K32 + SK_W - 1) / SK_W;
     const bf16_t *wg = a.Wp + ((size_t)(2 * j) * KS) * 512 + h * 128;
     f32x4 ag[NB], au[NB], gs, us;
-    const int R = skinny_dot<NB>(wg, wg + (size_t)KS * 512, a.X, a.pR, a.max_rows, 0, a.K, wave * per, min(K32, wave * per + per), lane, ag, au, [](int) {});
+    FewRms rms;
+    if constexpr (NORM) rms.request(a.ssq, a.K >> 4, wave, lane);
+    const int R = skinny_dot<NB, 2, NORM, sk_u(NB)>(wg, wg + (size_t)KS * 512, a.X, a.pR, a.max_rows, 0, a.K, wave * per, min(K32, wave * per + per), lane, ag, au,
+                                                    [&](int) { if constexpr (NORM) rms.add(rs, wave, lane); });
     if (R <= 0 || !skinny_sum<NB>(part, ag, au, wave, lane, gs, us)) return;
     const int row = wave * 16 + (lane & 15), n = j * 32 + h * 16 + (lane >> 4) * 4;
     if (row >= R || n >= a.N) return;
+    if constexpr (NORM) {
+        const float f = FewRms::factor(rs, row, a.K, a.eps);
+        gs *= f;
+        us *= f;
+    }
     float o[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = silu_f(gs[e]) * us[e];
-    *(uint2 *)(a.Yt + (size_t)row * a.n_out + n) = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
+    *(uint2 *)(a.Yt + (NORM ? few_off(row, n) : (size_t)row * a.n_out + n)) = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
 }
 
-// O and down projection: a workgroup owns a packed tile's 32 features and one of `splits` ranges of k; slabs as in the tiled kernel.
+// O of that chain, and down where few_down says so: all of k by the eight wavefronts of a workgroup of 16 features.  XP: rows in operand order (down).
+// Bound: the operands' requests of one workgroup, weights and rows alike 1 KB a k step, which a compute unit serves at 75 GB/s; four k steps a register set (four
+// wavefronts a SIMD) are as fast as six, 16 wavefronts or 32 features a workgroup slower (h = 1536, F = 8960, 8 rows, whole step 1502 us; six k steps 1504, 16
+// wavefronts 1518, 32 features 1652).  O with its norm, h = 1536, 5 rows: 9.1 us in two launches, now 5.2.
+constexpr int FEW_W = 8, FEW_U = 4;
+
+template <bool XP>
+__global__ __launch_bounds__(FEW_W * 64) void resid_few_k(MfmaArgs a)
+{
+    __shared__ f32x4 part[FEW_W][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t16 = blockIdx.x, n = t16 * 16 + (lane >> 4) * 4, row = lane & 15, K32 = a.K >> 5;
+    const bf16_t *w = a.Wp + (size_t)(t16 >> 1) * (a.K >> 4) * 512 + (t16 & 1) * 128;
+    const int kb = (int)((long)K32 * wave / FEW_W), ke = (int)((long)K32 * (wave + 1) / FEW_W);
+    f32x4 aa[1], ab[1], x;
+    uint2 g = make_uint2(0, 0);
+    const int R = skinny_dot<1, 1, XP, FEW_U>(w, w, a.X, a.pR, a.max_rows, 0, a.K, kb, ke, lane, aa, ab, [&](int rows) {
+        if (wave) return;
+        x = *(const f32x4 *)(a.Yf + (size_t)min(row, rows - 1) * a.n_out + n);
+        if (a.gain) g = *(const uint2 *)(a.gain + n);
+    });
+    if (R <= 0) return;
+    part[wave][lane] = aa[0];
+    __syncthreads();
+    if (wave) return;
+    f32x4 s = part[0][lane];
+#pragma unroll
+    for (int i = 1; i < FEW_W; ++i) s += part[i][lane];
+    x += s;
+    if (row < R) *(f32x4 *)(a.Yf + (size_t)row * a.n_out + n) = x;
+    if (!a.gain) return;   // behind the last layer
+    float ss = (x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]);
+    ss += __shfl_xor(ss, 16);
+    ss += __shfl_xor(ss, 32);
+    if (row >= R) return;
+    if (lane < 16) a.ssq[(size_t)row * (a.n_out >> 4) + t16] = ss;
+    const float g0 = bf16_to_f((bf16_t)(g.x & 0xffff)), g1 = bf16_to_f((bf16_t)(g.x >> 16)), g2 = bf16_to_f((bf16_t)(g.y & 0xffff)), g3 = bf16_to_f((bf16_t)(g.y >> 16));
+    *(uint2 *)(a.xg + few_off(row, n)) = make_uint2(pack_bf16(x[0] * g0, x[1] * g1), pack_bf16(x[2] * g2, x[3] * g3));
+}
+
+// The embeddings of that chain's rows, in the same three forms.  Four features a thread.
+__global__ __launch_bounds__(256) void embed_few_k(float *x, const bf16_t *E, const int32_t *tok, const int32_t *pR, int h, int V, const bf16_t *gain, bf16_t *xg, float *ssq)
+{
+    const int r = blockIdx.y, n = (blockIdx.x * 256 + threadIdx.x) * 4;   // h is a multiple of 64: the four lanes of 16 features are all there or none
+    if (r >= *pR || n >= h) return;
+    const uint2 e = *(const uint2 *)(E + (size_t)min(max(tok[r], 0), V - 1) * h + n), g = *(const uint2 *)(gain + n);
+    const float4 v = make_float4(bf16_to_f((bf16_t)(e.x & 0xffff)), bf16_to_f((bf16_t)(e.x >> 16)), bf16_to_f((bf16_t)(e.y & 0xffff)), bf16_to_f((bf16_t)(e.y >> 16)));
+    *(float4 *)(x + (size_t)r * h + n) = v;
+    *(uint2 *)(xg + few_off(r, n)) = make_uint2(pack_bf16(v.x * bf16_to_f((bf16_t)(g.x & 0xffff)), v.y * bf16_to_f((bf16_t)(g.x >> 16))),
+                                                pack_bf16(v.z * bf16_to_f((bf16_t)(g.y & 0xffff)), v.w * bf16_to_f((bf16_t)(g.y >> 16))));
+    float ss = (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+    ss += __shfl_xor(ss, 1);
+    ss += __shfl_xor(ss, 2);
+    if ((threadIdx.x & 3) == 0) ssq[(size_t)r * (h >> 4) + (n >> 4)] = ss;
+}
+
+// O and down projection: a workgroup owns a packed tile's 32 features and one of `splits` ranges of k; slabs as in the tiled kernel.  XP: rows in operand order.
+template <bool XP>
 __global__ __launch_bounds__(SK_W * 64) void resid_skinny_k(MfmaArgs a)
 {
     constexpr int NB = 1;
@@ -740,7 +856,7 @@ __global__ __launch_bounds__(SK_W * 64) void resid_skinny_k(MfmaArgs a)
     const int kb = min(k1, k0 + wave * per);
     const bf16_t *w = a.Wp + (size_t)tile * (a.K >> 4) * 512;
     f32x4 aa[NB], ab[NB], s[2];
-    const int R = skinny_dot<NB>(w, w + 128, a.X, a.pR, a.max_rows, 0, a.K, kb, min(k1, kb + per), lane, aa, ab, [](int) {});
+    const int R = skinny_dot<NB, 2, XP, sk_u(NB)>(w, w + 128, a.X, a.pR, a.max_rows, 0, a.K, kb, min(k1, kb + per), lane, aa, ab, [](int) {});
     if (R <= 0 || !skinny_sum<NB>(part, aa, ab, wave, lane, s[0], s[1])) return;
     const int row = wave * 16 + (lane & 15);
     if (row >= R) return;
@@ -767,10 +883,12 @@ struct QkvSkinnyArgs {
     RowMeta rm;
     SeqState st;
     const float2 *rope;
+    const float *ssq;       // NORM: X is x times the gains in operand order
+    float eps;
 };
 
 // The 16 NB rows from m0 on, columns `col`.
-template <int NB>
+template <int NB, bool NORM>
 __device__ inline void qkv_rope_rows(const QkvSkinnyArgs &a, f32x4 (&part)[SK_W][2][NB][64], int m0, int col, int lane, int wave)
 {
     const int head = col >> 2, t16 = col & 3;   // heads: Hq of q, then Hkv of k, then Hkv of v; t16: which 16 of the first 64 features
@@ -784,8 +902,12 @@ __device__ inline void qkv_rope_rows(const QkvSkinnyArgs &a, f32x4 (&part)[SK_W]
     float blo[4] = {0.f, 0.f, 0.f, 0.f}, bhi[4] = {0.f, 0.f, 0.f, 0.f};
     int page = -1, slot = 0;
     f32x4 aa[NB], ab[NB], sa, sb;
+    __shared__ float rs[NORM ? SK_W : 1][16];
+    FewRms rms;
+    if constexpr (NORM) rms.request(a.ssq, a.K >> 4, wave, lane);
     // what the epilogue needs beside the sums is requested with the operands: rotation factors, bias, the page of a cached position
-    const int R = skinny_dot<NB>(wa, wa + (size_t)2 * KS * 512, a.X, a.pR, a.max_rows, m0, a.K, wave * per, min(K32, wave * per + per), lane, aa, ab, [&](int rows) {
+    const int R = skinny_dot<NB, 2, NORM, sk_u(NB)>(wa, wa + (size_t)2 * KS * 512, a.X, a.pR, a.max_rows, m0, a.K, wave * per, min(K32, wave * per + per), lane, aa, ab, [&](int rows) {
+        if constexpr (NORM) rms.add(rs, wave, lane);
         if (wave >= NB) return;
         const int rr = min(row, rows - 1), pos = a.rm.pos[rr], kind = a.rm.kind[rr], b = a.rm.seq[rr], stg = a.rm.stg[rr];
 #pragma unroll
@@ -797,6 +919,11 @@ __device__ inline void qkv_rope_rows(const QkvSkinnyArgs &a, f32x4 (&part)[SK_W]
         if (!is_q && kind < 0) { page = a.st.page_table[(size_t)b * a.kg.pages_per_seq + pos / PAGE]; slot = pos % PAGE; }
     });
     if (R <= 0 || !skinny_sum<NB>(part, aa, ab, wave, lane, sa, sb) || row >= R) return;
+    if constexpr (NORM) {
+        const float f = FewRms::factor(rs, row, a.K, a.eps);
+        sa *= f;
+        sb *= f;
+    }
     float lo[4], hi[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -828,7 +955,7 @@ __device__ inline void qkv_rope_rows(const QkvSkinnyArgs &a, f32x4 (&part)[SK_W]
 }
 
 // Row blocks of 16 NB rows; those that may be empty are of 16 NR rows.
-template <int NB, int NR>
+template <int NB, int NR, bool NORM = false>
 __global__ __launch_bounds__(SK_W * 64, 2) void qkv_rope_skinny_k(QkvSkinnyArgs a)
 {
     __shared__ f32x4 part[SK_W * 2 * NB * 64];
@@ -843,8 +970,8 @@ __global__ __launch_bounds__(SK_W * 64, 2) void qkv_rope_skinny_k(QkvSkinnyArgs 
     const int m0 = NB == NR ? ((sure ? 0 : a.m_sure) + wg % mb) * NB * 16 : (sure ? 0 : a.m_sure * NB * 16) + wg % mb * (sure ? NB : NR) * 16;
     if (!sure && m0 >= *a.pR) return;
     // (one copy of the body where one will do, and the block's first row as one product: 0.2 us of a launch of 6.6)
-    if (NB == NR || sure) qkv_rope_rows<NB>(a, *reinterpret_cast<f32x4 (*)[SK_W][2][NB][64]>(part), m0, wg / mb, lane, wave);
-    else qkv_rope_rows<NR>(a, *reinterpret_cast<f32x4 (*)[SK_W][2][NR][64]>(part), m0, wg / mb, lane, wave);
+    if (NB == NR || sure) qkv_rope_rows<NB, NORM>(a, *reinterpret_cast<f32x4 (*)[SK_W][2][NB][64]>(part), m0, wg / mb, lane, wave);
+    else qkv_rope_rows<NR, false>(a, *reinterpret_cast<f32x4 (*)[SK_W][2][NR][64]>(part), m0, wg / mb, lane, wave);
 }
 
 static int sure_blocks(int rows, int min_rows, int MT)
@@ -889,17 +1016,19 @@ static QkvRows qkv_rows(const sdlm_model_cfg *m, int max_rows, int min_rows)
 bool qkv_rope_skinny_applies(const sdlm_model_cfg *m, int max_rows, int min_rows) { return qkv_rows(m, max_rows, min_rows).units > 0; }
 
 void launch_qkv_rope_skinny(hipStream_t s, const sdlm_model_cfg *m, const void *X, const void *w_packed, const void *bias, const int32_t *p_rows,
-                            int max_rows, int min_rows, void *q_out, void *pool_layer, const KvGeom &kg, const RowMeta &rm, const SeqState &st, const float2 *rope)
+                            int max_rows, int min_rows, void *q_out, void *pool_layer, const KvGeom &kg, const RowMeta &rm, const SeqState &st, const float2 *rope,
+                            const float *ssq, float eps)
 {
     const QkvRows q = qkv_rows(m, max_rows, min_rows);
     QkvSkinnyArgs a;
     a.X = (const bf16_t *)X; a.Wp = (const bf16_t *)w_packed; a.bias = (const bf16_t *)bias; a.pR = p_rows;
     a.max_rows = max_rows; a.K = m->hidden; a.Hq = m->n_q_heads;
     a.m_sure = q.m_sure; a.m_rest = q.m_rest;
-    a.q_out = (bf16_t *)q_out; a.pool = (bf16_t *)pool_layer; a.kg = kg; a.rm = rm; a.st = st; a.rope = rope;
+    a.q_out = (bf16_t *)q_out; a.pool = (bf16_t *)pool_layer; a.kg = kg; a.rm = rm; a.st = st; a.rope = rope; a.ssq = ssq; a.eps = eps;
     const int n_cols = 4 * (m->n_q_heads + 2 * m->n_kv_heads);
     const dim3 grid((n_cols * a.m_sure + 7) / 8 * 8 + (n_cols * a.m_rest + 7) / 8 * 8), block(SK_W * 64);
-    if (q.units == 1) hipLaunchKernelGGL((qkv_rope_skinny_k<1, 1>), grid, block, 0, s, a);
+    if (ssq) hipLaunchKernelGGL((qkv_rope_skinny_k<1, 1, true>), grid, block, 0, s, a);
+    else if (q.units == 1) hipLaunchKernelGGL((qkv_rope_skinny_k<1, 1>), grid, block, 0, s, a);
     else if (q.units == 2) hipLaunchKernelGGL((qkv_rope_skinny_k<2, 2>), grid, block, 0, s, a);
     else if (q.rest_units == 4) hipLaunchKernelGGL((qkv_rope_skinny_k<4, 4>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((qkv_rope_skinny_k<4, 2>), grid, block, 0, s, a);
@@ -945,6 +1074,8 @@ static bool few16_gateup(int min_rows, int N)
     return !(blocks32 >= 144 && blocks32 <= 256 && min_rows > 4) && !(blocks32 > 512 && min_rows > 12);
 }
 
+// (Both rules are those of passes with separate norms: prompts of at most 16 tokens, runs with taps.  In the chain of a decode step the operands' order makes the finer
+// gate/up blocks and the stream of down the better ones throughout: h = 5120, F = 27648, 16 rows, a step of 8 layers 1973 -> 1944 us.)
 // What a product runs as: FEW16 / FEW32 are the kernels without LDS tiles for steps of few rows (16 rows x two 16-feature tiles, 32 rows x two
 // 32-feature tiles a workgroup), TILED the tiled kernel.
 enum { TILED = 0, FEW16, FEW32 };
@@ -1122,15 +1253,54 @@ int launch_gemm_mfma(hipStream_t s, int epi, const GemmArgs &g, float *slabs, si
         default: launch_cfg<EPI_SWIGLU>(s, c, a, g.min_rows); break;
         }
     } else if (epi == EPI_RESID) {
-        hipLaunchKernelGGL(resid_skinny_k, dim3(a.n_tiles * c.splits), dim3(SK_W * 64), 0, s, a);
+        hipLaunchKernelGGL(resid_skinny_k<false>, dim3(a.n_tiles * c.splits), dim3(SK_W * 64), 0, s, a);
     } else if (c.kind == FEW16) {
-        hipLaunchKernelGGL(swiglu_skinny16_k, dim3(a.n_tiles), dim3(SK_W * 64), 0, s, a);
+        hipLaunchKernelGGL(swiglu_skinny16_k<false>, dim3(a.n_tiles), dim3(SK_W * 64), 0, s, a);
     } else {
         hipLaunchKernelGGL(swiglu_skinny32_k, dim3(a.n_tiles / 2), dim3(SK_W * 64), 0, s, a);
     }
     if (c.splits > 1 && epi == EPI_RESID && !defer_reduce)
         hipLaunchKernelGGL(reduce_slabs_k, dim3(g.max_rows), dim3(256), 0, s, g.Yf, slabs, c.splits, a.slab, g.N, g.pR, g.max_rows);
     return c.splits;   // slabs left for the consumer: always for STORE_F32, for RESID when defer_reduce
+}
+
+bool mfma_few_applies(const sdlm_model_cfg *m, int max_rows) { return mfma_supported(m) && max_rows <= 16 && m->hidden <= 1024 * FEW_SSQ; }
+
+void launch_embed_few(hipStream_t s, float *x, const void *E, const RowMeta &rm, int max_rows, int h, int V, const void *gain, void *xg, float *ssq)
+{
+    hipLaunchKernelGGL(embed_few_k, dim3((h + 1023) / 1024, max_rows), dim3(256), 0, s, x, (const bf16_t *)E, rm.tok, rm.counts, h, V, (const bf16_t *)gain, (bf16_t *)xg, ssq);
+}
+
+void launch_gateup_few(hipStream_t s, const GemmArgs &g, const float *ssq, float eps)
+{
+    MfmaArgs a{};
+    a.X = (const bf16_t *)g.X; a.Wp = (const bf16_t *)g.W; a.Yt = (bf16_t *)g.Yt; a.pR = g.pR; a.max_rows = g.max_rows; a.N = g.N; a.K = g.K; a.ssq = const_cast<float *>(ssq); a.eps = eps;
+    hipLaunchKernelGGL(swiglu_skinny16_k<true>, dim3(2 * (int)(mfma_pad_n(g.N) / 32)), dim3(SK_W * 64), 0, s, a);
+}
+
+void launch_resid_few(hipStream_t s, const GemmArgs &g, bool ordered, const void *gain, void *xg, float *ssq)
+{
+    MfmaArgs a{};
+    a.X = (const bf16_t *)g.X; a.Wp = (const bf16_t *)g.W; a.Yf = g.Yf; a.pR = g.pR; a.max_rows = g.max_rows; a.N = a.n_out = g.N; a.K = g.K;
+    a.gain = (const bf16_t *)gain; a.xg = (bf16_t *)xg; a.ssq = ssq;
+    if (ordered) hipLaunchKernelGGL(resid_few_k<true>, dim3(g.N / 16), dim3(FEW_W * 64), 0, s, a);
+    else hipLaunchKernelGGL(resid_few_k<false>, dim3(g.N / 16), dim3(FEW_W * 64), 0, s, a);
+}
+
+// Down of that chain by whole sums where its workgroups of 16 features are nearly one round of the units: h = 3584, F = 18944, 8 rows, 224 workgroups, a step of 8 layers 1168 us
+// with k splits and an RMSNorm, 1136 without.  Fewer leave units without work, which costs the launch what the norm's saves (h = 1536, 96 workgroups, 28 layers:
+// 8 rows 1509 / 1502, 16 rows 1595 / 1614; h = 2048, 128, 18 layers: 1222 / 1214, 1278 / 1302); more are an uneven second one (h = 5120, 320, 8 layers: 1963 / 2055).
+bool few_down_whole(int h) { return h / 16 > 192 && h / 16 <= 256; }
+
+int launch_down_split(hipStream_t s, const GemmArgs &g, float *slabs, size_t slab_room_floats)
+{
+    MfmaArgs a{};
+    a.X = (const bf16_t *)g.X; a.Wp = (const bf16_t *)g.W; a.pR = g.pR; a.max_rows = g.max_rows; a.N = a.n_out = g.N; a.K = g.K;
+    a.splits = skinny_splits(g.max_rows, g.N, g.K, slab_room_floats);
+    a.slab = (size_t)g.max_rows * g.N;
+    a.Yf = a.splits > 1 ? slabs : g.Yf;
+    hipLaunchKernelGGL(resid_skinny_k<true>, dim3(g.N / 32 * a.splits), dim3(SK_W * 64), 0, s, a);
+    return a.splits;
 }
 
 void launch_lmhead_mfma(hipStream_t s, const void *xhat, const void *w_packed, const int32_t *p_rows, int max_rows, int min_rows, int V, int h, float scale,

@@ -41,7 +41,18 @@ bool launch_attn_mfma(hipStream_t s, const sdlm_model_cfg *m, int max_seq_len, i
 // followed by the RoPE + K/V placement kernel, up to the order in which the k partial sums are added).
 bool qkv_rope_skinny_applies(const sdlm_model_cfg *m, int max_rows, int min_rows);   // min_rows: rows that are certainly there
 void launch_qkv_rope_skinny(hipStream_t s, const sdlm_model_cfg *m, const void *X, const void *w_packed, const void *bias, const int32_t *p_rows,
-                            int max_rows, int min_rows, void *q_out, void *pool_layer, const KvGeom &kg, const RowMeta &rm, const SeqState &st, const float2 *rope);
+                            int max_rows, int min_rows, void *q_out, void *pool_layer, const KvGeom &kg, const RowMeta &rm, const SeqState &st, const float2 *rope,
+                            const float *ssq = nullptr, float eps = 0.f);
+// Steps of at most 16 rows: norms inside the products.  The rows' operand `xg` (16 x h bf16: x times the gains of the coming norm, in the matrix instruction's order)
+// and their sums of squares `ssq` ([16][h / 16] floats) are left by the embedding and by O and down, and read by the fused QKV launch (which then gets ssq) and by
+// gate/up; gate/up leaves its result in that order too, which down reads (`ordered`).  gain: null where no layer follows.
+bool mfma_few_applies(const sdlm_model_cfg *m, int max_rows);
+void launch_embed_few(hipStream_t s, float *x, const void *E, const RowMeta &rm, int max_rows, int h, int V, const void *gain, void *xg, float *ssq);
+void launch_gateup_few(hipStream_t s, const GemmArgs &g, const float *ssq, float eps);
+void launch_resid_few(hipStream_t s, const GemmArgs &g, bool ordered, const void *gain, void *xg, float *ssq);
+// Down of such a step: by launch_resid_few, or split along k with its sums left to an RMSNorm (returns the splits, as launch_gemm_mfma; 1: complete).
+bool few_down_whole(int h);
+int launch_down_split(hipStream_t s, const GemmArgs &g, float *slabs, size_t slab_room_floats);
 void launch_lmhead_mfma(hipStream_t s, const void *xhat, const void *w_packed, const int32_t *p_rows, int max_rows, int min_rows, int V, int h,
                         float scale, int conf_fn, float *logits_out, void *scratch, int32_t *ids, float *conf);
 

@@ -281,21 +281,26 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
     c->pend_slabs = 0;   // a fresh residual stream: nothing pending from an earlier pass
     int max_len = c->r.max_seq_len;   // captured launches are replayed while the sequences grow
     if (!c->capturing) max_len = *std::max_element(c->n_ub.begin(), c->n_ub.begin() + c->batch);
-    if (!embedded) { Phase p(c, SDLM_PH_ROWS); launch_embed(s, dt, c->x, c->embed, c->rm, rows, h, m.vocab); }
+    // matrix-core path, at most 16 rows: norms inside the products
+    const bool few16 = !cache_only && c->L.mfma && c->taps.empty() && mfma_few_applies(&m, rows);
+    const bool ordered = few16 && few_down_whole(h);   // also across the layers
+    float *ssq = few16 ? c->slabs : nullptr;   // free where it is needed: slabs are written by down and read by the next norm
+    if (ordered) { Phase p(c, SDLM_PH_ROWS); launch_embed_few(s, c->x, c->embed, c->rm, rows, h, m.vocab, c->lw[0].attn_norm, c->xn, ssq); }
+    else if (!embedded) { Phase p(c, SDLM_PH_ROWS); launch_embed(s, dt, c->x, c->embed, c->rm, rows, h, m.vocab); }
     // generic path: norms, rotation and K/V placement inside the products (not in a prefill, whose cache contents do not depend on the other prompts)
     const bool few = !cache_only && few_rows(c, rows);
     for (int l = 0; l < m.n_layers; ++l) {
         const LayerW &w = c->lw[l];
         char *pool_l = c->pool + (size_t)l * c->kg.layer_stride * e;
         run_taps(c, l, 0, c->x, (size_t)rows * h * 4);
-        if (!few) { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xn, c->x, w.attn_norm, h, m.rms_eps, nullptr, c->rm.counts, rows, rows_sure, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
+        if (!few && !ordered) { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xn, c->x, w.attn_norm, h, m.rms_eps, nullptr, c->rm.counts, rows, rows_sure, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
         if (few) {
             Phase p(c, SDLM_PH_QKV);
             GemmArgs a{c->x, w.wqkv, nullptr, m.has_qkv_bias ? w.bqkv : nullptr, nullptr, nullptr, c->rm.counts, rows, nqkv, h, 1.f, rows_sure};
             launch_qkv_few(s, dt, a, w.attn_norm, m.rms_eps, c->q, pool_l, c->kg, c->rm, c->st, c->rope, m.n_q_heads);
         } else if (c->L.mfma && qkv_rope_skinny_applies(&m, rows, rows_sure)) {
             Phase p(c, SDLM_PH_QKV);   // projection, rotation and K/V placement in one launch
-            launch_qkv_rope_skinny(s, &m, c->xn, w.wqkv, m.has_qkv_bias ? w.bqkv : nullptr, c->rm.counts, rows, rows_sure, c->q, pool_l, c->kg, c->rm, c->st, c->rope);
+            launch_qkv_rope_skinny(s, &m, c->xn, w.wqkv, m.has_qkv_bias ? w.bqkv : nullptr, c->rm.counts, rows, rows_sure, c->q, pool_l, c->kg, c->rm, c->st, c->rope, ordered ? ssq : nullptr, m.rms_eps);
         } else {
             int qkv_slabs = 1;
             {
@@ -324,7 +329,8 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
         {
             Phase p(c, SDLM_PH_OPROJ);
             GemmArgs a{c->att, w.wo, nullptr, nullptr, c->x, nullptr, c->rm.counts, rows, h, nq, 1.f, rows_sure};
-            if (c->L.mfma) {
+            if (few16) launch_resid_few(s, a, false, w.ffn_norm, c->xn, ssq);
+            else if (c->L.mfma) {
                 // the split-k partial sums of a residual projection are added by the next RMSNorm (unless a tap wants x now)
                 int sp = launch_gemm_mfma(s, EPI_RESID, a, c->slabs, c->L.slab_floats, c->taps.empty());
                 if (sp > 1 && c->taps.empty()) { c->pend_slabs = sp; c->pend_stride = (size_t)rows * h; }
@@ -332,18 +338,24 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
             else launch_gemm_generic(s, dt, EPI_RESID, a);
         }
         run_taps(c, l, 6, c->x, (size_t)rows * h * 4);
-        if (!few) { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xn, c->x, w.ffn_norm, h, m.rms_eps, nullptr, c->rm.counts, rows, rows_sure, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
+        if (!few && !few16) { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xn, c->x, w.ffn_norm, h, m.rms_eps, nullptr, c->rm.counts, rows, rows_sure, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
         {
             Phase p(c, SDLM_PH_GATEUP);
             GemmArgs a{few ? (const void *)c->x : c->xn, w.w_gate, w.w_up, nullptr, nullptr, c->act, c->rm.counts, rows, F, h, 1.f, rows_sure};
             if (few) launch_gemm_few(s, dt, EPI_SWIGLU, a, w.ffn_norm, m.rms_eps, nullptr);
+            else if (few16) launch_gateup_few(s, a, ssq, m.rms_eps);
             else if (c->L.mfma) launch_gemm_mfma(s, EPI_SWIGLU, a, c->slabs, c->L.slab_floats, false); else launch_gemm_generic(s, dt, EPI_SWIGLU, a);
         }
         run_taps(c, l, 2, c->act, (size_t)rows * F * e);
         {
             Phase p(c, SDLM_PH_DOWN);
             GemmArgs a{c->act, w.w_down, nullptr, nullptr, c->x, nullptr, c->rm.counts, rows, h, F, 1.f, rows_sure};
-            if (c->L.mfma) {
+            if (few16 && ordered) launch_resid_few(s, a, true, l + 1 < m.n_layers ? c->lw[l + 1].attn_norm : nullptr, c->xn, ssq);
+            else if (few16) {
+                const int sp = launch_down_split(s, a, c->slabs, c->L.slab_floats);
+                if (sp > 1) { c->pend_slabs = sp; c->pend_stride = (size_t)rows * h; }
+            }
+            else if (c->L.mfma) {
                 // the split-k partial sums of a residual projection are added by the next RMSNorm (unless a tap wants x now)
                 int sp = launch_gemm_mfma(s, EPI_RESID, a, c->slabs, c->L.slab_floats, c->taps.empty());
                 if (sp > 1 && c->taps.empty()) { c->pend_slabs = sp; c->pend_stride = (size_t)rows * h; }

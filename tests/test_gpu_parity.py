@@ -714,6 +714,26 @@ def test_bf16_qkv_row_blocks(B, D, hidden, heads, kv):
     ctx.close()
 
 
+@pytest.mark.parametrize("B,D,hidden,ffn,heads", [(1, 1, 64, 64, 1), (1, 8, 192, 320, 3), (8, 1, 1024, 2112, 8), (2, 4, 3072, 128, 2), (2, 4, 3136, 128, 2),
+                                                   (1, 5, 4096, 64, 2), (1, 4, 4160, 448, 2), (1, 3, 8192, 64, 1), (1, 2, 8256, 64, 1)])
+def test_bf16_norms_inside_the_products(B, D, hidden, ffn, heads):
+    """Steps of at most 16 rows: O leaves the sums of squares and the operand of gate/up, down does so for QKV (above h = 3072 up to 4096, with the embeddings first) or
+    leaves k splits to an RMSNorm; fewer k steps than wavefronts, one and 16 rows, the widest stream (8192) and one beyond it.  Three layers: first, middle, last."""
+    m = mfma_cfg(n_layers=3, n_q_heads=heads, n_kv_heads=1, hidden=hidden, ffn=ffn, vocab=300, has_qkv_bias=True)
+    om, g_dev, layers_dev = both_models(m, seed=160 + B, std=1.0 / hidden ** 0.5)
+    prompts = [syn.uniform_int(6, f"np{i}", 3 + 4 * (i % 5), 0, m.vocab - 1).numpy() for i in range(B)]
+    steps = 3
+    ids, cnt = syn.make_overrides(27, steps, B, D, m.vocab)
+    cnt = cnt.clone()
+    cnt[0] = D                                       # then a step of B * 2D rows
+    max_len = max(len(p) for p in prompts) + steps * D + D
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=B, max_seq_len=max_len, D=D, tau=0.5)
+    assert ctx.kernel_info == "mfma-bf16"
+    st, _ = lockstep(ctx, om, prompts, D, 0.5, steps, logit_tol=2e-2, conf_tol=1e-3, overrides=(ids, cnt), bf16=True, max_len=max_len)
+    print("norms inside", (B, D, hidden, ffn, heads), st)
+    ctx.close()
+
+
 @pytest.mark.parametrize("B,D,hidden,ffn,heads", [(17, 1, 64, 64, 2), (32, 1, 192, 16448, 6), (4, 8, 320, 448, 28), (30, 2, 2112, 192, 3), (50, 4, 128, 8256, 2),
                                                    (9, 4, 128, 640, 2), (4, 3, 2112, 8256, 2)])
 def test_bf16_projections_on_the_128_row_tiles(B, D, hidden, ffn, heads):
