@@ -76,6 +76,12 @@ __host__ __device__ inline int attn_group_hint(int max_lim, int rows, int chunk_
     return (chunks < 1 ? 1 : chunks > 255 ? 255 : chunks) | rows << 8;
 }
 
+// Element (row, k) of an operand kept in the order of v_mfma_f32_16x16x32_bf16: by 16 rows, [k / 32][k / 8 % 4][row][8], so that a k step of 16 rows is one run of 1 KB.
+__host__ __device__ inline size_t ordered_off(int row, int k, int K)
+{
+    return (size_t)(row >> 4) * 16 * K + (size_t)(k >> 5) * 512 + (((k >> 3) & 3) * 16 + (row & 15)) * 8 + (k & 7);
+}
+
 // Packed description of the rows of one forward pass (device arrays).
 struct RowMeta {
     int32_t *tok, *pos, *seq, *kind, *lim;  // [max_rows]; kind: -1 = K/V go to the cache slot of pos, else the slot in the
@@ -146,7 +152,7 @@ void launch_verify_accept(hipStream_t s, const SeqState &st, const int32_t *ids_
                           int32_t *ids_out, int32_t *count_out);
 void launch_embed(hipStream_t s, int dtype, float *x, const void *E, const RowMeta &rm, int max_rows, int h, int V);
 void launch_rmsnorm(hipStream_t s, int dtype, void *out, float *x, const void *g, int h, float eps, const int32_t *row_index,
-                    const int32_t *p_count, int max_rows, int min_rows, const float *slabs, int n_slabs, size_t slab_stride);   // min_rows: rows that certainly exist
+                    const int32_t *p_count, int max_rows, int min_rows, const float *slabs, int n_slabs, size_t slab_stride, bool ordered = false);   // min_rows: rows that certainly exist; ordered (bf16): see ordered_off
 void launch_gemm_generic(hipStream_t s, int dtype, int epi, const GemmArgs &a);
 // Products of few rows with the RMSNorm in front of them (gate/up, logits: X is the fp32 residual stream) or without (residual), and the QKV
 // projection with norm, rotation and K/V placement.  row_index: rows of X, null: as they are.

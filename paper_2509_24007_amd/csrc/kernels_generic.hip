@@ -262,7 +262,7 @@ __device__ inline float block_sum(float v, float *red)
 // one row's reduction behind another's loads (see rmsnorm_t).
 template <typename T, int TH, int NV>
 __global__ __launch_bounds__(TH) void rmsnorm_k(T *out, float *x, const T *g, int h, float eps, const int32_t *row_index,
-                                                const int32_t *p_count, int sure, const float *slabs, int n_slabs, size_t slab_stride)
+                                                const int32_t *p_count, int sure, const float *slabs, int n_slabs, size_t slab_stride, int ordered)
 {
     __shared__ float red[TH / 64];
     const int j = blockIdx.x;
@@ -324,7 +324,7 @@ __global__ __launch_bounds__(TH) void rmsnorm_k(T *out, float *x, const T *g, in
         if (k >= h) continue;
         const float o0 = v[i].x * inv * gv[i].x, o1 = v[i].y * inv * gv[i].y;
         const float o2 = v[i].z * inv * gv[i].z, o3 = v[i].w * inv * gv[i].w;
-        T *dst = out + (size_t)j * h + k;
+        T *dst = out + (ordered ? ordered_off(j, k, h) : (size_t)j * h + k);
         if constexpr (sizeof(T) == 2) {
             *(uint2 *)dst = make_uint2((uint32_t)f_to_bf16(o0) | ((uint32_t)f_to_bf16(o1) << 16),
                                        (uint32_t)f_to_bf16(o2) | ((uint32_t)f_to_bf16(o3) << 16));
@@ -336,9 +336,9 @@ __global__ __launch_bounds__(TH) void rmsnorm_k(T *out, float *x, const T *g, in
 
 template <typename T>
 static void rmsnorm_t(hipStream_t s, void *out, float *x, const void *g, int h, float eps, const int32_t *row_index,
-                      const int32_t *p_count, int max_rows, int min_rows, const float *slabs, int n_slabs, size_t slab_stride)
+                      const int32_t *p_count, int max_rows, int min_rows, const float *slabs, int n_slabs, size_t slab_stride, int ordered)
 {
-#define SDLM_RMS(TH, NV) hipLaunchKernelGGL((rmsnorm_k<T, TH, NV>), dim3(max_rows), dim3(TH), 0, s, (T *)out, x, (const T *)g, h, eps, row_index, p_count, min_rows, slabs, n_slabs, slab_stride)
+#define SDLM_RMS(TH, NV) hipLaunchKernelGGL((rmsnorm_k<T, TH, NV>), dim3(max_rows), dim3(TH), 0, s, (T *)out, x, (const T *)g, h, eps, row_index, p_count, min_rows, slabs, n_slabs, slab_stride, ordered)
     // Wide workgroups while those of all rows are on the chip at once (four a compute unit of 512 threads, two of 1024, one of 1024 with more
     // than 4096 values a row, for their registers), counted in certain rows: a step has few more, as a rule.  us, 256 threads / wide:
     //   h = 2048   1024 rows without slabs 4.4 / 4.4, 2048 rows 6.6 / 6.7
@@ -354,10 +354,10 @@ static void rmsnorm_t(hipStream_t s, void *out, float *x, const void *g, int h, 
 }
 
 void launch_rmsnorm(hipStream_t s, int dtype, void *out, float *x, const void *g, int h, float eps, const int32_t *row_index,
-                    const int32_t *p_count, int max_rows, int min_rows, const float *slabs, int n_slabs, size_t slab_stride)
+                    const int32_t *p_count, int max_rows, int min_rows, const float *slabs, int n_slabs, size_t slab_stride, bool ordered)
 {
-    if (dtype == 0) rmsnorm_t<float>(s, out, x, g, h, eps, row_index, p_count, max_rows, min_rows, slabs, n_slabs, slab_stride);
-    else rmsnorm_t<bf16_t>(s, out, x, g, h, eps, row_index, p_count, max_rows, min_rows, slabs, n_slabs, slab_stride);
+    if (dtype == 0) rmsnorm_t<float>(s, out, x, g, h, eps, row_index, p_count, max_rows, min_rows, slabs, n_slabs, slab_stride, 0);
+    else rmsnorm_t<bf16_t>(s, out, x, g, h, eps, row_index, p_count, max_rows, min_rows, slabs, n_slabs, slab_stride, ordered);
 }
 
 // ------------------------------------------------------------------------------------------------ GEMM (FMA)

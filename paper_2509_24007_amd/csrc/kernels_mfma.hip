@@ -647,7 +647,6 @@ template <int NB, int NT, bool XP, int U, class F>
 __device__ inline int skinny_dot(const bf16_t *wa, const bf16_t *wb, const bf16_t *X, const int32_t *pR, int max_rows, int m0, int K, int k_begin, int k_end,
                                  int lane, f32x4 (&aa)[NB], f32x4 (&ab)[NB], F with_rows)
 {
-    static_assert(!XP || NB == 1, "the ordered rows are one block of 16");
     const int k_last = max(k_end, 1) - 1;   // a wavefront without any k step still requests within the matrix
     // lane -> k half of the step's 32 (lane / 32), 8 of 16 (lane / 16 % 2), feature (lane % 16)
     const uint32_t wl = (lane >> 5) * 512 + ((lane & 15) + ((lane >> 4) & 1) * 32) * 8;
@@ -687,7 +686,7 @@ __device__ inline int skinny_dot(const bf16_t *wa, const bf16_t *wb, const bf16_
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         const int r = min(m0 + nb * 16 + (lane & 15), R - 1);
-        xp[nb] = XP ? X + ((lane >> 4) * 16 + r) * 8 : X + (size_t)r * K + (lane >> 4) * 8;
+        xp[nb] = X + (XP ? ordered_off(r, (lane >> 4) * 8, K) : (size_t)r * K + (lane >> 4) * 8);
     }
     load_x(x0, k_begin);
     if (k_begin + U < k_end) load_x(x1, k_begin + U);
@@ -723,8 +722,6 @@ __device__ inline bool skinny_sum(f32x4 (&part)[SK_W][2][NB][64], const f32x4 (&
 // The operands are kept in the order of the matrix instruction, [k / 32][k / 8 % 4][row][8], so that a load is one run of up to 1 KB and not 64 pieces
 // of 16 bytes; gate/up leaves its result in that order too.  Whole steps of one sequence of 512 tokens, D = 4, us: h = 1536, F = 8960, 28 layers 1613 -> 1513, h = 2048, F = 11008, 18 layers
 // 1279 -> 1215, h = 3584, F = 18944, 8 layers 1209 -> 1138 (16 rows 1259 -> 1186), h = 5120, F = 27648, 8 layers 1976 -> 1965.
-__device__ inline size_t few_off(int row, int k) { return (size_t)(k >> 5) * 512 + (((k >> 3) & 3) * 16 + row) * 8 + (k & 7); }
-
 constexpr int FEW_SSQ = 8;   // requests of 16 bytes a lane: h up to 8192
 
 struct FewRms {
@@ -785,7 +782,7 @@ __global__ __launch_bounds__(SK_W * 64) void swiglu_skinny16_k(MfmaArgs a)
     float o[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = silu_f(gs[e]) * us[e];
-    *(uint2 *)(a.Yt + (NORM ? few_off(row, n) : (size_t)row * a.n_out + n)) = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
+    *(uint2 *)(a.Yt + (NORM ? ordered_off(row, n, a.N) : (size_t)row * a.n_out + n)) = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
 }
 
 // O of that chain, and down where few_down says so: all of k by the eight wavefronts of a workgroup of 16 features.  XP: rows in operand order (down).
@@ -825,7 +822,7 @@ __global__ __launch_bounds__(FEW_W * 64) void resid_few_k(MfmaArgs a)
     if (row >= R) return;
     if (lane < 16) a.ssq[(size_t)row * (a.n_out >> 4) + t16] = ss;
     const float g0 = bf16_to_f((bf16_t)(g.x & 0xffff)), g1 = bf16_to_f((bf16_t)(g.x >> 16)), g2 = bf16_to_f((bf16_t)(g.y & 0xffff)), g3 = bf16_to_f((bf16_t)(g.y >> 16));
-    *(uint2 *)(a.xg + few_off(row, n)) = make_uint2(pack_bf16(x[0] * g0, x[1] * g1), pack_bf16(x[2] * g2, x[3] * g3));
+    *(uint2 *)(a.xg + ordered_off(row, n, a.n_out)) = make_uint2(pack_bf16(x[0] * g0, x[1] * g1), pack_bf16(x[2] * g2, x[3] * g3));
 }
 
 // The embeddings of that chain's rows, in the same three forms.  Four features a thread.
@@ -836,7 +833,7 @@ __global__ __launch_bounds__(256) void embed_few_k(float *x, const bf16_t *E, co
     const uint2 e = *(const uint2 *)(E + (size_t)min(max(tok[r], 0), V - 1) * h + n), g = *(const uint2 *)(gain + n);
     const float4 v = make_float4(bf16_to_f((bf16_t)(e.x & 0xffff)), bf16_to_f((bf16_t)(e.x >> 16)), bf16_to_f((bf16_t)(e.y & 0xffff)), bf16_to_f((bf16_t)(e.y >> 16)));
     *(float4 *)(x + (size_t)r * h + n) = v;
-    *(uint2 *)(xg + few_off(r, n)) = make_uint2(pack_bf16(v.x * bf16_to_f((bf16_t)(g.x & 0xffff)), v.y * bf16_to_f((bf16_t)(g.x >> 16))),
+    *(uint2 *)(xg + ordered_off(r, n, h)) = make_uint2(pack_bf16(v.x * bf16_to_f((bf16_t)(g.x & 0xffff)), v.y * bf16_to_f((bf16_t)(g.x >> 16))),
                                                 pack_bf16(v.z * bf16_to_f((bf16_t)(g.y & 0xffff)), v.w * bf16_to_f((bf16_t)(g.y >> 16))));
     float ss = (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
     ss += __shfl_xor(ss, 1);
@@ -906,7 +903,7 @@ __device__ inline void qkv_rope_rows(const QkvSkinnyArgs &a, f32x4 (&part)[SK_W]
     FewRms rms;
     if constexpr (NORM) rms.request(a.ssq, a.K >> 4, wave, lane);
     // what the epilogue needs beside the sums is requested with the operands: rotation factors, bias, the page of a cached position
-    const int R = skinny_dot<NB, 2, NORM, sk_u(NB)>(wa, wa + (size_t)2 * KS * 512, a.X, a.pR, a.max_rows, m0, a.K, wave * per, min(K32, wave * per + per), lane, aa, ab, [&](int rows) {
+    const int R = skinny_dot<NB, 2, true, sk_u(NB)>(wa, wa + (size_t)2 * KS * 512, a.X, a.pR, a.max_rows, m0, a.K, wave * per, min(K32, wave * per + per), lane, aa, ab, [&](int rows) {
         if constexpr (NORM) rms.add(rs, wave, lane);
         if (wave >= NB) return;
         const int rr = min(row, rows - 1), pos = a.rm.pos[rr], kind = a.rm.kind[rr], b = a.rm.seq[rr], stg = a.rm.stg[rr];

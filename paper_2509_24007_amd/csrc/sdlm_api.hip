@@ -293,12 +293,13 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
         const LayerW &w = c->lw[l];
         char *pool_l = c->pool + (size_t)l * c->kg.layer_stride * e;
         run_taps(c, l, 0, c->x, (size_t)rows * h * 4);
-        if (!few && !ordered) { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xn, c->x, w.attn_norm, h, m.rms_eps, nullptr, c->rm.counts, rows, rows_sure, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
+        const bool qkv_fused = c->L.mfma && qkv_rope_skinny_applies(&m, rows, rows_sure);
+        if (!few && !ordered) { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xn, c->x, w.attn_norm, h, m.rms_eps, nullptr, c->rm.counts, rows, rows_sure, c->slabs, c->pend_slabs, c->pend_stride, qkv_fused); c->pend_slabs = 0; }
         if (few) {
             Phase p(c, SDLM_PH_QKV);
             GemmArgs a{c->x, w.wqkv, nullptr, m.has_qkv_bias ? w.bqkv : nullptr, nullptr, nullptr, c->rm.counts, rows, nqkv, h, 1.f, rows_sure};
             launch_qkv_few(s, dt, a, w.attn_norm, m.rms_eps, c->q, pool_l, c->kg, c->rm, c->st, c->rope, m.n_q_heads);
-        } else if (c->L.mfma && qkv_rope_skinny_applies(&m, rows, rows_sure)) {
+        } else if (qkv_fused) {
             Phase p(c, SDLM_PH_QKV);   // projection, rotation and K/V placement in one launch
             launch_qkv_rope_skinny(s, &m, c->xn, w.wqkv, m.has_qkv_bias ? w.bqkv : nullptr, c->rm.counts, rows, rows_sure, c->q, pool_l, c->kg, c->rm, c->st, c->rope, ordered ? ssq : nullptr, m.rms_eps);
         } else {
