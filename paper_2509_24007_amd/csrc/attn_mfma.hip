@@ -24,6 +24,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 constexpr int NQ = 4;     // 16-query tiles per work item
 constexpr int QMAX = NQ * 16;
 constexpr int HD = 128;
+constexpr int TEAM_KEYS = 256;        // at most 64 tiles
 constexpr float RESCALE_GAP = 8.0f;   // log2 units
 
 struct AttnArgs {
@@ -43,25 +44,32 @@ union Op8 { bf16x8 v; uint4 u; uint2 h[2]; uint32_t w[4]; };
 
 // TWO_STG: row groups may read a second staging tile (verification passes of block sizes above 4); decode steps and
 // prefill passes use the variant without it, which keeps the kernel at four workgroups per compute unit without spills.
-template <bool TWO_STG>
-__global__ __launch_bounds__(256, 4) void attn_mfma_k(AttnArgs a)
+//
+// TEAMS = 4: the chunks of a work item are four teams of four wavefronts of one workgroup, whose results meet in LDS: no merge launch behind it.
+// (See the rule in launch_attn_mfma, which admits at most TEAM_KEYS keys.)  The page table rides in a register, one entry a lane.
+template <bool TWO_STG, int TEAMS = 1>
+__global__ __launch_bounds__(256 * TEAMS, 4) void attn_mfma_k(AttnArgs a)
 {
-    const int g = blockIdx.x, hk = blockIdx.y, chunk = blockIdx.z;
+    const int g = blockIdx.x, hk = blockIdx.y;
+    const int chunk = TEAMS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : blockIdx.z;
     // The start of a work item is a chain of dependent lookups (group count -> group -> row limits -> page table ->
     // K/V).  The group's entries are in bounds for every group of the grid, and the page-table entries of the first
     // two tile pairs depend on the sequence and the chunk alone, so each is requested one step early: three memory
     // round trips before the first K/V request instead of five.
     const int n_groups = a.rm.counts[1];
-    const int cp = max(a.rm.counts[3], a.chunk_pages);   // tiles per KV chunk: chosen on the device from the actual lengths, never below the host's floor
+    int cp = TEAMS > 1 ? 0 : max(a.rm.counts[3], a.chunk_pages);   // tiles per KV chunk: chosen on the device from the actual lengths, never below the host's floor
     const int row0 = a.rm.grp_row0[g], nrows = a.rm.grp_n[g], b = a.rm.grp_seq[g];
     if (g >= n_groups) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = TEAMS > 1 ? threadIdx.x & 255 : threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ln = lane & 15, lg = lane >> 4;
     const int G = a.G, QR = nrows * G;
     const int32_t *ptab = a.st.page_table + (size_t)b * a.kg.pages_per_seq;
-    int pg_first[4];
+    int pg_first[4], pg_lane = 0;
+    if constexpr (TEAMS > 1) pg_lane = ptab[min(lane, a.kg.pages_per_seq - 1)];
+    else {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) pg_first[u] = ptab[min(chunk * cp + u, a.kg.pages_per_seq - 1)];
+        for (int u = 0; u < 4; ++u) pg_first[u] = ptab[min(chunk * cp + u, a.kg.pages_per_seq - 1)];
+    }
 
     int lim_l = lane < nrows ? a.rm.lim[row0 + lane] : 0;
     int blk_l = lane < nrows ? a.rm.smask[row0 + lane] : 0;   // OR over the group's rows: which staging tiles are seen at all
@@ -73,15 +81,18 @@ __global__ __launch_bounds__(256, 4) void attn_mfma_k(AttnArgs a)
     }
     const int max_lim = lim_l, min_lim = min_l, any_blk = blk_l;
     const int n_pages = (max_lim + PAGE - 1) / PAGE;
-    const int n_chunks = max(1, (n_pages + cp - 1) / cp);
-    if (chunk >= n_chunks) return;
+    if constexpr (TEAMS > 1) cp = (n_pages + 2 * TEAMS - 1) / (2 * TEAMS) * 2;
+    const int n_chunks = TEAMS > 1 ? 1 : max(1, (n_pages + cp - 1) / cp);
+    if (TEAMS == 1 && chunk >= n_chunks) return;
     const int c0 = chunk * cp, c1 = min(n_pages, c0 + cp);
-    const int n_cache = c1 - c0;
+    const int n_cache = TEAMS > 1 ? max(0, c1 - c0) : c1 - c0;
     // Staging tiles follow the cache tiles of chunk 0: first the group's second tile (if a row sees it: upper half of
     // the slot masks), then its own tile (lower half).
     const bool has1 = (any_blk & 0xffff) != 0, has2 = TWO_STG && ((uint32_t)any_blk >> 16) != 0;
-    const int nv = n_cache + (chunk == 0 ? (int)has1 + (int)has2 : 0);   // virtual tiles of this chunk; the last ones may be staging
+    const int nv = n_cache + (chunk == TEAMS - 1 ? (int)has1 + (int)has2 : 0);   // virtual tiles of this chunk; the last ones may be staging
     const int n_pairs = (nv + 1) / 2;
+    // the trips of all teams, whose barriers are common; the first team has the most cache tiles, the last one the staging tiles
+    const int n_trips = TEAMS > 1 ? max((min(cp, n_pages) + 1) / 2, (max(0, n_pages - (TEAMS - 1) * cp) + (int)has1 + (int)has2 + 1) / 2) : n_pairs;
 
     // This wavefront's 16 queries: B operands, lane (n = lane%16, group lg) holds q[32 kk + 8 lg .. +8] of query 16 wave + n
     const int qi = wave * 16 + ln;
@@ -108,7 +119,8 @@ __global__ __launch_bounds__(256, 4) void attn_mfma_k(AttnArgs a)
 
     // K/V of one tile pair (32 keys, 16 KB) is fetched by the whole workgroup, 64 bytes per thread, and shared
     // through LDS in the cache's own operand order; two LDS buffers, the next two pairs ride in registers meanwhile.
-    __shared__ __attribute__((aligned(16))) bf16_t kv[2][2][2 * PAGE * HD];   // [buffer][tile A/B][K block | V block]
+    __shared__ __attribute__((aligned(16))) bf16_t kv_all[TEAMS][2][2][2 * PAGE * HD];   // [team][buffer][tile A/B][K block | V block]
+    bf16_t (&kv)[2][2][2 * PAGE * HD] = kv_all[TEAMS > 1 ? chunk : 0];
     const size_t tile_elems = 2 * PAGE * HD;
     const int stg_last = max(a.rm.grp_stg[g], 0), stg_first = (TWO_STG && has2) ? max(a.rm.grp_stg2[g], 0) : stg_last;
     auto stg_of = [&](int u) { return (TWO_STG && u == n_cache) ? stg_first : stg_last; };   // staging tile behind virtual tile u >= n_cache
@@ -121,10 +133,11 @@ __global__ __launch_bounds__(256, 4) void attn_mfma_k(AttnArgs a)
         r[2] = *(const u32x4 *)(tB + tid * 8);
         r[3] = *(const u32x4 *)(tB + (256 + tid) * 8);
     };
+    auto page = [&](int u) { return TEAMS > 1 ? __builtin_amdgcn_readlane(pg_lane, c0 + u) : ptab[c0 + u]; };
     auto fetch = [&](int pp, u32x4 (&r)[4]) {
         const int uA = 2 * pp, uB = 2 * pp + 1;
-        const int pgA = uA >= n_cache ? stg_of(uA) : ptab[c0 + uA];
-        const int pgB = uB >= nv ? pgA : (uB >= n_cache ? stg_of(uB) : ptab[c0 + uB]);
+        const int pgA = uA >= n_cache ? stg_of(uA) : page(uA);
+        const int pgB = uB >= nv ? pgA : (uB >= n_cache ? stg_of(uB) : page(uB));
         fetch_pages(pgA, pgB, r);
     };
     auto fetch_first = [&](int pA, int pB, int uA, u32x4 (&r)[4]) {   // pairs 0 and 1: page ids requested at the top
@@ -205,21 +218,60 @@ __global__ __launch_bounds__(256, 4) void attn_mfma_k(AttnArgs a)
             }
         }
     };
-    fetch_first(pg_first[0], pg_first[1], 0, rB);   // both requests are out before the first is waited for
-    if (n_pairs > 1) fetch_first(pg_first[2], pg_first[3], 2, rA);
+    if constexpr (TEAMS > 1) {
+        fetch(0, rB);   // a team without any tile requests its staging tile
+        if (n_pairs > 1) fetch(1, rA);
+    } else {
+        fetch_first(pg_first[0], pg_first[1], 0, rB);   // both requests are out before the first is waited for
+        if (n_pairs > 1) fetch_first(pg_first[2], pg_first[3], 2, rA);
+    }
     stash(0, rB);
     __syncthreads();
     // iteration pp: regs hold pair pp+1, pair pp+2 is requested, pair pp is consumed from LDS
-    for (int pp = 0; pp < n_pairs; pp += 2) {
+    for (int pp = 0; pp < n_trips; pp += 2) {
         if (pp + 2 < n_pairs) fetch(pp + 2, rB);
-        compute(pp, 0);
+        if (TEAMS == 1 || pp < n_pairs) compute(pp, 0);
         if (pp + 1 < n_pairs) stash(1, rA);
         __syncthreads();
-        if (pp + 1 >= n_pairs) break;
+        if (pp + 1 >= n_trips) break;
         if (pp + 3 < n_pairs) fetch(pp + 3, rA);
-        compute(pp + 1, 1);
+        if (TEAMS == 1 || pp + 1 < n_pairs) compute(pp + 1, 1);
         if (pp + 2 < n_pairs) stash(0, rB);
         __syncthreads();
+    }
+    if constexpr (TEAMS > 1) {
+        // A team's accumulators go to its own K/V buffers (32 KB), in lane order; then each team finishes two of the eight 16-feature blocks.
+        __shared__ float2 ml[TEAMS][QMAX];
+        l_run += __shfl_xor(l_run, 16);
+        l_run += __shfl_xor(l_run, 32);
+        f32x4 *mine = (f32x4 *)&kv[0][0][0] + wave * 8 * 64 + lane;
+        if (wave_active) {
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt) mine[dt * 64] = O[dt];
+            if (lg == 0) ml[chunk][qi] = make_float2(m_run, l_run);
+        }
+        __syncthreads();
+        if (!qvalid) return;
+        float w[TEAMS], M = -INFINITY, L = 0.f;
+#pragma unroll
+        for (int t = 0; t < TEAMS; ++t) M = fmaxf(M, ml[t][qi].x);
+#pragma unroll
+        for (int t = 0; t < TEAMS; ++t) {
+            const float2 v = ml[t][qi];
+            w[t] = v.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((v.x - M) * a.c);
+            L += v.y * w[t];
+        }
+        const float inv = 1.0f / L;
+        bf16_t *op = a.out + ((size_t)qrow * a.Hq + hk * G + hg) * HD + lg * 4;
+#pragma unroll
+        for (int i = 0; i < 8 / TEAMS; ++i) {
+            const int dt = chunk * (8 / TEAMS) + i;
+            f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < TEAMS; ++t) o += ((const f32x4 *)&kv_all[t][0][0][0])[(wave * 8 + dt) * 64 + lane] * (w[t] * inv);
+            *(uint2 *)(op + dt * 16) = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
+        }
+        return;
     }
     if (!qvalid) return;
     l_run += __shfl_xor(l_run, 16);
@@ -441,7 +493,15 @@ bool launch_attn_mfma(hipStream_t s, const sdlm_model_cfg *m, int max_seq_len, i
     a.part_o = (float *)scratch;
     a.part_ml = (float2 *)((char *)scratch + items * QMAX * HD * 4);
     a.c = 1.4426950408889634f / sqrtf((float)HD);
+    // Short contexts of few row groups, at most one workgroup a unit: the chunks are teams of one workgroup, and the launch of the merge (5 us) is saved.  A team's trips are then
+    // four times fewer than the keys', not as few as there are chunks: us a step, separate merge / teams, 1.5B shape, one sequence of 100 keys 1491 / 1403, 200 1478 / 1431, 300 1518 / 1491, 512
+    // 1522 / 1555, 1000 1532 / 1731;  3B shape, 16 sequences, D = 8, 18 layers, 200 keys 1944 / 1887, 500 1966 / 1962;  four sequences of 500 1525 / 1571.
+    const bool teams = !two_staging && a.max_chunks > 1 && min(max_len, max_seq_len) <= TEAM_KEYS && max_groups * kg.n_kv_heads <= 256;
     if (part == 0) {
+        if (teams) {
+            hipLaunchKernelGGL((attn_mfma_k<false, 4>), dim3(max_groups, kg.n_kv_heads), dim3(1024), 0, s, a);
+            return false;
+        }
         if (two_staging) hipLaunchKernelGGL(attn_mfma_k<true>, dim3(max_groups, kg.n_kv_heads, a.max_chunks), dim3(256), 0, s, a);
         else hipLaunchKernelGGL(attn_mfma_k<false>, dim3(max_groups, kg.n_kv_heads, a.max_chunks), dim3(256), 0, s, a);
     }

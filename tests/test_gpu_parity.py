@@ -654,6 +654,23 @@ def test_bf16_gate_up_of_at_most_32_rows(B, D, hidden, ffn):
     ctx.close()
 
 
+@pytest.mark.parametrize("lens,D,heads,kv,paged", [([1, 16, 17, 240], 4, 4, 2, False), ([31, 112, 129, 230, 2], 3, 6, 1, True), ([97], 16, 2, 2, True), ([244], 4, 12, 2, False)])
+def test_bf16_attention_of_short_contexts(lens, D, heads, kv, paged):
+    """Contexts of at most 256 keys: four teams of one workgroup stream the cache and merge in LDS.  Teams without a tile, odd tile counts, staging tile alone in
+    its pair and beside a cache tile, several row groups a sequence; the last of the steps pass 256 keys, where the chunks are workgroups again."""
+    m = mfma_cfg(n_layers=2, n_q_heads=heads, n_kv_heads=kv, hidden=256, ffn=320, vocab=300, has_qkv_bias=True)
+    om, g_dev, layers_dev = both_models(m, seed=181, std=0.05)
+    prompts = [syn.uniform_int(7, f"sc{i}", n, 0, m.vocab - 1).numpy() for i, n in enumerate(lens)]
+    steps, B = 5, len(lens)
+    ids, cnt = syn.make_overrides(28, steps, B, D, m.vocab)
+    max_len = max(lens) + (steps + 1) * D
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=B, max_seq_len=max(max_len, 300), D=D, tau=0.5, paged=paged, n_pages=sum((n + (steps + 1) * D + 15) // 16 for n in lens) if paged else 0)
+    assert ctx.kernel_info == "mfma-bf16"
+    st, _ = lockstep(ctx, om, prompts, D, 0.5, steps, logit_tol=2e-2, conf_tol=1e-3, overrides=(ids, cnt), bf16=True, max_len=max(max_len, 300), verify_rule=0 if 2 <= D <= 4 else None)
+    print("short contexts", (lens, D, heads, kv, paged), st)
+    ctx.close()
+
+
 @pytest.mark.parametrize("B,D,hidden,ffn,heads", [(1, 1, 64, 64, 1), (1, 8, 192, 1024, 4), (2, 4, 576, 4160, 6), (1, 9, 1088, 8256, 10), (4, 2, 128, 9216, 8)])
 def test_bf16_products_of_few_rows(B, D, hidden, ffn, heads):
     """The weight streams of steps of at most 16 rows (and QKV up to 32): k extents that leave wavefronts without a k step, that end
