@@ -625,8 +625,9 @@ __global__ __launch_bounds__(SK_W * 64) void swiglu_skinny32_k(MfmaArgs a)
 // once.  They share one inner loop: a workgroup owns two 16-feature tiles, its four wavefronts each take a quarter of its k range,
 // and the quarters are added in wavefront order through LDS.  Both operands come straight from global memory in the order of
 // v_mfma_f32_16x16x32_bf16: a 16-feature half of a packed 32 x 16 tile pair is four runs of 256 bytes per load, the rows (shared by
-// every workgroup, so served by L2) are 64-byte pieces; rows beyond the live ones repeat the last row and their results are
-// dropped.  NB = 1 serves at most 16 rows, NB = 2 at most 32 (QKV also takes more rows, in blocks: see qkv_rows).  Against workgroups of 32-feature tiles (the tiled kernel for O and
+// every workgroup, so served by L2) are a run of 1 KB a step where their writer leaves them in operand order (ordered_off: QKV, and gate/up and down of
+// the chain below), else 64 pieces of 16 bytes; rows beyond the live ones repeat the last row and their results are dropped.  The order is worth most
+// with many rows: a step of the 3B shape, 18 layers, 160 rows 2156 -> 2098 us, 5 rows no difference.  NB = 1 serves at most 16 rows, NB = 2 at most 32 (QKV also takes more rows, in blocks: see qkv_rows).  Against workgroups of 32-feature tiles (the tiled kernel for O and
 // down, which also stages the rows in LDS slice by slice), before -> after in a step of 5 / 16 rows (us; what
 // is launched where is decided by few16_resid and few16_gateup):
 //   h = 1536, F = 8960    QKV 9.4 -> 6.8 / 10.0 -> 7.9,  O 5.5 -> 4.6 / 5.5 -> 5.0, down 9.3 -> 6.9 / 9.6 -> 7.9, gate/up 15.9 -> 14.7 / 17.2 -> 17.3
@@ -1141,7 +1142,9 @@ static TileChoice choose(int epi, int rows, int min_rows, int N, int K, size_t s
     // Gate/up with 129..192 certain rows and enough column blocks for one workgroup on (nearly) every compute unit: one
     // 192-row block per column block, so that no weight band is streamed by two workgroups.  (For the split-k
     // projections the same tile was measured: it wants more splits, and the slab traffic costs more than it saves.)
-    if (epi == EPI_SWIGLU && min_rows > 128 && min_rows <= 192 && rows <= 384 && (N + 127) / 128 >= 192) c.MT = 6;
+    // Where no row beyond 192 is possible also with fewer column blocks, as long as two 128-row blocks would be a second workgroup on some units: h = 3584,
+    // F = 18944 (148 column blocks), four layers of a pass, 150 rows 736 -> 692 us, 190 rows 754 -> 714 (h = 2048, F = 11008, 86 blocks: 435 -> 447).
+    if (epi == EPI_SWIGLU && min_rows > 128 && min_rows <= 192 && ((rows <= 384 && (N + 127) / 128 >= 192) || (rows <= 192 && (N + 127) / 128 > 132))) c.MT = 6;
     if (epi == EPI_STORE_F32 || epi == EPI_RESID) {
         const int S = K / 64;
         const long cap_m = (long)(slab_room_floats / ((size_t)rows * N));    // slabs must fit the scratch area
