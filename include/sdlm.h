@@ -238,7 +238,7 @@ int sdlm_debug_read_kv(sdlm_ctx *ctx, int32_t layer, int32_t seq, int32_t kv_hea
  * of splits along k between workgroups.  Columns count rows of the weight matrix, for epilogue 2 those of gate and up
  * together (n of each).  A tile of 16 rows, or for epilogue 2 of 32 x 64, is a kernel without LDS tiles; for epilogue 2, 64 or
  * 128 rows x 128 columns is a workgroup whose wavefronts take half of k each; 512 columns are eight wavefronts.  Not covered:
- * QKV projections of few rows, which run together with RoPE and the K/V placement in a launch of their own.  For tests of the
+ * QKV projections that run together with RoPE and the K/V placement, and decode steps of at most 16 rows, whose kernels hold the norms too.  For tests of the
  * tile policy.  Errors: SDLM_EINVAL.
  */
 int sdlm_debug_gemm_plan(int32_t epilogue, int32_t rows, int32_t min_rows, int32_t n, int32_t k, int32_t *tile_rows, int32_t *tile_cols,

@@ -984,13 +984,14 @@ static int sure_blocks(int rows, int min_rows, int MT)
 // Row blocks repeat the weight stream (from L2) and a workgroup's time grows with k times its rows, where the tiled kernel splits
 // k between workgroups: row blocks pay while all workgroups fit the chip at once (about one per compute unit).
 //   32-row blocks, counted for the mean of certain and possible rows: h = 2048, 66 rows, 240 workgroups 15.1 -> 10.5 us (both kernels
-//   before -> fused); h = 1536, 60 rows 13.6 -> 8.9; but h = 2048, 400 workgroups 17.1 -> 16.2, h = 3584, 432 workgroups 17.1 -> 22.5.
-//   64-row blocks, k of at most 2048: h = 2048, 160 rows, 240 workgroups 17.1 -> 15.2 us; h = 5120, 48 rows, 224 workgroups 28.2 -> 30.6.
-// Where the blocks that may be empty would put a second 64-row workgroup on some units, they are of 32 rows (a layer of h = 2048, 16 sequences, D = 8:
-// all 256 rows 129.5 us with 64 rows, 126.2 with 32, 127.9 with the separate kernels; 128 us at 160 rows were 111 either way).  With
-// 32 rows where they do fit, a layer takes 3 % longer (24 sequences, D = 4, 192 rows: 114.2 -> 118.2 us).  With k above 1536 the separate kernels take over
-// where even so the possible rows are more than 640 32-row workgroups (20 sequences, D = 8, all 320 rows: 147.4 -> 145.8 us a layer); k = 1536 gains there
-// still (48 sequences, D = 4, 384 rows: 122.9 -> 120.6).
+//   before -> fused); h = 1536, 60 rows 13.6 -> 8.9; h = 3584, 432 workgroups slower still (24 sequences, D = 4, a step of 8 layers 1733 -> 1772).
+//   64-row blocks, with the rows in operand order, in rounds of two workgroups a unit: k of at most 1536 until the certain rows are a little more than one round of them, four layers of a
+//   pass of h = 1536, us: 200 rows 417 -> 383, 320 rows 448 -> 417, 509 rows (512 workgroups) 546 -> 518, 640 rows (640) 596 -> 589, 800 rows 648 -> 647; steps of 14 layers, 64 sequences, D = 4
+//   1700 -> 1590, 40 sequences, D = 8 1795 -> 1723.  k of at most 2048 until 400: h = 2048, 320 rows 526 -> 508, 400 rows (560) 572 -> 577, 509 rows 644 -> 656; steps of 18 layers, 40 sequences, D = 4
+//   2290 -> 2230.  Longer k: h = 3584, 200 rows 769 -> 800.
+// Blocks that may be empty are of 32 rows, unless all blocks are on the chip at once anyway: a step's rows end in one of them, and a second 64-row workgroup on
+// some units would make the launch wait (64 sequences, D = 2, h = 2048, 10 layers 1256 us with 64 rows, 1246 with 32; 64 sequences, D = 4 1761, 1745).  With
+// 32 rows where they do fit, a layer takes 3 % longer (24 sequences, D = 4, 192 rows: 114.2 -> 118.2 us).
 struct QkvRows { int units, rest_units, m_sure, m_rest; };   // 16-row units of a certain row block and of one that may be empty; how many of each
 
 static QkvRows qkv_rows(const sdlm_model_cfg *m, int max_rows, int min_rows)
@@ -1005,10 +1006,9 @@ static QkvRows qkv_rows(const sdlm_model_cfg *m, int max_rows, int min_rows)
     if (max_rows <= 16) return with(1, 1);
     if (max_rows <= 32) return with(2, 2);
     if (cols * (sure_blocks(max_rows, min_rows, 1) + (max_rows + 31) / 32) <= 2 * chip) return with(2, 2);
-    if (m->hidden > 2048 || cols * sure_blocks(max_rows, min_rows, 2) > chip) return {};
-    if (cols * ((max_rows + 63) / 64) <= chip || m->hidden <= 1536) return with(4, 4);
-    const QkvRows q = with(4, 2);
-    return cols * (2 * q.m_sure + q.m_rest) <= 640 ? q : QkvRows{};
+    const int sure = cols * sure_blocks(max_rows, min_rows, 2), all = cols * ((max_rows + 63) / 64);
+    if (m->hidden > 2048 || sure > (m->hidden <= 1536 ? 576 : 400)) return {};
+    return all <= chip || all == sure ? with(4, 4) : with(4, 2);
 }
 
 bool qkv_rope_skinny_applies(const sdlm_model_cfg *m, int max_rows, int min_rows) { return qkv_rows(m, max_rows, min_rows).units > 0; }

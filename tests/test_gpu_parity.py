@@ -654,6 +654,24 @@ def test_bf16_gate_up_of_at_most_32_rows(B, D, hidden, ffn):
     ctx.close()
 
 
+@pytest.mark.parametrize("B,D,hidden,heads", [(64, 8, 128, 12), (66, 8, 128, 12), (35, 8, 1600, 16), (46, 8, 1600, 16)])
+def test_bf16_qkv_of_many_rows(B, D, hidden, heads):
+    """Steps of 315 to 1056 rows on both sides of the fused QKV launch's last lines: 9 certain 64-row blocks by 64 columns (576 workgroups) and 10 of them, 5 by 80 (400) and 7;
+    blocks that hold rows only after a full commit."""
+    m = mfma_cfg(n_layers=2, n_q_heads=heads, n_kv_heads=2, hidden=hidden, ffn=64, vocab=100, has_qkv_bias=True)
+    om, g_dev, layers_dev = both_models(m, seed=190 + B, std=0.03)
+    prompts = [syn.uniform_int(8, f"mr{i}", 2 + i % 9, 0, m.vocab - 1).numpy() for i in range(B)]
+    ids, cnt = syn.make_overrides(29, 2, B, D, m.vocab)
+    cnt = cnt.clone()
+    cnt[0] = D
+    max_len = max(len(p) for p in prompts) + 3 * D
+    ctx = gpu_context(m, g_dev, layers_dev, max_batch=B, max_seq_len=max_len, D=D, tau=0.5)
+    assert ctx.kernel_info == "mfma-bf16"
+    st, _ = lockstep(ctx, om, prompts, D, 0.5, 2, logit_tol=2e-2, conf_tol=1e-3, overrides=(ids, cnt), bf16=True, max_len=max_len)
+    print("qkv of many rows", (B, D, hidden, heads), st)
+    ctx.close()
+
+
 @pytest.mark.parametrize("lens,D,heads,kv,paged", [([1, 16, 17, 240], 4, 4, 2, False), ([31, 112, 129, 230, 2], 3, 6, 1, True), ([97], 16, 2, 2, True), ([244], 4, 12, 2, False)])
 def test_bf16_attention_of_short_contexts(lens, D, heads, kv, paged):
     """Contexts of at most 256 keys: four teams of one workgroup stream the cache and merge in LDS.  Teams without a tile, odd tile counts, staging tile alone in
@@ -714,7 +732,7 @@ def test_bf16_few_rows_on_the_kernels_for_more(B, D, hidden, ffn, heads):
 def test_bf16_qkv_row_blocks(B, D, hidden, heads, kv):
     """The fused QKV launch by row blocks of 32 and of 64 and the separate kernels on the other side of its rules: ragged last
     blocks, blocks that only exist after a full commit (B * 2D rows) and are empty after single tokens, such blocks of 64 rows and of 32
-    (h = 1600: 240 and 234 possible rows beside 135 and 130 certain ones; 320 beside 180 take the separate kernels)."""
+    (h = 1600: 240 and 234 possible rows beside 135 and 130 certain ones, 320 beside 180; h = 2112 takes the separate kernels)."""
     m = mfma_cfg(n_layers=2, n_q_heads=heads, n_kv_heads=kv, hidden=hidden, ffn=192, vocab=1000, has_qkv_bias=True)
     om, g_dev, layers_dev = both_models(m, seed=110 + B + heads, std=0.03)
     prompts = [syn.uniform_int(5, f"rb{i}", 3 + 5 * (i % 7), 0, m.vocab - 1).numpy() for i in range(B)]
