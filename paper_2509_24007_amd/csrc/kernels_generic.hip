@@ -260,9 +260,9 @@ __device__ inline float block_sum(float v, float *red)
 // its slabs be requested together.  256 threads -> now: h = 5120, 8 rows 11.0 -> 6.5 us; h = 3584, 70 rows 7.8 -> 5.7 us, 512 rows
 // 9.8 -> 8.6 us; h = 2048, 256 rows 6.5 -> 5.8 us.  With more rows than workgroups fit the chip at once: bandwidth, and small workgroups hide
 // one row's reduction behind another's loads (see rmsnorm_t).
-template <typename T, int TH, int NV>
+template <typename T, int TH, int NV, bool ORDERED>
 __global__ __launch_bounds__(TH) void rmsnorm_k(T *out, float *x, const T *g, int h, float eps, const int32_t *row_index,
-                                                const int32_t *p_count, int sure, const float *slabs, int n_slabs, size_t slab_stride, int ordered)
+                                                const int32_t *p_count, int sure, const float *slabs, int n_slabs, size_t slab_stride)
 {
     __shared__ float red[TH / 64];
     const int j = blockIdx.x;
@@ -324,7 +324,7 @@ __global__ __launch_bounds__(TH) void rmsnorm_k(T *out, float *x, const T *g, in
         if (k >= h) continue;
         const float o0 = v[i].x * inv * gv[i].x, o1 = v[i].y * inv * gv[i].y;
         const float o2 = v[i].z * inv * gv[i].z, o3 = v[i].w * inv * gv[i].w;
-        T *dst = out + (ordered ? ordered_off(j, k, h) : (size_t)j * h + k);
+        T *dst = out + (ORDERED ? ordered_off(j, k, h) : (size_t)j * h + k);
         if constexpr (sizeof(T) == 2) {
             *(uint2 *)dst = make_uint2((uint32_t)f_to_bf16(o0) | ((uint32_t)f_to_bf16(o1) << 16),
                                        (uint32_t)f_to_bf16(o2) | ((uint32_t)f_to_bf16(o3) << 16));
@@ -334,11 +334,11 @@ __global__ __launch_bounds__(TH) void rmsnorm_k(T *out, float *x, const T *g, in
     }
 }
 
-template <typename T>
+template <typename T, bool ORDERED>
 static void rmsnorm_t(hipStream_t s, void *out, float *x, const void *g, int h, float eps, const int32_t *row_index,
-                      const int32_t *p_count, int max_rows, int min_rows, const float *slabs, int n_slabs, size_t slab_stride, int ordered)
+                      const int32_t *p_count, int max_rows, int min_rows, const float *slabs, int n_slabs, size_t slab_stride)
 {
-#define SDLM_RMS(TH, NV) hipLaunchKernelGGL((rmsnorm_k<T, TH, NV>), dim3(max_rows), dim3(TH), 0, s, (T *)out, x, (const T *)g, h, eps, row_index, p_count, min_rows, slabs, n_slabs, slab_stride, ordered)
+#define SDLM_RMS(TH, NV) hipLaunchKernelGGL((rmsnorm_k<T, TH, NV, ORDERED>), dim3(max_rows), dim3(TH), 0, s, (T *)out, x, (const T *)g, h, eps, row_index, p_count, min_rows, slabs, n_slabs, slab_stride)
     // Wide workgroups while those of all rows are on the chip at once (four a compute unit of 512 threads, two of 1024, one of 1024 with more
     // than 4096 values a row, for their registers), counted in certain rows: a step has few more, as a rule.  us, 256 threads / wide:
     //   h = 2048   1024 rows without slabs 4.4 / 4.4, 2048 rows 6.6 / 6.7
@@ -356,8 +356,10 @@ static void rmsnorm_t(hipStream_t s, void *out, float *x, const void *g, int h, 
 void launch_rmsnorm(hipStream_t s, int dtype, void *out, float *x, const void *g, int h, float eps, const int32_t *row_index,
                     const int32_t *p_count, int max_rows, int min_rows, const float *slabs, int n_slabs, size_t slab_stride, bool ordered)
 {
-    if (dtype == 0) rmsnorm_t<float>(s, out, x, g, h, eps, row_index, p_count, max_rows, min_rows, slabs, n_slabs, slab_stride, 0);
-    else rmsnorm_t<bf16_t>(s, out, x, g, h, eps, row_index, p_count, max_rows, min_rows, slabs, n_slabs, slab_stride, ordered);
+    // (the order as a template argument: as a run-time one it cost every norm 0.2 us)
+    if (dtype == 0) rmsnorm_t<float, false>(s, out, x, g, h, eps, row_index, p_count, max_rows, min_rows, slabs, n_slabs, slab_stride);
+    else if (ordered) rmsnorm_t<bf16_t, true>(s, out, x, g, h, eps, row_index, p_count, max_rows, min_rows, slabs, n_slabs, slab_stride);
+    else rmsnorm_t<bf16_t, false>(s, out, x, g, h, eps, row_index, p_count, max_rows, min_rows, slabs, n_slabs, slab_stride);
 }
 
 // ------------------------------------------------------------------------------------------------ GEMM (FMA)

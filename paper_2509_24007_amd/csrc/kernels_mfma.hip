@@ -786,34 +786,35 @@ __global__ __launch_bounds__(SK_W * 64) void swiglu_skinny16_k(MfmaArgs a)
     *(uint2 *)(a.Yt + (NORM ? ordered_off(row, n, a.N) : (size_t)row * a.n_out + n)) = make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
 }
 
-// O of that chain, and down where few_down says so: all of k by the eight wavefronts of a workgroup of 16 features.  XP: rows in operand order (down).
+// O of that chain, and down where few_down_whole says so: all of k by the eight wavefronts of a workgroup of 16 NT features.  XP: rows in operand order (down).
 // Bound: the operands' requests of one workgroup, weights and rows alike 1 KB a k step, which a compute unit serves at 75 GB/s; four k steps a register set (four
 // wavefronts a SIMD) are as fast as six, 16 wavefronts or 32 features a workgroup slower (h = 1536, F = 8960, 8 rows, whole step 1502 us; six k steps 1504, 16
 // wavefronts 1518, 32 features 1652).  O with its norm, h = 1536, 5 rows: 9.1 us in two launches, now 5.2.
 constexpr int FEW_W = 8, FEW_U = 4;
 
-template <bool XP>
+template <bool XP, int NT>
 __global__ __launch_bounds__(FEW_W * 64) void resid_few_k(MfmaArgs a)
 {
-    __shared__ f32x4 part[FEW_W][64];
+    __shared__ f32x4 part[FEW_W][NT][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int t16 = blockIdx.x, n = t16 * 16 + (lane >> 4) * 4, row = lane & 15, K32 = a.K >> 5;
+    const int t16 = blockIdx.x * NT, n = (t16 + (NT == 2 ? wave & 1 : 0)) * 16 + (lane >> 4) * 4, row = lane & 15, K32 = a.K >> 5;
     const bf16_t *w = a.Wp + (size_t)(t16 >> 1) * (a.K >> 4) * 512 + (t16 & 1) * 128;
     const int kb = (int)((long)K32 * wave / FEW_W), ke = (int)((long)K32 * (wave + 1) / FEW_W);
     f32x4 aa[1], ab[1], x;
     uint2 g = make_uint2(0, 0);
-    const int R = skinny_dot<1, 1, XP, FEW_U>(w, w, a.X, a.pR, a.max_rows, 0, a.K, kb, ke, lane, aa, ab, [&](int rows) {
-        if (wave) return;
+    const int R = skinny_dot<1, NT, XP, FEW_U>(w, w + 128, a.X, a.pR, a.max_rows, 0, a.K, kb, ke, lane, aa, ab, [&](int rows) {
+        if (wave >= NT) return;
         x = *(const f32x4 *)(a.Yf + (size_t)min(row, rows - 1) * a.n_out + n);
         if (a.gain) g = *(const uint2 *)(a.gain + n);
     });
     if (R <= 0) return;
-    part[wave][lane] = aa[0];
+    part[wave][0][lane] = aa[0];
+    if constexpr (NT == 2) part[wave][1][lane] = ab[0];
     __syncthreads();
-    if (wave) return;
-    f32x4 s = part[0][lane];
+    if (wave >= NT) return;   // wavefront i finishes the features of tile i
+    f32x4 s = part[0][wave][lane];
 #pragma unroll
-    for (int i = 1; i < FEW_W; ++i) s += part[i][lane];
+    for (int i = 1; i < FEW_W; ++i) s += part[i][wave][lane];
     x += s;
     if (row < R) *(f32x4 *)(a.Yf + (size_t)row * a.n_out + n) = x;
     if (!a.gain) return;   // behind the last layer
@@ -821,7 +822,7 @@ __global__ __launch_bounds__(FEW_W * 64) void resid_few_k(MfmaArgs a)
     ss += __shfl_xor(ss, 16);
     ss += __shfl_xor(ss, 32);
     if (row >= R) return;
-    if (lane < 16) a.ssq[(size_t)row * (a.n_out >> 4) + t16] = ss;
+    if (lane < 16) a.ssq[(size_t)row * (a.n_out >> 4) + t16 + wave] = ss;
     const float g0 = bf16_to_f((bf16_t)(g.x & 0xffff)), g1 = bf16_to_f((bf16_t)(g.x >> 16)), g2 = bf16_to_f((bf16_t)(g.y & 0xffff)), g3 = bf16_to_f((bf16_t)(g.y >> 16));
     *(uint2 *)(a.xg + ordered_off(row, n, a.n_out)) = make_uint2(pack_bf16(x[0] * g0, x[1] * g1), pack_bf16(x[2] * g2, x[3] * g3));
 }
@@ -1283,8 +1284,11 @@ void launch_resid_few(hipStream_t s, const GemmArgs &g, bool ordered, const void
     MfmaArgs a{};
     a.X = (const bf16_t *)g.X; a.Wp = (const bf16_t *)g.W; a.Yf = g.Yf; a.pR = g.pR; a.max_rows = g.max_rows; a.N = a.n_out = g.N; a.K = g.K;
     a.gain = (const bf16_t *)gain; a.xg = (bf16_t *)xg; a.ssq = ssq;
-    if (ordered) hipLaunchKernelGGL(resid_few_k<true>, dim3(g.N / 16), dim3(FEW_W * 64), 0, s, a);
-    else hipLaunchKernelGGL(resid_few_k<false>, dim3(g.N / 16), dim3(FEW_W * 64), 0, s, a);
+    // O beyond one round of the units: 32 features a workgroup, whose rows are requested half as often (h = 5120, 320 -> 160 workgroups, 8 layers: 8 rows 1887 -> 1874 us, 16 rows 2000 -> 1988;
+    // h = 3584, 224 -> 112: 1133 -> 1147).
+    if (ordered) hipLaunchKernelGGL((resid_few_k<true, 1>), dim3(g.N / 16), dim3(FEW_W * 64), 0, s, a);
+    else if (g.N / 16 > 256) hipLaunchKernelGGL((resid_few_k<false, 2>), dim3(g.N / 32), dim3(FEW_W * 64), 0, s, a);
+    else hipLaunchKernelGGL((resid_few_k<false, 1>), dim3(g.N / 16), dim3(FEW_W * 64), 0, s, a);
 }
 
 // Down of that chain by whole sums where its workgroups of 16 features are nearly one round of the units: h = 3584, F = 18944, 8 rows, 224 workgroups, a step of 8 layers 1168 us
