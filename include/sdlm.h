@@ -158,9 +158,10 @@ int sdlm_decode_step_static(sdlm_ctx *ctx, int32_t *ids, int32_t *count, float *
 
 /*
  * Replay the decode step as a HIP graph.  The launch sequence of sdlm_decode_step is fixed once the batch is known
- * (row counts, lengths and page tables live in device memory), so with enable != 0 the first sdlm_decode_step after
- * a prefill, or after the output pointers change, captures its launches on the context's stream and later calls
- * replay the captured graph: one submission instead of ~9 launches per layer, which is what bounds the step for small
+ * (row counts, lengths and page tables live in device memory), except that the attention of short and of long contexts is
+ * launched differently.  With enable != 0 the first sdlm_decode_step after a prefill, after its first commit, after the output
+ * pointers change, or when the longest sequence passes such a line (at 256 keys and where the merge of the split cache
+ * changes: a few times in a generation) captures its launches on the context's stream and later calls replay the captured graph: one submission instead of ~9 launches per layer, which is what bounds the step for small
  * batches.  Results are identical to the eager path.  The step runs eagerly regardless while any phase is being
  * timed (sdlm_profile) or a debug tap is set.  sdlm_verify_step and sdlm_kv_commit are always eager.
  * Errors: SDLM_ESTATE if the context was created on the null stream (which cannot be captured).

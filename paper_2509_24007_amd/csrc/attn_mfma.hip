@@ -481,6 +481,32 @@ size_t mfma_attn_scratch_bytes(const sdlm_model_cfg *m, const sdlm_run_cfg *r, i
     return worst * ((size_t)QMAX * HD * 4 + QMAX * 8) + 256;
 }
 
+// What the attention of a pass is launched as, from the longest sequence that it may meet (max_len) and the row groups of the launch.
+enum { ATTN_WHOLE = 0, ATTN_TEAMS, ATTN_MERGE_1, ATTN_MERGE_4, ATTN_MERGE_FEW_9, ATTN_MERGE_FEW_17 };   // MERGE_*: chunks as workgroups, and which merge behind them
+
+static int attn_form(int chunk_pages, int max_chunks, int n_kv_heads, int max_seq_len, int max_len, int max_groups, bool two_staging)
+{
+    if (max_chunks <= 1) return ATTN_WHOLE;
+    const int keys = min(max_len, max_seq_len);
+    // Short contexts of few row groups, at most one workgroup a unit: the chunks are teams of one workgroup, and the launch of the merge (5 us) is saved.  A team's trips are then
+    // four times fewer than the keys', not as few as there are chunks: us a step, separate merge / teams, 1.5B shape, one sequence of 100 keys 1491 / 1403, 200 1478 / 1431, 300 1518 / 1491, 512
+    // 1522 / 1555, 1000 1532 / 1731;  3B shape, 16 sequences, D = 8, 18 layers, 200 keys 1944 / 1887, 500 1966 / 1962;  four sequences of 500 1525 / 1571.
+    if (!two_staging && keys <= TEAM_KEYS && max_groups * n_kv_heads <= 256) return ATTN_TEAMS;
+    // Which merge: by the chunks that the longest sequence may have now, not by those that the capacity admits.
+    const int chunks = (keys + PAGE * chunk_pages - 1) / (PAGE * chunk_pages);
+    const bool few = max_groups * n_kv_heads <= 64;
+    if (few && chunks > 16) return ATTN_MERGE_FEW_17;
+    if (few && chunks > 8) return ATTN_MERGE_FEW_9;
+    return max_chunks > 16 ? ATTN_MERGE_4 : ATTN_MERGE_1;
+}
+
+int mfma_attn_form(const sdlm_model_cfg *m, int max_seq_len, int max_len, int max_groups, size_t scratch_bytes, bool two_staging)
+{
+    int cp, mc;
+    chunk_floor(m, max_seq_len, max_groups, scratch_bytes, &cp, &mc);
+    return attn_form(cp, mc, m->n_kv_heads, max_seq_len, max_len, max_groups, two_staging);
+}
+
 bool launch_attn_mfma(hipStream_t s, const sdlm_model_cfg *m, int max_seq_len, int max_len, const void *q, void *out, const void *pool_layer,
                       const KvGeom &kg, const RowMeta &rm, const SeqState &st, int D, int max_groups, void *scratch, size_t scratch_bytes,
                       int part, bool two_staging)
@@ -493,29 +519,19 @@ bool launch_attn_mfma(hipStream_t s, const sdlm_model_cfg *m, int max_seq_len, i
     a.part_o = (float *)scratch;
     a.part_ml = (float2 *)((char *)scratch + items * QMAX * HD * 4);
     a.c = 1.4426950408889634f / sqrtf((float)HD);
-    // Short contexts of few row groups, at most one workgroup a unit: the chunks are teams of one workgroup, and the launch of the merge (5 us) is saved.  A team's trips are then
-    // four times fewer than the keys', not as few as there are chunks: us a step, separate merge / teams, 1.5B shape, one sequence of 100 keys 1491 / 1403, 200 1478 / 1431, 300 1518 / 1491, 512
-    // 1522 / 1555, 1000 1532 / 1731;  3B shape, 16 sequences, D = 8, 18 layers, 200 keys 1944 / 1887, 500 1966 / 1962;  four sequences of 500 1525 / 1571.
-    const bool teams = !two_staging && a.max_chunks > 1 && min(max_len, max_seq_len) <= TEAM_KEYS && max_groups * kg.n_kv_heads <= 256;
+    const int form = attn_form(a.chunk_pages, a.max_chunks, kg.n_kv_heads, max_seq_len, max_len, max_groups, two_staging);
     if (part == 0) {
-        if (teams) {
-            hipLaunchKernelGGL((attn_mfma_k<false, 4>), dim3(max_groups, kg.n_kv_heads), dim3(1024), 0, s, a);
-            return false;
-        }
-        if (two_staging) hipLaunchKernelGGL(attn_mfma_k<true>, dim3(max_groups, kg.n_kv_heads, a.max_chunks), dim3(256), 0, s, a);
+        if (form == ATTN_TEAMS) hipLaunchKernelGGL((attn_mfma_k<false, 4>), dim3(max_groups, kg.n_kv_heads), dim3(1024), 0, s, a);
+        else if (two_staging) hipLaunchKernelGGL(attn_mfma_k<true>, dim3(max_groups, kg.n_kv_heads, a.max_chunks), dim3(256), 0, s, a);
         else hipLaunchKernelGGL(attn_mfma_k<false>, dim3(max_groups, kg.n_kv_heads, a.max_chunks), dim3(256), 0, s, a);
-    }
-    else if (a.max_chunks > 1) {
-        // Which merge: by the chunks that the longest sequence may have now, not by those that the capacity admits.
-        const int chunks = (min(max_len, max_seq_len) + PAGE * a.chunk_pages - 1) / (PAGE * a.chunk_pages);
+    } else {
         const dim3 grid(max_groups, kg.n_kv_heads, NQ);
-        const bool few = max_groups * kg.n_kv_heads <= 64;
-        if (few && chunks > 16) hipLaunchKernelGGL((attn_combine_k<4, 8, 4>), grid, dim3(1024), 0, s, a);
-        else if (few && chunks > 8) hipLaunchKernelGGL((attn_combine_k<2, 8, 4>), grid, dim3(512), 0, s, a);
-        else if (a.max_chunks > 16) hipLaunchKernelGGL((attn_combine_k<1, 4, 4>), grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((attn_combine_k<1, 4, 1>), grid, dim3(256), 0, s, a);
+        if (form == ATTN_MERGE_FEW_17) hipLaunchKernelGGL((attn_combine_k<4, 8, 4>), grid, dim3(1024), 0, s, a);
+        else if (form == ATTN_MERGE_FEW_9) hipLaunchKernelGGL((attn_combine_k<2, 8, 4>), grid, dim3(512), 0, s, a);
+        else if (form == ATTN_MERGE_4) hipLaunchKernelGGL((attn_combine_k<1, 4, 4>), grid, dim3(256), 0, s, a);
+        else if (form == ATTN_MERGE_1) hipLaunchKernelGGL((attn_combine_k<1, 4, 1>), grid, dim3(256), 0, s, a);
     }
-    return a.max_chunks > 1;
+    return form >= ATTN_MERGE_1;
 }
 
 }  // namespace sdlm

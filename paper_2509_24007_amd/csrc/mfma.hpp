@@ -32,11 +32,13 @@ void mfma_gemm_plan(int epi, int rows, int min_rows, int N, int K, size_t slab_r
 int launch_gemm_mfma(hipStream_t s, int epi, const GemmArgs &a, float *slabs, size_t slab_room_floats, bool defer_reduce);
 // part 0: the attention kernel; part 1: the merge of the split-KV partials (a no-op when the launch has a single
 // chunk).  Returns whether the launch shape needs the merge.  max_seq_len: capacity, which sizes the launch; max_len: upper bound of the
-// sequences' present lengths, which only steers the kind of merge.  two_staging: row groups of this pass may read a second
+// sequences' present lengths, which together with the row groups decides the form of the launches (mfma_attn_form).  two_staging: row groups of this pass may read a second
 // staging tile (a verification pass whose rows do not fit one tile).
 bool launch_attn_mfma(hipStream_t s, const sdlm_model_cfg *m, int max_seq_len, int max_len, const void *q, void *out, const void *pool_layer,
                       const KvGeom &kg, const RowMeta &rm, const SeqState &st, int D, int max_groups, void *scratch, size_t scratch_bytes,
                       int part, bool two_staging);
+// That form, a small integer: a captured pass may be replayed while it stays the same.
+int mfma_attn_form(const sdlm_model_cfg *m, int max_seq_len, int max_len, int max_groups, size_t scratch_bytes, bool two_staging);
 // Steps of at most 32 rows, and of more where qkv_rope_skinny_applies: QKV projection, rotation and K/V placement in one launch (same results as the projection
 // followed by the RoPE + K/V placement kernel, up to the order in which the k partial sums are added).
 bool qkv_rope_skinny_applies(const sdlm_model_cfg *m, int max_rows, int min_rows);   // min_rows: rows that are certainly there

@@ -193,13 +193,13 @@ struct sdlm_ctx {
     std::vector<int32_t> n_host;         // landing buffer of refresh_lengths (sized once, so that a step allocates nothing)
     char *static_scratch = nullptr;      // this GPU's copy of the library-owned scratch array (sdlm_decode_step_static)
     std::string static_err;              // why static_scratch is missing
-    bool capturing = false;              // the launches of a step are being recorded into its graph
     bool no_events = false;              // a call that must not create HIP events is running
     std::vector<Tap> taps;
-    // graph replay of the decode step (opt-in): the launch sequence of a step is fixed once the batch is, all sizes
-    // that vary from step to step live in device memory
+    // graph replay of the decode step (opt-in): the launch sequence of a step is fixed once the batch and the form of its attention are, all
+    // sizes that vary from step to step live in device memory
     bool graph_on = false;
     hipGraphExec_t graph_exec = nullptr;
+    int graph_attn = 0;                  // the captured launches' attention form (mfma_attn_form)
     void *graph_key[4] = {nullptr, nullptr, nullptr, nullptr};   // the output pointers baked into the captured launches
     // profiling
     uint32_t prof = 0;                   // bit p: phase p is bracketed by events
@@ -254,6 +254,9 @@ struct Phase {
     }
 };
 
+// Host upper bound of the longest sequence's length.
+int longest(const sdlm_ctx *c) { return *std::max_element(c->n_ub.begin(), c->n_ub.begin() + c->batch); }
+
 void run_taps(sdlm_ctx *c, int layer, int which, const void *src, size_t bytes)
 {
     for (auto &t : c->taps)
@@ -279,8 +282,7 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
     const size_t e = c->L.esz;
     hipStream_t s = c->stream;
     c->pend_slabs = 0;   // a fresh residual stream: nothing pending from an earlier pass
-    int max_len = c->r.max_seq_len;   // captured launches are replayed while the sequences grow
-    if (!c->capturing) max_len = *std::max_element(c->n_ub.begin(), c->n_ub.begin() + c->batch);
+    const int max_len = longest(c);
     // matrix-core path, at most 16 rows: norms inside the products
     const bool few16 = !cache_only && c->L.mfma && c->taps.empty() && mfma_few_applies(&m, rows);
     const bool ordered = few16 && few_down_whole(h);   // also across the layers
@@ -674,8 +676,8 @@ static int decode_step_impl(sdlm_ctx *c, int32_t *ids, int32_t *count, float *co
                 return fail(c, SDLM_ECAPACITY, "sequence %d: %d tokens + a block of %d exceed max_seq_len %d", b, c->n_ub[b], D, c->r.max_seq_len);
     }
     hipStream_t s = c->stream;
+    const int rows = B * 2 * D, groups = B * ((2 * D + c->L.group_rows - 1) / c->L.group_rows);
     auto launch_all = [&]() {
-        const int rows = B * 2 * D, groups = B * ((2 * D + c->L.group_rows - 1) / c->L.group_rows);
         const int cp_floor = c->L.mfma ? mfma_attn_chunk_floor(&c->m, c->r.max_seq_len, groups, c->L.attn_bytes) : 0;
         const bool embeds = assemble_embeds(B, D, c->m.hidden);
         { Phase p(c, SDLM_PH_ROWS); launch_assemble_decode(s, c->st, c->rm, B, D, c->m.mask_token_id, c->L.group_rows, c->kg.staging_base, c->m.block_causal, c->m.n_kv_heads, cp_floor,
@@ -689,19 +691,21 @@ static int decode_step_impl(sdlm_ctx *c, int32_t *ids, int32_t *count, float *co
     };
     if (c->graph_on && c->prof == 0 && c->taps.empty() && !eager_only) {
         void *key[4] = {ids, count, conf, logits};
-        if (!c->graph_exec || memcmp(key, c->graph_key, sizeof key) != 0) {
+        // The attention's launches follow the longest sequence: captured again when their form changes (at 256 keys, and where the merge does), so that a
+        // replay runs what an eager step would.
+        const int attn = c->L.mfma ? mfma_attn_form(&c->m, c->r.max_seq_len, longest(c), groups, c->L.attn_bytes, false) : 0;
+        if (!c->graph_exec || attn != c->graph_attn || memcmp(key, c->graph_key, sizeof key) != 0) {
             drop_graph(c);
             hipGraph_t g = nullptr;
             HIPCHK(c, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-            c->capturing = true;
             launch_all();
-            c->capturing = false;
             hipError_t e1 = hipStreamEndCapture(s, &g);
             if (e1 != hipSuccess || !g) return fail(c, SDLM_EHIP, "graph capture of the decode step failed: %s", hipGetErrorString(e1));
             hipError_t e2 = hipGraphInstantiate(&c->graph_exec, g, nullptr, nullptr, 0);
             (void)hipGraphDestroy(g);
             if (e2 != hipSuccess) { c->graph_exec = nullptr; return fail(c, SDLM_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e2)); }
             memcpy(c->graph_key, key, sizeof key);
+            c->graph_attn = attn;
         }
         HIPCHK(c, hipGraphLaunch(c->graph_exec, s));
     } else {

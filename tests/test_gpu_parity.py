@@ -596,6 +596,36 @@ def test_graph_replay_matches_oracle_and_eager(kind):
     ctx.close()
 
 
+@pytest.mark.parametrize("start", [230, 490])
+def test_graph_replay_is_eager_bit_for_bit_as_contexts_grow(start):
+    """A context that holds far more than its sequences: replayed and eager steps agree in every bit before, at and after the lengths at which the
+    attention's launches change (256 keys: teams of one workgroup; 512: the merge for more than eight chunks)."""
+    m = mfma_cfg()
+    _, g_dev, layers_dev = both_models(m, seed=18, std=0.05)
+    D, steps = 8, 6
+    prompts = [syn.uniform_int(18, f"gg{i}", n, 0, m.vocab - 1).numpy() for i, n in enumerate([start, 33])]
+    ovr = syn.make_overrides(18, steps, 2, D, m.vocab)[0].to(torch.int32).cuda()
+    side = torch.cuda.Stream()
+    out = []
+    for use_graph in (True, False):
+        ctx = gpu_context(m, g_dev, layers_dev, stream=side, max_batch=2, max_seq_len=900, D=D, tau=0.5)
+        ctx.graph(use_graph)
+        ctx.prefill(prompts)
+        ids = torch.empty(2, D, dtype=torch.int32, device="cuda")
+        cnt = torch.empty(2, dtype=torch.int32, device="cuda")
+        logits = torch.empty(2 * D, m.vocab, dtype=torch.float32, device="cuda")
+        for t in range(steps):
+            for _ in range(2):                           # the second call replays what the first one captured
+                ctx.decode_step(ids, cnt, None, logits)
+                torch.cuda.synchronize()
+                out.append(logits.clone())
+            ctx.kv_commit(ovr[t].contiguous(), torch.full((2,), D, dtype=torch.int32, device="cuda"))
+        assert ctx.get_lengths()[0].tolist() == [start + steps * D, 33 + steps * D]
+        ctx.close()
+    for t, (a, b) in enumerate(zip(out[:2 * steps], out[2 * steps:])):
+        assert torch.equal(a, b), f"step {t // 2}: replay and eager differ by {(a - b).abs().max().item():.3e}"
+
+
 def test_graph_needs_a_real_stream():
     m = gpu_cfg()
     om, g_dev, layers_dev = both_models(m, seed=8, std=0.3)
