@@ -213,7 +213,7 @@ int sdlm_get_lengths(sdlm_ctx *ctx, int32_t *n, int32_t *c);
  *   4: normalised block rows entering the LM head    elem  [batch*D, hidden]   (layer ignored)
  *   5: rotated queries                               elem  [R, Hq*d]
  *   6: residual stream after the O projection        float [R, hidden]
- * "elem" is float in fp32 mode and bf16 in bf16 mode.  R is the step's packed row count: per sequence its
+ * The step's products, attention and results are those of an untapped step.  "elem" is float in fp32 mode and bf16 in bf16 mode.  R is the step's packed row count: per sequence its
  * pending rows then its D block rows.  `which` < 0 clears all taps.  dst must hold max_rows rows.
  */
 int sdlm_debug_tap(sdlm_ctx *ctx, int32_t layer, int32_t which, void *dst);

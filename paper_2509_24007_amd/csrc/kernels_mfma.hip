@@ -1073,7 +1073,7 @@ static bool few16_gateup(int min_rows, int N)
     return !(blocks32 >= 144 && blocks32 <= 256 && min_rows > 4) && !(blocks32 > 512 && min_rows > 12);
 }
 
-// (Both rules are those of passes with separate norms: prompts of at most 16 tokens, runs with taps.  In the chain of a decode step the operands' order makes the finer
+// (Both rules are those of passes with separate norms: prompts of at most 16 tokens, widths above 8192.  In the chain of a decode step the operands' order makes the finer
 // gate/up blocks and the stream of down the better ones throughout: h = 5120, F = 27648, 16 rows, a step of 8 layers 1973 -> 1944 us.)
 // What a product runs as: FEW16 / FEW32 are the kernels without LDS tiles for steps of few rows (16 rows x two 16-feature tiles, 32 rows x two
 // 32-feature tiles a workgroup), TILED the tiled kernel.
@@ -1296,7 +1296,7 @@ void launch_resid_few(hipStream_t s, const GemmArgs &g, bool ordered, const void
 // 8 rows 1509 / 1502, 16 rows 1595 / 1614; h = 2048, 128, 18 layers: 1222 / 1214, 1278 / 1302); more are an uneven second one (h = 5120, 320, 8 layers: 1963 / 2055).
 bool few_down_whole(int h) { return h / 16 > 192 && h / 16 <= 256; }
 
-int launch_down_split(hipStream_t s, const GemmArgs &g, float *slabs, size_t slab_room_floats)
+int launch_down_split(hipStream_t s, const GemmArgs &g, float *slabs, size_t slab_room_floats, bool defer_reduce)
 {
     MfmaArgs a{};
     a.X = (const bf16_t *)g.X; a.Wp = (const bf16_t *)g.W; a.pR = g.pR; a.max_rows = g.max_rows; a.N = a.n_out = g.N; a.K = g.K;
@@ -1304,7 +1304,25 @@ int launch_down_split(hipStream_t s, const GemmArgs &g, float *slabs, size_t sla
     a.slab = (size_t)g.max_rows * g.N;
     a.Yf = a.splits > 1 ? slabs : g.Yf;
     hipLaunchKernelGGL(resid_skinny_k<true>, dim3(g.N / 32 * a.splits), dim3(SK_W * 64), 0, s, a);
+    if (a.splits > 1 && !defer_reduce)
+        hipLaunchKernelGGL(reduce_slabs_k, dim3(g.max_rows), dim3(256), 0, s, g.Yf, slabs, a.splits, a.slab, g.N, g.pR, g.max_rows);
     return a.splits;
+}
+
+// dst[row, k], row-major, from an operand in the order of ordered_off; eight elements a thread (debug taps).
+__global__ __launch_bounds__(256) void unorder_k(bf16_t *dst, const bf16_t *src, int K)
+{
+    const int row = blockIdx.y, k = (blockIdx.x * 256 + threadIdx.x) * 8;   // K is a multiple of 64
+    if (k >= K) return;
+    bf16_t *d = dst + (size_t)row * K + k;   // the caller's pointer: element-wise, whatever its alignment
+    const bf16_t *v = src + ordered_off(row, k, K);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) d[e] = v[e];
+}
+
+void launch_unorder(hipStream_t s, void *dst, const void *src, int rows, int K)
+{
+    hipLaunchKernelGGL(unorder_k, dim3((K + 2047) / 2048, rows), dim3(256), 0, s, (bf16_t *)dst, (const bf16_t *)src, K);
 }
 
 void launch_lmhead_mfma(hipStream_t s, const void *xhat, const void *w_packed, const int32_t *p_rows, int max_rows, int min_rows, int V, int h, float scale,

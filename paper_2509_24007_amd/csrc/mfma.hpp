@@ -52,9 +52,10 @@ bool mfma_few_applies(const sdlm_model_cfg *m, int max_rows);
 void launch_embed_few(hipStream_t s, float *x, const void *E, const RowMeta &rm, int max_rows, int h, int V, const void *gain, void *xg, float *ssq);
 void launch_gateup_few(hipStream_t s, const GemmArgs &g, const float *ssq, float eps);
 void launch_resid_few(hipStream_t s, const GemmArgs &g, bool ordered, const void *gain, void *xg, float *ssq);
-// Down of such a step: by launch_resid_few, or split along k with its sums left to an RMSNorm (returns the splits, as launch_gemm_mfma; 1: complete).
+// Down of such a step: by launch_resid_few, or split along k with its sums left to an RMSNorm (defer_reduce and return value as in launch_gemm_mfma).
 bool few_down_whole(int h);
-int launch_down_split(hipStream_t s, const GemmArgs &g, float *slabs, size_t slab_room_floats);
+int launch_down_split(hipStream_t s, const GemmArgs &g, float *slabs, size_t slab_room_floats, bool defer_reduce);
+void launch_unorder(hipStream_t s, void *dst, const void *src, int rows, int K);   // an operand of that chain as rows (taps)
 void launch_lmhead_mfma(hipStream_t s, const void *xhat, const void *w_packed, const int32_t *p_rows, int max_rows, int min_rows, int V, int h,
                         float scale, int conf_fn, float *logits_out, void *scratch, int32_t *ids, float *conf);
 

@@ -264,16 +264,22 @@ void run_taps(sdlm_ctx *c, int layer, int which, const void *src, size_t bytes)
             (void)hipMemcpyAsync(t.dst, src, bytes, hipMemcpyDeviceToDevice, c->stream);
 }
 
-// Whether a pass of at most `rows` rows takes the generic path's kernels for few rows.  (Taps also read what these keep in registers.)
+bool tapped(const sdlm_ctx *c, int layer, int which)
+{
+    return std::any_of(c->taps.begin(), c->taps.end(), [&](const Tap &t) { return t.which == which && (which == 4 || t.layer == layer); });
+}
+
+// Whether a pass of at most `rows` rows takes the generic path's kernels for few rows.
 bool few_rows(const sdlm_ctx *c, int rows)
 {
-    return !c->L.mfma && c->taps.empty() && generic_few_applies(c->m.dtype, rows, c->m.hidden) && generic_few_applies(c->m.dtype, rows, c->m.ffn) &&
+    return !c->L.mfma && generic_few_applies(c->m.dtype, rows, c->m.hidden) && generic_few_applies(c->m.dtype, rows, c->m.ffn) &&
            generic_few_applies(c->m.dtype, rows, c->m.n_q_heads * c->m.head_dim);
 }
 
 // The decoder layers over the rows described by c->rm.  `rows` bounds the launch grids (the device-side row
 // count decides what is computed); `rows_sure` is a host-known lower bound of that count (it only steers launch shapes).
 // `cache_only`: the pass only has to leave its rows' K/V in the cache (prefill): the last layer then ends after the K/V placement.  `embedded`: x holds the rows' embeddings.
+// Taps change no product: they copy, add the split-k slabs that the next norm would have added (in the same order), and put operands back into rows.
 void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_only, bool embedded = false, bool two_staging = false)
 {
     const sdlm_model_cfg &m = c->m;
@@ -284,7 +290,7 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
     c->pend_slabs = 0;   // a fresh residual stream: nothing pending from an earlier pass
     const int max_len = longest(c);
     // matrix-core path, at most 16 rows: norms inside the products
-    const bool few16 = !cache_only && c->L.mfma && c->taps.empty() && mfma_few_applies(&m, rows);
+    const bool few16 = !cache_only && c->L.mfma && mfma_few_applies(&m, rows);
     const bool ordered = few16 && few_down_whole(h);   // also across the layers
     float *ssq = few16 ? c->slabs : nullptr;   // free where it is needed: slabs are written by down and read by the next norm
     if (ordered) { Phase p(c, SDLM_PH_ROWS); launch_embed_few(s, c->x, c->embed, c->rm, rows, h, m.vocab, c->lw[0].attn_norm, c->xn, ssq); }
@@ -349,14 +355,17 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
             else if (few16) launch_gateup_few(s, a, ssq, m.rms_eps);
             else if (c->L.mfma) launch_gemm_mfma(s, EPI_SWIGLU, a, c->slabs, c->L.slab_floats, false); else launch_gemm_generic(s, dt, EPI_SWIGLU, a);
         }
-        run_taps(c, l, 2, c->act, (size_t)rows * F * e);
+        if (few16) {
+            for (auto &t : c->taps)
+                if (t.which == 2 && t.layer == l) launch_unorder(s, t.dst, c->act, rows, F);
+        } else run_taps(c, l, 2, c->act, (size_t)rows * F * e);
         {
             Phase p(c, SDLM_PH_DOWN);
             GemmArgs a{c->act, w.w_down, nullptr, nullptr, c->x, nullptr, c->rm.counts, rows, h, F, 1.f, rows_sure};
             if (few16 && ordered) launch_resid_few(s, a, true, l + 1 < m.n_layers ? c->lw[l + 1].attn_norm : nullptr, c->xn, ssq);
             else if (few16) {
-                const int sp = launch_down_split(s, a, c->slabs, c->L.slab_floats);
-                if (sp > 1) { c->pend_slabs = sp; c->pend_stride = (size_t)rows * h; }
+                const int sp = launch_down_split(s, a, c->slabs, c->L.slab_floats, c->taps.empty());
+                if (sp > 1 && c->taps.empty()) { c->pend_slabs = sp; c->pend_stride = (size_t)rows * h; }
             }
             else if (c->L.mfma) {
                 // the split-k partial sums of a residual projection are added by the next RMSNorm (unless a tap wants x now)
@@ -376,7 +385,7 @@ void run_lm_head(sdlm_ctx *c, int lm_rows, float *logits, bool reduce = true)
     const int dt = c->m.dtype, h = c->m.hidden, V = c->m.vocab;
     // 8192: V = 20000, h = 896, 12 rows 10 us (fp32) and 36 us (bf16) slower with the norm inside, V = 4096, h = 256 0.6 faster
     const bool few = few_rows(c, lm_rows) && V <= 8192;
-    if (!few) { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xhat, c->x, c->final_norm, h, c->m.rms_eps, c->rm.blk_row, c->rm.counts + 2, lm_rows, lm_rows, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
+    if (!few || tapped(c, 0, 4)) { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xhat, c->x, c->final_norm, h, c->m.rms_eps, c->rm.blk_row, c->rm.counts + 2, lm_rows, lm_rows, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
     run_taps(c, 0, 4, c->xhat, (size_t)lm_rows * h * c->L.esz);
     {
         Phase p(c, SDLM_PH_LMHEAD);
