@@ -245,6 +245,22 @@ int sdlm_debug_read_kv(sdlm_ctx *ctx, int32_t layer, int32_t seq, int32_t kv_hea
 int sdlm_debug_gemm_plan(int32_t epilogue, int32_t rows, int32_t min_rows, int32_t n, int32_t k, int32_t *tile_rows, int32_t *tile_cols,
                          int32_t *splits);
 
+/*
+ * Host logic only (no GPU work): the forms that a decode step of `batch` sequences takes, the longest of them with `longest` known tokens, before
+ * (committed = 0) or after the first commit behind a prefill.  plan [host], SDLM_SP_N integers:
+ *   CHAIN      the layers: 0 separate kernels; steps of few rows with the norms inside the products: 1 generic path, 2 matrix-core path, 3 the same with
+ *              down by whole sums of k;
+ *   EMBEDS     the embeddings: 0 a launch of their own, 1 gathered by the row assembly, 2 with the first operands of form 3;
+ *   QKV_ROWS   matrix-core path, QKV with rotation and K/V placement in one launch: rows of a block that certainly holds some (0: separate launches);
+ *   QKV_REST   ... and of one that may be empty;
+ *   LM_HEAD    0 matrix-core kernel, 1 generic product behind a norm, 2 generic product with the norm inside;
+ *   LM_ACCEPT  1: vocabulary reduction and acceptance are one launch;
+ *   ATTN       matrix-core path: 0 one chunk, 1 chunks as teams of one workgroup, 2 to 5 chunks as workgroups and one of four merges behind them (-1: generic).
+ * For tests of the dispatch.  Errors: SDLM_EINVAL.
+ */
+enum { SDLM_SP_CHAIN = 0, SDLM_SP_EMBEDS, SDLM_SP_QKV_ROWS, SDLM_SP_QKV_REST, SDLM_SP_LM_HEAD, SDLM_SP_LM_ACCEPT, SDLM_SP_ATTN, SDLM_SP_N };
+int sdlm_debug_step_plan(const sdlm_model_cfg *m, const sdlm_run_cfg *r, int32_t batch, int32_t committed, int32_t longest, int32_t *plan);
+
 /* Rows the activation buffers are sized for (decode: batch * 2D; prefill pass size). */
 int32_t sdlm_max_rows(const sdlm_ctx *ctx);
 

@@ -1012,6 +1012,13 @@ static QkvRows qkv_rows(const sdlm_model_cfg *m, int max_rows, int min_rows)
     return all <= chip || all == sure ? with(4, 4) : with(4, 2);
 }
 
+void mfma_qkv_rows(const sdlm_model_cfg *m, int max_rows, int min_rows, int *rows, int *rest_rows)
+{
+    const QkvRows q = qkv_rows(m, max_rows, min_rows);
+    *rows = 16 * q.units;
+    *rest_rows = 16 * q.rest_units;
+}
+
 bool qkv_rope_skinny_applies(const sdlm_model_cfg *m, int max_rows, int min_rows) { return qkv_rows(m, max_rows, min_rows).units > 0; }
 
 void launch_qkv_rope_skinny(hipStream_t s, const sdlm_model_cfg *m, const void *X, const void *w_packed, const void *bias, const int32_t *p_rows,

@@ -42,6 +42,7 @@ int mfma_attn_form(const sdlm_model_cfg *m, int max_seq_len, int max_len, int ma
 // Steps of at most 32 rows, and of more where qkv_rope_skinny_applies: QKV projection, rotation and K/V placement in one launch (same results as the projection
 // followed by the RoPE + K/V placement kernel, up to the order in which the k partial sums are added).
 bool qkv_rope_skinny_applies(const sdlm_model_cfg *m, int max_rows, int min_rows);   // min_rows: rows that are certainly there
+void mfma_qkv_rows(const sdlm_model_cfg *m, int max_rows, int min_rows, int *rows, int *rest_rows);   // rows of a block that certainly holds some and of one that may be empty (0: not in one launch)
 void launch_qkv_rope_skinny(hipStream_t s, const sdlm_model_cfg *m, const void *X, const void *w_packed, const void *bias, const int32_t *p_rows,
                             int max_rows, int min_rows, void *q_out, void *pool_layer, const KvGeom &kg, const RowMeta &rm, const SeqState &st, const float2 *rope,
                             const float *ssq = nullptr, float eps = 0.f);

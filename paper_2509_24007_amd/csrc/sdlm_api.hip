@@ -269,16 +269,40 @@ bool tapped(const sdlm_ctx *c, int layer, int which)
     return std::any_of(c->taps.begin(), c->taps.end(), [&](const Tap &t) { return t.which == which && (which == 4 || t.layer == layer); });
 }
 
-// Whether a pass of at most `rows` rows takes the generic path's kernels for few rows.
-bool few_rows(const sdlm_ctx *c, int rows)
+// Which kernels a pass takes, in one place for the launches and for sdlm_debug_step_plan.
+// The layers: separate kernels, or those of few rows with the norms inside the products (not in a prefill, `cache_only`: on the generic path its cache contents do not
+// depend on the other prompts).  Matrix-core path: down by k splits with a norm behind it, or by whole sums, which carry the norm across the layers as well.
+enum { CHAIN_NONE = 0, CHAIN_GENERIC, CHAIN_MFMA, CHAIN_MFMA_WHOLE };
+int pass_chain(const sdlm_model_cfg &m, int rows, bool cache_only)
 {
-    return !c->L.mfma && generic_few_applies(c->m.dtype, rows, c->m.hidden) && generic_few_applies(c->m.dtype, rows, c->m.ffn) &&
-           generic_few_applies(c->m.dtype, rows, c->m.n_q_heads * c->m.head_dim);
+    if (cache_only) return CHAIN_NONE;
+    if (mfma_supported(&m)) return !mfma_few_applies(&m, rows) ? CHAIN_NONE : few_down_whole(m.hidden) ? CHAIN_MFMA_WHOLE : CHAIN_MFMA;
+    const bool few = generic_few_applies(m.dtype, rows, m.hidden) && generic_few_applies(m.dtype, rows, m.ffn) && generic_few_applies(m.dtype, rows, m.n_q_heads * m.head_dim);
+    return few ? CHAIN_GENERIC : CHAIN_NONE;
 }
+
+// Where the embeddings of a decode step are gathered: by a launch of their own, by the row assembly, or with the first operands of a chain whose layers start without a norm.
+enum { EMBED_LAUNCH = 0, EMBED_ASSEMBLY, EMBED_CHAIN };
+int step_embeds(const sdlm_model_cfg &m, int chain, int B, int D)
+{
+    return chain == CHAIN_MFMA_WHOLE ? EMBED_CHAIN : assemble_embeds(B, D, m.hidden) ? EMBED_ASSEMBLY : EMBED_LAUNCH;
+}
+
+// The LM head: matrix-core kernel, generic products behind a norm, or with the norm inside.
+enum { HEAD_MFMA = 0, HEAD_GENERIC, HEAD_FEW };
+int pass_head(const sdlm_model_cfg &m, int lm_rows)
+{
+    if (mfma_supported(&m)) return HEAD_MFMA;
+    // 8192: V = 20000, h = 896, 12 rows 10 us (fp32) and 36 us (bf16) slower with the norm inside, V = 4096, h = 256 0.6 faster
+    return pass_chain(m, lm_rows, false) == CHAIN_GENERIC && m.vocab <= 8192 ? HEAD_FEW : HEAD_GENERIC;
+}
+
+// Whether a decode step reduces the vocabulary and accepts in one launch.
+bool step_lm_accept(const sdlm_model_cfg &m) { return !mfma_supported(&m) && lm_accept_applies(m.vocab); }
 
 // The decoder layers over the rows described by c->rm.  `rows` bounds the launch grids (the device-side row
 // count decides what is computed); `rows_sure` is a host-known lower bound of that count (it only steers launch shapes).
-// `cache_only`: the pass only has to leave its rows' K/V in the cache (prefill): the last layer then ends after the K/V placement.  `embedded`: x holds the rows' embeddings.
+// `cache_only`: the pass only has to leave its rows' K/V in the cache (prefill): the last layer then ends after the K/V placement.  `embedded`: x holds the rows' embeddings already.
 // Taps change no product: they copy, add the split-k slabs that the next norm would have added (in the same order), and put operands back into rows.
 void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_only, bool embedded = false, bool two_staging = false)
 {
@@ -289,14 +313,11 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
     hipStream_t s = c->stream;
     c->pend_slabs = 0;   // a fresh residual stream: nothing pending from an earlier pass
     const int max_len = longest(c);
-    // matrix-core path, at most 16 rows: norms inside the products
-    const bool few16 = !cache_only && c->L.mfma && mfma_few_applies(&m, rows);
-    const bool ordered = few16 && few_down_whole(h);   // also across the layers
+    const int chain = pass_chain(m, rows, cache_only);
+    const bool few = chain == CHAIN_GENERIC, few16 = chain == CHAIN_MFMA || chain == CHAIN_MFMA_WHOLE, ordered = chain == CHAIN_MFMA_WHOLE;
     float *ssq = few16 ? c->slabs : nullptr;   // free where it is needed: slabs are written by down and read by the next norm
     if (ordered) { Phase p(c, SDLM_PH_ROWS); launch_embed_few(s, c->x, c->embed, c->rm, rows, h, m.vocab, c->lw[0].attn_norm, c->xn, ssq); }
     else if (!embedded) { Phase p(c, SDLM_PH_ROWS); launch_embed(s, dt, c->x, c->embed, c->rm, rows, h, m.vocab); }
-    // generic path: norms, rotation and K/V placement inside the products (not in a prefill, whose cache contents do not depend on the other prompts)
-    const bool few = !cache_only && few_rows(c, rows);
     for (int l = 0; l < m.n_layers; ++l) {
         const LayerW &w = c->lw[l];
         char *pool_l = c->pool + (size_t)l * c->kg.layer_stride * e;
@@ -383,8 +404,7 @@ void run_lm_head(sdlm_ctx *c, int lm_rows, float *logits, bool reduce = true)
 {
     hipStream_t s = c->stream;
     const int dt = c->m.dtype, h = c->m.hidden, V = c->m.vocab;
-    // 8192: V = 20000, h = 896, 12 rows 10 us (fp32) and 36 us (bf16) slower with the norm inside, V = 4096, h = 256 0.6 faster
-    const bool few = few_rows(c, lm_rows) && V <= 8192;
+    const bool few = pass_head(c->m, lm_rows) == HEAD_FEW;
     if (!few || tapped(c, 0, 4)) { Phase p(c, SDLM_PH_NORM); launch_rmsnorm(s, dt, c->xhat, c->x, c->final_norm, h, c->m.rms_eps, c->rm.blk_row, c->rm.counts + 2, lm_rows, lm_rows, c->slabs, c->pend_slabs, c->pend_stride); c->pend_slabs = 0; }
     run_taps(c, 0, 4, c->xhat, (size_t)lm_rows * h * c->L.esz);
     {
@@ -688,11 +708,11 @@ static int decode_step_impl(sdlm_ctx *c, int32_t *ids, int32_t *count, float *co
     const int rows = B * 2 * D, groups = B * ((2 * D + c->L.group_rows - 1) / c->L.group_rows);
     auto launch_all = [&]() {
         const int cp_floor = c->L.mfma ? mfma_attn_chunk_floor(&c->m, c->r.max_seq_len, groups, c->L.attn_bytes) : 0;
-        const bool embeds = assemble_embeds(B, D, c->m.hidden);
+        const bool embeds = step_embeds(c->m, pass_chain(c->m, rows, false), B, D) == EMBED_ASSEMBLY;
         { Phase p(c, SDLM_PH_ROWS); launch_assemble_decode(s, c->st, c->rm, B, D, c->m.mask_token_id, c->L.group_rows, c->kg.staging_base, c->m.block_causal, c->m.n_kv_heads, cp_floor,
                                                           c->m.dtype, c->x, embeds ? c->embed : nullptr, c->m.hidden, c->m.vocab); }
         run_layers(c, rows, groups, B * (D + (c->committed ? 1 : 0)), false, embeds);   // after a commit every sequence has >= 1 pending row
-        const bool reduce = c->L.mfma || !lm_accept_applies(c->m.vocab);
+        const bool reduce = !step_lm_accept(c->m);
         run_lm_head(c, B * D, logits, reduce);
         Phase p(c, SDLM_PH_ACCEPT);
         if (reduce) launch_accept(s, c->st, c->ids_rows, c->conf_rows, B, D, c->r.tau, c->r.accept_rule, ids, count, conf);
@@ -882,6 +902,21 @@ int sdlm_debug_gemm_plan(int32_t epilogue, int32_t rows, int32_t min_rows, int32
 {
     if (!tile_rows || !tile_cols || !splits || rows < 1 || n < 1 || k < 64 || k % 64 || epilogue < 0 || epilogue > 3) return SDLM_EINVAL;
     mfma_gemm_plan(epilogue == 3 ? 4 : epilogue, rows, min_rows, n, k, (size_t)16 << 20, tile_rows, tile_cols, splits);
+    return SDLM_OK;
+}
+
+int sdlm_debug_step_plan(const sdlm_model_cfg *m, const sdlm_run_cfg *r, int32_t batch, int32_t committed, int32_t longest, int32_t *out)
+{
+    if (!out || !validate(m, r, nullptr) || batch < 1 || batch > r->max_batch || longest < 1 || longest > r->max_seq_len) return SDLM_EINVAL;
+    Layout L;
+    plan(m, r, &L);
+    const int D = r->block_D, rows = batch * 2 * D, sure = batch * (D + (committed ? 1 : 0)), groups = batch * ((2 * D + L.group_rows - 1) / L.group_rows);
+    out[SDLM_SP_CHAIN] = pass_chain(*m, rows, false);
+    out[SDLM_SP_EMBEDS] = step_embeds(*m, out[SDLM_SP_CHAIN], batch, D);
+    mfma_qkv_rows(m, rows, sure, &out[SDLM_SP_QKV_ROWS], &out[SDLM_SP_QKV_REST]);
+    out[SDLM_SP_LM_HEAD] = pass_head(*m, batch * D);
+    out[SDLM_SP_LM_ACCEPT] = step_lm_accept(*m);
+    out[SDLM_SP_ATTN] = L.mfma ? mfma_attn_form(m, r->max_seq_len, longest, groups, L.attn_bytes, false) : -1;
     return SDLM_OK;
 }
 

@@ -18,9 +18,11 @@ LIB_PATH = os.path.join(_HERE, "libsdlm.so")
 PHASES = ("rows", "norm", "qkv", "rope", "attn", "oproj", "gateup", "down", "lmhead", "accept", "attn_merge")
 OK, EINVAL, ECAPACITY, ESTATE, EHIP = 0, -1, -2, -3, -4
 
+STEP_PLAN = ("chain", "embeds", "qkv_rows", "qkv_rest", "lm_head", "lm_accept", "attn")
+
 EXPORTS = ("sdlm_workspace_bytes", "sdlm_create", "sdlm_init_weights", "sdlm_prefill", "sdlm_decode_step",
            "sdlm_decode_step_static", "sdlm_graph", "sdlm_verify_step", "sdlm_kv_commit", "sdlm_get_lengths", "sdlm_debug_tap", "sdlm_debug_rows", "sdlm_debug_read_kv",
-           "sdlm_debug_gemm_plan", "sdlm_max_rows", "sdlm_profile", "sdlm_profile_every", "sdlm_profile_read", "sdlm_kernel_info", "sdlm_last_error",
+           "sdlm_debug_gemm_plan", "sdlm_debug_step_plan", "sdlm_max_rows", "sdlm_profile", "sdlm_profile_every", "sdlm_profile_read", "sdlm_kernel_info", "sdlm_last_error",
            "sdlm_destroy")
 
 
@@ -74,6 +76,8 @@ def load():
     L.sdlm_decode_step_static.argtypes = [vp, vp, vp, vp, vp]
     L.sdlm_debug_gemm_plan.restype = C.c_int
     L.sdlm_debug_gemm_plan.argtypes = [C.c_int32] * 5 + [vp, vp, vp]
+    L.sdlm_debug_step_plan.restype = C.c_int
+    L.sdlm_debug_step_plan.argtypes = [vp, vp, C.c_int32, C.c_int32, C.c_int32, vp]
     L.sdlm_graph.restype = C.c_int
     L.sdlm_graph.argtypes = [vp, C.c_int32]
     L.sdlm_verify_step.restype = C.c_int
@@ -126,6 +130,16 @@ def gemm_plan(epilogue: int, rows: int, min_rows: int, n: int, k: int):
     if rc != 0:
         raise SdlmError(rc, "bad arguments to sdlm_debug_gemm_plan")
     return tr.value, tc.value, sp.value
+
+
+def step_plan(mcfg: ModelCfg, batch: int, D: int, *, committed: bool = True, longest: int = 64, max_seq_len: int = 512) -> Dict[str, int]:
+    """The forms a decode step takes (see sdlm_debug_step_plan in the header); host logic, no GPU needed."""
+    run = RunCfg(batch, max_seq_len, D, 0, 16, 0, 0.5, 0, 0, 0)
+    out = (C.c_int32 * len(STEP_PLAN))()
+    rc = load().sdlm_debug_step_plan(C.byref(mcfg), C.byref(run), batch, int(committed), longest, out)
+    if rc != 0:
+        raise SdlmError(rc, "bad arguments to sdlm_debug_step_plan")
+    return dict(zip(STEP_PLAN, out))
 
 
 def _dp(t: Optional[torch.Tensor]):
