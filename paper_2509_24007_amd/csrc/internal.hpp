@@ -82,6 +82,15 @@ __host__ __device__ inline size_t ordered_off(int row, int k, int K)
     return (size_t)(row >> 4) * 16 * K + (size_t)(k >> 5) * 512 + (((k >> 3) & 3) * 16 + (row & 15)) * 8 + (k & 7);
 }
 
+// Rows to reckon with between the certain ones and the bound.  A step's bound is 2 B D rows and its certain ones B (D + 1), so that the difference of
+// min_rows to half the bound is B: as many pending rows again, two a sequence, are what a trained model leaves.
+inline int likely_rows(int rows, int min_rows)
+{
+    if (min_rows <= 0) return rows;
+    const int likely = min_rows > 2 * min_rows - rows / 2 ? min_rows : 2 * min_rows - rows / 2;
+    return likely < rows ? likely : rows;
+}
+
 // Packed description of the rows of one forward pass (device arrays).
 struct RowMeta {
     int32_t *tok, *pos, *seq, *kind, *lim;  // [max_rows]; kind: -1 = K/V go to the cache slot of pos, else the slot in the
@@ -157,6 +166,7 @@ void launch_gemm_generic(hipStream_t s, int dtype, int epi, const GemmArgs &a);
 // Products of few rows with the RMSNorm in front of them (gate/up, logits: X is the fp32 residual stream) or without (residual), and the QKV
 // projection with norm, rotation and K/V placement.  row_index: rows of X, null: as they are.
 bool generic_few_applies(int dtype, int rows, int K);
+bool generic_few_pays(int dtype, int likely, double layer_elems);   // likely: rows to reckon with; layer_elems: weights of a layer
 void launch_gemm_few(hipStream_t s, int dtype, int epi, const GemmArgs &a, const void *gain, float eps, const int32_t *row_index);
 void launch_qkv_few(hipStream_t s, int dtype, const GemmArgs &a, const void *gain, float eps, void *q_out, void *pool_layer, const KvGeom &kg, const RowMeta &rm,
                     const SeqState &st, const float2 *rope, int n_q_heads);

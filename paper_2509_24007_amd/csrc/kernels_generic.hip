@@ -544,8 +544,8 @@ __global__ __launch_bounds__(256) void gemm_rows_k(GemmArgs a)
 // XCD, so that a cache line of results has one owner (N = 256, K = 256, eight XCDs in every line of the residual stream: 6.9 us, so 2.9).  Sixteen lanes
 // a column request the rows four times over and walk k in turns (K = 688: 7.3 us, so 5.3); four columns a wavefront take longer with their arithmetic (8.0).
 // us a step, norms and products apart -> now: h = 256, F = 688, 2 layers, 8 rows 84.7 -> 60.1; h = 896, F = 4864, 4 layers fp32 8 / 16 / 32 rows 417 -> 258 / 438 -> 308 / 470 -> 370,
-// bf16 307 -> 219 / 330 -> 272 / 352 -> 340; h = 2048, F = 11008, 2 layers fp32 477 -> 350 / 551 -> 482 / 738 -> 674.  Beyond 32 rows the norms, repeated
-// for every column, outweigh their launches.
+// bf16 307 -> 219 / 330 -> 272 / 352 -> 340; h = 2048, F = 11008, 2 layers fp32 477 -> 350 / 551 -> 482 / 738 -> 674.  The requests of the rows, fp32 and repeated for
+// every column and group of eight rows, grow with the layer, what they save does not: the line is generic_few_pays.
 constexpr int FEW_ROWS = 32;
 
 struct FewArgs {
@@ -693,6 +693,17 @@ __global__ __launch_bounds__(256) void qkv_few_k(FewArgs a, T *q_out, T *pool, K
 }
 
 bool generic_few_applies(int dtype, int rows, int K) { return rows <= FEW_ROWS && K % (dtype == 0 ? 4 : 8) == 0; }
+
+// Up to which layer, in 10^6 weights, for one to four groups of eight rows.  A layer of separate kernels against this one, us saved (negative: lost), over 170 random shapes:
+//   fp32  8 rows  159 M +25, 223 M +87, 287 M -16, 357 M +56;  16 rows  92 M +23, 124 M +11, 148 M +62, 157 M -5, 179 M -16, 199 M -64;
+//         24 rows  64 M +13, 71 M +33, 84 M +7, 88 M -7, 108 M -30, 140 M -40;  32 rows  36 M +35, 44 M +21, 52 M -3, 60 M -7 and +21, 83 M -19
+//   bf16  8 rows  109 M +3, 125 M +2, 144 M +4, 173 M -13, 191 M -20, 232 M -28;  16 rows  31 M +10, 40 M +8, 45 M +3, 49 M +1, 60 M -5, 74 M -28, 165 M -61;
+//         24 rows  12 M +6, 16 M +3, 19 M -5 and +4, 22 M 0, 27 M -5, 35 M -10;  32 rows  4.7 M +3, 8.3 M +3, 8.7 M -1, 10.6 M -2, 13.5 M -3
+bool generic_few_pays(int dtype, int likely, double layer_elems)
+{
+    static const int fp32[4] = {360, 150, 80, 50}, bf16[4] = {160, 45, 18, 9};
+    return likely <= FEW_ROWS && layer_elems <= 1e6 * (dtype == 0 ? fp32 : bf16)[(likely + 7) / 8 - 1];
+}
 
 static dim3 few_grid(int cols, int rows) { return dim3((cols + 31) / 32 * 8, (rows + 7) / 8); }   // four columns a workgroup, a multiple of eight workgroups
 

@@ -1127,14 +1127,6 @@ static float tiled_us(int epi, int NT, int sp, int rows, int N, int K)
     return 2.9f + sqrtf(sqrtf(l2 * l2 + w2 * w2)) + slabs;
 }
 
-// Rows to reckon with between the certain ones and the bound.  A step's bound is 2 B D rows and its certain ones B (D + 1), so that the difference of
-// min_rows to half the bound is B: as many pending rows again, two a sequence, are what a trained model leaves.
-static int likely_rows(int rows, int min_rows)
-{
-    if (min_rows <= 0) return rows;
-    return min(rows, max(min_rows, 2 * min_rows - rows / 2));
-}
-
 // rows: bound of the launch (grid); min_rows: rows that are certainly there.  The one place where a launch shape is decided.
 static TileChoice choose(int epi, int rows, int min_rows, int N, int K, size_t slab_room_floats)
 {

@@ -273,12 +273,17 @@ bool tapped(const sdlm_ctx *c, int layer, int which)
 // The layers: separate kernels, or those of few rows with the norms inside the products (not in a prefill, `cache_only`: on the generic path its cache contents do not
 // depend on the other prompts).  Matrix-core path: down by k splits with a norm behind it, or by whole sums, which carry the norm across the layers as well.
 enum { CHAIN_NONE = 0, CHAIN_GENERIC, CHAIN_MFMA, CHAIN_MFMA_WHOLE };
-int pass_chain(const sdlm_model_cfg &m, int rows, bool cache_only)
+bool generic_few(const sdlm_model_cfg &m, int rows)
+{
+    return !mfma_supported(&m) && generic_few_applies(m.dtype, rows, m.hidden) && generic_few_applies(m.dtype, rows, m.ffn) &&
+           generic_few_applies(m.dtype, rows, m.n_q_heads * m.head_dim);
+}
+int pass_chain(const sdlm_model_cfg &m, int rows, int rows_sure, bool cache_only)
 {
     if (cache_only) return CHAIN_NONE;
     if (mfma_supported(&m)) return !mfma_few_applies(&m, rows) ? CHAIN_NONE : few_down_whole(m.hidden) ? CHAIN_MFMA_WHOLE : CHAIN_MFMA;
-    const bool few = generic_few_applies(m.dtype, rows, m.hidden) && generic_few_applies(m.dtype, rows, m.ffn) && generic_few_applies(m.dtype, rows, m.n_q_heads * m.head_dim);
-    return few ? CHAIN_GENERIC : CHAIN_NONE;
+    const double elems = (double)m.hidden * (2.0 * (m.n_q_heads + m.n_kv_heads) * m.head_dim + 3.0 * m.ffn);
+    return generic_few(m, rows) && generic_few_pays(m.dtype, likely_rows(rows, rows_sure), elems) ? CHAIN_GENERIC : CHAIN_NONE;
 }
 
 // Where the embeddings of a decode step are gathered: by a launch of their own, by the row assembly, or with the first operands of a chain whose layers start without a norm.
@@ -294,7 +299,7 @@ int pass_head(const sdlm_model_cfg &m, int lm_rows)
 {
     if (mfma_supported(&m)) return HEAD_MFMA;
     // 8192: V = 20000, h = 896, 12 rows 10 us (fp32) and 36 us (bf16) slower with the norm inside, V = 4096, h = 256 0.6 faster
-    return pass_chain(m, lm_rows, false) == CHAIN_GENERIC && m.vocab <= 8192 ? HEAD_FEW : HEAD_GENERIC;
+    return generic_few(m, lm_rows) && m.vocab <= 8192 ? HEAD_FEW : HEAD_GENERIC;
 }
 
 // Whether a decode step reduces the vocabulary and accepts in one launch.
@@ -313,7 +318,7 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
     hipStream_t s = c->stream;
     c->pend_slabs = 0;   // a fresh residual stream: nothing pending from an earlier pass
     const int max_len = longest(c);
-    const int chain = pass_chain(m, rows, cache_only);
+    const int chain = pass_chain(m, rows, rows_sure, cache_only);
     const bool few = chain == CHAIN_GENERIC, few16 = chain == CHAIN_MFMA || chain == CHAIN_MFMA_WHOLE, ordered = chain == CHAIN_MFMA_WHOLE;
     float *ssq = few16 ? c->slabs : nullptr;   // free where it is needed: slabs are written by down and read by the next norm
     if (ordered) { Phase p(c, SDLM_PH_ROWS); launch_embed_few(s, c->x, c->embed, c->rm, rows, h, m.vocab, c->lw[0].attn_norm, c->xn, ssq); }
@@ -706,12 +711,13 @@ static int decode_step_impl(sdlm_ctx *c, int32_t *ids, int32_t *count, float *co
     }
     hipStream_t s = c->stream;
     const int rows = B * 2 * D, groups = B * ((2 * D + c->L.group_rows - 1) / c->L.group_rows);
+    const int rows_sure = B * (D + (c->committed ? 1 : 0));   // after a commit every sequence has >= 1 pending row
     auto launch_all = [&]() {
         const int cp_floor = c->L.mfma ? mfma_attn_chunk_floor(&c->m, c->r.max_seq_len, groups, c->L.attn_bytes) : 0;
-        const bool embeds = step_embeds(c->m, pass_chain(c->m, rows, false), B, D) == EMBED_ASSEMBLY;
+        const bool embeds = step_embeds(c->m, pass_chain(c->m, rows, rows_sure, false), B, D) == EMBED_ASSEMBLY;
         { Phase p(c, SDLM_PH_ROWS); launch_assemble_decode(s, c->st, c->rm, B, D, c->m.mask_token_id, c->L.group_rows, c->kg.staging_base, c->m.block_causal, c->m.n_kv_heads, cp_floor,
                                                           c->m.dtype, c->x, embeds ? c->embed : nullptr, c->m.hidden, c->m.vocab); }
-        run_layers(c, rows, groups, B * (D + (c->committed ? 1 : 0)), false, embeds);   // after a commit every sequence has >= 1 pending row
+        run_layers(c, rows, groups, rows_sure, false, embeds);
         const bool reduce = !step_lm_accept(c->m);
         run_lm_head(c, B * D, logits, reduce);
         Phase p(c, SDLM_PH_ACCEPT);
@@ -911,7 +917,7 @@ int sdlm_debug_step_plan(const sdlm_model_cfg *m, const sdlm_run_cfg *r, int32_t
     Layout L;
     plan(m, r, &L);
     const int D = r->block_D, rows = batch * 2 * D, sure = batch * (D + (committed ? 1 : 0)), groups = batch * ((2 * D + L.group_rows - 1) / L.group_rows);
-    out[SDLM_SP_CHAIN] = pass_chain(*m, rows, false);
+    out[SDLM_SP_CHAIN] = pass_chain(*m, rows, sure, false);
     out[SDLM_SP_EMBEDS] = step_embeds(*m, out[SDLM_SP_CHAIN], batch, D);
     mfma_qkv_rows(m, rows, sure, &out[SDLM_SP_QKV_ROWS], &out[SDLM_SP_QKV_REST]);
     out[SDLM_SP_LM_HEAD] = pass_head(*m, batch * D);

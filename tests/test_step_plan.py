@@ -27,6 +27,21 @@ def test_embeddings_are_gathered_once():
             assert (p["embeds"] == ASSEMBLY) == (B <= 4 and B * 2 * D * h <= 8192)
 
 
+@pytest.mark.parametrize("dtype,h,F,hq,hk,d,B,D,few", [
+    # layers on both sides of the lines, eight rows and more: bf16 160, 45, 18 and 9 million weights, fp32 360, 150, 80 and 50
+    ("fp32", 256, 688, 4, 2, 64, 1, 4, True), ("fp32", 256, 688, 4, 2, 64, 4, 4, True), ("fp32", 256, 688, 4, 2, 64, 5, 4, False),
+    ("bf16", 896, 4864, 14, 2, 64, 1, 4, True), ("bf16", 896, 4864, 14, 2, 64, 4, 4, True), ("bf16", 896, 4864, 14, 2, 64, 16, 1, False),
+    ("bf16", 1800, 9720, 9, 9, 96, 3, 4, False), ("bf16", 1800, 9720, 9, 9, 96, 1, 4, True), ("bf16", 4000, 16000, 125, 125, 32, 4, 2, False),
+    ("bf16", 2856, 15416, 89, 1, 32, 4, 4, False), ("bf16", 3848, 13464, 120, 1, 32, 1, 4, False),
+    ("fp32", 2048, 11008, 16, 2, 128, 4, 4, True), ("fp32", 2712, 14640, 42, 2, 64, 4, 4, False), ("fp32", 3976, 15904, 31, 31, 64, 2, 5, False),
+    ("fp32", 3976, 15904, 31, 31, 64, 1, 4, True)])
+def test_generic_steps_of_few_rows_by_the_size_of_a_layer(dtype, h, F, hq, hk, d, B, D, few):
+    p = plan(B, D, dtype=dtype, hidden=h, ffn=F, n_q_heads=hq, n_kv_heads=hk, head_dim=d)
+    assert p["chain"] == (GENERIC if few else SEPARATE) and p["attn"] == -1 and p["qkv_rows"] == 0
+    # rows that are no whole 16-byte pieces never
+    assert plan(B, D, dtype=dtype, hidden=h, ffn=F + 2, n_q_heads=hq, n_kv_heads=hk, head_dim=d)["chain"] == SEPARATE
+
+
 def test_step_plan_rejects_bad_arguments():
     for bad in (dict(B=0, D=4), dict(B=1, D=17), dict(B=1, D=4, longest=0), dict(B=1, D=4, longest=513), dict(B=1, D=4, head_dim=48)):
         with pytest.raises(sdlm.SdlmError):
