@@ -167,6 +167,7 @@ void launch_gemm_generic(hipStream_t s, int dtype, int epi, const GemmArgs &a);
 // projection with norm, rotation and K/V placement.  row_index: rows of X, null: as they are.
 bool generic_few_applies(int dtype, int rows, int K);
 bool generic_few_pays(int dtype, int likely, double layer_elems);   // likely: rows to reckon with; layer_elems: weights of a layer
+bool generic_few_head_pays(int dtype, int rows, int V);
 void launch_gemm_few(hipStream_t s, int dtype, int epi, const GemmArgs &a, const void *gain, float eps, const int32_t *row_index);
 void launch_qkv_few(hipStream_t s, int dtype, const GemmArgs &a, const void *gain, float eps, void *q_out, void *pool_layer, const KvGeom &kg, const RowMeta &rm,
                     const SeqState &st, const float2 *rope, int n_q_heads);

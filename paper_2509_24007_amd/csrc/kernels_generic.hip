@@ -705,6 +705,12 @@ bool generic_few_pays(int dtype, int likely, double layer_elems)
     return likely <= FEW_ROWS && layer_elems <= 1e6 * (dtype == 0 ? fp32 : bf16)[(likely + 7) / 8 - 1];
 }
 
+// LM heads with the norm inside: up to 5000 (fp32) or 3000 (bf16) columns per group of eight rows; a wavefront a column, where the separate product has four columns a
+// wavefront, outweighs the norm's launch beyond.  us a step saved, 160 shapes of h = 64 to 2048:
+//   fp32  8 rows  V = 1500 +0.5 to +7, 4096 0 to +4, 6000 -1.4 to +4.5, 16000 -4;  16 rows  1500 0 to +6.5, 4096 -2.3 to +0.4, 8192 -3;  32 rows  512 +2, 1500 -2 to +6, 4096 -2
+//   bf16  8 rows  V = 1500 +1.5 to +2.7, 4096 -0.7 to +2, 6000 -2;  16 rows  1500 +0.6 to +1.3, 4096 -3.4 to -5;  32 rows  512 +4 to +5.5, 1500 -2 to 0, 4096 -7 to -16
+bool generic_few_head_pays(int dtype, int rows, int V) { return (long)V * ((rows + 7) / 8) <= (dtype == 0 ? 5000 : 3000); }
+
 static dim3 few_grid(int cols, int rows) { return dim3((cols + 31) / 32 * 8, (rows + 7) / 8); }   // four columns a workgroup, a multiple of eight workgroups
 
 template <typename T>

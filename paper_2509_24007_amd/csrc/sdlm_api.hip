@@ -298,8 +298,7 @@ enum { HEAD_MFMA = 0, HEAD_GENERIC, HEAD_FEW };
 int pass_head(const sdlm_model_cfg &m, int lm_rows)
 {
     if (mfma_supported(&m)) return HEAD_MFMA;
-    // 8192: V = 20000, h = 896, 12 rows 10 us (fp32) and 36 us (bf16) slower with the norm inside, V = 4096, h = 256 0.6 faster
-    return generic_few(m, lm_rows) && m.vocab <= 8192 ? HEAD_FEW : HEAD_GENERIC;
+    return generic_few(m, lm_rows) && generic_few_head_pays(m.dtype, lm_rows, m.vocab) ? HEAD_FEW : HEAD_GENERIC;
 }
 
 // Whether a decode step reduces the vocabulary and accepts in one launch.

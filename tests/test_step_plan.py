@@ -42,6 +42,12 @@ def test_generic_steps_of_few_rows_by_the_size_of_a_layer(dtype, h, F, hq, hk, d
     assert plan(B, D, dtype=dtype, hidden=h, ffn=F + 2, n_q_heads=hq, n_kv_heads=hk, head_dim=d)["chain"] == SEPARATE
 
 
+@pytest.mark.parametrize("dtype,V,B,D,head", [("fp32", 4096, 1, 4, 2), ("fp32", 5000, 1, 8, 2), ("fp32", 5001, 1, 8, 1), ("fp32", 2501, 1, 9, 1), ("fp32", 1250, 8, 4, 2), ("fp32", 300, 33, 1, 1),
+                                              ("bf16", 3000, 2, 4, 2), ("bf16", 4227, 2, 16, 1), ("bf16", 5106, 8, 4, 1), ("bf16", 4653, 4, 5, 1), ("bf16", 750, 2, 16, 2)])
+def test_generic_head_by_columns_and_rows(dtype, V, B, D, head):
+    assert plan(B, D, dtype=dtype, hidden=256, ffn=688, n_q_heads=4, n_kv_heads=2, head_dim=64, vocab=V)["lm_head"] == head
+
+
 def test_step_plan_rejects_bad_arguments():
     for bad in (dict(B=0, D=4), dict(B=1, D=17), dict(B=1, D=4, longest=0), dict(B=1, D=4, longest=513), dict(B=1, D=4, head_dim=48)):
         with pytest.raises(sdlm.SdlmError):
