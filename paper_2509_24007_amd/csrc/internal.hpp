@@ -180,7 +180,7 @@ void launch_lm_reduce(hipStream_t s, const float *logits, int V, int32_t *ids, f
 void launch_accept(hipStream_t s, const SeqState &st, const int32_t *ids_rows, const float *conf_rows, int B, int D,
                    float tau, int rule, int32_t *ids_out, int32_t *count_out, float *conf_out);
 // Reduction and acceptance in one launch, for small vocabularies.
-bool lm_accept_applies(int V);
+bool lm_accept_applies(int V, int D);
 void launch_lm_accept(hipStream_t s, const float *logits, int V, int conf_fn, const SeqState &st, int B, int D, float tau, int rule, int32_t *ids_out,
                       int32_t *count_out, float *conf_out);
 void launch_commit(hipStream_t s, const SeqState &st, int B, int D, const int32_t *ids_ovr, const int32_t *cnt_ovr,

@@ -1071,8 +1071,9 @@ __global__ void accept_k(SeqState st, const int32_t *ids_rows, const float *conf
 }
 
 // Vocabulary reduction and acceptance of one sequence's D rows in one launch, for small vocabularies: 1024 threads in equal parts of the rows (a
-// wavefront at least), each part as lm_reduce_k.  V = 4096, D = 4: 8.7 + 3.1 us as two launches, 5.8 here.  Beyond 16384 a row is
-// worth a workgroup of its own.
+// wavefront at least), each part as lm_reduce_k.  V = 4096, D = 4: 8.7 + 3.1 us as two launches, 5.8 here.  The line is by the threads of a row: with D up to 8 (two
+// wavefronts a row or more) one launch is faster at every V measured, us a step saved with one / 64 sequences: D = 1, V = 16384 20 / 21, D = 4 13 / 16, D = 8, V = 4096 3.2 / 3.5, 16384 6 / 20;
+// with one wavefront a row it reads the row for longer than the launch costs: D = 9 and 16, V = 1000 2.5 / 2.7, 2048 0.9 / 2, 4096 -0.7 / -0.5, 8192 -4 / -1, 16384 -14 / 2.
 __global__ __launch_bounds__(1024) void lm_accept_k(const float *logits, int V, int conf_fn, SeqState st, int D, int parts, float tau, int rule, int32_t *ids_out,
                                                     int32_t *count_out, float *conf_out)
 {
@@ -1128,7 +1129,7 @@ __global__ __launch_bounds__(1024) void lm_accept_k(const float *logits, int V, 
     if (threadIdx.x < D) accept_row(st, ids, conf, b, D, threadIdx.x, tau, rule, ids_out, count_out, conf_out);
 }
 
-bool lm_accept_applies(int V) { return V <= 16384; }
+bool lm_accept_applies(int V, int D) { return V <= (D <= 8 ? 16384 : 2048); }
 
 void launch_lm_accept(hipStream_t s, const float *logits, int V, int conf_fn, const SeqState &st, int B, int D, float tau, int rule, int32_t *ids_out,
                       int32_t *count_out, float *conf_out)

@@ -302,7 +302,7 @@ int pass_head(const sdlm_model_cfg &m, int lm_rows)
 }
 
 // Whether a decode step reduces the vocabulary and accepts in one launch.
-bool step_lm_accept(const sdlm_model_cfg &m) { return !mfma_supported(&m) && lm_accept_applies(m.vocab); }
+bool step_lm_accept(const sdlm_model_cfg &m, int D) { return !mfma_supported(&m) && lm_accept_applies(m.vocab, D); }
 
 // The decoder layers over the rows described by c->rm.  `rows` bounds the launch grids (the device-side row
 // count decides what is computed); `rows_sure` is a host-known lower bound of that count (it only steers launch shapes).
@@ -717,7 +717,7 @@ static int decode_step_impl(sdlm_ctx *c, int32_t *ids, int32_t *count, float *co
         { Phase p(c, SDLM_PH_ROWS); launch_assemble_decode(s, c->st, c->rm, B, D, c->m.mask_token_id, c->L.group_rows, c->kg.staging_base, c->m.block_causal, c->m.n_kv_heads, cp_floor,
                                                           c->m.dtype, c->x, embeds ? c->embed : nullptr, c->m.hidden, c->m.vocab); }
         run_layers(c, rows, groups, rows_sure, false, embeds);
-        const bool reduce = !step_lm_accept(c->m);
+        const bool reduce = !step_lm_accept(c->m, D);
         run_lm_head(c, B * D, logits, reduce);
         Phase p(c, SDLM_PH_ACCEPT);
         if (reduce) launch_accept(s, c->st, c->ids_rows, c->conf_rows, B, D, c->r.tau, c->r.accept_rule, ids, count, conf);
@@ -920,7 +920,7 @@ int sdlm_debug_step_plan(const sdlm_model_cfg *m, const sdlm_run_cfg *r, int32_t
     out[SDLM_SP_EMBEDS] = step_embeds(*m, out[SDLM_SP_CHAIN], batch, D);
     mfma_qkv_rows(m, rows, sure, &out[SDLM_SP_QKV_ROWS], &out[SDLM_SP_QKV_REST]);
     out[SDLM_SP_LM_HEAD] = pass_head(*m, batch * D);
-    out[SDLM_SP_LM_ACCEPT] = step_lm_accept(*m);
+    out[SDLM_SP_LM_ACCEPT] = step_lm_accept(*m, D);
     out[SDLM_SP_ATTN] = L.mfma ? mfma_attn_form(m, r->max_seq_len, longest, groups, L.attn_bytes, false) : -1;
     return SDLM_OK;
 }

@@ -1138,7 +1138,8 @@ def test_bf16_mfma_random_long_contexts(seed):
 @pytest.mark.parametrize("dtype,hidden,heads,kv,d,ffn,vocab,B,D", [
     ("fp32", 64, 4, 2, 32, 112, 300, 1, 1), ("fp32", 260, 3, 1, 96, 1100, 4096, 1, 4), ("fp32", 1028, 4, 4, 64, 772, 8192, 2, 8),
     ("fp32", 768, 6, 2, 128, 700, 8200, 3, 5), ("bf16", 72, 2, 1, 32, 136, 517, 1, 7), ("bf16", 520, 8, 2, 64, 1544, 16385, 1, 16),
-    ("bf16", 1032, 5, 1, 96, 520, 999, 2, 4), ("fp32", 256, 4, 2, 64, 688, 4096, 4, 4)])
+    ("bf16", 1032, 5, 1, 96, 520, 999, 2, 4), ("fp32", 256, 4, 2, 64, 688, 4096, 4, 4),
+    ("fp32", 64, 4, 2, 32, 112, 2048, 1, 9), ("fp32", 64, 4, 2, 32, 112, 2049, 1, 9)])
 def test_generic_steps_of_few_rows(dtype, hidden, heads, kv, d, ffn, vocab, B, D):
     """Steps of at most 32 rows on the generic path run norm, rotation and K/V placement inside the products, vocabulary reduction and acceptance
     in one launch: logits against the oracle, ids, confidences and counts against what the logits say.  Row counts on both sides of eight, sixteen and 32, k

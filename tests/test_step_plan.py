@@ -48,6 +48,13 @@ def test_generic_head_by_columns_and_rows(dtype, V, B, D, head):
     assert plan(B, D, dtype=dtype, hidden=256, ffn=688, n_q_heads=4, n_kv_heads=2, head_dim=64, vocab=V)["lm_head"] == head
 
 
+@pytest.mark.parametrize("V,D,one", [(16384, 1, 1), (16385, 1, 0), (16384, 8, 1), (2048, 9, 1), (2049, 9, 0), (16384, 16, 0), (97, 16, 1)])
+def test_reduction_and_acceptance_in_one_launch_by_threads_a_row(V, D, one):
+    for B in (1, 64):
+        assert plan(B, D, dtype="fp32", hidden=64, ffn=64, n_q_heads=2, n_kv_heads=1, head_dim=32, vocab=V)["lm_accept"] == one
+    assert plan(1, D, vocab=V)["lm_accept"] == 0
+
+
 def test_step_plan_rejects_bad_arguments():
     for bad in (dict(B=0, D=4), dict(B=1, D=17), dict(B=1, D=4, longest=0), dict(B=1, D=4, longest=513), dict(B=1, D=4, head_dim=48)):
         with pytest.raises(sdlm.SdlmError):
