@@ -1109,22 +1109,25 @@ static void refine_gateup(int rows, int min_rows, int N, int K, TileChoice *c)
 }
 
 // Estimate, in us, of a plain-store or residual product in 128-row tiles of 128 NT columns with `sp` k splits, and of the consumer's reading of the splits'
-// slabs.  Fitted to 2000 launches (12 matrices of h = 1536 to 5120, 34 to 4096 rows, every split count): a 64-deep slice takes 0.52 us with 128
-// columns and 0.82 with 256, whatever rows of the tile are live, and with more than 400 rows, where the weights are shared, the matrix pipes set 0.70 and 0.97;
-// workgroups of one compute unit share its load path, so their slices add up; weights come at 6.4 TB/s where nothing else bounds; slabs are written at 3.4 TB/s
-// and read by the RMSNorm at 9 and by the rotation at 20 (measured in whole steps).  Its choice is within 0.7 % of the best of the sweep in the geometric mean;
-// as many workgroups of the wide tile as units wherever that fits is 6 % (up to 400 rows) and 4 % slower.  us, (columns, splits):
+// slabs.  Fitted to whole steps with every tile and split count of 716 products (N = 512 to 10240, K = 320 to 32512, 34 to 2000 rows): a 64-deep slice takes 0.53 us with 128
+// columns and 0.97 with 256, whatever rows of the tile are live, and between 200 and 500 rows, where ever more of the weights are shared and the matrix pipes begin to bound, up to
+// 0.70 and 1.07; workgroups of one compute unit share its load path, a second one costs 1.4 times its own slices, later ones 1.5; weights come at 6.4 TB/s where nothing else
+// bounds; a megabyte of slabs is written and read in 0.42 us.  Its choice is 0.36 us from the best on average; as many workgroups of the wide tile as units wherever that fits 1.82; with
+// the slices' cost as a step at 400 rows and no more than its own slices for a second workgroup it was 0.54, and slower than that rule by up to 16 us.  us a step saved against that over four
+// layers, (columns, splits): N = 3840, K = 3072, 409 rows (256, 4) -> (128, 2) 16;  N = 6144, K = 24576, 274 rows (256, 7) -> (256, 3) 115.
+// us a launch, (columns, splits) as many as units -> now:
 // N = 2048, K = 11008, 160 rows (256, 16) 20.0 -> (128, 8) 18.0;  N = 3584, K = 18944, 49 rows (256, 16) 28.7 -> (128, 9) 27.1;  N = 5120 square,
 // 160 rows (256, 6) 20.3 -> (128, 3) 19.7, the norm behind each 0.6 to 2 us shorter;  N = 5120, K = 27648, 992 rows (128, 1) 386 -> (256, 3) 261.
-static float tiled_us(int epi, int NT, int sp, int rows, int N, int K)
+static float tiled_us(int NT, int sp, int rows, int N, int K)
 {
     const int S = K / 64, per = (S + sp - 1) / sp;
-    const long wgs = (long)((N + 128 * NT - 1) / (128 * NT)) * ((rows + 127) / 128) * sp;
-    const float slice = rows <= 400 ? (NT == 1 ? 0.517f : 0.821f) : (NT == 1 ? 0.70f : 0.97f);
-    const float loop = (float)((wgs + 255) / 256 * per) * slice, weights = (float)N * K * 2 / 6.45e6f;
+    const long wgs = (long)((N + 128 * NT - 1) / (128 * NT)) * ((rows + 127) / 128) * sp, rounds = (wgs + 255) / 256;
+    const float shared = fminf(1.f, fmaxf(0.f, (rows - 200) / 300.f));
+    const float slice = NT == 1 ? 0.53f + 0.17f * shared : 0.97f + 0.10f * shared;
+    const float loop = per * slice * (rounds > 1 ? 2.4f + 1.5f * (rounds - 2) : 1.f), weights = (float)N * K * 2 / 6.45e6f;
     const float l2 = loop * loop, w2 = weights * weights;
-    const float slabs = sp > 1 ? (float)sp * rows * N * 4 * (epi == EPI_RESID ? 1 / 3.44e6f + 1 / 9e6f : 1 / 3.44e6f + 1 / 20e6f) : 0.f;
-    return 2.9f + sqrtf(sqrtf(l2 * l2 + w2 * w2)) + slabs;
+    const float slabs = sp > 1 ? (float)sp * rows * N * 4 * 0.42e-6f : 0.f;
+    return sqrtf(sqrtf(l2 * l2 + w2 * w2)) + slabs;
 }
 
 // rows: bound of the launch (grid); min_rows: rows that are certainly there.  The one place where a launch shape is decided.
@@ -1172,7 +1175,7 @@ static TileChoice choose(int epi, int rows, int min_rows, int N, int K, size_t s
                     const int sp = clamp(want);
                     if (sp == last) continue;
                     last = sp;
-                    const float t = tiled_us(epi, NT, sp, at, N, K);
+                    const float t = tiled_us(NT, sp, at, N, K);
                     if (best == 0.f || t < best) { best = t; c.NT = NT; c.splits = sp; }
                 }
         }

@@ -104,6 +104,15 @@ def test_policy_on_the_benchmark_shapes():
     assert sdlm.gemm_plan(STORE, 4096, 4096, 4608, 3584) == (128, 256, 1)
 
 
+def test_projections_between_one_and_two_rounds_of_the_units():
+    # measured choices where the weights begin to be shared (250 to 500 rows) and where a second workgroup on a unit costs more than it saves
+    assert sdlm.gemm_plan(STORE, 630, 378, 3840, 3072) == (128, 128, 2)
+    assert sdlm.gemm_plan(STORE, 410, 410, 3584, 3072) == (128, 128, 2) and sdlm.gemm_plan(STORE, 451, 451, 3072, 2560) == (128, 128, 2)
+    assert sdlm.gemm_plan(RESID, 410, 410, 3072, 3072) == (128, 128, 2)
+    assert sdlm.gemm_plan(RESID, 274, 274, 6144, 24576) == (128, 256, 3)
+    assert sdlm.gemm_plan(RESID, 572, 572, 5120, 27136) == (128, 256, 2)
+
+
 def test_plan_rejects_bad_arguments():
     with pytest.raises(sdlm.SdlmError):
         sdlm.gemm_plan(0, 0, 0, 128, 128)
