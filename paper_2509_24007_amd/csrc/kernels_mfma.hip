@@ -1159,10 +1159,9 @@ static TileChoice choose(int epi, int rows, int min_rows, int N, int K, size_t s
             const int per = (S + (int)sp - 1) / (int)sp;
             return (S + per - 1) / per;
         };
-        if (c.MT == 1) {
-            // Up to 32 rows: workgroups of 128 columns, k split until they are about one round of the units, or with long k (many slices, small slabs) nearly two; a
-            // third workgroup on some units costs a third: 24 rows, N = 5120, K = 27648 13 splits (520 workgroups) 57.8 -> 11 splits 50.6 us;
-            // N = 4608, K = 3584 14 -> 7 splits, half the slabs, 10.6 -> 9.4.
+        if (c.MT == 1 && epi == EPI_RESID) {
+            // Up to 32 rows (of the plain-store products, QKV, none: see qkv_rows): workgroups of 128 columns, k split until they are about one round of the units, or with long
+            // k (many slices, small slabs) nearly two; a third workgroup on some units costs a third: 24 rows, N = 5120, K = 27648 13 splits (520 workgroups) 57.8 -> 11 splits 50.6 us.
             c.NT = 1;
             c.splits = clamp((K > 4096 ? 448 : 256) / ((N + 127) / 128));
         } else {
@@ -1222,7 +1221,7 @@ static void launch_cfg(hipStream_t s, const TileChoice &c, MfmaArgs &a, int min_
     } else if constexpr (EPI == EPI_SWIGLU) {   // up to 32 rows: the kernels without LDS tiles
         if (c.MT == 2) SDLM_GO(2, 2, EPI); else if (c.MT == 6) SDLM_GO(6, 2, EPI); else if (c.WV == 8) SDLM_GO(4, 2, EPI, 8); else SDLM_GO(4, 2, EPI);
     } else {
-        if (c.MT == 1) SDLM_GO(1, 1, EPI);
+        if (EPI == EPI_RESID && c.MT == 1) SDLM_GO(1, 1, EPI_RESID);
         else if (c.NT == 1) SDLM_GO(4, 1, EPI);
         else if (EPI == EPI_RESID && c.WV == 8) SDLM_GO(4, 2, EPI_RESID, 8);
         else SDLM_GO(4, 2, EPI);
