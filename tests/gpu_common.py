@@ -42,6 +42,7 @@ class Stats:
         self.id_flip_bf16 = self.gamma_flip_bf16 = 0    # bf16 only: outside the band, within the row's own measured error
         self.max_logit_err = self.max_conf_err = self.max_logconf_err = 0.0
         self.gammas = []
+        self.step_rows = []                             # packed rows of every step (pending and block rows of the sequences followed)
         self.row_errs = []
         self.model_errs = []                            # rounding-model oracle vs exact oracle, same rows (if requested)
         self.model_id_flips = self.model_gamma_flips = 0    # ... and how many of its decisions differ outside the band
@@ -60,7 +61,7 @@ def lockstep(ctx, om, prompts, D, tau, steps, *, logit_tol, conf_tol, conf_fn=0,
              bf16=False, max_len=None, verify_rule=None, oracle_seqs=None, flip_ceiling=FLIP_CEILING, floor_model=None):
     """Run the HIP library and one oracle sequence per prompt step by step on the same token history.
 
-    After every step both sides commit the same tokens: the seeded override tokens on steps where `overrides`
+    After every step both sides commit the same tokens: the seeded override tokens on odd steps where `overrides`
     supplies them, otherwise the oracle's own accepted prefix (through the library's NULL commit when the two
     agree, through the override arguments otherwise).  Returns Stats; asserts the parity bar:
 
@@ -112,6 +113,7 @@ def lockstep(ctx, om, prompts, D, tau, steps, *, logit_tol, conf_tol, conf_fn=0,
         st.verify_rows = st.verify_skipped = st.verify_near_tie = st.verify_flip_bf16 = 0
         st.verify_gammas = []
     for t in range(steps):
+        st.step_rows.append(sum(seqs[b].n - seqs[b].c + D for b in followed))
         ctx.decode_step(ids, cnt, conf, logits)
         if verify_rule is not None:
             v_log.fill_(float("nan"))
