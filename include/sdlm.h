@@ -133,7 +133,11 @@ int sdlm_prefill(sdlm_ctx *ctx, int32_t batch, const int32_t *ids_packed, const 
  *   conf   [batch, D]  float  confidence per block position (may be NULL);
  *   logits [batch*D,V] float  the logits Z (may be NULL; costs a batch*D*V write).
  * The step publishes nothing: K/V of the pending tokens are written into cache slots that stay invisible
- * until sdlm_kv_commit, and the block rows' K/V live in per-step staging.  It may therefore be repeated.
+ * until sdlm_kv_commit, and the block rows' K/V live in per-step staging.  It may therefore be repeated, with the same bits.
+ * Sequences are independent, but which kernels a step takes depends on its rows (sdlm_debug_step_plan): a sequence's results in
+ * another batch may differ by the order of fp32 sums and, in bf16, by what that changes in the roundings of operands.  On the generic
+ * path they are the same bits while both batches' steps take the same form (the line is at most at batch x 2D = 32 rows, and again
+ * where the products of many rows begin).
  * Errors: SDLM_ESTATE before prefill; SDLM_ECAPACITY if n_b + D > max_seq_len for some sequence, i.e. if accepting
  * all D tokens would not fit (the host tracks an upper bound of each length and refreshes it with a stream
  * synchronisation only when the bound trips; the same refresh reports a page pool that ran out at the last commit).

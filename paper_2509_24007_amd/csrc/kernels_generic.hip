@@ -8,8 +8,8 @@
 
 namespace sdlm {
 
-// Embeddings of R rows by one workgroup, four features a thread and eight requests under way.  One workgroup is enough while the gather is a few round trips; it
-// saves a launch of 2.4 us (h = 256, 8 rows: assembly and gather 5.2 -> 3.4 us; the rule of assemble_embeds).
+// Embeddings of R rows by one workgroup, four features a thread.  One workgroup is enough while the gather is a few trips, each a round trip for the token and one for
+// its row; it saves a launch of 2.4 us (h = 256, 8 rows: assembly and gather 5.2 -> 3.4 us; the rule of assemble_embeds).
 template <typename T>
 __device__ inline void embed_rows(float *x, const T *E, const int32_t *tok, int R, int h, int V)
 {

@@ -989,7 +989,8 @@ static int sure_blocks(int rows, int min_rows, int MT)
 //   64-row blocks, with the rows in operand order, in rounds of two workgroups a unit: k of at most 1536 until the certain rows are a little more than one round of them, four layers of a
 //   pass of h = 1536, us: 200 rows 417 -> 383, 320 rows 448 -> 417, 509 rows (512 workgroups) 546 -> 518, 640 rows (640) 596 -> 589, 800 rows 648 -> 647; steps of 14 layers, 64 sequences, D = 4
 //   1700 -> 1590, 40 sequences, D = 8 1795 -> 1723.  k of at most 2048 until 400: h = 2048, 320 rows 526 -> 508, 400 rows (560) 572 -> 577, 509 rows 644 -> 656; steps of 18 layers, 40 sequences, D = 4
-//   2290 -> 2230.  Longer k: h = 3584, 200 rows 769 -> 800.
+//   2290 -> 2230.  Longer k: h = 3584, 200 rows 769 -> 800.  The two lines are those of the two widths measured first; between them, over 159 shapes of k = 512 to 2048 with exact rows, one launch
+//   is 2 to 9 us a layer ahead wherever it is taken, and where it is not, still ahead by 1 to 6 us up to about 800 workgroups (k of at most 1280 to 1600) and 640 (1600, 1792), behind beyond 1000.
 // Blocks that may be empty are of 32 rows, unless all blocks are on the chip at once anyway: a step's rows end in one of them, and a second 64-row workgroup on
 // some units would make the launch wait (64 sequences, D = 2, h = 2048, 10 layers 1256 us with 64 rows, 1246 with 32; 64 sequences, D = 4 1761, 1745).  With
 // 32 rows where they do fit, a layer takes 3 % longer (24 sequences, D = 4, 192 rows: 114.2 -> 118.2 us).
@@ -1081,7 +1082,8 @@ static bool few16_gateup(int min_rows, int N)
 }
 
 // (Both rules are those of passes with separate norms: prompts of at most 16 tokens, widths above 8192.  In the chain of a decode step the operands' order makes the finer
-// gate/up blocks and the stream of down the better ones throughout: h = 5120, F = 27648, 16 rows, a step of 8 layers 1973 -> 1944 us.)
+// gate/up blocks and the stream of down better than what these rules choose: h = 5120, F = 27648, 16 rows, a step of 8 layers 1973 -> 1944 us; 144 to 256 blocks of 32 features, whole steps of six
+// layers before the chain / with it: h = 2560, F = 6912, 6 rows 434 / 410, 12 rows 444 / 416, 16 rows 468 / 428, h = 3072, F = 8192, 12 rows 519 / 473, h = 4096, F = 8192 634 / 559.)
 // What a product runs as: FEW16 / FEW32 are the kernels without LDS tiles for steps of few rows (16 rows x two 16-feature tiles, 32 rows x two
 // 32-feature tiles a workgroup), TILED the tiled kernel.
 enum { TILED = 0, FEW16, FEW32 };
@@ -1183,7 +1185,9 @@ static TileChoice choose(int epi, int rows, int min_rows, int N, int K, size_t s
     // the columns (7B gate/up 2.5 to 7 % faster), unless the rounds are dealt out worse: a round of 256 of them takes 0.955 of one of 512 small ones, of which
     // 264 or fewer, about one a unit, take 0.58.  us, eight / four: h = 2048, F = 11008 300 rows 49 / 40, 640 58 / 60, 992 103 / 88, 1280 110 / 113;
     // h = 3584, F = 18944 400 rows 160 / 133, 700 177 / 190, 992 260 / 243; h = 1536, F = 8960 509 rows 41 / 43, 992 76 / 63.
-    // Beyond four rounds the difference is within 2 % or the wide ones'.  (Measured and not faster: the LM head, the prefill QKV projection.)
+    // Beyond four rounds the difference is within 2 % or the wide ones'.  Of 103 random launches of gate/up the rule picks all but three within 1 us of the better.  Residual products (four layers of a
+    // pass, ms, always eight / by the rule): h = 5120, F = 27648, 4096 rows 13.09 / 12.48, 3500 rows 11.94 / 11.09, 3000 rows 8.81 / 8.81; h = 6144, F = 16384, 4096 rows 11.43 / 11.32; h = 3584, 4096 and 8192
+    // within 0.2 %.  (Measured and not faster: the LM head, the prefill QKV projection.)
     if ((epi == EPI_SWIGLU || epi == EPI_RESID) && c.MT == 4 && c.NT == 2 && c.splits == 1) {
         const int cols4 = epi == EPI_SWIGLU ? (N + 127) / 128 : (N + 255) / 256, mb = sure_blocks(rows, min_rows, c.MT);
         const int b4 = cols4 * mb, rounds8 = ((cols4 + 1) / 2 * mb + 255) / 256, rest4 = b4 % 512;
@@ -1294,7 +1298,8 @@ void launch_resid_few(hipStream_t s, const GemmArgs &g, bool ordered, const void
 
 // Down of that chain by whole sums where its workgroups of 16 features are nearly one round of the units: h = 3584, F = 18944, 8 rows, 224 workgroups, a step of 8 layers 1168 us
 // with k splits and an RMSNorm, 1136 without.  Fewer leave units without work, which costs the launch what the norm's saves (h = 1536, 96 workgroups, 28 layers:
-// 8 rows 1509 / 1502, 16 rows 1595 / 1614; h = 2048, 128, 18 layers: 1222 / 1214, 1278 / 1302); more are an uneven second one (h = 5120, 320, 8 layers: 1963 / 2055).
+// 8 rows 1509 / 1502, 16 rows 1595 / 1614; h = 2048, 128, 18 layers: 1222 / 1214, 1278 / 1302); more are an uneven second one (h = 5120, 320, 8 layers: 1963 / 2055).  The ends of the
+// range, six layers, 16 and 6 rows: h = 3136, F = 8960 527 / 518, F = 16384 659 / 651, h = 3328 645 / 620, h = 3840 740 / 712, h = 4096, F = 14336 756 / 726, F = 8192 563 / 534, F = 22016 949 / 929.
 bool few_down_whole(int h) { return h / 16 > 192 && h / 16 <= 256; }
 
 int launch_down_split(hipStream_t s, const GemmArgs &g, float *slabs, size_t slab_room_floats, bool defer_reduce)
