@@ -157,6 +157,8 @@ int sdlm_decode_step(sdlm_ctx *ctx, int32_t *ids, int32_t *count, float *conf, f
  * shares it: calls that overlap on one GPU (other streams, other contexts) race; calls in stream order do not, and
  * nothing in the array needs to start at zero (every partial result is written before it is read).  The device
  * current at sdlm_create is the one whose copy is used.  SDLM_EHIP if the array's address could not be obtained.
+ * A step (this or sdlm_decode_step) that the caller records into a graph of its own is launched for the capacity, not for the
+ * present lengths, and may be replayed at any of them, also behind another sdlm_prefill of the same batch.
  */
 int sdlm_decode_step_static(sdlm_ctx *ctx, int32_t *ids, int32_t *count, float *conf, float *logits);
 

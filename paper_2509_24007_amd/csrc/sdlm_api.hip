@@ -190,6 +190,7 @@ struct sdlm_ctx {
     bool prefilled = false, stepped = false;
     bool committed = false;              // a commit has happened since the prefill: every sequence has >= 1 pending row
     std::vector<int32_t> n_ub;           // host upper bound of n_b
+    bool commits_unseen = false;         // a caller's graph commits: lengths may be beyond n_ub
     std::vector<int32_t> n_host;         // landing buffer of refresh_lengths (sized once, so that a step allocates nothing)
     char *static_scratch = nullptr;      // this GPU's copy of the library-owned scratch array (sdlm_decode_step_static)
     std::string static_err;              // why static_scratch is missing
@@ -254,8 +255,19 @@ struct Phase {
     }
 };
 
+// Whether the caller is recording this context's stream into a graph of its own.
+bool callers_capture(const sdlm_ctx *c)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return c->stream && hipStreamIsCapturing(c->stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
 // Host upper bound of the longest sequence's length.
 int longest(const sdlm_ctx *c) { return *std::max_element(c->n_ub.begin(), c->n_ub.begin() + c->batch); }
+
+// ... that the launches of a step may meet: the capacity where the host does not know it, in a caller's graph, which may be replayed at any length, and once
+// such a graph commits (also behind a later prefill: it may be replayed there too).
+int longest_of_step(const sdlm_ctx *c) { return c->commits_unseen || callers_capture(c) ? c->r.max_seq_len : longest(c); }
 
 void run_taps(sdlm_ctx *c, int layer, int which, const void *src, size_t bytes)
 {
@@ -305,10 +317,10 @@ int pass_head(const sdlm_model_cfg &m, int lm_rows)
 bool step_lm_accept(const sdlm_model_cfg &m, int D) { return !mfma_supported(&m) && lm_accept_applies(m.vocab, D); }
 
 // The decoder layers over the rows described by c->rm.  `rows` bounds the launch grids (the device-side row
-// count decides what is computed); `rows_sure` is a host-known lower bound of that count (it only steers launch shapes).
+// count decides what is computed); `rows_sure` is a host-known lower bound of that count (it only steers launch shapes).  `max_len`: longest sequence that it may meet (longest, longest_of_step).
 // `cache_only`: the pass only has to leave its rows' K/V in the cache (prefill): the last layer then ends after the K/V placement.  `embedded`: x holds the rows' embeddings already.
 // Taps change no product: they copy, add the split-k slabs that the next norm would have added (in the same order), and put operands back into rows.
-void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_only, bool embedded = false, bool two_staging = false)
+void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, int max_len, bool cache_only, bool embedded = false, bool two_staging = false)
 {
     const sdlm_model_cfg &m = c->m;
     const int dt = m.dtype, h = m.hidden, F = m.ffn, d = m.head_dim;
@@ -316,7 +328,6 @@ void run_layers(sdlm_ctx *c, int rows, int groups, int rows_sure, bool cache_onl
     const size_t e = c->L.esz;
     hipStream_t s = c->stream;
     c->pend_slabs = 0;   // a fresh residual stream: nothing pending from an earlier pass
-    const int max_len = longest(c);
     const int chain = pass_chain(m, rows, rows_sure, cache_only);
     const bool few = chain == CHAIN_GENERIC, few16 = chain == CHAIN_MFMA || chain == CHAIN_MFMA_WHOLE, ordered = chain == CHAIN_MFMA_WHOLE;
     float *ssq = few16 ? c->slabs : nullptr;   // free where it is needed: slabs are written by down and read by the next norm
@@ -671,7 +682,7 @@ int sdlm_prefill(sdlm_ctx *c, int32_t batch, const int32_t *ids, const int32_t *
         HIPCHK(c, hipMemcpyAsync(c->rm.grp_seq, gs.data(), gs.size() * 4, hipMemcpyHostToDevice, s));
         HIPCHK(c, hipMemcpyAsync(c->rm.grp_hint, gh.data(), gh.size() * 4, hipMemcpyHostToDevice, s));
         HIPCHK(c, hipMemcpyAsync(c->rm.counts, counts, sizeof counts, hipMemcpyHostToDevice, s));
-        run_layers(c, R, (int)g0.size(), R, true);
+        run_layers(c, R, (int)g0.size(), R, longest(c), true);
         HIPCHK(c, hipStreamSynchronize(s));   // the host vectors are reused
         tok.clear(); pos.clear(); seq.clear(); kind.clear(); lim.clear(); g0.clear(); gn.clear(); gs.clear(); gh.clear();
         return SDLM_OK;
@@ -711,12 +722,13 @@ static int decode_step_impl(sdlm_ctx *c, int32_t *ids, int32_t *count, float *co
     hipStream_t s = c->stream;
     const int rows = B * 2 * D, groups = B * ((2 * D + c->L.group_rows - 1) / c->L.group_rows);
     const int rows_sure = B * (D + (c->committed ? 1 : 0));   // after a commit every sequence has >= 1 pending row
+    const int max_len = longest_of_step(c);   // before a capture of the library's own
     auto launch_all = [&]() {
         const int cp_floor = c->L.mfma ? mfma_attn_chunk_floor(&c->m, c->r.max_seq_len, groups, c->L.attn_bytes) : 0;
         const bool embeds = step_embeds(c->m, pass_chain(c->m, rows, rows_sure, false), B, D) == EMBED_ASSEMBLY;
         { Phase p(c, SDLM_PH_ROWS); launch_assemble_decode(s, c->st, c->rm, B, D, c->m.mask_token_id, c->L.group_rows, c->kg.staging_base, c->m.block_causal, c->m.n_kv_heads, cp_floor,
                                                           c->m.dtype, c->x, embeds ? c->embed : nullptr, c->m.hidden, c->m.vocab); }
-        run_layers(c, rows, groups, rows_sure, false, embeds);
+        run_layers(c, rows, groups, rows_sure, max_len, false, embeds);
         const bool reduce = !step_lm_accept(c->m, D);
         run_lm_head(c, B * D, logits, reduce);
         Phase p(c, SDLM_PH_ACCEPT);
@@ -727,7 +739,7 @@ static int decode_step_impl(sdlm_ctx *c, int32_t *ids, int32_t *count, float *co
         void *key[4] = {ids, count, conf, logits};
         // The attention's launches follow the longest sequence: captured again when their form changes (at 256 keys, and where the merge does), so that a
         // replay runs what an eager step would.
-        const int attn = c->L.mfma ? mfma_attn_form(&c->m, c->r.max_seq_len, longest(c), groups, c->L.attn_bytes, false) : 0;
+        const int attn = c->L.mfma ? mfma_attn_form(&c->m, c->r.max_seq_len, max_len, groups, c->L.attn_bytes, false) : 0;
         if (!c->graph_exec || attn != c->graph_attn || memcmp(key, c->graph_key, sizeof key) != 0) {
             drop_graph(c);
             hipGraph_t g = nullptr;
@@ -811,7 +823,7 @@ int sdlm_verify_step(sdlm_ctx *c, int32_t rule, int32_t *ids_tilde, int32_t *cou
         groups = verify_groups_per_seq(D, gr);
         const int cp_floor = c->L.mfma ? mfma_attn_chunk_floor(&c->m, c->r.max_seq_len, B * groups, c->L.attn_bytes) : 0;
         { Phase p(c, SDLM_PH_ROWS); launch_assemble_verify(s, c->st, c->rm, B, D, c->m.mask_token_id, gr, c->kg.staging_base, c->m.block_causal, c->m.n_kv_heads, cp_floor); }
-        run_layers(c, rows, B * groups, rows, false, false, !shared);
+        run_layers(c, rows, B * groups, rows, longest_of_step(c), false, false, !shared);
         run_lm_head(c, B * (D - 1), logits);
     }
     { Phase p(c, SDLM_PH_ACCEPT); launch_verify_accept(s, c->st, c->ids_rows, B, D, rule, ids_tilde, count); }
@@ -836,6 +848,7 @@ int sdlm_kv_commit(sdlm_ctx *c, const int32_t *ids_override, const int32_t *coun
     launch_commit(c->stream, c->st, B, D, ids_override, count_override, c->r.kv_layout, c->L.n_pages, c->L.pages_per_seq, c->m.vocab);
     HIPCHK(c, hipGetLastError());
     for (int b = 0; b < B; ++b) c->n_ub[b] += D;
+    c->commits_unseen |= callers_capture(c);
     c->stepped = false;
     if (!c->committed) { c->committed = true; drop_graph(c); }   // the certain-row bound of the step's launches changes
     return SDLM_OK;

@@ -658,6 +658,82 @@ def test_graph_replay_is_eager_bit_for_bit_as_contexts_grow(start):
         assert torch.equal(a, b), f"step {t // 2}: replay and eager differ by {(a - b).abs().max().item():.3e}"
 
 
+@pytest.mark.parametrize("static", [False, True])
+def test_step_in_a_callers_graph_at_any_length(static):
+    """A step that the caller records into a graph of its own at a short context is right at every length the context can hold: the attention's form for short
+    contexts (at most 256 keys; its page numbers ride in 64 lanes, 1024 keys) must not be baked into it.  The graph serves other prompts of the same batch: 1300 tokens, where its
+    launches are those of an eager step and so its bits, and again a short one, where only the order of the sums differs."""
+    m = mfma_cfg()
+    _, g_dev, layers_dev = both_models(m, seed=18, std=0.05)
+    D = 8
+    side = torch.cuda.Stream()
+    ctx = gpu_context(m, g_dev, layers_dev, stream=side, max_batch=2, max_seq_len=1400, D=D, tau=0.5)
+    ids = torch.empty(2, D, dtype=torch.int32, device="cuda")
+    cnt = torch.empty(2, dtype=torch.int32, device="cuda")
+    logits = torch.empty(2 * D, m.vocab, dtype=torch.float32, device="cuda")
+
+    def fresh(n):
+        ctx.prefill([syn.uniform_int(18, f"cg{n}{i}", k, 0, m.vocab - 1).numpy() for i, k in enumerate([n, 33])])
+        ctx.decode_step(ids, cnt, None, logits, static_scratch=static)
+        torch.cuda.synchronize()
+        return logits.clone()
+
+    eager = fresh(200)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side, capture_error_mode="thread_local"):
+        ctx.decode_step(ids, cnt, None, logits, static_scratch=static)
+    for n in (200, 1300, 200):
+        eager = fresh(n)
+        for _ in range(2):
+            logits.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            err = ((logits - eager).abs().amax(1) / eager.abs().amax(1)).max().item()
+            print("static" if static else "workspace", n, err)
+            assert torch.equal(logits, eager) if n == 1300 else err <= 2e-2, (n, err)   # (the bar of the bf16 path)
+    ctx.close()
+
+
+def test_eager_steps_behind_a_callers_graph_that_commits():
+    """A caller's graph of a step and its commit moves the lengths where the host does not see it; an eager step behind it is still that of the lengths there are."""
+    m = mfma_cfg()
+    _, g_dev, layers_dev = both_models(m, seed=18, std=0.05)
+    D, start, steps = 16, 200, 62
+    ovr = syn.make_overrides(19, 2, 1, D, m.vocab)[0][0].to(torch.int32).cuda().contiguous()
+    full = torch.full((1,), D, dtype=torch.int32, device="cuda")
+    prompt = [syn.uniform_int(18, "cc", start, 0, m.vocab - 1).numpy()]
+    side = torch.cuda.Stream()
+    out = []
+    for replayed in (False, True):
+        ctx = gpu_context(m, g_dev, layers_dev, stream=side, max_batch=1, max_seq_len=1300, D=D, tau=0.5)
+        ids = torch.empty(1, D, dtype=torch.int32, device="cuda")
+        cnt = torch.empty(1, dtype=torch.int32, device="cuda")
+        logits = torch.empty(D, m.vocab, dtype=torch.float32, device="cuda")
+        ctx.prefill(prompt)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        if replayed:
+            with torch.cuda.graph(graph, stream=side, capture_error_mode="thread_local"):
+                ctx.decode_step(ids, cnt)
+                ctx.kv_commit(ovr, full)
+        for _ in range(steps):
+            if replayed:
+                graph.replay()
+            else:
+                ctx.decode_step(ids, cnt)
+                ctx.kv_commit(ovr, full)
+            torch.cuda.synchronize()
+        ctx.decode_step(ids, cnt, None, logits)
+        torch.cuda.synchronize()
+        out.append(logits.clone())
+        assert ctx.get_lengths()[0].tolist() == [start + steps * D]
+        ctx.close()
+    err = ((out[1] - out[0]).abs().amax(1) / out[0].abs().amax(1)).max().item()
+    print("eager behind a replayed commit", err)
+    assert err <= 2e-2, err   # the cache is written by steps in another order of the sums (the bar of the bf16 path)
+
+
 def test_graph_needs_a_real_stream():
     m = gpu_cfg()
     om, g_dev, layers_dev = both_models(m, seed=8, std=0.3)
