@@ -1117,6 +1117,9 @@ static void refine_gateup(int rows, int min_rows, int N, int K, TileChoice *c)
 // bounds; a megabyte of slabs is written and read in 0.42 us.  Its choice is 0.36 us from the best on average; as many workgroups of the wide tile as units wherever that fits 1.82; with
 // the slices' cost as a step at 400 rows and no more than its own slices for a second workgroup it was 0.54, and slower than that rule by up to 16 us.  us a step saved against that over four
 // layers, (columns, splits): N = 3840, K = 3072, 409 rows (256, 4) -> (128, 2) 16;  N = 6144, K = 24576, 274 rows (256, 7) -> (256, 3) 115.
+// Over 1072 products of 390 other models (h = 1024 to 6144, 34 to 900 rows, many just beyond a multiple of 128) a step is 0.8 % faster than with as many workgroups as units on average, by
+// more than 2 % slower in 25 and by 6.9 % at worst (N = 4352, K = 19072, 756 rows, four layers 2402 -> 2567 us).  Blocks of few rows counted by their 32-row tiles, the mean of the costs at certain
+// and at likely rows, and the old choice wherever the estimates are close choose no better over those.
 // us a launch, (columns, splits) as many as units -> now:
 // N = 2048, K = 11008, 160 rows (256, 16) 20.0 -> (128, 8) 18.0;  N = 3584, K = 18944, 49 rows (256, 16) 28.7 -> (128, 9) 27.1;  N = 5120 square,
 // 160 rows (256, 6) 20.3 -> (128, 3) 19.7, the norm behind each 0.6 to 2 us shorter;  N = 5120, K = 27648, 992 rows (128, 1) 386 -> (256, 3) 261.
